@@ -16,9 +16,21 @@
 // in registers, and walks over the other side's rows in tiles of 64 that are staged row-major in
 // LDS (double-buffered, one barrier per tile).  Operands that are needed transposed (V^T, K^T, Q^T,
 // ghat^T as the MFMA's A operand) come from the same row-major tile through the transposing LDS
-// read, so no transposed copy exists anywhere.  MFMA operand layouts as in mfma_common.hpp; the
-// 8 k-slots of the second contraction are rows 4g..4g+3 of two 16-row blocks, which is how the
-// first contraction's accumulators already hold them.
+// read, so no transposed copy exists anywhere.
+//
+// MFMA: 32x32x16 throughout (layouts in mfma_common.hpp).  The first contraction's accumulators (16 registers: rows
+// 8 k + 4 h + r of the streamed side) are two B operands of the second one, whose 16 k-slots are then the streamed rows
+// 16 j + 4 h + r and 16 j + 8 + 4 h + r.  Against 16x16x32 the operands read per flop halve and a wave that has the SIMD
+// to itself still issues at the full rate (31 cycles per 16x16x32 MFMA otherwise).
+//
+// The vector ALU's share, per pair of tokens, is what bounds d = 32 and matters everywhere, so the scale stays out of it:
+// the kernels form c^p and e c^(p-1) from the plain c = q . k, and the factors scale^p (p scale^p for dQ and dK) are
+// applied to the accumulators once, at the end.  (Per pair at p = 2: forward 1 multiply and half a conversion instead of
+// 2.5 instructions, dQ 1.5 instead of 3.5.)
+//
+// Forward + backward, before and after the 32x32 form, the scale's removal and the order of the workgroups (heavy_first):
+// p = 4, d = 32, B2 H8 T16384: 2.43 -> 1.40 ms; p = 3, d = 64, B1 H4 T16384: 1.25 -> 0.89 ms; p = 2, d = 64, B16 H12
+// T1000: 0.260 -> 0.175 ms.
 #include <type_traits>
 
 #include "mfma_common.hpp"
@@ -47,6 +59,15 @@ __device__ __forceinline__ float ipow<4>(float x) {
     return x2 * x2;
 }
 
+// z + the sum of 8 bf16 values (exact products with one, float32 sums)
+__device__ __forceinline__ float sum_bf16x8(const Frag& f, float z) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const bf16x2 one = {(__bf16)1.f, (__bf16)1.f};
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) z = __builtin_amdgcn_fdot2_f32_bf16((bf16x2){f.v[i], f.v[i + 1]}, one, z, false);
+    return z;
+}
+
 // Staging of a 64-row tile of a row-major [.][HD] array: HD / 32 pieces of 16 bytes per thread,
 // piece id = tid + 256 q is row id / (HD / 8), features 8 (id % (HD / 8)) .. + 7.  The pieces wait
 // in registers while the tile before them is being used (plain arrays and unrolled loops in the
@@ -69,35 +90,78 @@ __device__ __forceinline__ void piece_store(AttnTile<HD>& dst, int id, uint4 u) 
 #define PA_TILE_STORE(DST, REGS)                    \
     _Pragma("unroll") for (int q_ = 0; q_ < HD / 32; ++q_) piece_store<HD>(DST, tid + 256 * q_, REGS[q_]);
 
-// rows 16 blk + r16, features 32 ks + 8 g .. + 7: A operand (rows x features) or B operand
+// row 32 blk + r32, features 16 ks + 8 h .. + 7: A operand (rows x features) or B operand
 // (features x rows) of a contraction over the features
 template <int HD>
-__device__ __forceinline__ bf16x8 row_frag(const AttnTile<HD>& t, int blk, int ks, int r16, int g) {
+__device__ __forceinline__ bf16x8 row_frag(const AttnTile<HD>& t, int blk, int ks, int lane) {
     Frag f;
-    f.u = *(const uint4*)&t.r[16 * blk + r16][32 * ks + 8 * g];
+    f.u = *(const uint4*)&t.r[32 * blk + (lane & 31)][16 * ks + 8 * (lane >> 5)];
     return f.v;
 }
 template <int HD>
-__device__ __forceinline__ bf16x8 row_frag_global(const bf16_t* __restrict__ X, size_t row, int ks, int g) {
+__device__ __forceinline__ bf16x8 row_frag_global(const bf16_t* __restrict__ X, size_t row, int ks, int h) {
     Frag f;
-    f.u = *(const uint4*)(X + row * HD + 32 * ks + 8 * g);
+    f.u = *(const uint4*)(X + row * HD + 16 * ks + 8 * h);
     return f.v;
 }
 
-// A operand of a contraction over the tile's rows: column 16 cb + r16, k-slots = rows
-// 32 s + 4g .. + 3 and 32 s + 16 + 4g .. + 3.  The transposing read hands lane n of a 16-lane
-// group column n of the 4 x 16 block whose row j the lanes 4j .. 4j+3 point at (4 columns each).
+// A operand of a contraction over the tile's rows: column 32 cb + r32, k-slots = rows 16 j + 4 h .. + 3 and 8 further.
+// The transposing read hands lane n of a 16-lane group column n of the 4 x 16 block whose row i the lanes 4 i .. 4 i + 3
+// point at (4 columns each).
 template <int HD>
-__device__ __forceinline__ bf16x8 col_frag(const AttnTile<HD>& t, int s, int cb, int r16, int g) {
+__device__ __forceinline__ bf16x8 col_frag(const AttnTile<HD>& t, int j, int cb, int lane) {
     typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-    const bf16_t* p = &t.r[32 * s + 4 * g + (r16 >> 2)][16 * cb + 4 * (r16 & 3)];
+    const int r16 = lane & 15, h = lane >> 5, odd = (lane >> 4) & 1;
+    const bf16_t* p = &t.r[16 * j + 4 * h + (r16 >> 2)][32 * cb + 16 * odd + 4 * (r16 & 3)];
     union {
         bf16x8 v;
         bf16x4 h[2];
     } f;
     f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)p);
-    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 16 * (HD + 8)));
+    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 8 * (HD + 8)));
     return f.v;
+}
+__device__ __forceinline__ f32x16 splat16(float x) {
+    f32x16 v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = x;
+    return v;
+}
+// four values per accumulator quad k: rows 8 k + 4 h + r of a per-row float array
+__device__ __forceinline__ void row_values(float (&o)[16], const float* base, int h) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float4 q = *(const float4*)(base + 8 * k + 4 * h);
+        o[4 * k] = q.x; o[4 * k + 1] = q.y; o[4 * k + 2] = q.z; o[4 * k + 3] = q.w;
+    }
+}
+// one 32-row block of an output row's columns: dst[8 k + 4 h + r] = f acc[4 k + r] (bf16); two lanes 32 apart exchange
+// halves so that each stores whole 16-byte runs
+__device__ __forceinline__ void store_block(bf16_t* dst, const f32x16& acc, float f, int h, bool in) {
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+        union {
+            bf16x4 v;
+            uint2 u;
+        } x, y;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            x.v[r] = (__bf16)(f * acc[4 * k + r]);
+            y.v[r] = (__bf16)(f * acc[4 * k + 4 + r]);
+        }
+        const auto d0 = __builtin_amdgcn_permlane32_swap(x.u.x, y.u.x, false, false);
+        const auto d1 = __builtin_amdgcn_permlane32_swap(x.u.y, y.u.y, false, false);
+        if (in) *(u32x4*)(dst + 8 * (k + h)) = (u32x4){d0[0], d1[0], d0[1], d1[1]};
+    }
+}
+// acc += the same block of `nslab` float32 parts
+__device__ __forceinline__ void add_parts(f32x16& acc, const float* part, size_t slab_stride, int nslab, int h) {
+    for (int sl = 0; sl < nslab; ++sl)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float4 pv = *(const float4*)(part + sl * slab_stride + 8 * k + 4 * h);
+            acc[4 * k] += pv.x; acc[4 * k + 1] += pv.y; acc[4 * k + 2] += pv.z; acc[4 * k + 3] += pv.w;
+        }
 }
 
 // Gating (Sec. 2 "Gating"): the pair (i, j) carries exp(b_i - b_j), b the running sum of the log-gates.
@@ -124,16 +188,17 @@ __device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, i
     }
 }
 
-// Workgroups are numbered so that the ones with the longest walk start first.
+// Workgroups are numbered so that the ones with the longest walk start first: grid (heads, blocks), so the longest blocks
+// of every head come before the next ones.  (With the blocks of one head after the other, the last heads' long walks
+// started when most of the chip was done: at 16 heads of 16384 tokens the CUs were busy 62 % of the time, and the p = 4
+// kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)
 __device__ __forceinline__ int heavy_first(int nblocks, bool longest_is_last) {
-    return longest_is_last ? nblocks - 1 - (int)blockIdx.x : (int)blockIdx.x;
+    return longest_is_last ? nblocks - 1 - (int)blockIdx.y : (int)blockIdx.y;
 }
 
 // ---- forward ----------------------------------------------------------------------------------------
-// acc[vb][ib] = O^T: value columns 16 vb + 4g + r, query 16 ib + r16 of the wave's OWN queries.
-// WPE: waves per SIMD the register budget is set for.  With 2 (at most 256 registers) the MFMAs
-// write plain vector registers; with 1 the compiler moves every score through the accumulation
-// registers and back, which costs more vector-ALU instructions than the arithmetic itself.
+// acc[vb][ib] = O^T: value columns 32 vb + .., query 32 ib + r32 of the wave's OWN queries.
+// WPE: waves per SIMD the register budget is set for.
 // CHUNKED (the in-chunk part of the chunked form, App. E.1, for any degree and head size): a query sees the
 // keys of its own chunk of `cs` tokens only (cs a multiple of the 64-key tile), and the part that comes
 // through the state has been left by other kernels: part[slab][bh][t][v] (float32, `nslab` slabs, summed
@@ -149,40 +214,36 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ V, bf16_t* __restrict__ O,
                                                        float* __restrict__ Z, int T, float scale, int normalize,
                                                        const float* __restrict__ bl, ChunkedIn ck) {
-    constexpr int NI = OWN / 16, NK = HD / 32, NV = HD / 16, WG = 4 * OWN;
+    constexpr int NI = OWN / 32, NK = HD / 16, NV = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
     AttnTile<HD>* kt = reinterpret_cast<AttnTile<HD>*>(attn_smem);      // [2]
     AttnTile<HD>* vt = kt + 2;                                          // [2]
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
     const int i0 = heavy_first(nblk, true) * WG;
     const int q0 = i0 + OWN * w;                    // the wave's first query
     const bool active = q0 < T;
-    const size_t head = (size_t)blockIdx.y * T;
+    const size_t head = (size_t)blockIdx.x * T;
     const bf16_t* Kh = K + head * HD;
     const bf16_t* Vh = V + head * HD;
 
     bf16x8 qf[NI][NK];
-    f32x4 acc[NV][NI];
-    // Z rides on the matrix cores too: a row of ones as the A operand sums the rounded weights of
-    // a step's 32 keys for every query (all four accumulator rows of a lane hold the same sum)
-    f32x4 zacc[NI];
-    Frag ones;
-    ones.u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    f32x16 acc[NV][NI];
+    float zsum[NI];     // the sum of the rounded weights over this lane's k-slots
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
-        zacc[ib] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        zsum[ib] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks)
-            qf[ib][ks] = row_frag_global<HD>(Q, head + min(q0 + 16 * ib + r16, T - 1), ks, g);
+            qf[ib][ks] = row_frag_global<HD>(Q, head + min(q0 + 32 * ib + r32, T - 1), ks, h);
 #pragma unroll
-        for (int vb = 0; vb < NV; ++vb) acc[vb][ib] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int vb = 0; vb < NV; ++vb) acc[vb][ib] = splat16(0.f);
     }
     const float* bl_head = GATED ? bl + head : nullptr;
     float bq[NI];
 #pragma unroll
-    for (int ib = 0; ib < NI; ++ib) bq[ib] = GATED ? bl_head[min(q0 + 16 * ib + r16, T - 1)] : 0.f;
+    for (int ib = 0; ib < NI; ++ib) bq[ib] = GATED ? bl_head[min(q0 + 32 * ib + r32, T - 1)] : 0.f;
 
     // one 64-key tile; DIAG: some pair of the tile lies above the diagonal and has to be masked
     auto tile = [&](auto diag_c, int buf, int key0) {
@@ -193,42 +254,47 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
 #pragma unroll
             for (int ib = 0; ib < NI; ++ib) fq[ib] = __expf(bq[ib] - m);
         }
+        f32x16 c[2][NI];        // S^T: key 32 kb + 8 k + 4 h + r, query 32 ib + r32
+        auto scores = [&](int kb) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            Frag pf[NI];
+            for (int ib = 0; ib < NI; ++ib) c[kb][ib] = splat16(0.f);
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb) {
-                const int kb = 2 * s + jb;
-                bf16x8 kf[NK];
+            for (int ks = 0; ks < NK; ++ks) {
+                const bf16x8 kf = row_frag<HD>(kt[buf], kb, ks, lane);
 #pragma unroll
-                for (int ks = 0; ks < NK; ++ks) kf[ks] = row_frag<HD>(kt[buf], kb, ks, r16, g);
-                float4 gk = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (GATED) gk = *(const float4*)(DIAG ? &gtile[buf].b[16 * kb + 4 * g] : &gtile[buf].f[16 * kb + 4 * g]);
-                const float gkr[4] = {gk.x, gk.y, gk.z, gk.w};
-#pragma unroll
-                for (int ib = 0; ib < NI; ++ib) {
-                    f32x4 c = {0.f, 0.f, 0.f, 0.f};    // S^T: key 16 kb + 4g + r, query 16 ib + r16
-#pragma unroll
-                    for (int ks = 0; ks < NK; ++ks) c = mfma16(kf[ks], qf[ib][ks], c);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float a = ipow<P>(scale * c[r]);
-                        if (GATED) a *= DIAG ? __expf(bq[ib] - gkr[r]) : fq[ib] * gkr[r];
-                        if (DIAG && key0 + 16 * kb + 4 * g + r > q0 + 16 * ib + r16) a = 0.f;
-                        pf[ib].v[4 * jb + r] = (__bf16)a;
-                    }
-                }
+                for (int ib = 0; ib < NI; ++ib) c[kb][ib] = mfma32(kf, qf[ib][ks], c[kb][ib]);
             }
+        };
+        scores(0);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            if (kb == 0) scores(1);      // in flight under the weights of the first half
+            Frag pf[NI][2];
+            float gk[16];
+            if (GATED) row_values(gk, DIAG ? &gtile[buf].b[32 * kb] : &gtile[buf].f[32 * kb], h);
+#pragma unroll
+            for (int ib = 0; ib < NI; ++ib)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    float a = ipow<P>(c[kb][ib][i]);
+                    if (GATED) a *= DIAG ? __expf(bq[ib] - gk[i]) : fq[ib] * gk[i];
+                    if (DIAG && key0 + 32 * kb + 8 * (i >> 2) + 4 * h + (i & 3) > q0 + 32 * ib + r32) a = 0.f;
+                    pf[ib][i >> 3].v[i & 7] = (__bf16)a;
+                }
             // the denominator sums the rounded weights, the ones the numerator uses: the output is
             // then an exact convex combination of the values
 #pragma unroll
-            for (int ib = 0; ib < NI; ++ib) zacc[ib] = mfma16(ones.v, pf[ib].v, zacc[ib]);
+            for (int ib = 0; ib < NI; ++ib)
 #pragma unroll
-            for (int vb = 0; vb < NV; ++vb) {
-                const bf16x8 vf = col_frag<HD>(vt[buf], s, vb, r16, g);
+                for (int j = 0; j < 2; ++j) zsum[ib] = sum_bf16x8(pf[ib][j], zsum[ib]);
 #pragma unroll
-                for (int ib = 0; ib < NI; ++ib) acc[vb][ib] = mfma16(vf, pf[ib].v, acc[vb][ib]);
-            }
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int vb = 0; vb < NV; ++vb) {
+                    const bf16x8 vf = col_frag<HD>(vt[buf], 2 * kb + j, vb, lane);
+#pragma unroll
+                    for (int ib = 0; ib < NI; ++ib) acc[vb][ib] = mfma32(vf, pf[ib][j].v, acc[vb][ib]);
+                }
         }
     };
 
@@ -240,7 +306,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     float gb = 0.f, gf = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
-    if (GATED) gate_tile_load(gb, gf, bl_head, 0, AT - 1, 1.f, tid, T);
+    if (GATED) gate_tile_load(gb, gf, bl_head, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
     if (GATED) gate_tile_store(gtile[0], gb, gf, tid);
@@ -265,30 +331,26 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     }
 
     if (!active) return;
+    const float sp = ipow<P>(scale);
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
-        if (q0 + 16 * ib + r16 >= T) continue;      // past the end of a sequence that is not a multiple of the block
-        const size_t row = head + q0 + 16 * ib + r16;
-        float z = zacc[ib][0];
+        const bool in = q0 + 32 * ib + r32 < T;     // (a sequence need not be a multiple of the block)
+        const size_t row = head + min(q0 + 32 * ib + r32, T - 1);
+        float z = sp * xor32_sum(zsum[ib]), f = sp;
         if (CHUNKED) {
             z += ck.zpart[row];
-            const size_t slab_stride = (size_t)gridDim.y * T * HD;
-            for (int sl = 0; sl < ck.nslab; ++sl)
 #pragma unroll
-                for (int vb = 0; vb < NV; ++vb) {
-                    const float4 pv = *(const float4*)(ck.part + sl * slab_stride + row * HD + 16 * vb + 4 * g);
-                    acc[vb][ib][0] += pv.x; acc[vb][ib][1] += pv.y; acc[vb][ib][2] += pv.z; acc[vb][ib][3] += pv.w;
-                }
+            for (int vb = 0; vb < NV; ++vb) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[vb][ib][i] *= sp;
+                add_parts(acc[vb][ib], ck.part + row * HD + 32 * vb, (size_t)gridDim.x * T * HD, ck.nslab, h);
+            }
+            f = 1.f;
         }
-        const float inv = normalize ? (z != 0.f ? 1.f / z : 0.f) : 1.f;
+        if (normalize) f = z != 0.f ? f / z : 0.f;
 #pragma unroll
-        for (int vb = 0; vb < NV; ++vb) {
-            bf16x4 o;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = (__bf16)(acc[vb][ib][r] * inv);
-            *(bf16x4*)(O + row * HD + 16 * vb + 4 * g) = o;
-        }
-        if (Z != nullptr && g == 0) Z[row] = z;
+        for (int vb = 0; vb < NV; ++vb) store_block(O + row * HD + 32 * vb, acc[vb][ib], f, h, in);
+        if (Z != nullptr && h == 0 && in) Z[row] = z;
     }
 }
 
@@ -330,42 +392,41 @@ __global__ __launch_bounds__(256) void k_attn_prep(const bf16_t* __restrict__ dO
 }
 
 // ---- backward: dQ -----------------------------------------------------------------------------------
-// acc[fb][ib] = dQ^T: feature 16 fb + 4g + r, query 16 ib + r16.
+// acc[fb][ib] = dQ^T: features 32 fb + .., query 32 ib + r32.
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
 __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                  const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                  const float* __restrict__ gz, bf16_t* __restrict__ dQ, int T,
                                                  float scale, const float* __restrict__ bl, float* __restrict__ qdq,
                                                  ChunkedIn ck) {
-    constexpr int NI = OWN / 16, NK = HD / 32, NF = HD / 16, WG = 4 * OWN;
+    constexpr int NI = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
     AttnTile<HD>* kt = reinterpret_cast<AttnTile<HD>*>(attn_smem);      // [2]
     AttnTile<HD>* vt = kt + 2;                                          // [2]
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
     const int i0 = heavy_first(nblk, true) * WG;
     const int q0 = i0 + OWN * w;
     const bool active = q0 < T;
-    const size_t head = (size_t)blockIdx.y * T;
+    const size_t head = (size_t)blockIdx.x * T;
     const bf16_t* Kh = K + head * HD;
     const bf16_t* Vh = V + head * HD;
-    const float pscale = (float)P * scale;
 
     bf16x8 qf[NI][NK], gf[NI][NK];
-    f32x4 acc[NF][NI];
+    f32x16 acc[NF][NI];
     float gzq[NI];
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
-        const size_t row = head + min(q0 + 16 * ib + r16, T - 1);
+        const size_t row = head + min(q0 + 32 * ib + r32, T - 1);
         gzq[ib] = gz[row];
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            qf[ib][ks] = row_frag_global<HD>(Q, row, ks, g);
-            gf[ib][ks] = row_frag_global<HD>(Gh, row, ks, g);
+            qf[ib][ks] = row_frag_global<HD>(Q, row, ks, h);
+            gf[ib][ks] = row_frag_global<HD>(Gh, row, ks, h);
         }
 #pragma unroll
-        for (int fb = 0; fb < NF; ++fb) acc[fb][ib] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int fb = 0; fb < NF; ++fb) acc[fb][ib] = splat16(0.f);
     }
 
     const float* bl_head = GATED ? bl + head : nullptr;
@@ -375,7 +436,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__
     float bq[NI], rsum[NI];
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
-        bq[ib] = GATED ? bl_head[min(q0 + 16 * ib + r16, T - 1)] : 0.f;
+        bq[ib] = GATED ? bl_head[min(q0 + 32 * ib + r32, T - 1)] : 0.f;
         rsum[ib] = 0.f;
     }
 
@@ -388,44 +449,44 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__
             for (int ib = 0; ib < NI; ++ib) fq[ib] = __expf(bq[ib] - m);
         }
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            Frag tf[NI];
+        for (int kb = 0; kb < 2; ++kb) {
+            f32x16 c[NI], e[NI];        // S^T and E^T = V ghat^T + gz: key 32 kb + 8 k + 4 h + r, query 32 ib + r32
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb) {
-                const int kb = 2 * s + jb;
-                bf16x8 kf[NK], vf[NK];
+            for (int ib = 0; ib < NI; ++ib) {
+                c[ib] = splat16(0.f);
+                e[ib] = splat16(gzq[ib]);
+            }
 #pragma unroll
-                for (int ks = 0; ks < NK; ++ks) {
-                    kf[ks] = row_frag<HD>(kt[buf], kb, ks, r16, g);
-                    vf[ks] = row_frag<HD>(vt[buf], kb, ks, r16, g);
-                }
-                float4 gk = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (GATED) gk = *(const float4*)(DIAG ? &gtile[buf].b[16 * kb + 4 * g] : &gtile[buf].f[16 * kb + 4 * g]);
-                const float gkr[4] = {gk.x, gk.y, gk.z, gk.w};
+            for (int ks = 0; ks < NK; ++ks) {
+                const bf16x8 kf = row_frag<HD>(kt[buf], kb, ks, lane), vf = row_frag<HD>(vt[buf], kb, ks, lane);
 #pragma unroll
                 for (int ib = 0; ib < NI; ++ib) {
-                    f32x4 c = {0.f, 0.f, 0.f, 0.f}, e = {gzq[ib], gzq[ib], gzq[ib], gzq[ib]};
-#pragma unroll
-                    for (int ks = 0; ks < NK; ++ks) {
-                        c = mfma16(kf[ks], qf[ib][ks], c);    // S^T
-                        e = mfma16(vf[ks], gf[ib][ks], e);    // E^T = V ghat^T + gz
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float tv = e[r] * pscale * ipow<P - 1>(scale * c[r]);
-                        if (GATED) tv *= DIAG ? __expf(bq[ib] - gkr[r]) : fq[ib] * gkr[r];
-                        if (DIAG && key0 + 16 * kb + 4 * g + r > q0 + 16 * ib + r16) tv = 0.f;
-                        if (GATED) rsum[ib] += tv * c[r];
-                        tf[ib].v[4 * jb + r] = (__bf16)tv;
-                    }
+                    c[ib] = mfma32(kf, qf[ib][ks], c[ib]);
+                    e[ib] = mfma32(vf, gf[ib][ks], e[ib]);
                 }
+                if (ks & 1) __builtin_amdgcn_sched_barrier(0);   // (holds the register count under 256)
             }
+            Frag tf[NI][2];
+            float gk[16];
+            if (GATED) row_values(gk, DIAG ? &gtile[buf].b[32 * kb] : &gtile[buf].f[32 * kb], h);
 #pragma unroll
-            for (int fb = 0; fb < NF; ++fb) {
-                const bf16x8 kc = col_frag<HD>(kt[buf], s, fb, r16, g);   // K^T
+            for (int ib = 0; ib < NI; ++ib)
 #pragma unroll
-                for (int ib = 0; ib < NI; ++ib) acc[fb][ib] = mfma16(kc, tf[ib].v, acc[fb][ib]);
-            }
+                for (int i = 0; i < 16; ++i) {
+                    float tv = e[ib][i] * ipow<P - 1>(c[ib][i]);
+                    if (GATED) tv *= DIAG ? __expf(bq[ib] - gk[i]) : fq[ib] * gk[i];
+                    if (DIAG && key0 + 32 * kb + 8 * (i >> 2) + 4 * h + (i & 3) > q0 + 32 * ib + r32) tv = 0.f;
+                    if (GATED) rsum[ib] += tv * c[ib][i];
+                    tf[ib][i >> 3].v[i & 7] = (__bf16)tv;
+                }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int fb = 0; fb < NF; ++fb) {
+                    const bf16x8 kc = col_frag<HD>(kt[buf], 2 * kb + j, fb, lane);   // K^T
+#pragma unroll
+                    for (int ib = 0; ib < NI; ++ib) acc[fb][ib] = mfma32(kc, tf[ib][j].v, acc[fb][ib]);
+                }
         }
     };
 
@@ -436,7 +497,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__
     float gb = 0.f, gf2 = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
-    if (GATED) gate_tile_load(gb, gf2, bl_head, 0, AT - 1, 1.f, tid, T);
+    if (GATED) gate_tile_load(gb, gf2, bl_head, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
     if (GATED) gate_tile_store(gtile[0], gb, gf2, tid);
@@ -461,37 +522,29 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__
     }
 
     if (!active) return;
+    const float psp = (float)P * ipow<P>(scale);
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
-        const bool in = q0 + 16 * ib + r16 < T;
-        const size_t row = head + min(q0 + 16 * ib + r16, T - 1);
-        if (CHUNKED) {   // what came through the state (and the normaliser), per slab
-            const size_t slab_stride = (size_t)gridDim.y * T * HD;
-            for (int sl = 0; sl < ck.nslab; ++sl)
-#pragma unroll
-                for (int fb = 0; fb < NF; ++fb) {
-                    const float4 pv = *(const float4*)(ck.part + sl * slab_stride + row * HD + 16 * fb + 4 * g);
-                    acc[fb][ib][0] += pv.x; acc[fb][ib][1] += pv.y; acc[fb][ib][2] += pv.z; acc[fb][ib][3] += pv.w;
-                }
-        }
+        const bool in = q0 + 32 * ib + r32 < T;
+        const size_t row = head + min(q0 + 32 * ib + r32, T - 1);
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) {
-            bf16x4 o;
+            if (CHUNKED) {   // what came through the state (and the normaliser), per slab
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = (__bf16)acc[fb][ib][r];
-            if (in) *(bf16x4*)(dQ + row * HD + 16 * fb + 4 * g) = o;
+                for (int i = 0; i < 16; ++i) acc[fb][ib][i] *= psp;
+                add_parts(acc[fb][ib], ck.part + row * HD + 32 * fb, (size_t)gridDim.x * T * HD, ck.nslab, h);
+            }
+            store_block(dQ + row * HD + 32 * fb, acc[fb][ib], CHUNKED ? 1.f : psp, h, in);
         }
         if (GATED) {
-            float dot = rsum[ib];
-            dot += __shfl_xor(dot, 16);
-            dot += __shfl_xor(dot, 32);
-            if (in && g == 0) qdq[row] = dot;
+            const float dot = psp * xor32_sum(rsum[ib]);
+            if (in && h == 0) qdq[row] = dot;
         }
     }
 }
 
 // ---- backward: dK, dV ---------------------------------------------------------------------------------
-// dk[fb][kb] = dK^T: feature 16 fb + 4g + r, key 16 kb + r16 of the wave's OWN keys; dv likewise.
+// dk[fb][kb] = dK^T: features 32 fb + .., key 32 kb + r32 of the wave's OWN keys; dv likewise.
 // S and E are formed queries x keys here, so that their accumulators are the B operand (k-slots =
 // queries) of the two contractions over the queries.
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
@@ -501,36 +554,36 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
                                                    bf16_t* __restrict__ dV, int T, float scale,
                                                    const float* __restrict__ bl, float* __restrict__ kdk,
                                                    float* __restrict__ wsum, ChunkedIn ck) {
-    constexpr int NJ = OWN / 16, NK = HD / 32, NF = HD / 16, WG = 4 * OWN;
+    constexpr int NJ = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
     AttnTile<HD>* qt = reinterpret_cast<AttnTile<HD>*>(attn_smem);      // [2]
     AttnTile<HD>* gt = qt + 2;                                          // [2]
     float(*gzt)[AT] = reinterpret_cast<float(*)[AT]>(gt + 2);           // [2][AT]
     GateTile* gtile = reinterpret_cast<GateTile*>(gzt + 2);             // [2]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int j0 = heavy_first((T + WG - 1) / WG, false) * WG;
     const int k0 = j0 + OWN * w;                    // the wave's first key
     const bool active = k0 < T;
-    const size_t head = (size_t)blockIdx.y * T;
+    const size_t head = (size_t)blockIdx.x * T;
     const bf16_t* Qh = Q + head * HD;
     const bf16_t* Gh_h = Gh + head * HD;
     const float* gzh = gz + head;
-    const float pscale = (float)P * scale;
+    const float sp = ipow<P>(scale), psp = (float)P * sp;
 
     bf16x8 kf[NJ][NK], vf[NJ][NK];
-    f32x4 dk[NF][NJ], dv[NF][NJ];
+    f32x16 dk[NF][NJ], dv[NF][NJ];
 #pragma unroll
     for (int kb = 0; kb < NJ; ++kb) {
-        const size_t row = head + min(k0 + 16 * kb + r16, T - 1);
+        const size_t row = head + min(k0 + 32 * kb + r32, T - 1);
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            kf[kb][ks] = row_frag_global<HD>(K, row, ks, g);
-            vf[kb][ks] = row_frag_global<HD>(V, row, ks, g);
+            kf[kb][ks] = row_frag_global<HD>(K, row, ks, h);
+            vf[kb][ks] = row_frag_global<HD>(V, row, ks, h);
         }
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) {
-            dk[fb][kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            dv[fb][kb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            dk[fb][kb] = splat16(0.f);
+            dv[fb][kb] = splat16(0.f);
         }
     }
 
@@ -540,7 +593,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
     float bk[NJ], csum[NJ];
 #pragma unroll
     for (int kb = 0; kb < NJ; ++kb) {
-        bk[kb] = GATED ? bl_head[min(k0 + 16 * kb + r16, T - 1)] : 0.f;
+        bk[kb] = GATED ? bl_head[min(k0 + 32 * kb + r32, T - 1)] : 0.f;
         csum[kb] = 0.f;
     }
 
@@ -554,60 +607,53 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
             for (int kb = 0; kb < NJ; ++kb) fk[kb] = __expf(m - bk[kb]);
         }
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            Frag tf[NJ], pf[NJ];
+        for (int qb = 0; qb < 2; ++qb) {
+            float g0[16];
+            row_values(g0, &gzt[buf][32 * qb], h);
+            f32x16 c[NJ], e[NJ];        // S and E = ghat V^T + gz: query 32 qb + 8 k + 4 h + r, key 32 kb + r32
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb) {
-                const int qb = 2 * s + jb;
-                bf16x8 qa[NK], ga[NK];
+            for (int kb = 0; kb < NJ; ++kb) {
+                c[kb] = splat16(0.f);
 #pragma unroll
-                for (int ks = 0; ks < NK; ++ks) {
-                    qa[ks] = row_frag<HD>(qt[buf], qb, ks, r16, g);
-                    ga[ks] = row_frag<HD>(gt[buf], qb, ks, r16, g);
-                }
-                const float4 gz4 = *(const float4*)&gzt[buf][16 * qb + 4 * g];
-                const f32x4 e0 = {gz4.x, gz4.y, gz4.z, gz4.w};
-                float4 gq = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (GATED) gq = *(const float4*)(DIAG ? &gtile[buf].b[16 * qb + 4 * g] : &gtile[buf].f[16 * qb + 4 * g]);
-                const float gqr[4] = {gq.x, gq.y, gq.z, gq.w};
-#pragma unroll
-                for (int kb = 0; kb < NJ; ++kb) {
-                    f32x4 c = {0.f, 0.f, 0.f, 0.f}, e = e0;   // query 16 qb + 4g + r, key 16 kb + r16
-#pragma unroll
-                    for (int ks = 0; ks < NK; ++ks) {
-                        c = mfma16(qa[ks], kf[kb][ks], c);    // S
-                        e = mfma16(ga[ks], vf[kb][ks], e);    // E = ghat V^T + gz
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float sc = scale * c[r];
-                        const float pw = ipow<P - 1>(sc);
-                        float a = pw * sc, tv = e[r] * pscale * pw;
-                        if (GATED) {
-                            const float gg = DIAG ? __expf(gqr[r] - bk[kb]) : gqr[r] * fk[kb];
-                            a *= gg;
-                            tv *= gg;
-                        }
-                        if (DIAG && q0 + 16 * qb + 4 * g + r < k0 + 16 * kb + r16) {
-                            a = 0.f;
-                            tv = 0.f;
-                        }
-                        if (GATED) csum[kb] += e[r] * a;
-                        pf[kb].v[4 * jb + r] = (__bf16)a;
-                        tf[kb].v[4 * jb + r] = (__bf16)tv;
-                    }
-                }
+                for (int i = 0; i < 16; ++i) e[kb][i] = g0[i];
             }
 #pragma unroll
-            for (int fb = 0; fb < NF; ++fb) {
-                const bf16x8 qc = col_frag<HD>(qt[buf], s, fb, r16, g);   // Q^T
-                const bf16x8 gc = col_frag<HD>(gt[buf], s, fb, r16, g);   // ghat^T
+            for (int ks = 0; ks < NK; ++ks) {
+                const bf16x8 qa = row_frag<HD>(qt[buf], qb, ks, lane), ga = row_frag<HD>(gt[buf], qb, ks, lane);
 #pragma unroll
                 for (int kb = 0; kb < NJ; ++kb) {
-                    dk[fb][kb] = mfma16(qc, tf[kb].v, dk[fb][kb]);
-                    dv[fb][kb] = mfma16(gc, pf[kb].v, dv[fb][kb]);
+                    c[kb] = mfma32(qa, kf[kb][ks], c[kb]);
+                    e[kb] = mfma32(ga, vf[kb][ks], e[kb]);
                 }
             }
+            Frag tf[NJ][2], pf[NJ][2];
+            float gq[16];
+            if (GATED) row_values(gq, DIAG ? &gtile[buf].b[32 * qb] : &gtile[buf].f[32 * qb], h);
+#pragma unroll
+            for (int kb = 0; kb < NJ; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    float pw = ipow<P - 1>(c[kb][i]);
+                    if (GATED) pw *= DIAG ? __expf(gq[i] - bk[kb]) : gq[i] * fk[kb];
+                    if (DIAG && q0 + 32 * qb + 8 * (i >> 2) + 4 * h + (i & 3) < k0 + 32 * kb + r32) pw = 0.f;
+                    // (p = 4 without gates or mask: the square's square is one multiply less deep than c^3 c)
+                    const float a = P == 4 && !GATED && !DIAG ? ipow<P>(c[kb][i]) : pw * c[kb][i];
+                    if (GATED) csum[kb] += e[kb][i] * a;
+                    pf[kb][i >> 3].v[i & 7] = (__bf16)a;
+                    tf[kb][i >> 3].v[i & 7] = (__bf16)(e[kb][i] * pw);
+                }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int fb = 0; fb < NF; ++fb) {
+                    const bf16x8 qc = col_frag<HD>(qt[buf], 2 * qb + j, fb, lane);   // Q^T
+                    const bf16x8 gc = col_frag<HD>(gt[buf], 2 * qb + j, fb, lane);   // ghat^T
+#pragma unroll
+                    for (int kb = 0; kb < NJ; ++kb) {
+                        dk[fb][kb] = mfma32(qc, tf[kb][j].v, dk[fb][kb]);
+                        dv[fb][kb] = mfma32(gc, pf[kb][j].v, dv[fb][kb]);
+                    }
+                }
         }
     };
 
@@ -649,7 +695,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
             for (int kb = 0; kb < NJ; ++kb) v += csum[kb];
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-            if (iblk > jblk && lane == 0) wsum[(((size_t)blockIdx.y * nblk + jblk) * nblk + iblk) * 4 + w] = v - wprev;
+            if (iblk > jblk && lane == 0) wsum[(((size_t)blockIdx.x * nblk + jblk) * nblk + iblk) * 4 + w] = sp * (v - wprev);
             wprev = v;
         }
         if (t + 1 < ntile) {
@@ -664,41 +710,26 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
     if (!active) return;
 #pragma unroll
     for (int kb = 0; kb < NJ; ++kb) {
-        const bool in = k0 + 16 * kb + r16 < T;
-        const size_t row = head + min(k0 + 16 * kb + r16, T - 1);
-        if (CHUNKED) {
-            const size_t slab_stride = (size_t)gridDim.y * T * HD;
-            for (int sl = 0; sl < ck.nslab; ++sl)
-#pragma unroll
-                for (int fb = 0; fb < NF; ++fb) {
-                    const float4 pv = *(const float4*)(ck.part + sl * slab_stride + row * HD + 16 * fb + 4 * g);
-                    dk[fb][kb][0] += pv.x; dk[fb][kb][1] += pv.y; dk[fb][kb][2] += pv.z; dk[fb][kb][3] += pv.w;
-                }
-            for (int sl = 0; sl < ck.nslab2; ++sl)
-#pragma unroll
-                for (int fb = 0; fb < NF; ++fb) {
-                    const float4 pv = *(const float4*)(ck.part2 + sl * slab_stride + row * HD + 16 * fb + 4 * g);
-                    dv[fb][kb][0] += pv.x; dv[fb][kb][1] += pv.y; dv[fb][kb][2] += pv.z; dv[fb][kb][3] += pv.w;
-                }
-        }
+        const bool in = k0 + 32 * kb + r32 < T;
+        const size_t row = head + min(k0 + 32 * kb + r32, T - 1);
+        const size_t slab_stride = (size_t)gridDim.x * T * HD;
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) {
-            bf16x4 a, b;
+            if (CHUNKED) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                a[r] = (__bf16)dk[fb][kb][r];
-                b[r] = (__bf16)dv[fb][kb][r];
+                for (int i = 0; i < 16; ++i) {
+                    dk[fb][kb][i] *= psp;
+                    dv[fb][kb][i] *= sp;
+                }
+                add_parts(dk[fb][kb], ck.part + row * HD + 32 * fb, slab_stride, ck.nslab, h);
+                add_parts(dv[fb][kb], ck.part2 + row * HD + 32 * fb, slab_stride, ck.nslab2, h);
             }
-            if (in) {
-                *(bf16x4*)(dK + row * HD + 16 * fb + 4 * g) = a;
-                *(bf16x4*)(dV + row * HD + 16 * fb + 4 * g) = b;
-            }
+            store_block(dK + row * HD + 32 * fb, dk[fb][kb], CHUNKED ? 1.f : psp, h, in);
+            store_block(dV + row * HD + 32 * fb, dv[fb][kb], CHUNKED ? 1.f : sp, h, in);
         }
         if (GATED) {
-            float dot = csum[kb];
-            dot += __shfl_xor(dot, 16);
-            dot += __shfl_xor(dot, 32);
-            if (in && g == 0) kdk[row] = (float)P * dot;
+            const float dot = psp * xor32_sum(csum[kb]);
+            if (in && h == 0) kdk[row] = dot;
         }
     }
 }
@@ -739,15 +770,16 @@ __global__ __launch_bounds__(64) void k_attn_gate_cols(const float* __restrict__
     xb[(size_t)bh * nblk + m] = acc;
 }
 
-// Rows of the block one wave owns and the waves per SIMD the kernel is compiled for.  Two waves
-// per SIMD (at most 256 registers) let one wave's vector-ALU work run under the other's MFMAs
-// and are worth more than the larger block: measured, dK / dV at d = 64 take 1.05 ms with 32 keys
-// per wave and two waves against 1.58 ms with 64 keys and one.  Only dK / dV at d = 128 (192
-// registers of operands and accumulators per wave) cannot fit two.
+// Rows of the block one wave owns and the waves per SIMD the kernel is compiled for, measured on MI355X.  At d = 64 the
+// 32-row waves read twice the LDS bytes per flop and are the faster ones all the same, because two to three of them share
+// a SIMD without spilling (4 heads of 16384 tokens, p = 3: forward 241 us against 277 with 64 rows; dQ 322 against 375
+// with 64 rows and one wave per SIMD, 877 with 64 rows and spills; dK / dV 437 against 504 with 64 keys and one wave).
+// At d = 32 the operands are half the size and 64 rows fit two waves (16 heads of 16384 tokens, p = 4: 330 / 445 / 587 us
+// against 336 / 463 / 620 with 32).  Only dK / dV at d = 128 (192 registers of operands and accumulators) runs alone.
 template <int HD>
 struct Shape {
-    static constexpr int FWD_OWN = HD == 128 ? 32 : 64, FWD_WPE = 2;
-    static constexpr int DQ_OWN = HD == 128 ? 32 : 64, DQ_WPE = 2;
+    static constexpr int FWD_OWN = HD == 32 ? 64 : 32, FWD_WPE = 2;
+    static constexpr int DQ_OWN = HD == 32 ? 64 : 32, DQ_WPE = 2;
     static constexpr int DKDV_OWN = HD == 32 ? 64 : 32, DKDV_WPE = HD == 128 ? 1 : 2;
 };
 
@@ -758,7 +790,7 @@ bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf1
     auto kern = k_attn_fwd<P, HD, Shape<HD>::FWD_OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
     LaunchScope ls(CHUNKED ? "chunk_fwd" : "attn_fwd", s);
-    hipLaunchKernelGGL(kern, dim3((T + WG - 1) / WG, BH), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T, scale, normalize,
+    hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T, scale, normalize,
                        bl, ck);
     return launch_ok();
 }
@@ -781,7 +813,7 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         auto kern = k_attn_dkdv<P, HD, Shape<HD>::DKDV_OWN, Shape<HD>::DKDV_WPE, GATED, CHUNKED>;
         if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
         LaunchScope ls(CHUNKED ? "chunk_bwd_dkdv" : "attn_bwd_dkdv", s);
-        hipLaunchKernelGGL(kern, dim3((T + WG - 1) / WG, BH), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dK, dV, T,
+        hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dK, dV, T,
                            scale, bl, gate.kdk, gate.wsum, ckk);
         if (!launch_ok()) return false;
         if (GATED) {
@@ -797,7 +829,7 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         auto kern = k_attn_dq<P, HD, Shape<HD>::DQ_OWN, Shape<HD>::DQ_WPE, GATED, CHUNKED>;
         if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
         LaunchScope ls(CHUNKED ? "chunk_bwd_dq" : "attn_bwd_dq", s);
-        hipLaunchKernelGGL(kern, dim3((T + WG - 1) / WG, BH), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, T, scale,
+        hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, T, scale,
                            bl, gate.qdq, ckq);
         if (!launch_ok()) return false;
     }
