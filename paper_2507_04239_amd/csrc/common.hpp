@@ -105,6 +105,13 @@ pa_status generic_fwd(const Ctx& c, const void* Q, const void* K, const void* V,
 pa_status generic_bwd(const Ctx& c, const void* Q, const void* K, const void* V, const void* O, const float* Z,
                       const void* dO, void* dQ, void* dK, void* dV);
 
+// float32 attention form on the matrix cores: what the generic entries run instead of the chunked kernels where it is the
+// faster one (c.ws: B H T floats for the backward pass)
+bool f32_attn_applies(const pa_problem& pr);
+bool f32_attn_fwd(const Ctx& c, const float* Q, const float* K, const float* V, float* O, float* Z);
+bool f32_attn_bwd(const Ctx& c, const float* Q, const float* K, const float* V, const float* O, const float* Z, const float* dO,
+                  float* dQ, float* dK, float* dV);
+
 // bf16 MFMA family (p = 2)
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward);
 long long mfma_state_rows(const pa_problem& pr);

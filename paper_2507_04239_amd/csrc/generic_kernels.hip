@@ -784,11 +784,16 @@ long long generic_state_rows(const pa_problem& pr) { return comb_ll(pr.d + pr.p 
 size_t generic_workspace_bytes(const pa_problem& pr, bool backward) { return make_layout(pr, backward).total; }
 
 pa_status generic_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z) {
+    if (f32_attn_applies(c.prob))
+        return f32_attn_fwd(c, (const float*)Q, (const float*)K, (const float*)V, (float*)O, Z) ? PA_OK : PA_ERR_HIP;
     return dispatch(false, c, Q, K, V, nullptr, nullptr, nullptr, O, Z, nullptr, nullptr, nullptr);
 }
 
 pa_status generic_bwd(const Ctx& c, const void* Q, const void* K, const void* V, const void* O, const float* Z,
                       const void* dO, void* dQ, void* dK, void* dV) {
+    if (f32_attn_applies(c.prob))
+        return f32_attn_bwd(c, (const float*)Q, (const float*)K, (const float*)V, (const float*)O, Z, (const float*)dO, (float*)dQ,
+                            (float*)dK, (float*)dV) ? PA_OK : PA_ERR_HIP;
     return dispatch(true, c, Q, K, V, O, Z, dO, nullptr, nullptr, dQ, dK, dV);
 }
 
