@@ -14,7 +14,7 @@
 //     part  [B*H][nblk][v+1]             partial read-outs of the step in flight
 // A step reads and writes S and gamma once: it is bound by HBM bandwidth, 8 bytes per state
 // element and token.
-#include "common.hpp"
+#include "mfma_common.hpp"
 
 namespace pa {
 namespace {
@@ -269,6 +269,209 @@ __global__ __launch_bounds__(256) void k_decode_absorb(const T* __restrict__ K, 
     if (xg == 0) *grow = accz;
 }
 
+// The same for p = 2, bf16 tokens, d = v in {32, 64, 128} on the matrix cores, with nothing rounded below float32.
+// The product k_i k_j of two bf16 numbers has at most 16 significant bits, so it is exactly the sum of two bf16 numbers
+// (its upper and its lower half), and the two MFMAs that contract the halves with the values form the float32 sum of exact
+// products.  With gates the product carries its token's decay to the end of the 64-token tile, is a float32 number like any
+// other and takes three parts; the accumulators decay from tile to tile.  The sum over the prompt joins the state, which
+// has decayed across the whole prompt, at the end.
+//
+// A state row is a pair i <= j.  A wave owns the rows of 16 consecutive j (operand row = j) for 2 consecutive i: k_j for 8
+// tokens per lane is formed once per 32 tokens and multiplied by two broadcast k_i.  Eight such waves share the staged tokens
+// (four waves of 4 i each take 169 us at the size below: too few waves to cover the LDS and MFMA latency).  Tokens are staged feature-major, so
+// that every operand is one 16-byte LDS read.  Blocks on the diagonal also form the pairs j < i and drop them (23 % more
+// products at d = 64).  The vector ALU (4 operations per product and lane) and the matrix pipe are loaded
+// about equally, each less than half of the time; the rest is the chain barrier, LDS read, product, MFMA of a tile.
+// MI355X, B4 H12 T3000 d64: 2160 us on the vector ALUs (k_decode_absorb, one thread per row and 4 columns) -> 156 us.
+constexpr int AXT = 64;         // tokens per tile
+constexpr int AXP = AXT + 8;    // pitch of a feature's tokens: 16 rows read 16 bytes each from distinct banks
+template <int HD>
+struct AbsorbTile {
+    bf16_t k[HD][AXP], v[HD][AXP];
+    float w[AXT];               // decay of each token to the end of the tile
+};
+// the units of a head: (j block, i pair) with the pair not beyond the block's last row
+template <int HD>
+constexpr int absorb_units() {
+    return (HD / 16) * (HD / 16 + 1) * 4;
+}
+template <int HD, bool GATED>
+__global__ __launch_bounds__(512, HD == 128 ? 2 : 4) void k_decode_absorb_mfma(const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+                                                               const float* __restrict__ log_g, float* __restrict__ S,
+                                                               float* __restrict__ gam, long long D, int Tlen) {
+    using namespace mfma;
+    constexpr int NV = HD / 16, NP = GATED ? 3 : 2, NI = 2;
+    constexpr int NPC = (HD + 63) / 64;     // pieces of 8 features per thread and operand (d = 32: of the first four waves)
+    extern __shared__ __attribute__((aligned(16))) unsigned char absorb_smem[];
+    AbsorbTile<HD>* tiles = reinterpret_cast<AbsorbTile<HD>*>(absorb_smem);      // [2]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, g = lane >> 4;
+    const size_t bh = blockIdx.y;
+    int unit = 8 * (int)blockIdx.x + w, jb = 0;       // jb has 8 jb + 8 pairs
+    while (unit >= 8 * jb + 8) unit -= 8 * jb++ + 8;
+    const int j0 = 16 * jb, i0 = NI * unit;
+    const bf16_t *Kh = K + bh * Tlen * HD, *Vh = V + bh * Tlen * HD;
+
+    f32x4 acc[NI][NV], accz[NI];
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii) {
+        accz[ii] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int vb = 0; vb < NV; ++vb) acc[ii][vb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    Frag ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones.v[e] = (__bf16)1.f;
+
+    // thread: token `lane` of the tile, features 8 (NPC w + c) .. + 7.  Tokens past the end are zeros (log-gate 0).
+    Frag kr[NPC], vr[NPC];
+    float lg = 0.f, decay = 1.f;
+    auto load = [&](int t0) {
+        const int t = t0 + lane;
+        const size_t off = (size_t)min(t, Tlen - 1) * HD + 8 * NPC * w;
+        if (GATED) lg = t < Tlen ? log_g[bh * Tlen + t] : 0.f;
+        if (HD == 32 && w >= 4) return;
+#pragma unroll
+        for (int c = 0; c < NPC; ++c) {
+            kr[c].u = *(const uint4*)(Kh + off + 8 * c);
+            vr[c].u = *(const uint4*)(Vh + off + 8 * c);
+            if (t >= Tlen) kr[c].u = vr[c].u = make_uint4(0, 0, 0, 0);
+        }
+    };
+    float tile_decay = 1.f;     // across the tile that `store` was last called for
+    auto store = [&](AbsorbTile<HD>& dst) {
+        if (HD != 32 || w < 4)
+#pragma unroll
+        for (int c = 0; c < NPC; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int f = 8 * (NPC * w + c) + e;
+                dst.k[f][lane] = (bf16_t)(((e & 1) ? kr[c].q[e / 2] >> 16 : kr[c].q[e / 2]) & 0xffffu);
+                dst.v[f][lane] = (bf16_t)(((e & 1) ? vr[c].q[e / 2] >> 16 : vr[c].q[e / 2]) & 0xffffu);
+            }
+        if (GATED) {
+            float s = lg;       // sum of the log-gates of this token and those after it in the tile
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const float o = __shfl_down(s, off);
+                if (lane + off < 64) s += o;
+            }
+            tile_decay = expf(__shfl(s, 0));
+            const float after = __shfl_down(s, 1);
+            if (w == 0) dst.w[lane] = lane < 63 ? expf(after) : 1.f;
+        }
+    };
+
+    load(0);
+    store(tiles[0]);
+    float cur_decay = tile_decay;
+    __syncthreads();
+    int buf = 0;
+    for (int t0 = 0; t0 < Tlen; t0 += AXT, buf ^= 1) {
+        const bool more = t0 + AXT < Tlen;
+        if (more) load(t0 + AXT);
+        const AbsorbTile<HD>& tl = tiles[buf];
+        if (GATED) {
+            decay *= cur_decay;
+#pragma unroll
+            for (int ii = 0; ii < NI; ++ii) {
+                accz[ii] *= cur_decay;
+#pragma unroll
+                for (int vb = 0; vb < NV; ++vb) acc[ii][vb] *= cur_decay;
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < AXT; ks += 32) {
+            Frag f;
+            f.u = *(const uint4*)&tl.k[j0 + r16][ks + 8 * g];
+            float kj[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) kj[e] = (e & 1) ? bf_hi(f.q[e / 2]) : bf_lo(f.q[e / 2]);
+            if (GATED) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) kj[e] *= tl.w[ks + 8 * g + e];
+            }
+            Frag vf[NV];
+#pragma unroll
+            for (int vb = 0; vb < NV; ++vb) vf[vb].u = *(const uint4*)&tl.v[16 * vb + r16][ks + 8 * g];
+#pragma unroll
+            for (int ii = 0; ii < NI; ++ii) {
+                Frag fi, part[NP];
+                fi.u = *(const uint4*)&tl.k[i0 + ii][ks + 8 * g];
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    float x0 = kj[e] * bf_lo(fi.q[e / 2]), x1 = kj[e + 1] * bf_hi(fi.q[e / 2]);
+#pragma unroll
+                    for (int n = 0; n < NP; ++n) {      // the upper 16 bits of both, then what is left
+                        const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+                        part[n].q[e / 2] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+                        if (n + 1 < NP) {
+                            x0 -= __uint_as_float(u0 & 0xffff0000u);
+                            x1 -= __uint_as_float(u1 & 0xffff0000u);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int n = 0; n < NP; ++n) {
+                    accz[ii] = mfma16(part[n].v, ones.v, accz[ii]);
+#pragma unroll
+                    for (int vb = 0; vb < NV; ++vb) acc[ii][vb] = mfma16(part[n].v, vf[vb].v, acc[ii][vb]);
+                }
+            }
+        }
+        if (more) store(tiles[buf ^ 1]);
+        cur_decay = tile_decay;
+        __syncthreads();
+    }
+    // acc[ii][vb][r]: i = i0 + ii, j = j0 + 4 g + r, column 16 vb + r16
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + ii, j = j0 + 4 * g + r;
+            if (j < i) continue;
+            const size_t row = bh * D + (size_t)(i * HD - i * (i - 1) / 2 + j - i);
+            const float m = i == j ? 1.f : 2.f;
+#pragma unroll
+            for (int vb = 0; vb < NV; ++vb) {
+                float* dst = S + row * HD + 16 * vb + r16;
+                *dst = decay * *dst + m * acc[ii][vb][r];
+            }
+            if (r16 == 0) gam[row] = decay * gam[row] + m * accz[ii][r];
+        }
+}
+
+template <int HD, bool GATED>
+bool absorb_mfma_t(const pa_problem& pr, const DecodeLayout& L, const void* K, const void* V, const float* log_g, char* st,
+                   hipStream_t s) {
+    static_assert(absorb_units<HD>() % 8 == 0, "whole workgroups");
+    constexpr size_t smem = 2 * sizeof(AbsorbTile<HD>);
+    auto kern = k_decode_absorb_mfma<HD, GATED>;
+    if (smem > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) {
+            note_hip_error(e, "hipFuncSetAttribute(max dynamic LDS)");
+            return false;
+        }
+    }
+    LaunchScope ls("decode_absorb", s);
+    hipLaunchKernelGGL(kern, dim3(absorb_units<HD>() / 8, pr.B * pr.H), dim3(512), smem, s, (const bf16_t*)K, (const bf16_t*)V, log_g,
+                       (float*)(st + L.off_s), (float*)(st + L.off_gam), L.D, pr.T);
+    return launch_ok();
+}
+bool absorb_mfma_applies(const pa_problem& pr) {
+    return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && pr.d == pr.v && (pr.d == 32 || pr.d == 64 || pr.d == 128);
+}
+bool absorb_mfma(const pa_problem& pr, const DecodeLayout& L, const void* K, const void* V, const float* log_g, char* st,
+                 hipStream_t s) {
+#define PA_GO(DD)                                                                  \
+    if (pr.d == DD)                                                                \
+        return log_g != nullptr ? absorb_mfma_t<DD, true>(pr, L, K, V, log_g, st, s) \
+                                : absorb_mfma_t<DD, false>(pr, L, K, V, log_g, st, s);
+    PA_GO(32) PA_GO(64) PA_GO(128)
+#undef PA_GO
+    return false;
+}
+
 // grid B*H: sums the blocks' partial read-outs, divides, stores
 template <typename T>
 __global__ __launch_bounds__(256) void k_decode_finish(const float* __restrict__ part, int nblk, T* __restrict__ o,
@@ -373,8 +576,12 @@ size_t decode_absorb_workspace_bytes(const pa_problem& pr) {
     return decode_supported(pr) == PA_OK ? mfma_absorb_workspace_bytes(pr) : 0;
 }
 
-// With a workspace, and where the matrix-core scan applies, the prompt goes through that (the sums are then
-// rounded to bf16 once, like the chunk states of the forward pass); else through the float32 kernel above.
+// With a workspace, and where the matrix-core scan applies, the prompt goes through that (the sums are then rounded to bf16
+// once, like the chunk states of the forward pass).  The exact matrix-core kernel runs every other bf16, p = 2 prompt.  At
+// d = 64 the scan is the faster one for long prompts of few heads (12 heads of 65536 tokens: 579 us against 1896; 12 of 2048:
+// 45 against 70) and the exact kernel for short ones (48 heads of 512: 39 against 77), but which of the two rounds its sums is
+// the caller's choice, made with the workspace, so the line does not follow the time.  The rest takes the float32 kernel on the
+// vector ALUs.
 pa_status decode_absorb(const pa_problem& pr, const void* K, const void* V, const float* log_g, void* state, void* ws,
                         size_t ws_bytes, hipStream_t s) {
     pa_status st = decode_supported(pr);
@@ -383,6 +590,7 @@ pa_status decode_absorb(const pa_problem& pr, const void* K, const void* V, cons
     if (ws != nullptr && mfma_absorb_supported(pr) && ws_bytes >= mfma_absorb_workspace_bytes(pr))
         return mfma_absorb(pr, K, V, log_g, (char*)ws, s, (float*)((char*)state + L.off_s), (float*)((char*)state + L.off_gam),
                            (int)L.D);
+    if (absorb_mfma_applies(pr)) return absorb_mfma(pr, L, K, V, log_g, (char*)state, s) ? PA_OK : PA_ERR_HIP;
     const bool ok = pr.dtype == PA_DTYPE_F32 ? launch_absorb_p<float>(pr, L, K, V, log_g, (char*)state, s)
                                              : launch_absorb_p<bf16_t>(pr, L, K, V, log_g, (char*)state, s);
     return ok ? PA_OK : PA_ERR_HIP;
