@@ -48,6 +48,7 @@ def algorithmic_flops(w):
     f["chunk_fwd"] = pairs * (2 * d + 2 * (v + 1))
     f["chunk_dq"] = pairs * (4 * d + 2 * v + 2)
     f["chunk_dkdv"] = pairs * (2 * d + 2 * v)
+    f["pairs_bwd"] = f["chunk_dq"] + f["chunk_dkdv"]                      # both in one launch
     # tiled kernels: each state contraction is a launch of its own, the in-chunk parts run on the chunk_* kernels
     f["query_state"] = state
     f["dphi"] = state
@@ -55,6 +56,9 @@ def algorithmic_flops(w):
     f["recompute"] = 0   # a backward pass that rebuilds the chunk states: executed, not credited
     f["fwd_total"] = f["update_state"] + f["fwd_chunk"]
     f["bwd_total"] = f["state_grad"] + f["bwd_dq"] + f["bwd_dkdv"]
+    # float32 attention form, whatever the chunk: credited what the chunked form would need, the state gradient with dK / dV
+    f["f32_dq"] = f["bwd_dq"]
+    f["f32_dkdv"] = f["state_grad"] + f["bwd_dkdv"]
     return f
 
 
@@ -84,6 +88,9 @@ def algorithmic_bytes(w):
         "walk_fwd": 3 * tok + BH * T * v * 4, "walk_dq": 4 * tok + BH * T * d * 4,
         "walk_dv": 3 * tok + BH * T * v * 4, "walk_dk": 4 * tok + BH * T * d * 4,
         "chunk_fwd": 4 * tok + BH * T * 4, "chunk_dq": 5 * tok + BH * T * 4, "chunk_dkdv": 7 * tok + BH * T * 4,
+        "pairs_bwd": 8 * tok + BH * T * 4,
+        # float32 attention form: no states
+        "fwd_total": 4 * tok + BH * T * 4, "f32_dq": 6 * tok + 2 * BH * T * 4, "f32_dkdv": 6 * tok + 2 * BH * T * 4,
         # tiled kernels: the states once, the token rows in, the float32 result out
         "query_state": states + tok + BH * T * (v + 1) * 4, "dphi": states + 2 * tok + BH * T * d * 4,
         "dv_readout": states + tok + BH * T * v * 4,
@@ -97,6 +104,9 @@ KERNEL_ROLE = {
     "generic_state_scan_reverse": ("state_grad", PEAK_FP32_VECTOR_TFLOPS),
     "generic_bwd_dq": ("bwd_dq", PEAK_FP32_VECTOR_TFLOPS),
     "generic_bwd_dkdv": ("bwd_dkdv", PEAK_FP32_VECTOR_TFLOPS),
+    "f32_attn_fwd": ("fwd_total", PEAK_FP32_VECTOR_TFLOPS),   # (the float32 matrix instructions' peak is the same)
+    "f32_attn_dq": ("f32_dq", PEAK_FP32_VECTOR_TFLOPS),
+    "f32_attn_dkdv": ("f32_dkdv", PEAK_FP32_VECTOR_TFLOPS),
     "mfma_state_scan": ("update_state", PEAK_BF16_MFMA_TFLOPS),
     "mfma_state_scan_bwd": ("recompute", PEAK_BF16_MFMA_TFLOPS),
     "mfma_fwd_chunk": ("fwd_chunk", PEAK_BF16_MFMA_TFLOPS),
@@ -120,10 +130,12 @@ KERNEL_ROLE = {
     "tiled_dv": ("dv_readout", PEAK_BF16_MFMA_TFLOPS),
     "mfma_fwd_chunk_partial": ("chunk_fwd", PEAK_BF16_MFMA_TFLOPS),
     "chunk_fwd": ("chunk_fwd", PEAK_BF16_MFMA_TFLOPS),
+    "chunk_bwd": ("pairs_bwd", PEAK_BF16_MFMA_TFLOPS),
     "chunk_bwd_dq": ("chunk_dq", PEAK_BF16_MFMA_TFLOPS),
     "chunk_bwd_dkdv": ("chunk_dkdv", PEAK_BF16_MFMA_TFLOPS),
     # attention form (one chunk, no state): the same formulas with n = 1
     "attn_fwd": ("fwd_chunk", PEAK_BF16_MFMA_TFLOPS),
+    "attn_bwd": ("pairs_bwd", PEAK_BF16_MFMA_TFLOPS),
     "attn_bwd_dq": ("bwd_dq", PEAK_BF16_MFMA_TFLOPS),
     "attn_bwd_dkdv": ("bwd_dkdv", PEAK_BF16_MFMA_TFLOPS),
 }

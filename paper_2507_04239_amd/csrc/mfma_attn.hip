@@ -28,7 +28,7 @@
 // applied to the accumulators once, at the end.  (Per pair at p = 2: forward 1 multiply and half a conversion instead of
 // 2.5 instructions, dQ 1.5 instead of 3.5.)
 //
-// Forward + backward, before and after the 32x32 form, the scale's removal and the order of the workgroups (heavy_first):
+// Forward + backward, before and after the 32x32 form, the scale's removal and the order of the workgroups:
 // p = 4, d = 32, B2 H8 T16384: 2.43 -> 1.40 ms; p = 3, d = 64, B1 H4 T16384: 1.25 -> 0.89 ms; p = 2, d = 64, B16 H12
 // T1000: 0.260 -> 0.175 ms.
 #include <type_traits>
@@ -192,9 +192,6 @@ __device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, i
 // of every head come before the next ones.  (With the blocks of one head after the other, the last heads' long walks
 // started when most of the chip was done: at 16 heads of 16384 tokens the CUs were busy 62 % of the time, and the p = 4
 // kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)
-__device__ __forceinline__ int heavy_first(int nblocks, bool longest_is_last) {
-    return longest_is_last ? nblocks - 1 - (int)blockIdx.y : (int)blockIdx.y;
-}
 
 // ---- forward ----------------------------------------------------------------------------------------
 // acc[vb][ib] = O^T: value columns 32 vb + .., query 32 ib + r32 of the wave's OWN queries.
@@ -221,7 +218,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
-    const int i0 = heavy_first(nblk, true) * WG;
+    const int i0 = (nblk - 1 - (int)blockIdx.y) * WG;
     const int q0 = i0 + OWN * w;                    // the wave's first query
     const bool active = q0 < T;
     const size_t head = (size_t)blockIdx.x * T;
@@ -393,8 +390,8 @@ __global__ __launch_bounds__(256) void k_attn_prep(const bf16_t* __restrict__ dO
 
 // ---- backward: dQ -----------------------------------------------------------------------------------
 // acc[fb][ib] = dQ^T: features 32 fb + .., query 32 ib + r32.
-template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
-__global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
+__device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                  const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                  const float* __restrict__ gz, bf16_t* __restrict__ dQ, int T,
                                                  float scale, const float* __restrict__ bl, float* __restrict__ qdq,
@@ -406,7 +403,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
-    const int i0 = heavy_first(nblk, true) * WG;
+    const int i0 = (nblk - 1 - rank) * WG;
     const int q0 = i0 + OWN * w;
     const bool active = q0 < T;
     const size_t head = (size_t)blockIdx.x * T;
@@ -547,8 +544,8 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dq(const bf16_t* __restrict__
 // dk[fb][kb] = dK^T: features 32 fb + .., key 32 kb + r32 of the wave's OWN keys; dv likewise.
 // S and E are formed queries x keys here, so that their accumulators are the B operand (k-slots =
 // queries) of the two contractions over the queries.
-template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
-__global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
+__device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                    const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                    const float* __restrict__ gz, bf16_t* __restrict__ dK,
                                                    bf16_t* __restrict__ dV, int T, float scale,
@@ -561,7 +558,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
     float(*gzt)[AT] = reinterpret_cast<float(*)[AT]>(gt + 2);           // [2][AT]
     GateTile* gtile = reinterpret_cast<GateTile*>(gzt + 2);             // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
-    const int j0 = heavy_first((T + WG - 1) / WG, false) * WG;
+    const int j0 = rank * WG;
     const int k0 = j0 + OWN * w;                    // the wave's first key
     const bool active = k0 < T;
     const size_t head = (size_t)blockIdx.x * T;
@@ -734,6 +731,27 @@ __global__ __launch_bounds__(256, WPE) void k_attn_dkdv(const bf16_t* __restrict
     }
 }
 
+// One launch for both halves of the backward pass, or for one of them; `rank` counts the blocks from the longest walk down.
+// Both: blocks of either kind alternate, so that the tail of one is filled by the other.  A walk is a serial chain (a lone wave
+// takes 4 times the MFMA time for a tile), and with few workgroups the longest one sets a kernel's time.  Backward pass, dK / dV
+// and then dQ -> one launch: p = 3, d = 64, 2 heads of 16384 tokens 577 -> 370 us, 4 heads 681 -> 599; p = 2, 12 heads of 4096
+// 166 -> 115, 24 heads 210 -> 200; p = 4, d = 32, 4 heads of 16384 604 -> 396.
+enum class Bwd { dkdv, dq, both };
+template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED, Bwd WHAT>
+__global__ __launch_bounds__(256, WPE) void k_attn_bwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+                                                       const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
+                                                       const float* __restrict__ gz, bf16_t* __restrict__ dQ,
+                                                       bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int T, float scale,
+                                                       const float* __restrict__ bl, float* __restrict__ qdq,
+                                                       float* __restrict__ kdk, float* __restrict__ wsum, ChunkedIn ckq,
+                                                       ChunkedIn ckk) {
+    const int rank = WHAT == Bwd::both ? (int)blockIdx.y >> 1 : (int)blockIdx.y;
+    if (WHAT == Bwd::dq || (WHAT == Bwd::both && (blockIdx.y & 1)))
+        dq_block<P, HD, OWN, GATED, CHUNKED>(rank, Q, K, V, Gh, gz, dQ, T, scale, bl, qdq, ckq);
+    else
+        dkdv_block<P, HD, OWN, GATED, CHUNKED>(rank, Q, K, V, Gh, gz, dK, dV, T, scale, bl, kdk, wsum, ckk);
+}
+
 template <int HD>
 constexpr size_t attn_smem_bytes() {
     return 4 * sizeof(AttnTile<HD>) + 2 * AT * sizeof(float) + 2 * sizeof(GateTile);
@@ -808,31 +826,38 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
                            normalize);
         if (!launch_ok()) return false;
     }
-    {
-        constexpr int WG = 4 * Shape<HD>::DKDV_OWN;
-        auto kern = k_attn_dkdv<P, HD, Shape<HD>::DKDV_OWN, Shape<HD>::DKDV_WPE, GATED, CHUNKED>;
+    constexpr int WG = 4 * Shape<HD>::DKDV_OWN;
+    static_assert(Shape<HD>::DQ_OWN == Shape<HD>::DKDV_OWN, "the blocks of dQ and dK / dV alternate in one grid");
+    const int nblk = (T + WG - 1) / WG;
+    auto launch = [&](auto what, const char* name, int wgs) {
+        constexpr Bwd W = decltype(what)::value;
+        constexpr int WPE = W == Bwd::dq ? Shape<HD>::DQ_WPE : Shape<HD>::DKDV_WPE;
+        auto kern = k_attn_bwd<P, HD, Shape<HD>::DKDV_OWN, WPE, GATED, CHUNKED, W>;
         if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
-        LaunchScope ls(CHUNKED ? "chunk_bwd_dkdv" : "attn_bwd_dkdv", s);
-        hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dK, dV, T,
-                           scale, bl, gate.kdk, gate.wsum, ckk);
-        if (!launch_ok()) return false;
-        if (GATED) {
-            const int nblk = T / WG;
-            LaunchScope ls2("attn_gate_boundary", s);
-            hipLaunchKernelGGL(k_attn_gate_rows, dim3((nblk + 63) / 64, BH), dim3(64), 0, s, gate.wsum, nblk);
-            hipLaunchKernelGGL(k_attn_gate_cols, dim3((nblk + 63) / 64, BH), dim3(64), 0, s, gate.wsum, gate.xb, nblk);
-            if (!launch_ok()) return false;
-        }
+        LaunchScope ls(name, s);
+        hipLaunchKernelGGL(kern, dim3(BH, wgs), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, T, scale, bl,
+                           gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
+        return launch_ok();
+    };
+    // One launch holds every wave to the registers of the larger half (d = 64: two waves of dQ per SIMD instead of three), which
+    // costs what the filled tail saves from 3 to 4 workgroups of each kind per CU on (d = 64, 24 heads of 4096 tokens, 768 of each
+    // kind: 210 us in two, 201 in one; T1000, 1536: 124 either way; 96 heads of 4096, 3072: 782 and 801; d = 32, 1024: 1065 and
+    // 1071).  At d = 128 dQ would lose
+    // half of its waves.
+    bool both = false;
+    if constexpr (HD < 128) {
+        both = (long long)BH * nblk <= 768 && 2 * nblk <= 65535;      // (and the grid's limit)
+        if (both && !launch(std::integral_constant<Bwd, Bwd::both>{}, CHUNKED ? "chunk_bwd" : "attn_bwd", 2 * nblk)) return false;
     }
-    {
-        constexpr int WG = 4 * Shape<HD>::DQ_OWN;
-        auto kern = k_attn_dq<P, HD, Shape<HD>::DQ_OWN, Shape<HD>::DQ_WPE, GATED, CHUNKED>;
-        if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
-        LaunchScope ls(CHUNKED ? "chunk_bwd_dq" : "attn_bwd_dq", s);
-        hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, T, scale,
-                           bl, gate.qdq, ckq);
+    if (!both && !launch(std::integral_constant<Bwd, Bwd::dkdv>{}, CHUNKED ? "chunk_bwd_dkdv" : "attn_bwd_dkdv", nblk)) return false;
+    if (GATED) {
+        const int ngate = T / WG;
+        LaunchScope ls2("attn_gate_boundary", s);
+        hipLaunchKernelGGL(k_attn_gate_rows, dim3((ngate + 63) / 64, BH), dim3(64), 0, s, gate.wsum, ngate);
+        hipLaunchKernelGGL(k_attn_gate_cols, dim3((ngate + 63) / 64, BH), dim3(64), 0, s, gate.wsum, gate.xb, ngate);
         if (!launch_ok()) return false;
     }
+    if (!both && !launch(std::integral_constant<Bwd, Bwd::dq>{}, CHUNKED ? "chunk_bwd_dq" : "attn_bwd_dq", nblk)) return false;
     return true;
 }
 
