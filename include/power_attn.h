@@ -87,7 +87,9 @@ typedef struct {
                            sequence padded with zero rows inside the workspace; elsewhere it is
                            PA_ERR_UNSUPPORTED */
     int   normalize;    /* 1: divide by the sum of the scores; 0: leave un-normalised */
-    float scale;        /* multiplies q.k before the power ("softmax scaling", App. E.1 step 2) */
+    float scale;        /* multiplies q.k before the power ("softmax scaling", App. E.1 step 2).  Some kernels multiply q
+                           (or k) by it, or by its power of two, before the product: q.k, scale q, scale k and the
+                           powers of scale q.k have to lie in the range of float32 (= that of bf16) */
     int   dtype;        /* pa_dtype of Q, K, V, O, dO, dQ, dK, dV; accumulation is always float32 */
     int   impl;         /* pa_impl */
     int   keep_state;   /* 0: power_attn_bwd rebuilds the chunk states itself (nothing but O and Z is

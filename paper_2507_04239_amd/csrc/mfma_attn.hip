@@ -23,14 +23,19 @@
 // 16 j + 4 h + r and 16 j + 8 + 4 h + r.  Against 16x16x32 the operands read per flop halve and a wave that has the SIMD
 // to itself still issues at the full rate (31 cycles per 16x16x32 MFMA otherwise).
 //
-// The vector ALU's share, per pair of tokens, is what bounds d = 32 and matters everywhere, so the scale stays out of it:
-// the kernels form c^p and e c^(p-1) from the plain c = q . k, and the factors scale^p (p scale^p for dQ and dK) are
-// applied to the accumulators once, at the end.  (Per pair at p = 2: forward 1 multiply and half a conversion instead of
-// 2.5 instructions, dQ 1.5 instead of 3.5.)
+// The vector ALU's share, per pair of tokens, is what bounds d = 32 and matters everywhere, so the scale stays out of it.
+// scale = fold * rest, fold a power of two and 1 <= |rest| < 2.  The operand of the scores that a wave holds for the whole
+// walk (Q; K for dK / dV) is multiplied by fold as it is loaded, exactly, so that the kernels' c is q . k at the magnitude of
+// the score s = rest c; they form c^p and e c^(p-1), and the factors rest^p (p fold rest^p for dQ and dK) are applied to the
+// accumulators once, at the end.  Powers and sums then overflow or vanish where those of s do, within rest^p < 16; with all of
+// scale^p left to the end they would where those of q . k or scale^p itself do.  (Per pair at p = 2: forward 1 multiply and
+// half a conversion instead of 2.5 instructions, dQ 1.5 instead of 3.5.)
 //
 // Forward + backward, before and after the 32x32 form, the scale's removal and the order of the workgroups:
 // p = 4, d = 32, B2 H8 T16384: 2.43 -> 1.40 ms; p = 3, d = 64, B1 H4 T16384: 1.25 -> 0.89 ms; p = 2, d = 64, B16 H12
 // T1000: 0.260 -> 0.175 ms.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "mfma_common.hpp"
@@ -103,6 +108,27 @@ __device__ __forceinline__ bf16x8 row_frag_global(const bf16_t* __restrict__ X, 
     Frag f;
     f.u = *(const uint4*)(X + row * HD + 16 * ks + 8 * h);
     return f.v;
+}
+
+// scale as fold * rest (see above)
+struct ScaleParts {
+    float fold, rest;
+};
+ScaleParts split_scale(float scale) {
+    if (!std::isfinite(scale)) return {1.f, scale};
+    int e = 0;
+    (void)std::frexp(scale, &e);
+    e = std::max(e - 1, -126);      // (a subnormal scale: |rest| < 1)
+    return {std::ldexp(1.f, e), std::ldexp(scale, -e)};
+}
+// a held operand times `fold`: exact, but for results that are subnormal or too large for bf16
+template <int N>
+__device__ __forceinline__ void fold_in(bf16x8 (&f)[N], float fold) {
+    if (fold == 1.f) return;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[i][e] = (__bf16)(fold * (float)f[i][e]);
 }
 
 // A operand of a contraction over the tile's rows: column 32 cb + r32, k-slots = rows 16 j + 4 h .. + 3 and 8 further.
@@ -209,7 +235,7 @@ struct ChunkedIn {
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
 __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                        const bf16_t* __restrict__ V, bf16_t* __restrict__ O,
-                                                       float* __restrict__ Z, int T, float scale, int normalize,
+                                                       float* __restrict__ Z, int T, ScaleParts scale, int normalize,
                                                        const float* __restrict__ bl, ChunkedIn ck) {
     constexpr int NI = OWN / 32, NK = HD / 16, NV = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
@@ -234,6 +260,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks)
             qf[ib][ks] = row_frag_global<HD>(Q, head + min(q0 + 32 * ib + r32, T - 1), ks, h);
+        fold_in(qf[ib], scale.fold);
 #pragma unroll
         for (int vb = 0; vb < NV; ++vb) acc[vb][ib] = splat16(0.f);
     }
@@ -328,7 +355,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     }
 
     if (!active) return;
-    const float sp = ipow<P>(scale);
+    const float sp = ipow<P>(scale.rest);
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
         const bool in = q0 + 32 * ib + r32 < T;     // (a sequence need not be a multiple of the block)
@@ -394,7 +421,7 @@ template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
 __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                  const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                  const float* __restrict__ gz, bf16_t* __restrict__ dQ, int T,
-                                                 float scale, const float* __restrict__ bl, float* __restrict__ qdq,
+                                                 ScaleParts scale, const float* __restrict__ bl, float* __restrict__ qdq,
                                                  ChunkedIn ck) {
     constexpr int NI = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
@@ -422,13 +449,14 @@ __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q,
             qf[ib][ks] = row_frag_global<HD>(Q, row, ks, h);
             gf[ib][ks] = row_frag_global<HD>(Gh, row, ks, h);
         }
+        fold_in(qf[ib], scale.fold);
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) acc[fb][ib] = splat16(0.f);
     }
 
     const float* bl_head = GATED ? bl + head : nullptr;
-    // gated: rsum = sum_j t_ij (q_i . k_j) = q_i . dq_i, the row's share of the gate gradient, summed
-    // here from the unrounded t (the dot product of the stored dq with q carries bf16 noise that a
+    // gated: rsum = sum_j e_ij c_ij^p = q_i . dq_i / (p rest^p), the row's share of the gate gradient, summed
+    // here from the unrounded terms (the dot product of the stored dq with q carries bf16 noise that a
     // sum over a block of tokens amplifies)
     float bq[NI], rsum[NI];
 #pragma unroll
@@ -519,7 +547,7 @@ __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q,
     }
 
     if (!active) return;
-    const float psp = (float)P * ipow<P>(scale);
+    const float psp = (float)P * ipow<P>(scale.rest), dsp = psp * scale.fold;
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
         const bool in = q0 + 32 * ib + r32 < T;
@@ -528,10 +556,10 @@ __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q,
         for (int fb = 0; fb < NF; ++fb) {
             if (CHUNKED) {   // what came through the state (and the normaliser), per slab
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[fb][ib][i] *= psp;
+                for (int i = 0; i < 16; ++i) acc[fb][ib][i] *= dsp;
                 add_parts(acc[fb][ib], ck.part + row * HD + 32 * fb, (size_t)gridDim.x * T * HD, ck.nslab, h);
             }
-            store_block(dQ + row * HD + 32 * fb, acc[fb][ib], CHUNKED ? 1.f : psp, h, in);
+            store_block(dQ + row * HD + 32 * fb, acc[fb][ib], CHUNKED ? 1.f : dsp, h, in);
         }
         if (GATED) {
             const float dot = psp * xor32_sum(rsum[ib]);
@@ -548,7 +576,7 @@ template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
 __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                    const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                    const float* __restrict__ gz, bf16_t* __restrict__ dK,
-                                                   bf16_t* __restrict__ dV, int T, float scale,
+                                                   bf16_t* __restrict__ dV, int T, ScaleParts scale,
                                                    const float* __restrict__ bl, float* __restrict__ kdk,
                                                    float* __restrict__ wsum, ChunkedIn ck) {
     constexpr int NJ = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
@@ -565,7 +593,7 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
     const bf16_t* Qh = Q + head * HD;
     const bf16_t* Gh_h = Gh + head * HD;
     const float* gzh = gz + head;
-    const float sp = ipow<P>(scale), psp = (float)P * sp;
+    const float sp = ipow<P>(scale.rest), psp = (float)P * sp, dsp = psp * scale.fold;
 
     bf16x8 kf[NJ][NK], vf[NJ][NK];
     f32x16 dk[NF][NJ], dv[NF][NJ];
@@ -577,6 +605,7 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
             kf[kb][ks] = row_frag_global<HD>(K, row, ks, h);
             vf[kb][ks] = row_frag_global<HD>(V, row, ks, h);
         }
+        fold_in(kf[kb], scale.fold);
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) {
             dk[fb][kb] = splat16(0.f);
@@ -585,7 +614,7 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
     }
 
     const float* bl_head = GATED ? bl + head : nullptr;
-    // gated: csum = sum_i e_ij a_ij = k_j . dk_j / p, the key's share of the gate gradient, from the
+    // gated: csum = sum_i e_ij a_ij = k_j . dk_j / (p rest^p), the key's share of the gate gradient, from the
     // unrounded weights
     float bk[NJ], csum[NJ];
 #pragma unroll
@@ -715,13 +744,13 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
             if (CHUNKED) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    dk[fb][kb][i] *= psp;
+                    dk[fb][kb][i] *= dsp;
                     dv[fb][kb][i] *= sp;
                 }
                 add_parts(dk[fb][kb], ck.part + row * HD + 32 * fb, slab_stride, ck.nslab, h);
                 add_parts(dv[fb][kb], ck.part2 + row * HD + 32 * fb, slab_stride, ck.nslab2, h);
             }
-            store_block(dK + row * HD + 32 * fb, dk[fb][kb], CHUNKED ? 1.f : psp, h, in);
+            store_block(dK + row * HD + 32 * fb, dk[fb][kb], CHUNKED ? 1.f : dsp, h, in);
             store_block(dV + row * HD + 32 * fb, dv[fb][kb], CHUNKED ? 1.f : sp, h, in);
         }
         if (GATED) {
@@ -741,7 +770,7 @@ template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED, Bwd WHAT>
 __global__ __launch_bounds__(256, WPE) void k_attn_bwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                        const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                        const float* __restrict__ gz, bf16_t* __restrict__ dQ,
-                                                       bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int T, float scale,
+                                                       bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int T, ScaleParts scale,
                                                        const float* __restrict__ bl, float* __restrict__ qdq,
                                                        float* __restrict__ kdk, float* __restrict__ wsum, ChunkedIn ckq,
                                                        ChunkedIn ckk) {
@@ -808,8 +837,8 @@ bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf1
     auto kern = k_attn_fwd<P, HD, Shape<HD>::FWD_OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
     LaunchScope ls(CHUNKED ? "chunk_fwd" : "attn_fwd", s);
-    hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T, scale, normalize,
-                       bl, ck);
+    hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T,
+                       split_scale(scale), normalize, bl, ck);
     return launch_ok();
 }
 
@@ -835,8 +864,8 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         auto kern = k_attn_bwd<P, HD, Shape<HD>::DKDV_OWN, WPE, GATED, CHUNKED, W>;
         if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
         LaunchScope ls(name, s);
-        hipLaunchKernelGGL(kern, dim3(BH, wgs), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, T, scale, bl,
-                           gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
+        hipLaunchKernelGGL(kern, dim3(BH, wgs), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, T,
+                           split_scale(scale), bl, gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
         return launch_ok();
     };
     // One launch holds every wave to the registers of the larger half (d = 64: two waves of dQ per SIMD instead of three), which
