@@ -269,6 +269,52 @@ __global__ __launch_bounds__(256) void k_decode_absorb(const T* __restrict__ K, 
     if (xg == 0) *grow = accz;
 }
 
+// Rows (i, j0 .. j0 + 7) of a p = 2 state from j = i on, token by token in float32 as above, by one wave: lane = column.
+// (Kept small: the matrix-core kernel below reaches it only for sums that are not finite, and shares its registers with it.)
+template <int HD, bool GATED>
+__device__ __forceinline__ void absorb_rows(const bf16_t* __restrict__ Kh, const bf16_t* __restrict__ Vh, const float* __restrict__ lgh,
+                                            float* __restrict__ Sh, float* __restrict__ gamh, int Tlen, int i, int j0, int lane) {
+    using namespace mfma;
+    constexpr int NC = (HD + 63) / 64, NR = 8;
+    const int col = lane % HD;      // (d = 32: the upper half of the wave repeats the lower one's columns)
+    // row of (i, j0); those of j < i are rows of other pairs, read and dropped
+    const int row0 = i * HD - i * (i - 1) / 2 + j0 - i;
+    float* S0 = Sh + (size_t)row0 * HD + col;
+    float* g0 = gamh + row0;
+    float acc[NR][NC], accz[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        accz[r] = g0[r];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[r][c] = S0[r * HD + 64 * c];
+    }
+#pragma unroll 1
+    for (int t = 0; t < Tlen; ++t) {
+        const bf16_t* kt = Kh + (size_t)t * HD;
+        const float g = GATED ? __expf(lgh[t]) : 1.f, ki = io<bf16_t>::ld(kt + i);
+        Frag kj;
+        kj.u = *(const uint4*)(kt + j0);
+        float v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = io<bf16_t>::ld(Vh + (size_t)t * HD + 64 * c + col);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const float coef = (j0 + r == i ? 1.f : 2.f) * (ki * ((r & 1) ? bf_hi(kj.q[r / 2]) : bf_lo(kj.q[r / 2])));
+            accz[r] = GATED ? g * accz[r] + coef : accz[r] + coef;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[r][c] = (GATED ? g * acc[r][c] : acc[r][c]) + coef * v[c];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        if (j0 + r < i) continue;
+        if (lane == 0) g0[r] = accz[r];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (lane < HD) S0[r * HD + 64 * c] = acc[r][c];
+    }
+}
+
 // The same for p = 2, bf16 tokens, d = v in {32, 64, 128} on the matrix cores, with nothing rounded below float32.
 // The product k_i k_j of two bf16 numbers has at most 16 significant bits, so it is exactly the sum of two bf16 numbers
 // (its upper and its lower half), and the two MFMAs that contract the halves with the values form the float32 sum of exact
@@ -280,7 +326,9 @@ __global__ __launch_bounds__(256) void k_decode_absorb(const T* __restrict__ K, 
 // tokens per lane is formed once per 32 tokens and multiplied by two broadcast k_i.  Eight such waves share the staged tokens
 // (four waves of 4 i each take 169 us at the size below: too few waves to cover the LDS and MFMA latency).  Tokens are staged feature-major, so
 // that every operand is one 16-byte LDS read.  Blocks on the diagonal also form the pairs j < i and drop them (23 % more
-// products at d = 64).  The vector ALU (4 operations per product and lane) and the matrix pipe are loaded
+// products at d = 64).  The parts of an infinite product, and of any product beside an infinite value, are not the product's
+// (inf - inf, 0 inf): a wave that ends with anything but finite sums forms its rows token by token instead (absorb_rows), at
+// the vector kernel's speed.  The vector ALU (4 operations per product and lane) and the matrix pipe are loaded
 // about equally, each less than half of the time; the rest is the chain barrier, LDS read, product, MFMA of a tile.
 // MI355X, B4 H12 T3000 d64: 2160 us on the vector ALUs (k_decode_absorb, one thread per row and 4 columns) -> 156 us.
 constexpr int AXT = 64;         // tokens per tile
@@ -296,7 +344,7 @@ constexpr int absorb_units() {
     return (HD / 16) * (HD / 16 + 1) * 4;
 }
 template <int HD, bool GATED>
-__global__ __launch_bounds__(512, HD == 128 ? 2 : 4) void k_decode_absorb_mfma(const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+__global__ __launch_bounds__(512, HD == 128 ? 2 : HD == 32 ? (GATED ? 5 : 6) : 4) void k_decode_absorb_mfma(const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                                                                const float* __restrict__ log_g, float* __restrict__ S,
                                                                float* __restrict__ gam, long long D, int Tlen) {
     using namespace mfma;
@@ -423,21 +471,44 @@ __global__ __launch_bounds__(512, HD == 128 ? 2 : 4) void k_decode_absorb_mfma(c
         __syncthreads();
     }
     // acc[ii][vb][r]: i = i0 + ii, j = j0 + 4 g + r, column 16 vb + r16
+    auto each_row = [&](auto&& f) {
 #pragma unroll
-    for (int ii = 0; ii < NI; ++ii)
+        for (int ii = 0; ii < NI; ++ii)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = i0 + ii, j = j0 + 4 * g + r;
-            if (j < i) continue;
-            const size_t row = bh * D + (size_t)(i * HD - i * (i - 1) / 2 + j - i);
-            const float m = i == j ? 1.f : 2.f;
-#pragma unroll
-            for (int vb = 0; vb < NV; ++vb) {
-                float* dst = S + row * HD + 16 * vb + r16;
-                *dst = decay * *dst + m * acc[ii][vb][r];
+            for (int r = 0; r < 4; ++r) {
+                const int i = i0 + ii, j = j0 + 4 * g + r;
+                if (j >= i) f(ii, r, bh * D + (size_t)(i * HD - i * (i - 1) / 2 + j - i), i == j ? 1.f : 2.f);
             }
-            if (r16 == 0) gam[row] = decay * gam[row] + m * accz[ii][r];
+    };
+    f32x4 nought4 = {0.f * decay, 0.f, 0.f, 0.f};       // NaN if any sum is infinite or NaN
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii) {
+        nought4 += 0.f * accz[ii];
+#pragma unroll
+        for (int vb = 0; vb < NV; ++vb) nought4 += 0.f * acc[ii][vb];
+    }
+    float nought = nought4[0] + nought4[1] + nought4[2] + nought4[3];
+    if (GATED && decay == 0.f)      // a product of gates that has vanished keeps an infinity in the state, a gate of zero does not
+        each_row([&](int, int, size_t row, float) {
+            nought += 0.f * gam[row];
+#pragma unroll
+            for (int vb = 0; vb < NV; ++vb) nought += 0.f * S[row * HD + 16 * vb + r16];
+        });
+    if (!__all(nought == 0.f)) {
+#pragma unroll 1
+        for (int n = 0; n < 2 * NI; ++n)
+            absorb_rows<HD, GATED>(Kh, Vh, GATED ? log_g + bh * Tlen : nullptr, S + bh * D * HD, gam + bh * D, Tlen,
+                                   __builtin_amdgcn_readfirstlane(i0) + n / 2, __builtin_amdgcn_readfirstlane(j0) + 8 * (n & 1), lane);
+        return;
+    }
+    each_row([&](int ii, int r, size_t row, float m) {
+#pragma unroll
+        for (int vb = 0; vb < NV; ++vb) {
+            float* dst = S + row * HD + 16 * vb + r16;
+            *dst = decay * *dst + m * acc[ii][vb][r];
         }
+        if (r16 == 0) gam[row] = decay * gam[row] + m * accz[ii][r];
+    });
 }
 
 template <int HD, bool GATED>

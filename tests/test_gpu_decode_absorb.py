@@ -49,3 +49,84 @@ def test_exact_hand_over(T, d, gated):
         for got, want, mag in ((S[0, h], phi.T @ v, np.abs(phi).T @ np.abs(v)), (gam[0, h], phi.sum(0), np.abs(phi).sum(0))):
             assert rel_l2(got, want) <= 2e-6
             assert np.all(np.abs(got - want) <= (n + 8) * 2.0 ** -24 * mag + 1e-30)
+
+
+def _recurrence(K, V, lg, S, gam):
+    """The state after the tokens K, V [T, d], in float32 and in order."""
+    i, j = np.triu_indices(K.shape[1])
+    mult = np.where(i == j, 1.0, 2.0).astype(np.float32)
+    with np.errstate(all="ignore"):
+        for t in range(K.shape[0]):
+            g = np.float32(1.0 if lg is None else np.exp(np.float32(lg[t])))
+            coef = mult * (K[t, i] * K[t, j])
+            S = g * S + coef[:, None] * V[t][None, :]
+            gam = g * gam + coef
+    return S, gam
+
+
+@pytest.mark.parametrize("gated", [False, True], ids=["plain", "gated"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("what", ["infinite product", "infinite value", "infinite key", "not a number", "overflowing sum", "infinite state",
+                                  "infinite state, vanishing gates", "infinite state, a gate of zero", "growing gates"])
+def test_hand_over_of_numbers_that_are_not_finite(what, d, gated):
+    """Infinities in the tokens, products that overflow and states that already hold infinities leave what the recurrence
+    leaves in float32: infinities of the same sign and NaN in the same places, and finite sums everywhere else."""
+    import torch
+    B, H, T, p = 1, 2, 100, 2
+    print("case", what, d, gated, flush=True)
+    _, K, V, _ = inputs.make_qkvg(B, H, T, d, seed=9350 + d, dtype="bf16", with_grad=False)
+    lg = inputs.make_log_gates(B, H, T, 9450, 0.05) if gated else None
+    K, V = K.copy(), V.copy()
+    K[0, 1, 20] = np.sign(K[0, 1, 20])      # products with an empty lower half
+    if what == "infinite product":
+        K[0, 1, 70, 3], K[0, 1, 70, d - 2] = 2.0 ** 66, -2.0 ** 67
+    elif what == "infinite value":
+        V[0, 1, 20, 5] = np.inf
+        V[0, 1, 90, 6] = -np.inf
+    elif what == "infinite key":
+        K[0, 1, 33, 17] = -np.inf
+    elif what == "not a number":
+        K[0, 1, 40, 9] = np.nan
+    elif what == "overflowing sum":
+        K[0, 1, 50:60, 4] = 2.0 ** 63
+        V[0, 1, 50:60, 1] = 1.0
+    if not gated and "gate" in what:
+        pytest.skip("gates only")
+    if what == "infinite state, vanishing gates":
+        lg[:] = -2.0            # their product is no float32
+    elif what == "infinite state, a gate of zero":
+        lg[0, 1, 50] = -np.inf
+    elif what == "growing gates":
+        lg[0, 1] = 1.5          # (log-gates are <= 0 in use)
+    tk, tv = to_dev(K, "bf16"), to_dev(V, "bf16")
+    tl = None if lg is None else torch.from_numpy(np.ascontiguousarray(lg)).to("cuda:0")
+    n_s = B * H * (d * (d + 1) // 2) * d
+    D = d * (d + 1) // 2
+    off_gam = ((n_s * 4 + 255) // 256 * 256) // 4
+    one = binding.make_problem(B, H, 1, d, d, p, 1, True, 1.0, "bf16", "auto", False, gated)
+    state = binding.power_attn_decode_init(one)
+    words = state.view(torch.float32)
+    if "infinite state" in what:
+        words[(D + 3) * d + 1] = np.inf
+        words[off_gam + D + 7] = -np.inf
+    S0 = to_np(words[:n_s]).reshape(H, D, d)
+    gam0 = to_np(words[off_gam: off_gam + H * D]).reshape(H, D)
+    prob = binding.make_problem(B, H, T, d, d, p, 1, True, 1.0, "bf16", "auto", False, gated)
+    binding.power_attn_decode_absorb(prob, tk, tv, state, tl, fast=False)
+    torch.cuda.synchronize()
+    S = to_np(words[:n_s]).reshape(H, D, d)
+    gam = to_np(words[off_gam: off_gam + H * D]).reshape(H, D)
+    bad = 0
+    for h in range(H):
+        want_S, want_g = _recurrence(K[0, h], V[0, h], None if lg is None else lg[0, h], S0[h], gam0[h])
+        with np.errstate(all="ignore"):
+            mag_S, mag_g = _recurrence(np.abs(K[0, h]), np.abs(V[0, h]), None if lg is None else lg[0, h], np.abs(S0[h]), np.abs(gam0[h]))
+        for got, want, mag in ((S[h], want_S, mag_S), (gam[h], want_g, mag_g)):
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            inf = np.isinf(want)
+            assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+            fin = np.isfinite(want)
+            bad += int((~fin).sum())
+            # two float32 sums of T terms, each product rounded up to three times
+            assert np.all(np.abs(got[fin].astype(np.float64) - want[fin]) <= 2 * (T + 8) * 2.0 ** -24 * mag[fin].astype(np.float64) + 1e-30)
+    assert bad > 0
