@@ -215,9 +215,16 @@ __device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, i
 }
 
 // Workgroups are numbered so that the ones with the longest walk start first: grid (heads, blocks), so the longest blocks
-// of every head come before the next ones.  (With the blocks of one head after the other, the last heads' long walks
+// of every head come before the next ones; more blocks than y takes (65535 of them are 8.4 M tokens at 128 rows each) go on
+// in z.  (With the blocks of one head after the other, the last heads' long walks
 // started when most of the chip was done: at 16 heads of 16384 tokens the CUs were busy 62 % of the time, and the p = 4
 // kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)
+
+__device__ __forceinline__ int block_rank() { return (int)(blockIdx.z * gridDim.y + blockIdx.y); }
+dim3 block_grid(int heads, int blocks) {
+    const int y = std::min(blocks, 32768);
+    return dim3((unsigned)heads, (unsigned)y, (unsigned)((blocks + y - 1) / y));
+}
 
 // ---- forward ----------------------------------------------------------------------------------------
 // acc[vb][ib] = O^T: value columns 32 vb + .., query 32 ib + r32 of the wave's OWN queries.
@@ -244,7 +251,8 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
-    const int i0 = (nblk - 1 - (int)blockIdx.y) * WG;
+    const int i0 = (nblk - 1 - block_rank()) * WG;
+    if (i0 < 0) return;
     const int q0 = i0 + OWN * w;                    // the wave's first query
     const bool active = q0 < T;
     const size_t head = (size_t)blockIdx.x * T;
@@ -774,8 +782,9 @@ __global__ __launch_bounds__(256, WPE) void k_attn_bwd(const bf16_t* __restrict_
                                                        const float* __restrict__ bl, float* __restrict__ qdq,
                                                        float* __restrict__ kdk, float* __restrict__ wsum, ChunkedIn ckq,
                                                        ChunkedIn ckk) {
-    const int rank = WHAT == Bwd::both ? (int)blockIdx.y >> 1 : (int)blockIdx.y;
-    if (WHAT == Bwd::dq || (WHAT == Bwd::both && (blockIdx.y & 1)))
+    const int n = block_rank(), rank = WHAT == Bwd::both ? n >> 1 : n;
+    if (rank >= (T + 4 * OWN - 1) / (4 * OWN)) return;
+    if (WHAT == Bwd::dq || (WHAT == Bwd::both && (n & 1)))
         dq_block<P, HD, OWN, GATED, CHUNKED>(rank, Q, K, V, Gh, gz, dQ, T, scale, bl, qdq, ckq);
     else
         dkdv_block<P, HD, OWN, GATED, CHUNKED>(rank, Q, K, V, Gh, gz, dK, dV, T, scale, bl, kdk, wsum, ckk);
@@ -837,7 +846,7 @@ bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf1
     auto kern = k_attn_fwd<P, HD, Shape<HD>::FWD_OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
     LaunchScope ls(CHUNKED ? "chunk_fwd" : "attn_fwd", s);
-    hipLaunchKernelGGL(kern, dim3(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T,
+    hipLaunchKernelGGL(kern, block_grid(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T,
                        split_scale(scale), normalize, bl, ck);
     return launch_ok();
 }
@@ -864,7 +873,7 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         auto kern = k_attn_bwd<P, HD, Shape<HD>::DKDV_OWN, WPE, GATED, CHUNKED, W>;
         if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
         LaunchScope ls(name, s);
-        hipLaunchKernelGGL(kern, dim3(BH, wgs), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, T,
+        hipLaunchKernelGGL(kern, block_grid(BH, wgs), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, T,
                            split_scale(scale), bl, gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
         return launch_ok();
     };
@@ -875,7 +884,7 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
     // half of its waves.
     bool both = false;
     if constexpr (HD < 128) {
-        both = (long long)BH * nblk <= 768 && 2 * nblk <= 65535;      // (and the grid's limit)
+        both = (long long)BH * nblk <= 768;
         if (both && !launch(std::integral_constant<Bwd, Bwd::both>{}, CHUNKED ? "chunk_bwd" : "attn_bwd", 2 * nblk)) return false;
     }
     if (!both && !launch(std::integral_constant<Bwd, Bwd::dkdv>{}, CHUNKED ? "chunk_bwd_dkdv" : "attn_bwd_dkdv", nblk)) return false;
