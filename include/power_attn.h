@@ -202,7 +202,9 @@ pa_status power_attn_decode_step(const pa_problem* prob, const void* q, const vo
                                  const float* log_g, void* state, size_t state_bytes,
                                  void* o, float* z, void* hip_stream);
 
-/* The chunk size the calls use for `prob` (prob->chunk itself unless it is 0; 0 on an invalid problem). */
+/* The chunk size the calls use for `prob` (prob->chunk itself unless it is 0; 0 on an invalid problem).  Un-gated float32
+ * calls under PA_IMPL_AUTO with d = v in {16, 32, 64, 128} and T <= 4096 (<= 16384 where B H T <= 262144) run the attention
+ * form at any chunk; the chunk, and the state rows below, are then those of the chunked form it takes the place of. */
 int power_attn_resolved_chunk(const pa_problem* prob);
 
 /* Expanded state rows the chosen kernel family keeps per head for `prob`: C(d+p-1, p) for

@@ -781,7 +781,12 @@ pa_status generic_supported(const pa_problem& pr) {
 
 long long generic_state_rows(const pa_problem& pr) { return comb_ll(pr.d + pr.p - 1, pr.p); }
 
-size_t generic_workspace_bytes(const pa_problem& pr, bool backward) { return make_layout(pr, backward).total; }
+// The attention form builds no state: dO . O per row in the backward pass is all it keeps.  (Its forward pass asks for the
+// smallest workspace rather than none, so that every float32 call goes on to need one.)
+size_t generic_workspace_bytes(const pa_problem& pr, bool backward) {
+    if (f32_attn_applies(pr)) return backward ? align_up((size_t)pr.B * pr.H * pr.T * sizeof(float), 256) : 256;
+    return make_layout(pr, backward).total;
+}
 
 pa_status generic_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z) {
     if (f32_attn_applies(c.prob))

@@ -6,7 +6,7 @@ import pytest
 from oracle import power_attn_oracle as orc
 from paper_2507_04239_amd import inputs
 
-from gpu_util import assert_close, rel_l2, run_fwd_bwd
+from gpu_util import assert_close, rel_l2, run_fwd_bwd, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -48,6 +48,20 @@ def test_float32_attention_form(case):
         print(f"{n}: {e_new:.2e} (chunked kernels {e_old:.2e})", flush=True)
         # sums of at most T products in float32: T 2^-24 relative to the sum of magnitudes, 8 of cancellation
         assert e_new <= max(2 * e_old, 8 * (T + d) * 2.0 ** -24)
+
+
+def test_static_scratch_takes_a_length_without_small_divisors():
+    """No chunk but 1 and T divides a prime T: what used to mean a state per token needs no scratch here."""
+    import torch
+    from paper_2507_04239_amd.binding import power_attn_fwd_static
+    B, H, T, d = 1, 8, 1009, 64
+    print("case", T, flush=True)
+    Q, K, V, _ = inputs.make_qkvg(B, H, T, d, seed=9250, dtype="f32", with_grad=False)
+    tq, tk, tv = (to_dev(x, "f32") for x in (Q, K, V))
+    O, Z = torch.full_like(tv, float("nan")), torch.full((B, H, T), float("nan"), device="cuda:0")
+    power_attn_fwd_static(tq, tk, tv, O, Z, 2, 0)
+    want_O, want_Z = orc.fwd_bhtd(Q, K, V, 2, None, True, 1.0)
+    assert_close(dict(O=to_np(O), Z=to_np(Z)), dict(O=want_O, Z=want_Z), "f32", "static scratch")
 
 
 def test_float32_attention_form_repeats_bit_for_bit():

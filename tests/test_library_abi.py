@@ -59,6 +59,19 @@ def test_validation_and_sizes(lib):
     assert lib.power_attn_fwd(ctypes.byref(ok), fake, fake, fake, fake, None, None, 0, None) == 3
 
 
+@pytest.mark.parametrize("chunk", [0, 1, 7])
+@pytest.mark.parametrize("d,p", [(16, 1), (32, 2), (64, 2), (128, 4)])
+def test_float32_attention_form_asks_for_no_states(lib, d, p, chunk):
+    """Its scratch is one float per token (backward), at any chunk; the sizes beside it keep the chunked kernels' states."""
+    bytes_of = binding.power_attn_workspace_bytes
+    T = 7 * 429
+    pr = binding.make_problem(2, 3, T, d, d, p, chunk, normalize=p % 2 == 0, dtype="f32")
+    assert 0 < bytes_of(pr, False) <= 256 and 4 * 6 * T <= bytes_of(pr, True) < 4 * 6 * T + 256
+    for other in (dict(impl="generic"), dict(gated=True)):
+        pr = binding.make_problem(2, 3, T, d, d, p, chunk, normalize=p % 2 == 0, dtype="f32", **other)
+        assert bytes_of(pr, False) >= 4 * 6 * T * d
+
+
 def test_state_rows_match_the_embedding_dimension(lib):
     import math
     for d, p in [(16, 2), (32, 4), (12, 3)]:
