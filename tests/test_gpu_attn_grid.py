@@ -3,7 +3,7 @@
 import pytest
 
 from oracle import power_attn_oracle as orc
-from paper_2507_04239_amd import inputs
+from paper_2507_04239_amd import binding, inputs
 
 from gpu_util import assert_close, run_fwd_bwd
 
@@ -25,6 +25,36 @@ def test_backward_on_either_side_of_the_one_launch_line(p, d, H, T):
         O, Z = orc.fwd_bhtd(Q[sl], K[sl], V[sl], p, None, True, 1.0)
         dQ, dK, dV = orc.bwd_bhtd(Q[sl], K[sl], V[sl], G[sl], p, None, True, 1.0)
         assert_close({n: x[sl] for n, x in got.items()}, dict(O=O, Z=Z, dQ=dQ, dK=dK, dV=dV), "bf16", f"head {h}")
+
+
+def _run(case, kernels, Q, K, V, G, p, chunk, impl, normalize=True, log_g=None):
+    print("case", case, flush=True)
+    binding.profile_begin()
+    got = run_fwd_bwd(Q, K, V, G, p, chunk, "bf16", normalize, impl=impl, log_g=log_g)
+    names = set(binding.profile_end())
+    assert kernels <= names and not ({"attn_bwd", "attn_bwd_dq", "chunk_bwd", "chunk_bwd_dq"} - kernels) & names, names
+    for h in (0, Q.shape[1] - 1):
+        sl = (slice(None), slice(h, h + 1))
+        lg = None if log_g is None else log_g[sl]
+        O, Z = orc.fwd_bhtd(Q[sl], K[sl], V[sl], p, None, normalize, 1.0, log_g=lg)
+        grads = orc.bwd_bhtd(Q[sl], K[sl], V[sl], G[sl], p, None, normalize, 1.0, log_g=lg)
+        assert_close({n: x[sl] for n, x in got.items()}, dict(zip(("O", "Z", "dQ", "dK", "dV", "dlog_g"), (O, Z, *grads))), "bf16", f"head {h}")
+
+
+@pytest.mark.parametrize("p,d,H,T,one", [(2, 64, 384, 256, True), (2, 64, 385, 256, False), (4, 32, 384, 512, True), (4, 32, 385, 512, False)])
+def test_gated_backward_on_either_side_of_the_one_launch_line(p, d, H, T, one):
+    """2 blocks of 128 (256) rows a head: the sums across the block boundary come from the dK / dV half of either launch."""
+    Q, K, V, G = inputs.make_qkvg(1, H, T, d, seed=9510 + H, dtype="bf16")
+    lg = inputs.make_log_gates(1, H, T, 9511, 0.02)
+    _run((p, d, H, T), {"attn_bwd"} if one else {"attn_bwd_dkdv", "attn_bwd_dq"}, Q, K, V, G, p, T, "mfma", log_g=lg)
+
+
+@pytest.mark.parametrize("p,d,H,T,one", [(2, 32, 768, 256, True), (2, 32, 769, 256, False), (3, 64, 12, 256, True), (2, 32, 384, 384, True),
+                                         (2, 32, 385, 384, False), (2, 128, 3, 384, False)])
+def test_in_chunk_backward_on_either_side_of_the_one_launch_line(p, d, H, T, one):
+    """The in-chunk kernels of the tiled family, chunks of 128 (d = 32: half a block of rows, the last block not full at T = 384)."""
+    Q, K, V, G = inputs.make_qkvg(1, H, T, d, seed=9520 + H, dtype="bf16")
+    _run((p, d, H, T), {"chunk_bwd"} if one else {"chunk_bwd_dkdv", "chunk_bwd_dq"}, Q, K, V, G, p, 128, "tiled", p % 2 == 0)
 
 
 def test_more_row_blocks_than_one_grid_dimension_takes():
