@@ -214,16 +214,29 @@ __device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, i
     }
 }
 
-// Workgroups are numbered so that the ones with the longest walk start first: grid (heads, blocks), so the longest blocks
-// of every head come before the next ones; more blocks than y takes (65535 of them are 8.4 M tokens at 128 rows each) go on
-// in z.  (With the blocks of one head after the other, the last heads' long walks
-// started when most of the chip was done: at 16 heads of 16384 tokens the CUs were busy 62 % of the time, and the p = 4
-// kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)
-
-__device__ __forceinline__ int block_rank() { return (int)(blockIdx.z * gridDim.y + blockIdx.y); }
-dim3 block_grid(int heads, int blocks) {
+// Workgroups are numbered so that the ones with the longest walk start first: grid (heads of a group, blocks, groups), so the
+// longest blocks of every head of a group come before the next ones.  (With the blocks of one head after the other, the last
+// heads' long walks started when most of the chip was done: at 16 heads of 16384 tokens the CUs were busy 62 % of the time, and
+// the p = 4 kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)  More blocks than y is given go on in z.
+struct Order {
+    int group, parts;       // heads per group; slices of y that a group's blocks take
+};
+struct Place {
+    int head, rank;         // rank counts the blocks from the longest walk down
+};
+__device__ __forceinline__ Place place(Order o) {
+    int z = (int)blockIdx.z, part = 0;
+    if (o.parts > 1) {
+        const int g = __builtin_amdgcn_readfirstlane(z / o.parts);
+        part = z - g * o.parts;
+        z = g;
+    }
+    return {z * o.group + (int)blockIdx.x, part * (int)gridDim.y + (int)blockIdx.y};
+}
+dim3 block_grid(int heads, int blocks, Order& o) {
     const int y = std::min(blocks, 32768);
-    return dim3((unsigned)heads, (unsigned)y, (unsigned)((blocks + y - 1) / y));
+    o.parts = (blocks + y - 1) / y;
+    return dim3((unsigned)o.group, (unsigned)y, (unsigned)((heads + o.group - 1) / o.group * o.parts));
 }
 
 // ---- forward ----------------------------------------------------------------------------------------
@@ -242,7 +255,7 @@ struct ChunkedIn {
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
 __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                        const bf16_t* __restrict__ V, bf16_t* __restrict__ O,
-                                                       float* __restrict__ Z, int T, ScaleParts scale, int normalize,
+                                                       float* __restrict__ Z, int BH, Order order, int T, ScaleParts scale, int normalize,
                                                        const float* __restrict__ bl, ChunkedIn ck) {
     constexpr int NI = OWN / 32, NK = HD / 16, NV = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
@@ -251,11 +264,12 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
-    const int i0 = (nblk - 1 - block_rank()) * WG;
-    if (i0 < 0) return;
+    const Place at = place(order);
+    const int i0 = (nblk - 1 - at.rank) * WG;
+    if (i0 < 0 || at.head >= BH) return;
     const int q0 = i0 + OWN * w;                    // the wave's first query
     const bool active = q0 < T;
-    const size_t head = (size_t)blockIdx.x * T;
+    const size_t head = (size_t)at.head * T;
     const bf16_t* Kh = K + head * HD;
     const bf16_t* Vh = V + head * HD;
 
@@ -375,7 +389,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
             for (int vb = 0; vb < NV; ++vb) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[vb][ib][i] *= sp;
-                add_parts(acc[vb][ib], ck.part + row * HD + 32 * vb, (size_t)gridDim.x * T * HD, ck.nslab, h);
+                add_parts(acc[vb][ib], ck.part + row * HD + 32 * vb, (size_t)BH * T * HD, ck.nslab, h);
             }
             f = 1.f;
         }
@@ -426,9 +440,9 @@ __global__ __launch_bounds__(256) void k_attn_prep(const bf16_t* __restrict__ dO
 // ---- backward: dQ -----------------------------------------------------------------------------------
 // acc[fb][ib] = dQ^T: features 32 fb + .., query 32 ib + r32.
 template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
-__device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+__device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                  const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
-                                                 const float* __restrict__ gz, bf16_t* __restrict__ dQ, int T,
+                                                 const float* __restrict__ gz, bf16_t* __restrict__ dQ, int BH, int T,
                                                  ScaleParts scale, const float* __restrict__ bl, float* __restrict__ qdq,
                                                  ChunkedIn ck) {
     constexpr int NI = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
@@ -438,10 +452,10 @@ __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q,
     GateTile* gtile = reinterpret_cast<GateTile*>(vt + 2);              // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
     const int nblk = (T + WG - 1) / WG;
-    const int i0 = (nblk - 1 - rank) * WG;
+    const int i0 = (nblk - 1 - at.rank) * WG;
     const int q0 = i0 + OWN * w;
     const bool active = q0 < T;
-    const size_t head = (size_t)blockIdx.x * T;
+    const size_t head = (size_t)at.head * T;
     const bf16_t* Kh = K + head * HD;
     const bf16_t* Vh = V + head * HD;
 
@@ -565,7 +579,7 @@ __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q,
             if (CHUNKED) {   // what came through the state (and the normaliser), per slab
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[fb][ib][i] *= dsp;
-                add_parts(acc[fb][ib], ck.part + row * HD + 32 * fb, (size_t)gridDim.x * T * HD, ck.nslab, h);
+                add_parts(acc[fb][ib], ck.part + row * HD + 32 * fb, (size_t)BH * T * HD, ck.nslab, h);
             }
             store_block(dQ + row * HD + 32 * fb, acc[fb][ib], CHUNKED ? 1.f : dsp, h, in);
         }
@@ -581,10 +595,10 @@ __device__ __forceinline__ void dq_block(int rank, const bf16_t* __restrict__ Q,
 // S and E are formed queries x keys here, so that their accumulators are the B operand (k-slots =
 // queries) of the two contractions over the queries.
 template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
-__device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+__device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                    const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                    const float* __restrict__ gz, bf16_t* __restrict__ dK,
-                                                   bf16_t* __restrict__ dV, int T, ScaleParts scale,
+                                                   bf16_t* __restrict__ dV, int BH, int T, ScaleParts scale,
                                                    const float* __restrict__ bl, float* __restrict__ kdk,
                                                    float* __restrict__ wsum, ChunkedIn ck) {
     constexpr int NJ = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
@@ -594,10 +608,10 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
     float(*gzt)[AT] = reinterpret_cast<float(*)[AT]>(gt + 2);           // [2][AT]
     GateTile* gtile = reinterpret_cast<GateTile*>(gzt + 2);             // [2]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r32 = lane & 31, h = lane >> 5;
-    const int j0 = rank * WG;
+    const int j0 = at.rank * WG;
     const int k0 = j0 + OWN * w;                    // the wave's first key
     const bool active = k0 < T;
-    const size_t head = (size_t)blockIdx.x * T;
+    const size_t head = (size_t)at.head * T;
     const bf16_t* Qh = Q + head * HD;
     const bf16_t* Gh_h = Gh + head * HD;
     const float* gzh = gz + head;
@@ -729,7 +743,7 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
             for (int kb = 0; kb < NJ; ++kb) v += csum[kb];
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-            if (iblk > jblk && lane == 0) wsum[(((size_t)blockIdx.x * nblk + jblk) * nblk + iblk) * 4 + w] = sp * (v - wprev);
+            if (iblk > jblk && lane == 0) wsum[(((size_t)at.head * nblk + jblk) * nblk + iblk) * 4 + w] = sp * (v - wprev);
             wprev = v;
         }
         if (t + 1 < ntile) {
@@ -746,7 +760,7 @@ __device__ __forceinline__ void dkdv_block(int rank, const bf16_t* __restrict__ 
     for (int kb = 0; kb < NJ; ++kb) {
         const bool in = k0 + 32 * kb + r32 < T;
         const size_t row = head + min(k0 + 32 * kb + r32, T - 1);
-        const size_t slab_stride = (size_t)gridDim.x * T * HD;
+        const size_t slab_stride = (size_t)BH * T * HD;
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) {
             if (CHUNKED) {
@@ -778,16 +792,18 @@ template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED, Bwd WHAT>
 __global__ __launch_bounds__(256, WPE) void k_attn_bwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                        const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                        const float* __restrict__ gz, bf16_t* __restrict__ dQ,
-                                                       bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int T, ScaleParts scale,
-                                                       const float* __restrict__ bl, float* __restrict__ qdq,
+                                                       bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int BH, Order order,
+                                                       int T, ScaleParts scale, const float* __restrict__ bl, float* __restrict__ qdq,
                                                        float* __restrict__ kdk, float* __restrict__ wsum, ChunkedIn ckq,
                                                        ChunkedIn ckk) {
-    const int n = block_rank(), rank = WHAT == Bwd::both ? n >> 1 : n;
-    if (rank >= (T + 4 * OWN - 1) / (4 * OWN)) return;
-    if (WHAT == Bwd::dq || (WHAT == Bwd::both && (n & 1)))
-        dq_block<P, HD, OWN, GATED, CHUNKED>(rank, Q, K, V, Gh, gz, dQ, T, scale, bl, qdq, ckq);
+    Place at = place(order);
+    const bool dq = WHAT == Bwd::dq || (WHAT == Bwd::both && (at.rank & 1));
+    if (WHAT == Bwd::both) at.rank >>= 1;
+    if (at.rank >= (T + 4 * OWN - 1) / (4 * OWN) || at.head >= BH) return;
+    if (dq)
+        dq_block<P, HD, OWN, GATED, CHUNKED>(at, Q, K, V, Gh, gz, dQ, BH, T, scale, bl, qdq, ckq);
     else
-        dkdv_block<P, HD, OWN, GATED, CHUNKED>(rank, Q, K, V, Gh, gz, dK, dV, T, scale, bl, kdk, wsum, ckk);
+        dkdv_block<P, HD, OWN, GATED, CHUNKED>(at, Q, K, V, Gh, gz, dK, dV, BH, T, scale, bl, kdk, wsum, ckk);
 }
 
 template <int HD>
@@ -839,6 +855,27 @@ struct Shape {
     static constexpr int DKDV_OWN = HD == 32 ? 64 : 32, DKDV_WPE = HD == 128 ? 1 : 2;
 };
 
+// Heads whose blocks are taken together.  All of them, as long as their K and V (Q and dO / Z) fit half of the 256 MB memory-side
+// cache; beyond, every walk comes from HBM (B8 H16 T32768, d = 128, forward / dK, dV / dQ in ms: 43.8 / 80.2 / 52.3 with all heads
+// together, 34.9 / 74.6 / 44.4 with 8, 40.0 / 82.1 / 49.5 with one; 192 heads of 8192, d = 64: 1.84 / 3.45 / 2.20, 1.67 / 3.08 / 2.12,
+// 2.18 / 3.94 / 2.56, and 1.58 / 2.95 / 2.04 with 32).  Eight is the least: a head then has an XCD and its L2 to itself.  Groups are of
+// one size, for a small last one would leave the chip idle behind it (40 heads of 32768, d = 64: 5.43 ms forward in eights, 7.87
+// as 32 + 8), and a power of two where it can be (the heads that meet on an XCD are then the fewest).  In-chunk walks that read
+// no block but their own share nothing: there the blocks of a head stay together and read memory in order (12 heads of 65536, d = 64,
+// chunk 128: dK / dV 410 us, 429 with the heads together).
+template <int HD, bool CHUNKED, int WG>
+int head_group(int BH, int T, const ChunkedIn& ck) {
+    if (CHUNKED && ck.cs <= WG) return 1;
+    const int fit = std::max(8, (int)((128 << 20) / (4LL * T * HD)));
+    if (BH <= fit) return BH;
+    int g = 8;
+    while (2 * g <= fit) g *= 2;
+    for (; g >= 4; g /= 2)
+        if (BH % g == 0) return g;
+    const int groups = (BH + fit - 1) / fit;
+    return (BH + groups - 1) / groups;
+}
+
 template <int P, int HD, bool GATED, bool CHUNKED = false>
 bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
            int normalize, const float* bl, ChunkedIn ck = ChunkedIn()) {
@@ -846,7 +883,9 @@ bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf1
     auto kern = k_attn_fwd<P, HD, Shape<HD>::FWD_OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
     LaunchScope ls(CHUNKED ? "chunk_fwd" : "attn_fwd", s);
-    hipLaunchKernelGGL(kern, block_grid(BH, (T + WG - 1) / WG), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, T,
+    Order order{head_group<HD, CHUNKED, WG>(BH, T, ck)};
+    const dim3 grid = block_grid(BH, (T + WG - 1) / WG, order);
+    hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, BH, order, T,
                        split_scale(scale), normalize, bl, ck);
     return launch_ok();
 }
@@ -873,7 +912,9 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         auto kern = k_attn_bwd<P, HD, Shape<HD>::DKDV_OWN, WPE, GATED, CHUNKED, W>;
         if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
         LaunchScope ls(name, s);
-        hipLaunchKernelGGL(kern, block_grid(BH, wgs), dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, T,
+        Order order{head_group<HD, CHUNKED, WG>(BH, T, ckq)};
+        const dim3 grid = block_grid(BH, wgs, order);
+        hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, BH, order, T,
                            split_scale(scale), bl, gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
         return launch_ok();
     };

@@ -84,3 +84,26 @@ def test_more_row_blocks_than_one_grid_dimension_takes():
         assert not x[:, :, chunk:-chunk].any()
     to_np = lambda x: x.float().cpu().numpy()
     assert_close({m: to_np(ends(x)) for m, x in got.items()}, {m: to_np(x) for m, x in want.items()}, "bf16", f"T = {T}", 0.1)
+
+
+@pytest.mark.parametrize("d,H,T,p", [(128, 9, 32768, 2), (128, 16, 32768, 2), (64, 12, 65536, 2)])
+def test_heads_in_groups(d, H, T, p):
+    """Heads whose keys and values outgrow the memory-side cache are taken in groups: 5 + 4 (the last one short), 8 + 8, 4 + 4 + 4.
+    Every head against the chunked kernels."""
+    import torch
+    from paper_2507_04239_amd import power_attn_bwd, power_attn_fwd
+    print("case", d, H, T, flush=True)
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(9560 + H)
+    Q, K, V, G = (torch.randn((1, H, T, d), device=dev, generator=gen, dtype=torch.bfloat16) * s for s in (d ** -.5, d ** -.5, 1., 1.))
+
+    def step(chunk):
+        O, Z = power_attn_fwd(Q, K, V, p, chunk, impl="mfma")
+        return dict(zip(("O", "Z", "dQ", "dK", "dV"), (O, Z, *power_attn_bwd(Q, K, V, O, Z, G, p, chunk, impl="mfma"))))
+
+    got, want = step(T), step(256)
+    for n, w in want.items():
+        e = (got[n].float() - w.float()).flatten(2).norm(dim=2) / w.float().flatten(2).norm(dim=2)
+        print(n, e.max().item(), flush=True)
+        assert e.max() <= 1e-2, n       # two bf16 evaluations, each within about 4e-3 of the definition
