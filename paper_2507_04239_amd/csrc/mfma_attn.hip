@@ -511,7 +511,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
                     c[ib] = mfma32(kf, qf[ib][ks], c[ib]);
                     e[ib] = mfma32(vf, gf[ib][ks], e[ib]);
                 }
-                if (ks & 1) __builtin_amdgcn_sched_barrier(0);   // (holds the register count under 256)
+                if (ks & 1) __builtin_amdgcn_sched_barrier(0);   // (holds the register count under 256; gated, d = 128: 5 spills)
             }
             Frag tf[NI][2];
             float gk[16];
@@ -843,11 +843,12 @@ __global__ __launch_bounds__(64) void k_attn_gate_cols(const float* __restrict__
 }
 
 // Rows of the block one wave owns and the waves per SIMD the kernel is compiled for, measured on MI355X.  At d = 64 the
-// 32-row waves read twice the LDS bytes per flop and are the faster ones all the same, because two to three of them share
-// a SIMD without spilling (4 heads of 16384 tokens, p = 3: forward 241 us against 277 with 64 rows; dQ 322 against 375
-// with 64 rows and one wave per SIMD, 877 with 64 rows and spills; dK / dV 437 against 504 with 64 keys and one wave).
-// At d = 32 the operands are half the size and 64 rows fit two waves (16 heads of 16384 tokens, p = 4: 330 / 445 / 587 us
-// against 336 / 463 / 620 with 32).  Only dK / dV at d = 128 (192 registers of operands and accumulators) runs alone.
+// 32-row waves read twice the LDS bytes per flop, but two to three of them share a SIMD without spilling (4 heads of 16384
+// tokens, p = 3: forward 241 us against 277 with 64 rows; dQ 322 against 375 with 64 rows and one wave per SIMD, 877 with 64
+// rows and spills; dK / dV 437 against 504 with 64 keys and one wave).  The forward pass takes 64 rows all the same where the grid is
+// large (fwd_wide).  At d = 32 the operands are half the size and 64 rows fit two waves (16 heads of 16384 tokens, p = 4:
+// 330 / 445 / 587 us against 336 / 463 / 620 with 32).  Only dK / dV at d = 128 (192 registers of operands and accumulators)
+// runs alone.
 template <int HD>
 struct Shape {
     static constexpr int FWD_OWN = HD == 32 ? 64 : 32, FWD_WPE = 2;
@@ -876,11 +877,16 @@ int head_group(int BH, int T, const ChunkedIn& ck) {
     return (BH + groups - 1) / groups;
 }
 
-template <int P, int HD, bool GATED, bool CHUNKED = false>
-bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
-           int normalize, const float* bl, ChunkedIn ck = ChunkedIn()) {
-    constexpr int WG = 4 * Shape<HD>::FWD_OWN;
-    auto kern = k_attn_fwd<P, HD, Shape<HD>::FWD_OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
+// d = 64, whole sequences: 64 query rows per wave in place of 32 read half the LDS bytes per flop, and are the faster ones once
+// their blocks of 256 rows, half as many, still fill the chip (32 and 64 rows, us, p = 2): 8 heads of 16384 (512 blocks) 285 / 307, 96 of
+// 2048 (768) 60.3 / 61.7, 24 of 8192 (768) 209 / 198, 256 of 1024 (1024) 47.3 / 47.6, 128 of 2048 (1024) 76.9 / 74.9, 64 of 4096 (1024)
+// 142 / 135, 64 of 8192 531 / 469, 16 of 131072 33.0 / 28.9 ms.
+bool fwd_wide(int BH, int T) { return T >= 2048 && (long long)BH * ((T + 255) / 256) >= 1024; }
+template <int P, int HD, bool GATED, bool CHUNKED, int OWN>
+bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
+             int normalize, const float* bl, ChunkedIn ck) {
+    constexpr int WG = 4 * OWN;
+    auto kern = k_attn_fwd<P, HD, OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
     LaunchScope ls(CHUNKED ? "chunk_fwd" : "attn_fwd", s);
     Order order{head_group<HD, CHUNKED, WG>(BH, T, ck)};
@@ -888,6 +894,13 @@ bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf1
     hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, BH, order, T,
                        split_scale(scale), normalize, bl, ck);
     return launch_ok();
+}
+template <int P, int HD, bool GATED, bool CHUNKED = false>
+bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
+           int normalize, const float* bl, ChunkedIn ck = ChunkedIn()) {
+    if constexpr (HD == 64 && !CHUNKED)
+        if (fwd_wide(BH, T)) return fwd_own<P, HD, GATED, CHUNKED, 64>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
+    return fwd_own<P, HD, GATED, CHUNKED, Shape<HD>::FWD_OWN>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
 }
 
 template <int P, int HD, bool GATED, bool CHUNKED = false>
@@ -921,8 +934,9 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
     // One launch holds every wave to the registers of the larger half (d = 64: two waves of dQ per SIMD instead of three), which
     // costs what the filled tail saves from 3 to 4 workgroups of each kind per CU on (d = 64, 24 heads of 4096 tokens, 768 of each
     // kind: 210 us in two, 201 in one; T1000, 1536: 124 either way; 96 heads of 4096, 3072: 782 and 801; d = 32, 1024: 1065 and
-    // 1071).  At d = 128 dQ would lose
-    // half of its waves.
+    // 1071).  Gated: 12 heads of 4096 (384 of each kind) 240 and 165, 24 heads (768) 271 and 253.  In-chunk, whole backward passes
+    // of the tiled kernels, d = 32: 24 heads of 1024 tokens, chunk 128, 114 and 106; 1 of 16384, chunk 4096, 538 and 487; 12 of
+    // 16384, chunk 256, 727 and 720; no shape slower in one.  At d = 128 dQ would lose half of its waves.
     bool both = false;
     if constexpr (HD < 128) {
         both = (long long)BH * nblk <= 768;

@@ -5,7 +5,7 @@ import pytest
 from oracle import power_attn_oracle as orc
 from paper_2507_04239_amd import binding, inputs
 
-from gpu_util import assert_close, run_fwd_bwd
+from gpu_util import assert_close, run_fwd_bwd, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +107,21 @@ def test_heads_in_groups(d, H, T, p):
         e = (got[n].float() - w.float()).flatten(2).norm(dim=2) / w.float().flatten(2).norm(dim=2)
         print(n, e.max().item(), flush=True)
         assert e.max() <= 1e-2, n       # two bf16 evaluations, each within about 4e-3 of the definition
+
+
+@pytest.mark.parametrize("p,H,T,gated", [(2, 127, 2048, False), (2, 128, 2047, False), (2, 128, 2048, False), (3, 114, 2100, False),
+                                         (4, 103, 2305, False), (2, 128, 2048, True), (4, 114, 2176, True)])
+def test_forward_on_either_side_of_the_wide_wave_line(p, H, T, gated):
+    """d = 64: 64 rows per wave from 1024 blocks of 256 rows and 2048 tokens on, through blocks that are not full."""
+    import torch
+    from paper_2507_04239_amd import power_attn_fwd
+    d = 64
+    print("case", p, H, T, gated, flush=True)
+    Q, K, V, _ = inputs.make_qkvg(1, H, T, d, seed=9570 + H, dtype="bf16", with_grad=False)
+    lg = inputs.make_log_gates(1, H, T, 9571, 0.02) if gated else None
+    tq, tk, tv = (to_dev(x, "bf16") for x in (Q, K, V))
+    O, Z = power_attn_fwd(tq, tk, tv, p, T, p % 2 == 0, impl="mfma", log_g=None if lg is None else torch.from_numpy(lg).to("cuda:0"))
+    for h in (0, H - 1):
+        sl = (slice(None), slice(h, h + 1))
+        wO, wZ = orc.fwd_bhtd(Q[sl], K[sl], V[sl], p, None, p % 2 == 0, 1.0, log_g=None if lg is None else lg[sl])
+        assert_close(dict(O=to_np(O[sl]), Z=to_np(Z[sl])), dict(O=wO, Z=wZ), "bf16", f"head {h}")
