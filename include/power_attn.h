@@ -192,8 +192,9 @@ pa_status power_attn_decode_init(const pa_problem* prob, void* state, size_t sta
  * what power_attn_fwd returns for the prompt.  May be called on a state that already holds tokens.
  * workspace (DEVICE, 256-byte aligned, may be NULL): with power_attn_decode_absorb_workspace_bytes(prob)
  * bytes of it (0 = no such path for this problem: bf16, p = 2, d = v = 64, T a multiple of 128 have one)
- * the prompt goes through the matrix-core state scan, some 20x faster, its sums rounded to bf16 once
- * as the chunk states of power_attn_fwd are; without, through a float32 kernel on the vector ALUs. */
+ * the prompt goes through the matrix-core state scan, its sums rounded to bf16 once as the chunk states of power_attn_fwd
+ * are: the faster one for long prompts of few heads.  Without, the sums are float32: on the matrix cores for bf16, p = 2,
+ * d = v in {32, 64, 128} (any T; the faster one for short prompts), on the vector ALUs for the rest. */
 size_t power_attn_decode_absorb_workspace_bytes(const pa_problem* prob);
 pa_status power_attn_decode_absorb(const pa_problem* prob, const void* K, const void* V, const float* log_g,
                                    void* state, size_t state_bytes, void* workspace, size_t workspace_bytes,

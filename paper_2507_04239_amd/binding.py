@@ -316,8 +316,9 @@ def power_attn_decode_absorb_workspace_bytes(prob: PaProblem) -> int:
 
 def power_attn_decode_absorb(prob: PaProblem, K, V, state, log_g=None, fast: bool = True):
     """Feeds the prompt K [B, H, T, d], V [B, H, T, v] (prob.T = T) into the state, as T decode steps
-    would, without outputs.  fast: give the library the workspace its matrix-core path asks for, where
-    it has one (sums rounded to bf16 once); else the float32 kernel runs."""
+    would, without outputs.  fast: give the library the workspace its state scan asks for, where it has one
+    (sums rounded to bf16 once); else the sums are float32 (on the matrix cores for bf16, p = 2, d = v in
+    {32, 64, 128})."""
     import torch
     lib = load_library()
     lg = None if log_g is None else _dev_ptr(log_g, name="log_g")

@@ -357,7 +357,7 @@ bool bwd_n(const Ctx& c, const float* Q, const float* K, const float* V, const f
 template <int P, int HD>
 bool bwd_t(const Ctx& c, const float* Q, const float* K, const float* V, const float* O, const float* Z, const float* dO, float* dQ,
            float* dK, float* dV) {
-    // at d = 128 two blocks of operands and accumulators would not leave two waves per SIMD
+    // at d = 128 one block of operands and accumulators already fills the registers of a wave (dK / dV: 288, one wave per SIMD)
     if constexpr (HD < 128)
         if (wide_blocks(c.prob.B * c.prob.H, c.prob.T)) return bwd_n<P, HD, 2>(c, Q, K, V, O, Z, dO, dQ, dK, dV);
     return bwd_n<P, HD, 1>(c, Q, K, V, O, Z, dO, dQ, dK, dV);
