@@ -217,7 +217,8 @@ __device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, i
 // Workgroups are numbered so that the ones with the longest walk start first: grid (heads of a group, blocks, groups), so the
 // longest blocks of every head of a group come before the next ones.  (With the blocks of one head after the other, the last
 // heads' long walks started when most of the chip was done: at 16 heads of 16384 tokens the CUs were busy 62 % of the time, and
-// the p = 4 kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)  More blocks than y is given go on in z.
+// the p = 4 kernels took 468 / 685 / 926 us instead of 330 / 445 / 587.)  More blocks than y is given go on in z (the device
+// states 65536 as the most of either).
 struct Order {
     int group, parts;       // heads per group; slices of y that a group's blocks take
 };
