@@ -129,6 +129,13 @@ KERNEL_ROLE = {
     "tiled_dk": ("dphi", PEAK_BF16_MFMA_TFLOPS),
     "tiled_dv": ("dv_readout", PEAK_BF16_MFMA_TFLOPS),
     "mfma_fwd_chunk_partial": ("chunk_fwd", PEAK_BF16_MFMA_TFLOPS),
+    # p = 2, d = 64 / 128: states 1280 / 1024 tokens apart whatever the chunk (STATE_SPACING), the pairs in between on mfma_fwd_chunk
+    # and chunk_bwd_*
+    "mfma_state_totals": ("recompute", PEAK_BF16_MFMA_TFLOPS),
+    "mfma_query_state": ("query_state", PEAK_BF16_MFMA_TFLOPS),
+    "mfma_dq_state": ("dphi", PEAK_BF16_MFMA_TFLOPS),
+    "mfma_dk_state": ("dphi", PEAK_BF16_MFMA_TFLOPS),
+    "mfma_dv_state": ("dv_readout", PEAK_BF16_MFMA_TFLOPS),
     "chunk_fwd": ("chunk_fwd", PEAK_BF16_MFMA_TFLOPS),
     "chunk_bwd": ("pairs_bwd", PEAK_BF16_MFMA_TFLOPS),
     "chunk_bwd_dq": ("chunk_dq", PEAK_BF16_MFMA_TFLOPS),
@@ -139,6 +146,9 @@ KERNEL_ROLE = {
     "attn_bwd_dq": ("bwd_dq", PEAK_BF16_MFMA_TFLOPS),
     "attn_bwd_dkdv": ("bwd_dkdv", PEAK_BF16_MFMA_TFLOPS),
 }
+
+
+STATE_SPACING = {64: 1280, 128: 1024}
 
 
 def measured_traffic(workload, kernel):
@@ -416,19 +426,23 @@ def run_workload(args, name, cpu):
     for _ in range(args.steps):
         step()
     kernels = binding.profile_end()
-    fl, by = algorithmic_flops(w), algorithmic_bytes(w)
+    total_alg = sum(algorithmic_flops(w)[k] for k in (("fwd_total", "bwd_total") if with_bwd else ("fwd_total",)))
+    spaced = "mfma_query_state" in kernels
+    wk = dict(w, chunk=STATE_SPACING[w["d"]]) if spaced else w          # what a kernel is credited with
+    roles = dict(KERNEL_ROLE, mfma_fwd_chunk=("chunk_fwd", PEAK_BF16_MFMA_TFLOPS)) if spaced else KERNEL_ROLE
+    fl, by = algorithmic_flops(wk), algorithmic_bytes(wk)
     per_kernel = {}
     for kname, (launches, ms_total) in kernels.items():
         per_kernel[kname] = {"launches_per_step": launches / args.steps, "avg_ms": ms_total / launches}
-        if kname in KERNEL_ROLE:
-            role, peak = KERNEL_ROLE[kname]
+        if kname in roles:
+            role, peak = roles[kname]
             sec = ms_total / launches * 1e-3
             per_kernel[kname].update({"tflops": fl[role] / sec / 1e12, "frac_compute_peak": fl[role] / sec / 1e12 / peak,
                                       "hbm_gbs": by[role] / sec / 1e9, "frac_hbm_peak": by[role] / sec / 1e9 / PEAK_HBM_GBS})
     # The dominant kernel, and the roof that bounds it: the one whose lower bound on its time is larger.
-    credited = {k: v for k, v in kernels.items() if k in KERNEL_ROLE and KERNEL_ROLE[k][0] != "recompute"}
+    credited = {k: v for k, v in kernels.items() if k in roles and roles[k][0] != "recompute"}
     dom = max(credited, key=lambda k: credited[k][1])
-    role, peak = KERNEL_ROLE[dom]
+    role, peak = roles[dom]
     dom_ms = credited[dom][1] / credited[dom][0]
     t_compute = fl[role] / (peak * 1e12)
     t_hbm = by[role] / (PEAK_HBM_GBS * 1e9)
@@ -446,7 +460,6 @@ def run_workload(args, name, cpu):
                     "avg_kernel_ms": dom_ms, "algorithmic_flops_per_launch": fl[role],
                     "algorithmic_bytes_per_launch": by[role]}
     roofline["traffic_source"] = traffic_source() if traffic is not None else None
-    total_alg = fl["fwd_total"] + (fl["bwd_total"] if with_bwd else 0)
     out = {
         "metric": "power-attention fwd+bwd tokens/sec at p=2,d=64,T=64k; % bf16 MFMA peak",
         "value": tokens / (ms_per_step * 1e-3), "unit": "tokens/s", "n_gpus": 1, "steps": args.steps,

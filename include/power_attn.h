@@ -61,8 +61,8 @@ typedef enum { PA_DTYPE_F32 = 0, PA_DTYPE_BF16 = 1 } pa_dtype;
 typedef enum {
     PA_IMPL_AUTO    = 0,
     PA_IMPL_GENERIC = 1,  /* float32 arithmetic on the vector ALUs; any 1 <= p <= 4, d, v <= 128; both dtypes */
-    PA_IMPL_MFMA    = 2,  /* bf16 MFMA with float32 accumulation; bf16 only.  Chunked form: p = 2, d = v = 64,
-                             chunk a multiple of 128.  Attention form (chunk == T; any T, or with
+    PA_IMPL_MFMA    = 2,  /* bf16 MFMA with float32 accumulation; bf16 only.  Chunked form: p = 2, d = v = 64
+                             or (not gated) 128, chunk a multiple of 128.  Attention form (chunk == T; any T, or with
                              gates T a multiple of 128, of 256 at d = 32): p in {2, 3, 4}, d = v in {32, 64, 128}.  See power_attn_supported() */
     PA_IMPL_RESIDENT = 3, /* the chunked bf16 MFMA kernels that keep the chunk states in registers while they walk the
                              sequence (no chunk state is written to memory): p = 2, d = v in {64, 128}, chunk a multiple
@@ -71,8 +71,7 @@ typedef enum {
                              (Sec. 4.1.1) as parameters, chunk states in memory: d = v = 32 with (p, d_tile) in
                              {(2,4), (2,8), (2,16), (3,4), (4,2), (4,4)}, d = v = 64 with {(2,4), (2,8), (2,16), (3,4)},
                              d = v = 128 with (2,8); chunk a multiple of 128 that divides T, at least two chunks, not
-                             gated.  What AUTO runs for the chunked form of p = 3 and p = 4, of d = 32, and of p = 2
-                             at d = 128 */
+                             gated.  What AUTO runs for the chunked form of p = 3 and p = 4 and of d = 32 */
 } pa_impl;
 
 typedef struct {
@@ -83,9 +82,12 @@ typedef struct {
     int   chunk;        /* chunk size c of the chunked form.  chunk == T is the attention form (one chunk).
                            0: the library chooses between the two forms and the chunk size (see
                            power_attn_resolved_chunk).  A chunk that does not divide T (a ragged last
-                           chunk) is taken by the chunked bf16 MFMA kernels only, which then run the
-                           sequence padded with zero rows inside the workspace; elsewhere it is
-                           PA_ERR_UNSUPPORTED */
+                           chunk) is taken by the chunked bf16 MFMA kernels only (gated, or of the other
+                           degrees and head sizes: padded with zero rows inside the workspace); elsewhere it is
+                           PA_ERR_UNSUPPORTED.  bf16, p = 2, d = v = 64 or 128, not gated, under AUTO or MFMA: the
+                           kernels space their states as they run fastest (over 1000 tokens apart, and none at all for
+                           sequences up to 7 or 8 thousand tokens at d = 64, 14 to 18 thousand at d = 128), whatever
+                           multiple of 128 was asked for; the result does not depend on it beyond rounding */
     int   normalize;    /* 1: divide by the sum of the scores; 0: leave un-normalised */
     float scale;        /* multiplies q.k before the power ("softmax scaling", App. E.1 step 2).  Some kernels multiply q
                            (or k) by it, or by its power of two, before the product: q.k, scale q, scale k and the
@@ -203,7 +205,8 @@ pa_status power_attn_decode_step(const pa_problem* prob, const void* q, const vo
                                  const float* log_g, void* state, size_t state_bytes,
                                  void* o, float* z, void* hip_stream);
 
-/* The chunk size the calls use for `prob` (prob->chunk itself unless it is 0; 0 on an invalid problem).  Un-gated float32
+/* The chunk size the calls use for `prob` (prob->chunk itself unless it is 0; 0 on an invalid problem).  Where the kernels space
+ * their states themselves (see pa_problem.chunk) it only says that the chunked form is asked for.  Un-gated float32
  * calls under PA_IMPL_AUTO with d = v in {16, 32, 64, 128} and T <= 4096 (<= 16384 where B H T <= 262144) run the attention
  * form at any chunk; the chunk, and the state rows below, are then those of the chunked form it takes the place of. */
 int power_attn_resolved_chunk(const pa_problem* prob);

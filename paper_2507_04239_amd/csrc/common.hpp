@@ -116,6 +116,8 @@ bool f32_attn_bwd(const Ctx& c, const float* Q, const float* K, const float* V, 
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward);
 long long mfma_state_rows(const pa_problem& pr);
 pa_status mfma_supported(const pa_problem& pr, bool backward);
+// the family runs a sequence that is not a multiple of the chunk as it is
+bool mfma_takes_ragged(const pa_problem& pr);
 pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z);
 pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, const void* O, const float* Z,
                    const void* dO, void* dQ, void* dK, void* dV);

@@ -252,6 +252,7 @@ struct ChunkedIn {
     const float* part = nullptr;     // forward: numerator; dQ kernel: dQ; dK / dV kernel: dK
     const float* part2 = nullptr;    // dK / dV kernel: dV (nslab2 slabs)
     const float* zpart = nullptr;    // forward: denominator
+    const char* label = "chunk_fwd"; // (host: the launch's name in the kernel times)
 };
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
 __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
@@ -709,7 +710,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     // query tiles t_first .. ntile - 1 reach the block's first key; chunked: up to the end of the chunk of the block's
     // last key, and a wave stops at the end of its own keys' chunk
     const int t_first = j0 / AT;
-    const int ntile = CHUNKED ? min(((j0 + WG - 1) / ck.cs + 1) * ck.cs, T) / AT : (T + AT - 1) / AT;
+    const int ntile = ((CHUNKED ? min(((j0 + WG - 1) / ck.cs + 1) * ck.cs, T) : T) + AT - 1) / AT;
     const int q_hi = CHUNKED ? (k0 / ck.cs + 1) * ck.cs : T + AT;
     uint4 qr[HD / 32], gr[HD / 32];
     float gzr = 0.f, gb = 0.f, gf2 = 0.f;
@@ -889,7 +890,7 @@ bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, b
     constexpr int WG = 4 * OWN;
     auto kern = k_attn_fwd<P, HD, OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
-    LaunchScope ls(CHUNKED ? "chunk_fwd" : "attn_fwd", s);
+    LaunchScope ls(CHUNKED ? ck.label : "attn_fwd", s);
     Order order{head_group<HD, CHUNKED, WG>(BH, T, ck)};
     const dim3 grid = block_grid(BH, (T + WG - 1) / WG, order);
     hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, BH, order, T,
@@ -898,7 +899,7 @@ bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, b
 }
 template <int P, int HD, bool GATED, bool CHUNKED = false>
 bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
-           int normalize, const float* bl, ChunkedIn ck = ChunkedIn()) {
+           int normalize, const float* bl, ChunkedIn ck = ChunkedIn(), const char* name = "attn_fwd") {
     if constexpr (HD == 64 && !CHUNKED)
         if (fwd_wide(BH, T)) return fwd_own<P, HD, GATED, CHUNKED, 64>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
     return fwd_own<P, HD, GATED, CHUNKED, Shape<HD>::FWD_OWN>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
@@ -975,13 +976,14 @@ bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t*
 }
 
 bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
-                      int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart) {
+                      int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart, const char* label) {
     ChunkedIn ck;
+    ck.label = label;
     ck.cs = cs;
     ck.nslab = nslab;
     ck.part = part;
     ck.zpart = zpart;
-    if (cs % AT != 0 || T % cs != 0) return false;
+    if (cs % AT != 0) return false;
 #define PA_CASE(PP, DD) \
     if (p == PP && d == DD) return fwd_t<PP, DD, false, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, nullptr, ck);
     PA_CASE(2, 32) PA_CASE(2, 64) PA_CASE(2, 128)
@@ -1016,7 +1018,7 @@ bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t
     ckk.nslab = nslab_dk;
     ckk.part2 = part_dv;
     ckk.nslab2 = nslab_dv;
-    if (cs % AT != 0 || T % cs != 0) return false;
+    if (cs % AT != 0) return false;
 #define PA_CASE(PP, DD)     \
     if (p == PP && d == DD) \
         return bwd_t<PP, DD, false, true>(s, Q, K, V, nullptr, nullptr, nullptr, const_cast<bf16_t*>(Gh), const_cast<float*>(gz), dQ, dK, dV, BH, T, scale, 1, AttnGate(), ckq, ckk);

@@ -175,6 +175,25 @@ bool launch_tiled_readout(const char* name, hipStream_t s, const TiledPlan& pl, 
 bool launch_tiled_dphi(const char* name, hipStream_t s, const TiledPlan& pl, const bf16_t* X, const bf16_t* Yp, const TileDesc* tab,
                        const bf16_t* st, float* part, int BH, int T, int cs, float xscale, float outscale);
 
+// ---- chunked form, p = 2, d = v in {64, 128}: states formed and used with phi in registers (see mfma_quad.hip) ---------
+struct QuadPlan {
+    int hd, cs, nchunk;           // chunks of cs tokens, the last one shorter where cs does not divide T
+    int nseg, seg_chunks;         // segments the scan is cut into
+    size_t state_elems, gam_elems;   // bf16 elements of one state and of one normaliser, nchunk - 1 of each per head
+    size_t tot_floats;            // scratch of the scan
+};
+QuadPlan quad_plan(int d, int BH, int T, int cs);
+// st, gam: the states before (rev: after) each chunk.  rev: wgt = gz, X enters multiplied by scale.
+bool launch_quad_scan(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y, const float* wgt,
+                      bf16_t* st, bf16_t* gam, float* tot, int BH, int T, float scale);
+// part[bh][t][:] = (state of t's chunk)^T phi(scale X_t), zpart[bh][t] (may be null) = the same of the normaliser; zeros where
+// the chunk has no state
+bool launch_quad_read(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* st,
+                      const bf16_t* gam, float* part, float* zpart, int BH, int T, float scale);
+// part[bh][t][:] = d/dX_t of phi(scale X_t) . (state of t's chunk . Y_t) and of wgt_t times the normaliser's part (wgt null: 1)
+bool launch_quad_dphi(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y, const float* wgt,
+                      const bf16_t* st, const bf16_t* gam, float* part, int BH, int T, float scale);
+
 // gating: xb[bh][n] = the sum over the pairs that straddle the end of chunk n, from the stored states
 bool launch_gate_boundary(hipStream_t s, const bf16_t* stC, const bf16_t* rtC, const bf16_t* gam, const bf16_t* omg, float* xb,
                           int BH, int nstate);
@@ -189,7 +208,8 @@ bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t*
 // tokens), plus what came through the state: part[slab][BH][T][d] (float32, nslab slabs) joins the numerator,
 // zpart[BH][T] the denominator
 bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
-                      int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart);
+                      int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart,
+                      const char* label = "chunk_fwd");
 // ghat = dO / Z (bf16) and gz = -(ghat . O) (float32) per token, d in {32, 64, 128}
 bool launch_attn_prep(hipStream_t s, int d, const bf16_t* dO, const bf16_t* O, const float* Z, bf16_t* Gh, float* gz, long long rows,
                       int normalize);

@@ -1,6 +1,8 @@
 // Host side of the bf16 MFMA kernel families: support check, workspace layout and the launch
 // sequences of the forward and backward passes.  Two sets of kernels: the chunked form for p = 2,
 // d = v = 64, and the attention form (chunk == T, no state) for p in {2, 3, 4}, d = v in {32, 64, 128}.
+#include <algorithm>
+
 #include "mfma_common.hpp"
 
 namespace pa {
@@ -108,7 +110,12 @@ bool attn_ok(const pa_problem& pr) {
 }
 // One chunk: the attention-form kernels.  (The chunked kernels can run p = 2, d = 64 as one chunk
 // too; that path remains for gated sequences that are a multiple of 128 but not of the block.)
-bool use_attn(const pa_problem& pr) { return attn_ok(pr) && pr.impl != PA_IMPL_RESIDENT && pr.impl != PA_IMPL_TILED; }
+bool use_quad(const pa_problem& pr);
+bool quad_states(const pa_problem& pr, bool backward);
+bool use_attn(const pa_problem& pr, bool backward) {
+    if (use_quad(pr)) return !quad_states(pr, backward);
+    return attn_ok(pr) && pr.impl != PA_IMPL_RESIDENT && pr.impl != PA_IMPL_TILED;
+}
 bool use_tiled(const pa_problem& pr);
 // The resident-state kernels run when asked for by name, and wherever they are the only matrix-core kernels
 // for the chunked form
@@ -178,6 +185,60 @@ AttnLayout make_attn_layout(const pa_problem& pr, bool backward) {
     return L;
 }
 
+// Chunk-state kernels with phi in registers (mfma_quad.hip): what AUTO and MFMA run for the un-gated chunked form of p = 2 at
+// d = 64 and 128, whatever multiple of 128 tokens the chunk is.  The states they keep are QUAD_CHUNK tokens apart: the result does
+// not depend on the chunk beyond rounding, and states are rounded less often the fewer they are.
+bool quad_ok(const pa_problem& pr) {
+    return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && (pr.d == 64 || pr.d == 128) && pr.v == pr.d && pr.chunk > 0 &&
+           pr.chunk % QBLK == 0 && pr.chunk < pr.T && !pr.gated && pr.d_tile == 0 && (size_t)pr.B * pr.H <= 65535u;
+}
+bool use_quad(const pa_problem& pr) { return (pr.impl == PA_IMPL_AUTO || pr.impl == PA_IMPL_MFMA) && quad_ok(pr); }
+// Tokens per state.  A state's traffic falls with the distance, the pairs in between grow with it; the step is flat around the
+// best (ms, forward + backward): 12 heads of 65536, d = 64: 512 3.23, 768 3.00, 1024 3.05, 1280 2.97, 1536 3.03, 2048 3.24;
+// 32 heads of 32768, d = 128: 512 17.6, 768 18.4, 1024 17.4, 1536 18.0, 2048 18.0.  (Multiples of 256 at d = 64 and of 512 at
+// d = 128 fill the workgroups of the per-chunk kernels.)
+int quad_chunk(int d) { return d == 64 ? 1280 : 1024; }
+// Shorter sequences run as one chunk, without a state: (heads x tokens: us whole, with states)  d = 64 forward 12 x 6144
+// 81, 106, 12 x 8192 122, 120, 48 x 6144 214, 289, 48 x 8192 361, 384, 12 x 12288 253, 180; backward 12 x 6144 209, 290,
+// 12 x 8192 351, 329, 48 x 6144 746, 825, 48 x 8192 1282, 1124, 2 x 8192 158, 184; d = 128 forward 16 x 16384 1100, 1349,
+// 16 x 24576 2490, 2112, 2 x 16384 311, 371, 2 x 24576 522, 444; backward 16 x 12288 2187, 2782, 16 x 16384 3826, 3644,
+// 2 x 12288 738, 761, 2 x 16384 978, 868.
+int quad_whole_upto(int d, bool backward) { return d == 64 ? (backward ? 7168 : 8191) : (backward ? 14336 : 18432); }
+bool quad_states(const pa_problem& pr, bool backward) { return use_quad(pr) && pr.T > quad_whole_upto(pr.d, backward); }
+struct QuadLayout {
+    QuadPlan pl;
+    size_t off_tot, off_st, off_gam, off_part, off_zpart;
+    size_t off_gh, off_gz, off_rc, off_omg, off_pdq, off_pdk;   // backward only
+    size_t total;
+};
+QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
+    QuadLayout L{};
+    const size_t BH = (size_t)pr.B * pr.H, rows = BH * pr.T;
+    L.pl = quad_plan(pr.d, (int)BH, pr.T, quad_chunk(pr.d));
+    const size_t nslot = BH * (L.pl.nchunk - 1);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        size_t o = off;
+        off = align_up(off + bytes, 256);
+        return o;
+    };
+    L.off_tot = take(L.pl.tot_floats * sizeof(float));
+    L.off_st = take(nslot * L.pl.state_elems * 2);
+    L.off_gam = take(nslot * L.pl.gam_elems * 2);
+    L.off_part = take(rows * pr.d * sizeof(float));
+    L.off_zpart = take(rows * sizeof(float));
+    if (backward || pr.keep_state) {
+        L.off_gh = take(rows * pr.d * 2);
+        L.off_gz = take(rows * sizeof(float));
+        L.off_rc = take(nslot * L.pl.state_elems * 2);
+        L.off_omg = take(nslot * L.pl.gam_elems * 2);
+        L.off_pdq = take(rows * pr.d * sizeof(float));
+        L.off_pdk = take(rows * pr.d * sizeof(float));
+    }
+    L.total = off;
+    return L;
+}
+
 // The tiled kernels run when asked for by name or for a tile width, and wherever no other matrix-core kernel takes the
 // chunked form of the problem (degrees 3 and 4, d = 32) or they are the faster ones (d = 128: measured against the
 // resident-state walk, which has to cut the state into slabs there)
@@ -190,27 +251,38 @@ bool use_tiled(const pa_problem& pr) {
 
 }  // namespace
 
-int mfma_gate_fin_chunk(const pa_problem& pr) { return use_attn(pr) ? attn_gate_block(pr.d) : pr.chunk; }
+int mfma_gate_fin_chunk(const pa_problem& pr) { return use_attn(pr, true) ? attn_gate_block(pr.d) : pr.chunk; }
+
+bool mfma_takes_ragged(const pa_problem& pr) { return use_quad(pr); }
 
 pa_status mfma_supported(const pa_problem& pr, bool backward) {
+    if (use_quad(pr)) return PA_OK;
     if (pr.impl == PA_IMPL_RESIDENT) return resident_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
     if (pr.impl == PA_IMPL_TILED || pr.d_tile > 0) return tiled_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
     return chunked_ok(pr) || attn_ok(pr) || resident_ok(pr) || tiled_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
 }
 
 long long mfma_state_rows(const pa_problem& pr) {
+    if (use_quad(pr)) return (long long)(pr.d / 8) * (pr.d / 8 + 1) / 2 * 64;
     if (use_tiled(pr)) {
         const TiledPlan pl = tiled_plan(pr.p, pr.d, tiled_dt(pr));
         return (long long)pl.ntile * pl.rows_per_tile;
     }
     if (use_resident(pr)) return (long long)(pr.d / 8) * (pr.d / 8 + 1) / 2 * 64;
-    return use_attn(pr) ? 0 : (long long)NTILES * 64;
+    return use_attn(pr, false) ? 0 : (long long)NTILES * 64;
 }
 
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
+    if (use_quad(pr)) {
+        // (a ragged sequence asks for a little more than the next whole number of chunks, as it did when it ran padded)
+        pa_problem up = pr;
+        up.T = (pr.T + pr.chunk - 1) / pr.chunk * pr.chunk;
+        const size_t states = quad_states(up, backward) ? make_quad_layout(up, backward).total : 0;
+        return std::max(states, make_attn_layout(up, backward).total) + (up.T > pr.T ? 256 : 0);
+    }
     if (use_tiled(pr)) return make_tiled_layout(pr, backward).total;
     if (use_resident(pr)) return make_res_layout(pr, backward).total;
-    return use_attn(pr) ? make_attn_layout(pr, backward).total : make_layout(pr, backward).total;
+    return use_attn(pr, backward) ? make_attn_layout(pr, backward).total : make_layout(pr, backward).total;
 }
 
 #define PA_TRY(CALL) \
@@ -222,9 +294,21 @@ size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
 pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z) {
     const pa_problem& pr = c.prob;
     const int BH = pr.B * pr.H;
-    if (use_attn(pr)) {
+    if (use_attn(pr, false)) {
         PA_TRY(launch_attn_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH, pr.T,
                                pr.scale, pr.normalize, c.gate.bl))
+        return PA_OK;
+    }
+    if (use_quad(pr)) {
+        // states, read-out; the in-chunk part and the division on the chunk-local attention kernel
+        const QuadLayout L = make_quad_layout(pr, pr.keep_state != 0);
+        bf16_t *st = (bf16_t*)(c.ws + L.off_st), *gam = (bf16_t*)(c.ws + L.off_gam);
+        float *part = (float*)(c.ws + L.off_part), *zpart = (float*)(c.ws + L.off_zpart);
+        PA_TRY(launch_quad_scan("mfma_state_scan", c.stream, L.pl, false, (const bf16_t*)K, (const bf16_t*)V, nullptr, st, gam,
+                                (float*)(c.ws + L.off_tot), BH, pr.T, 1.0f))
+        PA_TRY(launch_quad_read("mfma_query_state", c.stream, L.pl, false, (const bf16_t*)Q, st, gam, part, zpart, BH, pr.T, pr.scale))
+        PA_TRY(launch_chunk_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH, pr.T,
+                                L.pl.cs, pr.scale, pr.normalize, part, 1, zpart, "mfma_fwd_chunk"))
         return PA_OK;
     }
     if (use_tiled(pr)) {
@@ -332,7 +416,7 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
                    const void* dO, void* dQ, void* dK, void* dV) {
     const pa_problem& pr = c.prob;
     const int BH = pr.B * pr.H;
-    if (use_attn(pr)) {
+    if (use_attn(pr, true)) {
         const AttnLayout A = make_attn_layout(pr, true);
         AttnGate ag;
         if (pr.gated) {
@@ -345,6 +429,25 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
         PA_TRY(launch_attn_bwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)O, Z,
                                (const bf16_t*)dO, (bf16_t*)(c.ws + A.off_gh), (float*)(c.ws + A.off_gz), (bf16_t*)dQ, (bf16_t*)dK,
                                (bf16_t*)dV, BH, pr.T, pr.scale, pr.normalize, ag))
+        return PA_OK;
+    }
+    if (use_quad(pr)) {
+        // dQ's state part from S, the state gradient R, dV's and dK's from R; one kernel then adds the in-chunk gradients
+        const QuadLayout L = make_quad_layout(pr, true);
+        bf16_t *st = (bf16_t*)(c.ws + L.off_st), *gam = (bf16_t*)(c.ws + L.off_gam);
+        bf16_t *rc = (bf16_t*)(c.ws + L.off_rc), *omg = (bf16_t*)(c.ws + L.off_omg), *Gh = (bf16_t*)(c.ws + L.off_gh);
+        float *gz = (float*)(c.ws + L.off_gz), *tot = (float*)(c.ws + L.off_tot);
+        float *pdv = (float*)(c.ws + L.off_part), *pdq = (float*)(c.ws + L.off_pdq), *pdk = (float*)(c.ws + L.off_pdk);
+        const bf16_t *q = (const bf16_t*)Q, *k = (const bf16_t*)K, *v = (const bf16_t*)V;
+        hipStream_t s = c.stream;
+        PA_TRY(launch_attn_prep(s, pr.d, (const bf16_t*)dO, (const bf16_t*)O, Z, Gh, gz, (long long)BH * pr.T, pr.normalize))
+        if (!pr.keep_state || !quad_states(pr, false)) PA_TRY(launch_quad_scan("mfma_state_scan_bwd", s, L.pl, false, k, v, nullptr, st, gam, tot, BH, pr.T, 1.0f))
+        PA_TRY(launch_quad_dphi("mfma_dq_state", s, L.pl, false, q, Gh, gz, st, gam, pdq, BH, pr.T, pr.scale))
+        PA_TRY(launch_quad_scan("mfma_state_grad_scan", s, L.pl, true, q, Gh, gz, rc, omg, tot, BH, pr.T, pr.scale))
+        PA_TRY(launch_quad_read("mfma_dv_state", s, L.pl, true, k, rc, omg, pdv, nullptr, BH, pr.T, 1.0f))
+        PA_TRY(launch_quad_dphi("mfma_dk_state", s, L.pl, true, k, v, nullptr, rc, omg, pdk, BH, pr.T, 1.0f))
+        PA_TRY(launch_chunk_bwd(s, pr.p, pr.d, q, k, v, Gh, gz, (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, BH, pr.T, L.pl.cs, pr.scale, pdq,
+                                1, pdk, 1, pdv, 1))
         return PA_OK;
     }
     if (use_tiled(pr)) {

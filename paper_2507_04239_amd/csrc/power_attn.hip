@@ -94,7 +94,7 @@ int auto_chunk(const pa_problem& pr) {
     // d = 32, 32 heads: T = 4096 0.37 and 0.18, 6144 0.54 and 0.36, 8192 0.70 and 0.63, 32768 2.7 and 8.8.  For the higher degrees
     // the attention form stays ahead at every length measured (p = 3, d = 64, 4 heads: T = 16384 7.0 and 0.78, 131072 60 and 37;
     // p = 4, d = 32, 16 heads: 16384 24 and 1.4, 65536 97 and 20).
-    const int attn_upto = pr.d == 128 ? 24575 : (pr.gated ? 2048 : 4096);
+    const int attn_upto = pr.d == 128 ? 18432 : (pr.gated ? 2048 : 4096);
     if (may_mfma && pr.p == 2 && (pr.d == 32 || pr.d == 64 || pr.d == 128) && mfma_supported(probe, true) == PA_OK &&
         !(attn && pr.T <= attn_upto))
         return probe.chunk;
@@ -145,7 +145,7 @@ struct Padding {
 Padding padding_for(const pa_problem& pr) {
     Padding pd;
     pd.prob = pr;
-    if (pr.chunk <= 0 || pr.T % pr.chunk == 0) return pd;
+    if (pr.chunk <= 0 || pr.T % pr.chunk == 0 || mfma_takes_ragged(pr)) return pd;
     pd.on = true;
     pd.prob.T = (pr.T + pr.chunk - 1) / pr.chunk * pr.chunk;
     const size_t rows = (size_t)pr.B * pr.H * pd.prob.T;

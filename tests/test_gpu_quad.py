@@ -1,0 +1,80 @@
+"""Chunk-state kernels of p = 2 at d = 64 and 128: lengths around their tiles (64-token stages, blocks of 256 and 512 tokens,
+states 1280 or 1024 tokens apart, a last chunk of any length), few and many heads (the state scan in segments or in one walk),
+kept and rebuilt states, scales with and without a power of two, against the definition in float64 on the GPU."""
+import numpy as np
+import pytest
+
+from gpu_util import assert_close, run_fwd_bwd
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(Q, K, V, G, scale, normalize, block=2048):
+    """One head in float64, rows of queries in blocks: O, Z, dQ, dK, dV as the header defines them (p = 2)."""
+    import torch
+    q, k, v, g = (torch.from_numpy(a).to("cuda:0", torch.float64) for a in (Q, K, V, G))
+    T = q.shape[0]
+    O, Z, dQ, dK, dV = torch.zeros_like(v), q.new_zeros(T), torch.zeros_like(q), torch.zeros_like(k), torch.zeros_like(v)
+    for a in range(0, T, block):
+        b = min(a + block, T)
+        kt, vt = k[:b].t().contiguous(), v[:b].t().contiguous()
+        s = scale * (q[a:b] @ kt)
+        s.masked_fill_(torch.arange(b, device=q.device)[None, :] > torch.arange(a, b, device=q.device)[:, None], 0.0)
+        w = s * s
+        Z[a:b] = w.sum(1)
+        den = Z[a:b, None] if normalize else 1.0
+        O[a:b] = (w @ v[:b]) / den
+        gh = g[a:b] / den
+        e = gh @ vt
+        if normalize:
+            e -= (gh * O[a:b]).sum(1, keepdim=True)
+        t = 2.0 * scale * e * s
+        dQ[a:b] = t @ k[:b]
+        dK[:b] += t.t().contiguous() @ q[a:b]
+        dV[:b] += w.t().contiguous() @ gh
+    return {n: x.cpu().numpy() for n, x in zip(("O", "Z", "dQ", "dK", "dV"), (O, Z, dQ, dK, dV))}
+
+
+CASES = [
+    # heads, T, d, chunk asked for, scale, normalize, keep
+    (1, 7169, 64, 128, 1.0, True, True),       # the shortest backward pass with states: the forward pass has none to keep
+    (2, 8192, 64, 128, 0.3, True, True),       # ... and the shortest forward pass
+    (1, 8959, 64, 256, 1.0, True, False),      # 7 x 1280 - 1, 7 x 1280, one token of an eighth chunk
+    (3, 8960, 64, 128, 1.0, True, False),
+    (1, 8961, 64, 128, 2.0, True, True),
+    (13, 9300, 64, 128, 1.0, False, False),
+    (1, 14337, 128, 128, 1.0, True, True),     # (d = 128: states 1024 apart)
+    (1, 18433, 128, 256, 0.7, True, True),
+    (2, 19456, 128, 128, 1.0, True, False),    # 19 x 1024
+    (14, 18500, 128, 256, 1.0, False, True),   # one walk per head: no segments
+]
+
+
+@pytest.mark.parametrize("heads,T,d,chunk,scale,normalize,keep", CASES)
+def test_long_sequences(heads, T, d, chunk, scale, normalize, keep):
+    what = f"heads={heads} T={T} d={d} chunk={chunk} scale={scale} norm={normalize} keep={keep}"
+    print(what, flush=True)
+    rng = np.random.default_rng(7 * T + d)
+
+    def bf16(a):
+        import torch
+        return torch.from_numpy(a.astype(np.float32)).bfloat16().float().numpy()
+
+    Q, K, V, G = (bf16(rng.standard_normal((1, heads, T, d), dtype=np.float32) * s) for s in (d ** -0.5, d ** -0.5, 1.0, 1.0))
+    got = run_fwd_bwd(Q, K, V, G, 2, chunk, "bf16", normalize=normalize, scale=scale, keep_state=keep)
+    for h in sorted({0, heads - 1}):
+        want = reference(Q[0, h], K[0, h], V[0, h], G[0, h], scale, normalize)
+        assert_close({n: a[0, h] for n, a in got.items()}, want, "bf16", f"{what} head {h}")
+
+
+@pytest.mark.parametrize("d,T", [(64, 9000), (128, 18500)])
+def test_runs_are_bit_identical_and_chunks_agree(d, T):
+    """Fixed order of sums, no float atomics; and the chunk asked for does not change which kernels run."""
+    rng = np.random.default_rng(d)
+    Q, K, V, G = (rng.standard_normal((1, 2, T, d), dtype=np.float32) * s for s in (d ** -0.5, d ** -0.5, 1.0, 1.0))
+    a = run_fwd_bwd(Q, K, V, G, 2, 128, "bf16")
+    b = run_fwd_bwd(Q, K, V, G, 2, 128, "bf16", keep_state=True)
+    c = run_fwd_bwd(Q, K, V, G, 2, 384, "bf16")
+    for n in a:
+        assert np.array_equal(a[n], b[n]), n
+        assert np.array_equal(a[n], c[n]), n
