@@ -61,12 +61,13 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 //   bl    [BH][T]       bl_i; a pair inside a chunk carries exp(bl_i - bl_j)
 //   qfac  [BH][T]       exp(bl_i): decay of query i since the start of its chunk
 //   kfac  [BH][T]       exp(bl_end - bl_j): decay of key j until the end of its chunk
-//   lam   [BH][T/chunk] exp(bl_end): decay across the whole chunk
+//   lam   [BH][chunks]  exp(bl_end): decay across the whole chunk
+// (a chunk being what the kernels that read them take for one: see mfma_gate_chunk)
 //   db    [BH][T]       backward pass: q_i . dq_i, written by the family's dQ kernel from its float32 accumulators
 //   db2   [BH][T]       backward pass: k_i . dk_i, likewise
 struct GateBuf {
     float *bl = nullptr, *qfac = nullptr, *kfac = nullptr, *lam = nullptr, *db = nullptr, *db2 = nullptr;
-    float* xb = nullptr;    // [BH][T/chunk] backward: <R_m, S_{m+1}>, the pairs that straddle the end of chunk m (0 for the last)
+    float* xb = nullptr;    // [BH][chunks] backward: <R_m, S_{m+1}>, the pairs that straddle the end of chunk m (0 for the last)
 };
 
 struct Ctx {
@@ -80,10 +81,11 @@ struct Ctx {
 // gating (family-independent kernels)
 size_t gate_workspace_bytes(const pa_problem& pr, bool backward);
 GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base);
-pa_status gate_prepare(const Ctx& c, const float* log_g);
+pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk);
 // The family has already written gate.xb, q.dq into gate.db and k.dk into gate.db2.
-// fin_chunk: the token granularity of gate.xb (the problem's chunk, or finer when the family says so)
-pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk);
+// fin_chunk: the token granularity of gate.xb (the problem's chunk, or what the family says); xparts: terms that an entry of
+// gate.xb is kept in
+pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts);
 
 // generic (vector-ALU, float32) family
 size_t generic_workspace_bytes(const pa_problem& pr, bool backward);
@@ -117,7 +119,9 @@ size_t mfma_workspace_bytes(const pa_problem& pr, bool backward);
 long long mfma_state_rows(const pa_problem& pr);
 pa_status mfma_supported(const pa_problem& pr, bool backward);
 // the family runs a sequence that is not a multiple of the chunk as it is
-bool mfma_takes_ragged(const pa_problem& pr);
+bool mfma_takes_ragged(const pa_problem& pr, bool backward);
+// gated: tokens after which the running sums of the log-gates start anew
+int mfma_gate_chunk(const pa_problem& pr, bool backward);
 pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z);
 pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, const void* O, const float* Z,
                    const void* dO, void* dQ, void* dK, void* dV);
@@ -129,7 +133,7 @@ pa_status mfma_absorb(const pa_problem& pr, const void* K, const void* V, const 
                       float* gamd, int D);
 // destroys the calling thread's side stream and events of the MFMA backward pass, if it has any
 void mfma_release_side_stream();
-// tokens per entry of GateBuf::xb as mfma_bwd leaves it (gated problems)
-int mfma_gate_fin_chunk(const pa_problem& pr);
+// tokens per entry of GateBuf::xb as mfma_bwd leaves it (gated problems), and the terms of an entry
+int mfma_gate_fin_chunk(const pa_problem& pr, int& xparts);
 
 }  // namespace pa

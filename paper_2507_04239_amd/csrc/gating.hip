@@ -19,8 +19,9 @@ __global__ __launch_bounds__(GT) void k_gate_prep(const float* __restrict__ log_
     __shared__ float part[GT];
     const int n = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
     const size_t base = (size_t)bh * T + (size_t)n * chunk;
-    const int per = (chunk + GT - 1) / GT;        // consecutive tokens per thread
-    const int lo = min(tid * per, chunk), hi = min(lo + per, chunk);
+    const int len = min(chunk, T - n * chunk);    // (the last chunk may be shorter)
+    const int per = (len + GT - 1) / GT;          // consecutive tokens per thread
+    const int lo = min(tid * per, len), hi = min(lo + per, len);
     float s = 0.f;
     for (int i = lo; i < hi; ++i) s += log_g[base + i];
     part[tid] = s;
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(GT) void k_gate_prep(const float* __restrict__ log_
         qfac[base + i] = __expf(run);
         kfac[base + i] = __expf(total - run);
     }
-    if (tid == 0) lam[(size_t)bh * (T / chunk) + n] = __expf(total);
+    if (tid == 0) lam[(size_t)bh * gridDim.x + n] = __expf(total);
 }
 
 // dlog_g[t] = sum_{i >= t} dL/db_i.  A running sum over the whole sequence would pile up the
@@ -55,13 +56,14 @@ __device__ __forceinline__ float gate_term(const float* __restrict__ db, const f
 }
 
 __global__ __launch_bounds__(GT) void k_gate_finish(const float* __restrict__ db, const float* __restrict__ db2, float inv_p,
-                                                    const float* __restrict__ xb, float* __restrict__ dlog_g,
+                                                    const float* __restrict__ xb, int xparts, float* __restrict__ dlog_g,
                                                     int T, int chunk) {
     __shared__ float part[GT];
     const int n = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
     const size_t base = (size_t)bh * T + (size_t)n * chunk;
-    const int per = (chunk + GT - 1) / GT;
-    const int lo = min(tid * per, chunk), hi = min(lo + per, chunk);
+    const int len = min(chunk, T - n * chunk);
+    const int per = (len + GT - 1) / GT;
+    const int lo = min(tid * per, len), hi = min(lo + per, len);
     float s = 0.f;
     for (int i = lo; i < hi; ++i) s += gate_term(db, db2, inv_p, base + i);
     part[tid] = s;
@@ -72,7 +74,8 @@ __global__ __launch_bounds__(GT) void k_gate_finish(const float* __restrict__ db
         part[tid] += add;
         __syncthreads();
     }
-    float run = xb[(size_t)bh * (T / chunk) + n] + (tid + 1 < GT ? part[tid + 1] : 0.f);
+    float run = tid + 1 < GT ? part[tid + 1] : 0.f;
+    for (int k = 0; k < xparts; ++k) run += xb[((size_t)bh * gridDim.x + n) * xparts + k];
     for (int i = hi - 1; i >= lo; --i) {
         run += gate_term(db, db2, inv_p, base + i);
         dlog_g[base + i] = run;
@@ -112,15 +115,15 @@ GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base) {
     return g;
 }
 
-pa_status gate_prepare(const Ctx& c, const float* log_g) {
+pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk) {
     const pa_problem& pr = c.prob;
     LaunchScope ls("gate_prep", c.stream);
-    hipLaunchKernelGGL(k_gate_prep, dim3(pr.T / pr.chunk, pr.B * pr.H), dim3(GT), 0, c.stream, log_g, c.gate.bl, c.gate.qfac,
-                       c.gate.kfac, c.gate.lam, pr.T, pr.chunk);
+    hipLaunchKernelGGL(k_gate_prep, dim3((pr.T + chunk - 1) / chunk, pr.B * pr.H), dim3(GT), 0, c.stream, log_g, c.gate.bl, c.gate.qfac,
+                       c.gate.kfac, c.gate.lam, pr.T, chunk);
     return launch_ok() ? PA_OK : PA_ERR_HIP;
 }
 
-pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk) {
+pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts) {
     const pa_problem& pr = c.prob;
     // Under the sum normalisation q_i . dq_i is zero in exact arithmetic, yet the term stays: what the
     // device finds there is dO_i . (O_i - rounded O_i), and the k_j . dk_j of the keys after t contain
@@ -129,8 +132,8 @@ pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk) {
     // (Measured, bf16, decay 0.5 per step: relative L2 error of dlog_g 1.8e-2 without the row term, 9e-3
     // with it from rounded outputs, 3e-3 from the accumulators; no worse at weak decay.)
     LaunchScope ls("gate_finish", c.stream);
-    hipLaunchKernelGGL(k_gate_finish, dim3(pr.T / fin_chunk, pr.B * pr.H), dim3(GT), 0, c.stream, (const float*)c.gate.db,
-                       (const float*)c.gate.db2, 1.f / pr.p, (const float*)c.gate.xb, dlog_g, pr.T, fin_chunk);
+    hipLaunchKernelGGL(k_gate_finish, dim3((pr.T + fin_chunk - 1) / fin_chunk, pr.B * pr.H), dim3(GT), 0, c.stream, (const float*)c.gate.db,
+                       (const float*)c.gate.db2, 1.f / pr.p, (const float*)c.gate.xb, xparts, dlog_g, pr.T, fin_chunk);
     return launch_ok() ? PA_OK : PA_ERR_HIP;
 }
 

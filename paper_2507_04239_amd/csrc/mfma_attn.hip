@@ -252,6 +252,7 @@ struct ChunkedIn {
     const float* part = nullptr;     // forward: numerator; dQ kernel: dQ; dK / dV kernel: dK
     const float* part2 = nullptr;    // dK / dV kernel: dV (nslab2 slabs)
     const float* zpart = nullptr;    // forward: denominator
+    const float* dot = nullptr;      // gated, dQ and dK / dV kernels: the states' part of q . dq and k . dk
     const char* label = "chunk_fwd"; // (host: the launch's name in the kernel times)
 };
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
@@ -586,7 +587,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
             store_block(dQ + row * HD + 32 * fb, acc[fb][ib], CHUNKED ? 1.f : dsp, h, in);
         }
         if (GATED) {
-            const float dot = psp * xor32_sum(rsum[ib]);
+            const float dot = psp * xor32_sum(rsum[ib]) + (CHUNKED ? ck.dot[row] : 0.f);
             if (in && h == 0) qdq[row] = dot;
         }
     }
@@ -735,7 +736,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
             if (q0 < k0 + OWN - 1) tile(std::true_type{}, buf, q0);   // some pair of this tile lies above the diagonal
             else tile(std::false_type{}, buf, q0);
         }
-        if (GATED && active && (q0 + AT) % WG == 0) {
+        if (GATED && !CHUNKED && active && (q0 + AT) % WG == 0) {
             // a block of queries is complete: the wave's sum goes to wsum[head][key block][query block][wave]
             // (the key block's own query block is not a boundary sum: its pairs are summed per token)
             // = what the block added to the wave's running column sums
@@ -778,7 +779,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
             store_block(dV + row * HD + 32 * fb, dv[fb][kb], CHUNKED ? 1.f : sp, h, in);
         }
         if (GATED) {
-            const float dot = psp * xor32_sum(csum[kb]);
+            const float dot = psp * xor32_sum(csum[kb]) + (CHUNKED ? ck.dot[row] : 0.f);
             if (in && h == 0) kdk[row] = dot;
         }
     }
@@ -945,7 +946,7 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         if (both && !launch(std::integral_constant<Bwd, Bwd::both>{}, CHUNKED ? "chunk_bwd" : "attn_bwd", 2 * nblk)) return false;
     }
     if (!both && !launch(std::integral_constant<Bwd, Bwd::dkdv>{}, CHUNKED ? "chunk_bwd_dkdv" : "attn_bwd_dkdv", nblk)) return false;
-    if (GATED) {
+    if (GATED && !CHUNKED) {
         const int ngate = T / WG;
         LaunchScope ls2("attn_gate_boundary", s);
         hipLaunchKernelGGL(k_attn_gate_rows, dim3((ngate + 63) / 64, BH), dim3(64), 0, s, gate.wsum, ngate);
@@ -976,7 +977,8 @@ bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t*
 }
 
 bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
-                      int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart, const char* label) {
+                      int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart, const char* label,
+                      const float* bl) {
     ChunkedIn ck;
     ck.label = label;
     ck.cs = cs;
@@ -984,6 +986,7 @@ bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t
     ck.part = part;
     ck.zpart = zpart;
     if (cs % AT != 0) return false;
+    if (bl != nullptr) return p == 2 && d == 64 && fwd_t<2, 64, true, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
 #define PA_CASE(PP, DD) \
     if (p == PP && d == DD) return fwd_t<PP, DD, false, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, nullptr, ck);
     PA_CASE(2, 32) PA_CASE(2, 64) PA_CASE(2, 128)
@@ -1009,7 +1012,8 @@ bool launch_attn_prep(hipStream_t s, int d, const bf16_t* dO, const bf16_t* O, c
 
 bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* Gh,
                       const float* gz, bf16_t* dQ, bf16_t* dK, bf16_t* dV, int BH, int T, int cs, float scale, const float* part_dq,
-                      int nslab_dq, const float* part_dk, int nslab_dk, const float* part_dv, int nslab_dv) {
+                      int nslab_dq, const float* part_dk, int nslab_dk, const float* part_dv, int nslab_dv, const AttnGate& gate,
+                      const float* dotq, const float* dotk) {
     ChunkedIn ckq, ckk;
     ckq.cs = ckk.cs = cs;
     ckq.part = part_dq;
@@ -1018,7 +1022,13 @@ bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t
     ckk.nslab = nslab_dk;
     ckk.part2 = part_dv;
     ckk.nslab2 = nslab_dv;
+    ckq.dot = dotq;
+    ckk.dot = dotk;
     if (cs % AT != 0) return false;
+    if (gate.bl != nullptr)
+        return p == 2 && d == 64 &&
+               bwd_t<2, 64, true, true>(s, Q, K, V, nullptr, nullptr, nullptr, const_cast<bf16_t*>(Gh), const_cast<float*>(gz), dQ, dK, dV, BH, T,
+                                        scale, 1, gate, ckq, ckk);
 #define PA_CASE(PP, DD)     \
     if (p == PP && d == DD) \
         return bwd_t<PP, DD, false, true>(s, Q, K, V, nullptr, nullptr, nullptr, const_cast<bf16_t*>(Gh), const_cast<float*>(gz), dQ, dK, dV, BH, T, scale, 1, AttnGate(), ckq, ckk);

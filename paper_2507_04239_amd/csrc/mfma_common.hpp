@@ -101,22 +101,6 @@ bool launch_transpose(hipStream_t s, const bf16_t* in, bf16_t* out, int BH, int 
 // gam receives Gamma (rev = 0) or Omega (rev = 1).
 bool launch_scan(const char* name, hipStream_t s, bool rev, const bf16_t* Xt, const bf16_t* Yt, const float* wgt, bf16_t* stC,
                  bf16_t* gam, int BH, int T, int cs, float out_scale, const float* lam = nullptr);
-// `bl`, `qfac` / `kfac`: per-token gating arrays (see GateBuf), all null when not gated; gated dQ / dK kernels
-// also write q_i . dq_i (qdq) and k_j . dk_j (kdk) from their float32 accumulators
-// part (may be null): instead of reading the chunk state stC out, the kernel adds the nslab partial
-// read-outs part[slab][bh][t][:] (float32) that launch_res_walk left
-bool launch_fwd_chunk(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* Vt, const bf16_t* stC,
-                      const bf16_t* gam, bf16_t* O, float* Z, int BH, int T, int cs, float scale, int normalize,
-                      const float* bl, const float* qfac, const float* part = nullptr, int nslab = 0);
-bool launch_bwd_prep(hipStream_t s, const bf16_t* dO, const bf16_t* O, const float* Z, bf16_t* Gh, float* gz,
-                     long long rows, int normalize);
-bool launch_bwd_dq(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* Gh,
-                   const float* gz, const bf16_t* Kt, const bf16_t* stC, const bf16_t* gam, bf16_t* dQ, int BH, int T,
-                   int cs, float scale, const float* bl, const float* qfac, float* qdq);
-bool launch_bwd_dkdv(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* Gh, const float* gz,
-                     const bf16_t* Qt, const bf16_t* Ght, const bf16_t* rtC, const bf16_t* omg, bf16_t* dK, bf16_t* dV, int BH,
-                     int T, int cs, float scale, const float* bl, const float* kfac, float* kdk);
-
 // ---- resident-state kernels (chunk states kept in registers; see mfma_resident.hip) ----------------
 struct ResidentPlan {
     int nhp, nslab;            // half-pairs per wave; workgroups (slabs of state rows) per head
@@ -183,20 +167,22 @@ struct QuadPlan {
     size_t tot_floats;            // scratch of the scan
 };
 QuadPlan quad_plan(int d, int BH, int T, int cs);
+// Gates (d = 64; null without): tw [BH][T], the decay that goes with a token (GateBuf::kfac, rev: qfac; the other one where a
+// state is used), lam [BH][nchunk].
 // st, gam: the states before (rev: after) each chunk.  rev: wgt = gz, X enters multiplied by scale.
 bool launch_quad_scan(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y, const float* wgt,
-                      bf16_t* st, bf16_t* gam, float* tot, int BH, int T, float scale);
+                      bf16_t* st, bf16_t* gam, float* tot, int BH, int T, float scale, const float* tw, const float* lam);
 // part[bh][t][:] = (state of t's chunk)^T phi(scale X_t), zpart[bh][t] (may be null) = the same of the normaliser; zeros where
 // the chunk has no state
 bool launch_quad_read(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* st,
-                      const bf16_t* gam, float* part, float* zpart, int BH, int T, float scale);
-// part[bh][t][:] = d/dX_t of phi(scale X_t) . (state of t's chunk . Y_t) and of wgt_t times the normaliser's part (wgt null: 1)
+                      const bf16_t* gam, float* part, float* zpart, int BH, int T, float scale, const float* tw);
+// part[bh][t][:] = d/dX_t of phi(scale X_t) . (state of t's chunk . Y_t) and of wgt_t times the normaliser's part (wgt null: 1); dot[bh][t] (may be null) = X_t . part
 bool launch_quad_dphi(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y, const float* wgt,
-                      const bf16_t* st, const bf16_t* gam, float* part, int BH, int T, float scale);
-
-// gating: xb[bh][n] = the sum over the pairs that straddle the end of chunk n, from the stored states
-bool launch_gate_boundary(hipStream_t s, const bf16_t* stC, const bf16_t* rtC, const bf16_t* gam, const bf16_t* omg, float* xb,
-                          int BH, int nstate);
+                      const bf16_t* st, const bf16_t* gam, float* part, int BH, int T, float scale, const float* tw, float* dot);
+// d = 64: xb[bh][n][QUAD_XPARTS] = terms of the sum over the pairs that straddle the end of chunk n, from the states
+constexpr int QUAD_XPARTS = 8;
+bool launch_quad_boundary(hipStream_t s, const QuadPlan& p, const bf16_t* st, const bf16_t* rc, const bf16_t* gam, const bf16_t* omg,
+                          float* xb, int BH);
 
 // attention form (chunk == T): p in {2, 3, 4}, d = v in {32, 64, 128}, any T.
 // Gh [BH][T][d] bf16 and gz [BH][T] float32 are scratch of the backward pass.
@@ -209,15 +195,10 @@ bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t*
 // zpart[BH][T] the denominator
 bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
                       int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart,
-                      const char* label = "chunk_fwd");
+                      const char* label = "chunk_fwd", const float* bl = nullptr);
 // ghat = dO / Z (bf16) and gz = -(ghat . O) (float32) per token, d in {32, 64, 128}
 bool launch_attn_prep(hipStream_t s, int d, const bf16_t* dO, const bf16_t* O, const float* Z, bf16_t* Gh, float* gz, long long rows,
                       int normalize);
-// backward of the same: the in-chunk gradients plus the per-slab parts that came through the states (float32
-// [slab][BH][T][d]; the slab counts include the normaliser's slab where there is one)
-bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* Gh,
-                      const float* gz, bf16_t* dQ, bf16_t* dK, bf16_t* dV, int BH, int T, int cs, float scale, const float* part_dq,
-                      int nslab_dq, const float* part_dk, int nslab_dk, const float* part_dv, int nslab_dv);
 // Gated backward pass (bl non-null; T a multiple of attn_gate_block(d)): also leaves what the gradient of
 // the log-gates needs: qdq [BH][T] = q_i . dq_i, kdk [BH][T] = k_j . dk_j (from float32 accumulators) and
 // xb [BH][T / block] = the sum of e_ij a_ij over the pairs j <= end of block m < i.
@@ -227,6 +208,13 @@ struct AttnGate {
     float *qdq = nullptr, *kdk = nullptr, *xb = nullptr, *wsum = nullptr;
 };
 int attn_gate_block(int d);
+// backward of launch_chunk_fwd: the in-chunk gradients plus the per-slab parts that came through the states (float32
+// [slab][BH][T][d]; the slab counts include the normaliser's slab where there is one).  Gated (p = 2, d = 64): gate.bl, running
+// sums from the start of the chunk, gate.qdq and gate.kdk, to which the states' parts dotq and dotk [BH][T] are added.
+bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* Gh,
+                      const float* gz, bf16_t* dQ, bf16_t* dK, bf16_t* dV, int BH, int T, int cs, float scale, const float* part_dq,
+                      int nslab_dq, const float* part_dk, int nslab_dk, const float* part_dv, int nslab_dv,
+                      const AttnGate& gate = AttnGate(), const float* dotq = nullptr, const float* dotk = nullptr);
 bool launch_attn_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* O,
                      const float* Z, const bf16_t* dO, bf16_t* Gh, float* gz, bf16_t* dQ, bf16_t* dK, bf16_t* dV, int BH, int T,
                      float scale, int normalize, const AttnGate& gate = AttnGate());

@@ -1,6 +1,6 @@
 // Host side of the bf16 MFMA kernel families: support check, workspace layout and the launch
-// sequences of the forward and backward passes.  Two sets of kernels: the chunked form for p = 2,
-// d = v = 64, and the attention form (chunk == T, no state) for p in {2, 3, 4}, d = v in {32, 64, 128}.
+// sequences of the forward and backward passes: chunk states for p = 2 (mfma_quad.hip, mfma_resident.hip) and for any degree
+// (mfma_tiled.hip), and the attention form (no state) for p in {2, 3, 4}, d = v in {32, 64, 128}.
 #include <algorithm>
 
 #include "mfma_common.hpp"
@@ -9,51 +9,6 @@ namespace pa {
 namespace {
 
 using namespace mfma;
-
-struct Layout {
-    int cs, nstate;
-    bool keep;
-    size_t off_kt, off_vt, off_gam, off_sc;                      // forward
-    size_t off_qt, off_gh, off_ght, off_gz, off_omg, off_rc;     // backward only
-    size_t off_kts, off_qts;                                     // gated: copies of K, Q scaled for the scans
-    size_t total;
-};
-
-// One layout serves both passes: the forward part comes first and the backward part is appended,
-// so a forward pass that keeps its states leaves them where the backward pass looks for them.
-Layout make_layout(const pa_problem& pr, bool backward) {
-    Layout L{};
-    L.cs = pr.chunk;
-    L.nstate = pr.T / L.cs;
-    L.keep = pr.keep_state != 0;
-    const size_t BH = (size_t)pr.B * pr.H;
-    const size_t tok = BH * pr.T * DH * 2;
-    const size_t st = BH * L.nstate * (size_t)STATE_ELEMS * 2;
-    const size_t gm = BH * L.nstate * (size_t)DH * DH * 2;
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        size_t o = off;
-        off = align_up(off + bytes, 256);
-        return o;
-    };
-    L.off_kt = take(tok);
-    L.off_vt = take(tok);
-    L.off_gam = take(gm);
-    L.off_sc = take(st);
-    L.off_kts = pr.gated ? take(tok) : L.off_kt;
-    L.off_qts = 0;
-    if (backward || L.keep) {
-        L.off_qt = take(tok);
-        L.off_gh = take(tok);
-        L.off_ght = take(tok);
-        L.off_gz = take(BH * pr.T * sizeof(float));
-        L.off_omg = take(gm);
-        L.off_rc = take(st);
-        L.off_qts = pr.gated ? take(tok) : L.off_qt;
-    }
-    L.total = off;
-    return L;
-}
 
 // resident-state kernels: workspace of the forward pass (the backward part is appended)
 struct ResLayout {
@@ -99,17 +54,12 @@ bool resident_ok(const pa_problem& pr) {
     return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && (pr.d == 64 || pr.d == 128) && pr.v == pr.d && pr.chunk > 0 &&
            pr.chunk % QBLK == 0 && pr.T % pr.chunk == 0 && !pr.gated && (size_t)pr.B * pr.H <= 65535u;
 }
-bool chunked_ok(const pa_problem& pr) {
-    return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && pr.d == DH && pr.v == DH && pr.chunk % QBLK == 0 &&
-           (size_t)pr.B * pr.H <= 65535u;
-}
 // gated: the boundary sums of the gate gradient are kept per block of keys of the dK / dV kernel
 bool attn_ok(const pa_problem& pr) {
     return pr.dtype == PA_DTYPE_BF16 && pr.d == pr.v && attn_shape_ok(pr.p, pr.d) && pr.chunk == pr.T &&
            (!pr.gated || pr.T % attn_gate_block(pr.d) == 0) && (size_t)pr.B * pr.H <= 65535u;
 }
-// One chunk: the attention-form kernels.  (The chunked kernels can run p = 2, d = 64 as one chunk
-// too; that path remains for gated sequences that are a multiple of 128 but not of the block.)
+// One chunk: the attention-form kernels.
 bool use_quad(const pa_problem& pr);
 bool quad_states(const pa_problem& pr, bool backward);
 bool use_attn(const pa_problem& pr, bool backward) {
@@ -121,7 +71,7 @@ bool use_tiled(const pa_problem& pr);
 // for the chunked form
 bool use_resident(const pa_problem& pr) {
     if (pr.impl == PA_IMPL_TILED || !resident_ok(pr)) return false;
-    return pr.impl == PA_IMPL_RESIDENT || (!chunked_ok(pr) && !attn_ok(pr) && !use_tiled(pr));
+    return pr.impl == PA_IMPL_RESIDENT || (!use_quad(pr) && !attn_ok(pr) && !use_tiled(pr));
 }
 
 // tiled kernels (any degree and tile width, chunk states in memory): workspace of the forward pass, the backward
@@ -190,7 +140,7 @@ AttnLayout make_attn_layout(const pa_problem& pr, bool backward) {
 // not depend on the chunk beyond rounding, and states are rounded less often the fewer they are.
 bool quad_ok(const pa_problem& pr) {
     return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && (pr.d == 64 || pr.d == 128) && pr.v == pr.d && pr.chunk > 0 &&
-           pr.chunk % QBLK == 0 && pr.chunk < pr.T && !pr.gated && pr.d_tile == 0 && (size_t)pr.B * pr.H <= 65535u;
+           pr.chunk % QBLK == 0 && pr.chunk < pr.T && (!pr.gated || pr.d == 64) && pr.d_tile == 0 && (size_t)pr.B * pr.H <= 65535u;
 }
 bool use_quad(const pa_problem& pr) { return (pr.impl == PA_IMPL_AUTO || pr.impl == PA_IMPL_MFMA) && quad_ok(pr); }
 // Tokens per state.  A state's traffic falls with the distance, the pairs in between grow with it; the step is flat around the
@@ -203,12 +153,19 @@ int quad_chunk(int d) { return d == 64 ? 1280 : 1024; }
 // 12 x 8192 351, 329, 48 x 6144 746, 825, 48 x 8192 1282, 1124, 2 x 8192 158, 184; d = 128 forward 16 x 16384 1100, 1349,
 // 16 x 24576 2490, 2112, 2 x 16384 311, 371, 2 x 24576 522, 444; backward 16 x 12288 2187, 2782, 16 x 16384 3826, 3644,
 // 2 x 12288 738, 761, 2 x 16384 978, 868.
-int quad_whole_upto(int d, bool backward) { return d == 64 ? (backward ? 7168 : 8191) : (backward ? 14336 : 18432); }
-bool quad_states(const pa_problem& pr, bool backward) { return use_quad(pr) && pr.T > quad_whole_upto(pr.d, backward); }
+int quad_whole_upto(int d, bool gated, bool backward) {
+    if (gated) return 5632;
+    return d == 64 ? (backward ? 7168 : 8191) : (backward ? 14336 : 18432);
+}
+bool quad_states(const pa_problem& pr, bool backward) { return use_quad(pr) && pr.T > quad_whole_upto(pr.d, pr.gated, backward); }
+// the forward pass leaves its states for the backward pass
+bool quad_kept(const pa_problem& pr) { return pr.keep_state != 0 && quad_states(pr, false); }
 struct QuadLayout {
     QuadPlan pl;
     size_t off_tot, off_st, off_gam, off_part, off_zpart;
     size_t off_gh, off_gz, off_rc, off_omg, off_pdq, off_pdk;   // backward only
+    size_t off_tot2;                                            // scratch of the other scan, where both run side by side
+    size_t off_dotq, off_dotk;                                  // ... gated: the states' part of q . dq and k . dk
     size_t total;
 };
 QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
@@ -234,6 +191,11 @@ QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
         L.off_omg = take(nslot * L.pl.gam_elems * 2);
         L.off_pdq = take(rows * pr.d * sizeof(float));
         L.off_pdk = take(rows * pr.d * sizeof(float));
+        L.off_tot2 = quad_kept(pr) ? L.off_tot : take(L.pl.tot_floats * sizeof(float));
+        if (pr.gated) {
+            L.off_dotq = take(rows * sizeof(float));
+            L.off_dotk = take(rows * sizeof(float));
+        }
     }
     L.total = off;
     return L;
@@ -246,20 +208,26 @@ bool use_tiled(const pa_problem& pr) {
     if (!tiled_ok(pr)) return false;
     if (pr.impl == PA_IMPL_TILED) return true;
     if (pr.impl == PA_IMPL_RESIDENT) return false;
-    return pr.d_tile > 0 || (!chunked_ok(pr) && !attn_ok(pr));
+    return pr.d_tile > 0 || (!use_quad(pr) && !attn_ok(pr));
 }
 
 }  // namespace
 
-int mfma_gate_fin_chunk(const pa_problem& pr) { return use_attn(pr, true) ? attn_gate_block(pr.d) : pr.chunk; }
+int mfma_gate_chunk(const pa_problem& pr, bool backward) { return use_attn(pr, backward) ? pr.T : quad_chunk(pr.d); }
+int mfma_gate_fin_chunk(const pa_problem& pr, int& xparts) {
+    const bool attn = use_attn(pr, true);
+    xparts = attn ? 1 : QUAD_XPARTS;
+    return attn ? attn_gate_block(pr.d) : quad_chunk(pr.d);
+}
 
-bool mfma_takes_ragged(const pa_problem& pr) { return use_quad(pr); }
+// (whole, a gated sequence has to be a multiple of the attention form's key block)
+bool mfma_takes_ragged(const pa_problem& pr, bool backward) { return use_quad(pr) && (!pr.gated || quad_states(pr, backward)); }
 
 pa_status mfma_supported(const pa_problem& pr, bool backward) {
     if (use_quad(pr)) return PA_OK;
     if (pr.impl == PA_IMPL_RESIDENT) return resident_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
     if (pr.impl == PA_IMPL_TILED || pr.d_tile > 0) return tiled_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
-    return chunked_ok(pr) || attn_ok(pr) || resident_ok(pr) || tiled_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
+    return attn_ok(pr) || resident_ok(pr) || tiled_ok(pr) ? PA_OK : PA_ERR_UNSUPPORTED;
 }
 
 long long mfma_state_rows(const pa_problem& pr) {
@@ -269,7 +237,7 @@ long long mfma_state_rows(const pa_problem& pr) {
         return (long long)pl.ntile * pl.rows_per_tile;
     }
     if (use_resident(pr)) return (long long)(pr.d / 8) * (pr.d / 8 + 1) / 2 * 64;
-    return use_attn(pr, false) ? 0 : (long long)NTILES * 64;
+    return 0;      // attention form
 }
 
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
@@ -277,20 +245,19 @@ size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
         // (a ragged sequence asks for a little more than the next whole number of chunks, as it did when it ran padded)
         pa_problem up = pr;
         up.T = (pr.T + pr.chunk - 1) / pr.chunk * pr.chunk;
-        const size_t states = quad_states(up, backward) ? make_quad_layout(up, backward).total : 0;
-        return std::max(states, make_attn_layout(up, backward).total) + (up.T > pr.T ? 256 : 0);
+        auto bytes = [&](const pa_problem& p) {
+            return quad_states(p, backward) ? make_quad_layout(p, backward).total : make_attn_layout(p, backward).total;
+        };
+        return std::max(bytes(pr), bytes(up)) + (up.T > pr.T ? 256 : 0);
     }
     if (use_tiled(pr)) return make_tiled_layout(pr, backward).total;
     if (use_resident(pr)) return make_res_layout(pr, backward).total;
-    return use_attn(pr, backward) ? make_attn_layout(pr, backward).total : make_layout(pr, backward).total;
+    return make_attn_layout(pr, backward).total;
 }
 
 #define PA_TRY(CALL) \
     if (!(CALL)) return PA_ERR_HIP;
 
-// Gated problems (c.gate non-null): the scans read copies of K (Q in the backward pass) scaled by
-// the square root of the per-token decay, and multiply the running sum by the per-chunk decay;
-// the per-chunk kernels apply the remaining factors (see the chunk kernels).
 pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z) {
     const pa_problem& pr = c.prob;
     const int BH = pr.B * pr.H;
@@ -305,10 +272,11 @@ pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, vo
         bf16_t *st = (bf16_t*)(c.ws + L.off_st), *gam = (bf16_t*)(c.ws + L.off_gam);
         float *part = (float*)(c.ws + L.off_part), *zpart = (float*)(c.ws + L.off_zpart);
         PA_TRY(launch_quad_scan("mfma_state_scan", c.stream, L.pl, false, (const bf16_t*)K, (const bf16_t*)V, nullptr, st, gam,
-                                (float*)(c.ws + L.off_tot), BH, pr.T, 1.0f))
-        PA_TRY(launch_quad_read("mfma_query_state", c.stream, L.pl, false, (const bf16_t*)Q, st, gam, part, zpart, BH, pr.T, pr.scale))
+                                (float*)(c.ws + L.off_tot), BH, pr.T, 1.0f, c.gate.kfac, c.gate.lam))
+        PA_TRY(launch_quad_read("mfma_query_state", c.stream, L.pl, false, (const bf16_t*)Q, st, gam, part, zpart, BH, pr.T, pr.scale,
+                                c.gate.qfac))
         PA_TRY(launch_chunk_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH, pr.T,
-                                L.pl.cs, pr.scale, pr.normalize, part, 1, zpart, "mfma_fwd_chunk"))
+                                L.pl.cs, pr.scale, pr.normalize, part, 1, zpart, "mfma_fwd_chunk", c.gate.bl))
         return PA_OK;
     }
     if (use_tiled(pr)) {
@@ -346,39 +314,18 @@ pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, vo
                                    pr.chunk, R.pl, 1.0f))
         PA_TRY(launch_res_walk("res_state_walk", c.stream, pr.d, false, 1, Kt, Vt, (const bf16_t*)Q, nullptr, tot, part, BH, pr.T,
                                pr.chunk, R.pl, pr.scale * pr.scale))
-        if (pr.d == DH) {
-            PA_TRY(launch_fwd_chunk(c.stream, (const bf16_t*)Q, (const bf16_t*)K, Vt, nullptr, Gam, (bf16_t*)O, Z, BH, pr.T,
-                                    pr.chunk, pr.scale, pr.normalize, nullptr, nullptr, part, R.pl.nslab))
-        } else {
-            // the normaliser's share of the denominator, then the in-chunk part on the attention-form kernel
-            PA_TRY(launch_gram_apply(c.stream, pr.d, (const bf16_t*)Q, Gam, nullptr, nullptr, zpart, BH, pr.T, pr.chunk, 0.f,
-                                     pr.scale * pr.scale))
-            PA_TRY(launch_chunk_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH,
-                                    pr.T, pr.chunk, pr.scale, pr.normalize, part, R.pl.nslab, zpart))
-        }
+        // the normaliser's share of the denominator, then the in-chunk part on the attention-form kernel
+        PA_TRY(launch_gram_apply(c.stream, pr.d, (const bf16_t*)Q, Gam, nullptr, nullptr, zpart, BH, pr.T, pr.chunk, 0.f,
+                                 pr.scale * pr.scale))
+        PA_TRY(launch_chunk_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH,
+                                pr.T, pr.chunk, pr.scale, pr.normalize, part, R.pl.nslab, zpart))
         return PA_OK;
     }
-    const Layout L = make_layout(pr, false);
-    const GateBuf& gt = c.gate;
-    bf16_t* Kt = (bf16_t*)(c.ws + L.off_kt);
-    bf16_t* Kts = (bf16_t*)(c.ws + L.off_kts);
-    bf16_t* Vt = (bf16_t*)(c.ws + L.off_vt);
-    bf16_t* Sc = (bf16_t*)(c.ws + L.off_sc);
-    bf16_t* Gam = (bf16_t*)(c.ws + L.off_gam);
-    if (!pr.gated || L.keep)   // the plain copy of K serves the scan (un-gated) and the backward pass's dQ
-        PA_TRY(launch_transpose(c.stream, (const bf16_t*)K, Kt, BH, pr.T))
-    if (pr.gated) PA_TRY(launch_transpose(c.stream, (const bf16_t*)K, Kts, BH, pr.T, gt.kfac))
-    PA_TRY(launch_transpose(c.stream, (const bf16_t*)V, Vt, BH, pr.T))
-    PA_TRY(launch_scan("mfma_state_scan", c.stream, false, Kts, Vt, nullptr, Sc, Gam, BH, pr.T, L.cs, 1.0f, gt.lam))
-    PA_TRY(launch_fwd_chunk(c.stream, (const bf16_t*)Q, (const bf16_t*)K, Vt, Sc, Gam, (bf16_t*)O, Z, BH, pr.T, L.cs,
-                            pr.scale, pr.normalize, gt.bl, gt.qfac))
-    return PA_OK;
+    return PA_ERR_UNSUPPORTED;     // (no family: not reached behind mfma_supported)
 }
 
-// The backward pass has two independent strands that meet only at the end: dQ needs the forward
-// state S, while dK / dV need the state gradient R, whose scan is a long chain of small steps
-// that leaves most of each CU idle.  The R strand therefore runs on a second stream (created
-// once, default priority) so that dQ's workgroups fill the CUs under the scan.
+// The backward pass with states has two strands, dQ from S and dK, dV from R, that do not fill the chip to their ends: the first
+// runs on a second stream (created once, default priority).
 struct SideStream {
     hipStream_t stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr, scanned = nullptr;
@@ -441,13 +388,33 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
         const bf16_t *q = (const bf16_t*)Q, *k = (const bf16_t*)K, *v = (const bf16_t*)V;
         hipStream_t s = c.stream;
         PA_TRY(launch_attn_prep(s, pr.d, (const bf16_t*)dO, (const bf16_t*)O, Z, Gh, gz, (long long)BH * pr.T, pr.normalize))
-        if (!pr.keep_state || !quad_states(pr, false)) PA_TRY(launch_quad_scan("mfma_state_scan_bwd", s, L.pl, false, k, v, nullptr, st, gam, tot, BH, pr.T, 1.0f))
-        PA_TRY(launch_quad_dphi("mfma_dq_state", s, L.pl, false, q, Gh, gz, st, gam, pdq, BH, pr.T, pr.scale))
-        PA_TRY(launch_quad_scan("mfma_state_grad_scan", s, L.pl, true, q, Gh, gz, rc, omg, tot, BH, pr.T, pr.scale))
-        PA_TRY(launch_quad_read("mfma_dv_state", s, L.pl, true, k, rc, omg, pdv, nullptr, BH, pr.T, 1.0f))
-        PA_TRY(launch_quad_dphi("mfma_dk_state", s, L.pl, true, k, v, nullptr, rc, omg, pdk, BH, pr.T, 1.0f))
+        const GateBuf& gt = c.gate;       // (all null without gates)
+        float *dotq = pr.gated ? (float*)(c.ws + L.off_dotq) : nullptr, *dotk = pr.gated ? (float*)(c.ws + L.off_dotk) : nullptr;
+        // Two strands that meet at the in-chunk gradients: dQ's part from S (on the side stream), and R with dV's and dK's.  Neither
+        // fills the chip to its end.
+        SideStream side = side_stream();
+        if (profile_enabled()) side.ok = false;   // timed kernel by kernel: no overlap
+        hipStream_t s2 = side.ok ? side.stream : s;
+        if (side.ok && (hipEventRecord(side.fork, s) != hipSuccess || hipStreamWaitEvent(s2, side.fork, 0) != hipSuccess)) return PA_ERR_HIP;
+        PA_TRY(launch_quad_scan("mfma_state_grad_scan", s, L.pl, true, q, Gh, gz, rc, omg, tot, BH, pr.T, pr.scale, gt.qfac, gt.lam))
+        if (pr.gated && side.ok && hipEventRecord(side.scanned, s) != hipSuccess) return PA_ERR_HIP;
+        if (!quad_kept(pr))
+            PA_TRY(launch_quad_scan("mfma_state_scan_bwd", s2, L.pl, false, k, v, nullptr, st, gam, (float*)(c.ws + L.off_tot2), BH, pr.T, 1.0f,
+                                    gt.kfac, gt.lam))
+        PA_TRY(launch_quad_dphi("mfma_dq_state", s2, L.pl, false, q, Gh, gz, st, gam, pdq, BH, pr.T, pr.scale, gt.qfac, dotq))
+        PA_TRY(launch_quad_read("mfma_dv_state", s, L.pl, true, k, rc, omg, pdv, nullptr, BH, pr.T, 1.0f, gt.kfac))
+        PA_TRY(launch_quad_dphi("mfma_dk_state", s, L.pl, true, k, v, nullptr, rc, omg, pdk, BH, pr.T, 1.0f, gt.kfac, dotk))
+        if (pr.gated) {
+            if (side.ok && hipStreamWaitEvent(s2, side.scanned, 0) != hipSuccess) return PA_ERR_HIP;
+            PA_TRY(launch_quad_boundary(s2, L.pl, st, rc, gam, omg, gt.xb, BH))
+        }
+        if (side.ok && (hipEventRecord(side.join, s2) != hipSuccess || hipStreamWaitEvent(s, side.join, 0) != hipSuccess)) return PA_ERR_HIP;
+        AttnGate ag;
+        ag.bl = gt.bl;
+        ag.qdq = gt.db;
+        ag.kdk = gt.db2;
         PA_TRY(launch_chunk_bwd(s, pr.p, pr.d, q, k, v, Gh, gz, (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, BH, pr.T, L.pl.cs, pr.scale, pdq,
-                                1, pdk, 1, pdv, 1))
+                                1, pdk, 1, pdv, 1, ag, dotq, dotk))
         return PA_OK;
     }
     if (use_tiled(pr)) {
@@ -530,61 +497,7 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
                                 pdq, R.pl.nslab + 1, pdk, R.pl.nslab + 1, pdv, R.pl.nslab))
         return PA_OK;
     }
-    const Layout L = make_layout(pr, true);
-    const GateBuf& gt = c.gate;
-    bf16_t* Kt = (bf16_t*)(c.ws + L.off_kt);
-    bf16_t* Kts = (bf16_t*)(c.ws + L.off_kts);
-    bf16_t* Vt = (bf16_t*)(c.ws + L.off_vt);
-    bf16_t* Qt = (bf16_t*)(c.ws + L.off_qt);
-    bf16_t* Qts = (bf16_t*)(c.ws + L.off_qts);
-    bf16_t* Gh = (bf16_t*)(c.ws + L.off_gh);
-    bf16_t* Ght = (bf16_t*)(c.ws + L.off_ght);
-    float* gz = (float*)(c.ws + L.off_gz);
-    bf16_t* Gam = (bf16_t*)(c.ws + L.off_gam);
-    bf16_t* Omg = (bf16_t*)(c.ws + L.off_omg);
-    bf16_t* Sc = (bf16_t*)(c.ws + L.off_sc);
-    bf16_t* Rc = (bf16_t*)(c.ws + L.off_rc);
-    const bf16_t *q = (const bf16_t*)Q, *k = (const bf16_t*)K, *v = (const bf16_t*)V;
-    const float s2 = pr.scale * pr.scale;
-    SideStream side = side_stream();
-    if (profile_enabled()) side.ok = false;   // timed kernel by kernel: no overlap
-    hipStream_t s_main = c.stream, s_side = side.ok ? side.stream : c.stream;
-
-    PA_TRY(launch_bwd_prep(s_main, (const bf16_t*)dO, (const bf16_t*)O, Z, Gh, gz, (long long)BH * pr.T, pr.normalize))
-    PA_TRY(launch_transpose(s_main, q, Qt, BH, pr.T))
-    if (pr.gated) PA_TRY(launch_transpose(s_main, q, Qts, BH, pr.T, gt.qfac))
-    PA_TRY(launch_transpose(s_main, Gh, Ght, BH, pr.T))
-    // The fork sits here, not right after the preparation kernel that dQ depends on: the scan's
-    // workgroups need most of a CU's LDS and must be placed before dQ's fill the CUs.
-    if (side.ok) {
-        if (hipEventRecord(side.fork, s_main) != hipSuccess || hipStreamWaitEvent(s_side, side.fork, 0) != hipSuccess)
-            return PA_ERR_HIP;
-    }
-    // strand R (caller's stream, so that its workgroups are placed first): state-gradient scan
-    PA_TRY(launch_scan("mfma_state_grad_scan", s_main, true, Qts, Ght, gz, Rc, Omg, BH, pr.T, L.cs, s2, gt.lam))
-    if (pr.gated && side.ok && hipEventRecord(side.scanned, s_main) != hipSuccess) return PA_ERR_HIP;
-    // strand S (side stream): dQ from the forward state
-    if (!L.keep) {
-        // nothing but O and Z was saved: rebuild the chunk states
-        PA_TRY(launch_transpose(s_side, k, Kt, BH, pr.T))
-        if (pr.gated) PA_TRY(launch_transpose(s_side, k, Kts, BH, pr.T, gt.kfac))
-        PA_TRY(launch_transpose(s_side, v, Vt, BH, pr.T))
-        PA_TRY(launch_scan("mfma_state_scan_bwd", s_side, false, Kts, Vt, nullptr, Sc, Gam, BH, pr.T, L.cs, 1.0f, gt.lam))
-    }
-    PA_TRY(launch_bwd_dq(s_side, q, k, v, Gh, gz, Kt, Sc, Gam, (bf16_t*)dQ, BH, pr.T, L.cs, pr.scale, gt.bl, gt.qfac, gt.db))
-    PA_TRY(launch_bwd_dkdv(s_main, q, k, v, Gh, gz, Qt, Ght, Rc, Omg, (bf16_t*)dK, (bf16_t*)dV, BH, pr.T, L.cs, pr.scale,
-                           gt.bl, gt.kfac, gt.db2))
-    if (pr.gated) {
-        // the pairs that straddle the chunk boundaries, from both sets of states: behind dQ on the side
-        // strand (S is complete there), once the scan on the caller's stream has produced R
-        if (side.ok && hipStreamWaitEvent(s_side, side.scanned, 0) != hipSuccess) return PA_ERR_HIP;
-        PA_TRY(launch_gate_boundary(s_side, Sc, Rc, Gam, Omg, gt.xb, BH, L.nstate))
-    }
-    if (side.ok) {
-        if (hipEventRecord(side.join, s_side) != hipSuccess || hipStreamWaitEvent(s_main, side.join, 0) != hipSuccess)
-            return PA_ERR_HIP;
-    }
-    return PA_OK;
+    return PA_ERR_UNSUPPORTED;
 }
 
 // ---- a prompt into a decode state, through the state scan ----------------------------------------------
@@ -670,7 +583,7 @@ pa_status mfma_absorb(const pa_problem& pr, const void* K, const void* V, const 
         gp.chunk = pr.T;
         gp.gated = 1;
         Ctx c{gp, s, ws, L.total, gate_buffers(gp, false, ws + L.off_gate)};
-        pa_status st = gate_prepare(c, log_g);
+        pa_status st = gate_prepare(c, log_g, pr.T);
         if (st != PA_OK) return st;
         kfac = c.gate.kfac;
         lam = c.gate.lam;

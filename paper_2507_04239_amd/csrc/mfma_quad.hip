@@ -514,8 +514,9 @@ __device__ __forceinline__ void stage_rows(bf16_t* xs, const bf16_t* __restrict_
 struct StateArgs {
     const bf16_t *X, *Y;       // Y: d phi only
     const float* wgt;          // d phi: weight of the normaliser's term per token (null: 1)
+    const float* tw;           // gated: the token's decay, a factor of all results (null: 1)
     const bf16_t *st, *gam;
-    float *part, *zpart;       // zpart may be null
+    float *part, *zpart;       // zpart may be null; d phi: zpart = X . part
     int T, cs, nchunk, heads, rev, blocks;   // blocks per chunk
     float fold, out_scale;
 };
@@ -643,7 +644,7 @@ __global__ __launch_bounds__(64 * ReadCfg<HD>::NW, 2) void k_quad_read(StateArgs
         const int t = tok0 + 64 * w + 32 * tb + r32;
         const bool in = t < t_end;
         float* dst = A.part + (head + (in ? t : 0)) * HD;
-        const float f = A.out_scale;
+        const float f = A.tw != nullptr && in ? A.out_scale * A.tw[head + t] : A.out_scale;
         if (in) {
 #pragma unroll
             for (int vb = 0; vb < NV; ++vb)
@@ -893,10 +894,25 @@ __global__ __launch_bounds__(64 * DphiCfg<HD>::NW, 2) void k_quad_dphi(StateArgs
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
         const int t = tok0 + 64 * wt + 32 * tb + r32;
-        const float f = A.out_scale;
-        float* dst = A.part + (head + min(t, A.T - 1)) * HD;
         const bool in = t < t_end;
+        const float f = A.tw != nullptr && in ? A.out_scale * A.tw[head + t] : A.out_scale;
+        float* dst = A.part + (head + min(t, A.T - 1)) * HD;
         if constexpr (RS == 1) {
+            if (A.zpart != nullptr) {       // (rows of x are in LDS unless the chunk has no state, and dx is zero then)
+                const bf16_t* xrow = xs + (64 * wt + 32 * tb + r32) * HD;
+                float dot = 0.f;
+                if (slot >= 0 && slot < A.nchunk - 1) {
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        float x[4];
+                        unpack4(x, *(const uint2*)(xrow + 8 * (i ^ (r32 & 7)) + 4 * hl));
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) dot += dx[i][tb][r] * x[r];
+                    }
+                }
+                dot = f / A.fold * xor32_sum(dot);
+                if (in && hl == 0) A.zpart[head + t] = dot;
+            }
 #pragma unroll
             for (int i = 0; i < NB; ++i)
                 if (in) *(float4*)(dst + 8 * i + 4 * hl) = make_float4(f * dx[i][tb][0], f * dx[i][tb][1], f * dx[i][tb][2], f * dx[i][tb][3]);
@@ -910,6 +926,44 @@ __global__ __launch_bounds__(64 * DphiCfg<HD>::NW, 2) void k_quad_dphi(StateArgs
             }
         }
     }
+}
+
+// ---- gated: the pairs that straddle a chunk boundary ----------------------------------------------------------
+// <R_m, S_{m+1}> + <Omega_m, Gamma_{m+1}>, which sit in the same slot; off-diagonal tiles carry their multiplicity in both states.
+// QUAD_XPARTS workgroups per boundary, every eighth tile (the normaliser's 64 x 64 is one more).
+__device__ __forceinline__ float dot8(const uint4& a, const uint4& b) {
+    float x[8], y[8], s = 0.f;
+    unpack8(x, a);
+    unpack8(y, b);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += x[i] * y[i];
+    return s;
+}
+__global__ __launch_bounds__(256) void k_quad_boundary(const bf16_t* __restrict__ st, const bf16_t* __restrict__ rc,
+                                                       const bf16_t* __restrict__ gam, const bf16_t* __restrict__ omg,
+                                                       float* __restrict__ xb, int nchunk) {
+    using D = QD<64>;
+    __shared__ float red[4];
+    const int part = blockIdx.x, n = blockIdx.y, bh = blockIdx.z, tid = threadIdx.x;
+    float acc = 0.f;
+    if (n < nchunk - 1) {
+        const size_t slot = (size_t)bh * (nchunk - 1) + n;
+        static_assert(D::TILE == D::GAM && D::TILE / 8 == 512, "two pieces per thread");
+        for (int tile = part; tile <= D::NTILE; tile += QUAD_XPARTS) {
+            const bool norm = tile == D::NTILE;
+            const uint4* a = (const uint4*)(norm ? gam + slot * D::GAM : st + slot * D::STATE + (size_t)tile * D::TILE) + tid;
+            const uint4* b = (const uint4*)(norm ? omg + slot * D::GAM : rc + slot * D::STATE + (size_t)tile * D::TILE) + tid;
+            bool diag = norm;
+            for (int t = 0; t < D::NB; ++t) diag = diag || tile == t * (t + 1) / 2 + t;
+            const float s = dot8(a[0], b[0]) + dot8(a[256], b[256]);
+            acc += diag ? s : 0.5f * s;
+        }
+    }
+    acc = xor32_sum(xor16_sum(acc));
+    for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) xb[((size_t)bh * nchunk + n) * QUAD_XPARTS + part] = red[0] + red[1] + red[2] + red[3];
 }
 
 template <typename F>
@@ -974,22 +1028,27 @@ QuadPlan quad_plan(int d, int BH, int T, int cs) {
 }
 
 bool launch_quad_scan(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y,
-                      const float* wgt, bf16_t* st, bf16_t* gam, float* tot, int BH, int T, float scale) {
+                      const float* wgt, bf16_t* st, bf16_t* gam, float* tot, int BH, int T, float scale, const float* tw,
+                      const float* lam) {
     if (p.nchunk < 2) return true;
     ScanArgs a{};
-    a.X = X; a.Y = Y; a.gz = wgt; a.st = st; a.gam = gam; a.tot = tot;
+    a.X = X; a.Y = Y; a.gz = wgt; a.tw = tw; a.lam = lam; a.st = st; a.gam = gam; a.tot = tot;
     a.T = T; a.cs = p.cs; a.nchunk = p.nchunk; a.nseg = p.nseg; a.seg_chunks = p.seg_chunks; a.heads = BH;
     float rest;
     split_scale(scale, a.fold, rest);
     a.out_scale = rest * rest;
-#define PA_GO(HD_)                                                                     \
-    if (p.hd == HD_) {                                                                 \
-        if (!rev) return scan_go<HD_, false, false, false>(name, s, a);                       \
-        return a.fold == 1.f ? scan_go<HD_, true, false, false>(name, s, a) : scan_go<HD_, true, true, false>(name, s, a); \
+#define PA_GO(HD_, G_)                                                                                                            \
+    if (!rev) return scan_go<HD_, false, false, G_>(name, s, a);                                                                  \
+    return a.fold == 1.f ? scan_go<HD_, true, false, G_>(name, s, a) : scan_go<HD_, true, true, G_>(name, s, a);
+    if (p.hd == 128) {
+        if (tw != nullptr) return false;
+        PA_GO(128, false)
     }
-    PA_GO(64) PA_GO(128)
+    if (tw != nullptr) {
+        PA_GO(64, true)
+    }
+    PA_GO(64, false)
 #undef PA_GO
-    return false;
 }
 
 static StateArgs state_args(const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* st, const bf16_t* gam, float* part, int BH,
@@ -1002,13 +1061,14 @@ static StateArgs state_args(const QuadPlan& p, bool rev, const bf16_t* X, const 
 }
 
 bool launch_quad_read(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* st,
-                      const bf16_t* gam, float* part, float* zpart, int BH, int T, float scale) {
+                      const bf16_t* gam, float* part, float* zpart, int BH, int T, float scale, const float* tw) {
     float rest;
 #define PA_GO(HD_)                                                                                                          \
     if (p.hd == HD_) {                                                                                                      \
         using C = ReadCfg<HD_>;                                                                                             \
         StateArgs a = state_args(p, rev, X, st, gam, part, BH, T, C::TOK);                                                  \
         a.zpart = zpart;                                                                                                    \
+        a.tw = tw;                                                                                                          \
         split_scale(scale, a.fold, rest);                                                                                   \
         a.out_scale = rest * rest;                                                                                          \
         if (!allow_smem(k_quad_read<HD_>, C::SMEM)) return false;                                                           \
@@ -1022,14 +1082,18 @@ bool launch_quad_read(const char* name, hipStream_t s, const QuadPlan& p, bool r
 }
 
 bool launch_quad_dphi(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y,
-                      const float* wgt, const bf16_t* st, const bf16_t* gam, float* part, int BH, int T, float scale) {
+                      const float* wgt, const bf16_t* st, const bf16_t* gam, float* part, int BH, int T, float scale, const float* tw,
+                      float* dot) {
     float rest;
+    if (dot != nullptr && p.hd != 64) return false;
 #define PA_GO(HD_)                                                                                                          \
     if (p.hd == HD_) {                                                                                                      \
         using C = DphiCfg<HD_>;                                                                                             \
         StateArgs a = state_args(p, rev, X, st, gam, part, BH, T, C::TOK);                                                  \
         a.Y = Y;                                                                                                            \
         a.wgt = wgt;                                                                                                        \
+        a.tw = tw;                                                                                                          \
+        a.zpart = dot;                                                                                                      \
         split_scale(scale, a.fold, rest);                                                                                   \
         a.out_scale = scale * rest;                                                                                         \
         if (!allow_smem(k_quad_dphi<HD_>, C::SMEM)) return false;                                                           \
@@ -1040,6 +1104,13 @@ bool launch_quad_dphi(const char* name, hipStream_t s, const QuadPlan& p, bool r
     PA_GO(64) PA_GO(128)
 #undef PA_GO
     return false;
+}
+
+bool launch_quad_boundary(hipStream_t s, const QuadPlan& p, const bf16_t* st, const bf16_t* rc, const bf16_t* gam, const bf16_t* omg,
+                          float* xb, int BH) {
+    LaunchScope ls("mfma_gate_boundary", s);
+    hipLaunchKernelGGL(k_quad_boundary, dim3(QUAD_XPARTS, p.nchunk, BH), dim3(256), 0, s, st, rc, gam, omg, xb, p.nchunk);
+    return launch_ok();
 }
 
 }  // namespace mfma

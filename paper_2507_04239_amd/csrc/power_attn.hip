@@ -142,10 +142,10 @@ struct Padding {
     size_t tok = 0, vec = 0;   // bytes of one padded [B,H,T,d] operand and of one padded [B,H,T] float array
 };
 
-Padding padding_for(const pa_problem& pr) {
+Padding padding_for(const pa_problem& pr, bool backward) {
     Padding pd;
     pd.prob = pr;
-    if (pr.chunk <= 0 || pr.T % pr.chunk == 0 || mfma_takes_ragged(pr)) return pd;
+    if (pr.chunk <= 0 || pr.T % pr.chunk == 0 || mfma_takes_ragged(pr, backward)) return pd;
     pd.on = true;
     pd.prob.T = (pr.T + pr.chunk - 1) / pr.chunk * pr.chunk;
     const size_t rows = (size_t)pr.B * pr.H * pd.prob.T;
@@ -201,7 +201,7 @@ pa_status run_fwd(const pa_problem* prob, const void* Q, const void* K, const vo
     if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O) || !aligned16(Z) || !aligned16(log_g))
         return PA_ERR_INVALID_ARG;
     const pa_problem asked = resolved(prob);
-    const Padding pd = padding_for(asked);
+    const Padding pd = padding_for(asked, false);
     prob = &pd.prob;
     pa_status why = PA_ERR_UNSUPPORTED;
     int impl = choose(*prob, false, &why);
@@ -237,7 +237,7 @@ pa_status run_fwd(const pa_problem* prob, const void* Q, const void* K, const vo
     }
     Ctx c{*prob, s, (char*)workspace, workspace_bytes, gate_buffers(*prob, false, (char*)workspace + fam)};
     if (gated) {
-        st = gate_prepare(c, log_g);
+        st = gate_prepare(c, log_g, impl == PA_IMPL_MFMA ? mfma_gate_chunk(*prob, false) : prob->chunk);
         if (st != PA_OK) return st;
     }
     st = impl == PA_IMPL_MFMA ? mfma_fwd(c, Q, K, V, O, Z) : generic_fwd(c, Q, K, V, O, Z);
@@ -262,7 +262,7 @@ pa_status run_bwd(const pa_problem* prob, const void* Q, const void* K, const vo
         !aligned16(dK) || !aligned16(dV) || !aligned16(log_g) || !aligned16(dlog_g))
         return PA_ERR_INVALID_ARG;
     const pa_problem asked = resolved(prob);
-    const Padding pd = padding_for(asked);
+    const Padding pd = padding_for(asked, true);
     prob = &pd.prob;
     pa_status why = PA_ERR_UNSUPPORTED;
     int impl = choose(*prob, true, &why);
@@ -308,12 +308,15 @@ pa_status run_bwd(const pa_problem* prob, const void* Q, const void* K, const vo
     Ctx c{*prob, s, (char*)workspace, workspace_bytes, gate_buffers(*prob, true, (char*)workspace + fam)};
     if (gated) {
         // the factors are rebuilt here: the forward pass keeps its own copy only inside its workspace
-        st = gate_prepare(c, log_g);
+        st = gate_prepare(c, log_g, impl == PA_IMPL_MFMA ? mfma_gate_chunk(*prob, true) : prob->chunk);
         if (st != PA_OK) return st;
     }
     st = impl == PA_IMPL_MFMA ? mfma_bwd(c, Q, K, V, O, Z, dO, dQ, dK, dV) : generic_bwd(c, Q, K, V, O, Z, dO, dQ, dK, dV);
-    if (st == PA_OK && gated)
-        st = gate_gradient(c, dlog_g, impl == PA_IMPL_MFMA ? mfma_gate_fin_chunk(*prob) : prob->chunk);
+    if (st == PA_OK && gated) {
+        int xparts = 1;
+        const int fin = impl == PA_IMPL_MFMA ? mfma_gate_fin_chunk(*prob, xparts) : prob->chunk;
+        st = gate_gradient(c, dlog_g, fin, xparts);
+    }
     if (st != PA_OK || !pd.on) return st;
     const int row = asked.d * 2;
     if (!copy_rows(s, dQ, dQout, BH, prob->T, asked.T, row) || !copy_rows(s, dK, dKout, BH, prob->T, asked.T, row) ||
@@ -370,7 +373,7 @@ const char* power_attn_status_string(pa_status s) {
 pa_status power_attn_supported(const pa_problem* prob, int for_backward) {
     pa_status st = validate(prob);
     if (st != PA_OK) return st;
-    const Padding pd = padding_for(resolved(prob));
+    const Padding pd = padding_for(resolved(prob), for_backward != 0);
     pa_status why = PA_ERR_UNSUPPORTED;
     const int impl = choose(pd.prob, for_backward != 0, &why);
     if (impl < 0) return why;
@@ -379,7 +382,7 @@ pa_status power_attn_supported(const pa_problem* prob, int for_backward) {
 
 size_t power_attn_workspace_bytes(const pa_problem* prob, int for_backward) {
     if (validate(prob) != PA_OK) return 0;
-    const Padding pd = padding_for(resolved(prob));
+    const Padding pd = padding_for(resolved(prob), for_backward != 0);
     pa_status why;
     int impl = choose(pd.prob, for_backward != 0, &why);
     if (impl < 0 || (pd.on && impl != PA_IMPL_MFMA)) return 0;
@@ -389,7 +392,7 @@ size_t power_attn_workspace_bytes(const pa_problem* prob, int for_backward) {
 
 long long power_attn_state_rows(const pa_problem* prob) {
     if (validate(prob) != PA_OK) return 0;
-    const Padding pd = padding_for(resolved(prob));
+    const Padding pd = padding_for(resolved(prob), false);
     pa_status why;
     int impl = choose(pd.prob, false, &why);
     if (impl < 0 || (pd.on && impl != PA_IMPL_MFMA)) return 0;

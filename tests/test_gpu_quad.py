@@ -1,6 +1,6 @@
 """Chunk-state kernels of p = 2 at d = 64 and 128: lengths around their tiles (64-token stages, blocks of 256 and 512 tokens,
 states 1280 or 1024 tokens apart, a last chunk of any length), few and many heads (the state scan in segments or in one walk),
-kept and rebuilt states, scales with and without a power of two, against the definition in float64 on the GPU."""
+kept and rebuilt states, scales with and without a power of two, gates, against the definition in float64 on the GPU."""
 import numpy as np
 import pytest
 
@@ -9,11 +9,13 @@ from gpu_util import assert_close, run_fwd_bwd
 pytestmark = pytest.mark.gpu
 
 
-def reference(Q, K, V, G, scale, normalize, block=2048):
-    """One head in float64, rows of queries in blocks: O, Z, dQ, dK, dV as the header defines them (p = 2)."""
+def reference(Q, K, V, G, scale, normalize, log_g=None, block=2048):
+    """One head in float64, rows of queries in blocks: O, Z, dQ, dK, dV (and dlog_g) as the header defines them (p = 2)."""
     import torch
     q, k, v, g = (torch.from_numpy(a).to("cuda:0", torch.float64) for a in (Q, K, V, G))
     T = q.shape[0]
+    b_sum = None if log_g is None else torch.cumsum(torch.from_numpy(log_g).to("cuda:0", torch.float64), 0)
+    db = q.new_zeros(T)
     O, Z, dQ, dK, dV = torch.zeros_like(v), q.new_zeros(T), torch.zeros_like(q), torch.zeros_like(k), torch.zeros_like(v)
     for a in range(0, T, block):
         b = min(a + block, T)
@@ -21,6 +23,9 @@ def reference(Q, K, V, G, scale, normalize, block=2048):
         s = scale * (q[a:b] @ kt)
         s.masked_fill_(torch.arange(b, device=q.device)[None, :] > torch.arange(a, b, device=q.device)[:, None], 0.0)
         w = s * s
+        if b_sum is not None:
+            f = torch.exp((b_sum[a:b, None] - b_sum[None, :b]).clamp_(max=0.0))
+            w *= f
         Z[a:b] = w.sum(1)
         den = Z[a:b, None] if normalize else 1.0
         O[a:b] = (w @ v[:b]) / den
@@ -29,14 +34,22 @@ def reference(Q, K, V, G, scale, normalize, block=2048):
         if normalize:
             e -= (gh * O[a:b]).sum(1, keepdim=True)
         t = 2.0 * scale * e * s
+        if b_sum is not None:
+            t *= f
+            ea = e * w
+            db[a:b] += ea.sum(1)
+            db[:b] -= ea.sum(0)
         dQ[a:b] = t @ k[:b]
         dK[:b] += t.t().contiguous() @ q[a:b]
         dV[:b] += w.t().contiguous() @ gh
-    return {n: x.cpu().numpy() for n, x in zip(("O", "Z", "dQ", "dK", "dV"), (O, Z, dQ, dK, dV))}
+    out = {n: x.cpu().numpy() for n, x in zip(("O", "Z", "dQ", "dK", "dV"), (O, Z, dQ, dK, dV))}
+    if b_sum is not None:
+        out["dlog_g"] = torch.flip(torch.cumsum(torch.flip(db, [0]), 0), [0]).cpu().numpy()
+    return out
 
 
 CASES = [
-    # heads, T, d, chunk asked for, scale, normalize, keep
+    # heads, T, d, chunk asked for, scale, normalize, keep (, mean log-gate)
     (1, 7169, 64, 128, 1.0, True, True),       # the shortest backward pass with states: the forward pass has none to keep
     (2, 8192, 64, 128, 0.3, True, True),       # ... and the shortest forward pass
     (1, 8959, 64, 256, 1.0, True, False),      # 7 x 1280 - 1, 7 x 1280, one token of an eighth chunk
@@ -47,12 +60,17 @@ CASES = [
     (1, 18433, 128, 256, 0.7, True, True),
     (2, 19456, 128, 128, 1.0, True, False),    # 19 x 1024
     (14, 18500, 128, 256, 1.0, False, True),   # one walk per head: no segments
+    (1, 5632, 64, 128, 1.0, True, True, 0.02),     # gated: the longest sequence that runs whole
+    (2, 5633, 64, 128, 1.0, True, True, 0.02),     # ... and the shortest with states, 513 tokens in the last chunk
+    (1, 6400, 64, 256, 0.3, True, False, 0.1),     # 5 x 1280
+    (13, 6401, 64, 384, 1.0, False, False, 0.005),
 ]
 
 
-@pytest.mark.parametrize("heads,T,d,chunk,scale,normalize,keep", CASES)
-def test_long_sequences(heads, T, d, chunk, scale, normalize, keep):
-    what = f"heads={heads} T={T} d={d} chunk={chunk} scale={scale} norm={normalize} keep={keep}"
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(x) for x in c))
+def test_long_sequences(case):
+    heads, T, d, chunk, scale, normalize, keep = case[:7]
+    what = f"heads={heads} T={T} d={d} chunk={chunk} scale={scale} norm={normalize} keep={keep} gates={case[7:]}"
     print(what, flush=True)
     rng = np.random.default_rng(7 * T + d)
 
@@ -61,9 +79,10 @@ def test_long_sequences(heads, T, d, chunk, scale, normalize, keep):
         return torch.from_numpy(a.astype(np.float32)).bfloat16().float().numpy()
 
     Q, K, V, G = (bf16(rng.standard_normal((1, heads, T, d), dtype=np.float32) * s) for s in (d ** -0.5, d ** -0.5, 1.0, 1.0))
-    got = run_fwd_bwd(Q, K, V, G, 2, chunk, "bf16", normalize=normalize, scale=scale, keep_state=keep)
+    lg = None if len(case) == 7 else -case[7] * rng.standard_exponential((1, heads, T), dtype=np.float32)
+    got = run_fwd_bwd(Q, K, V, G, 2, chunk, "bf16", normalize=normalize, scale=scale, keep_state=keep, log_g=lg)
     for h in sorted({0, heads - 1}):
-        want = reference(Q[0, h], K[0, h], V[0, h], G[0, h], scale, normalize)
+        want = reference(Q[0, h], K[0, h], V[0, h], G[0, h], scale, normalize, None if lg is None else lg[0, h])
         assert_close({n: a[0, h] for n, a in got.items()}, want, "bf16", f"{what} head {h}")
 
 
