@@ -8,6 +8,7 @@ workspace with torch.  No arithmetic of the method happens here.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -137,18 +138,39 @@ def make_problem(B, H, T, d, v, p, chunk, normalize=True, scale=1.0, dtype="bf16
                      int(bool(gated)), int(d_tile))
 
 
-def _problem_of(Q, V, p, chunk, normalize, scale, impl, keep_state=False, gated=False, d_tile=0) -> PaProblem:
+def _dtype_name(Q) -> str:
     import torch
+    if Q.dtype is torch.bfloat16:
+        return "bf16"
+    if Q.dtype is torch.float32:
+        return "f32"
+    raise PowerAttnError(f"unsupported dtype {Q.dtype}")
+
+
+def _problem_of(Q, V, p, chunk, normalize, scale, impl, keep_state=False, gated=False, d_tile=0) -> PaProblem:
     if Q.dim() != 4 or V.dim() != 4:
         raise PowerAttnError("tensors must be [B, H, T, d]")
-    if Q.dtype == torch.bfloat16:
-        dtype = "bf16"
-    elif Q.dtype == torch.float32:
-        dtype = "f32"
-    else:
-        raise PowerAttnError(f"unsupported dtype {Q.dtype}")
     B, H, T, d = Q.shape
-    return make_problem(B, H, T, d, V.shape[3], p, chunk, normalize, scale, dtype, impl, keep_state, gated, d_tile)
+    return make_problem(B, H, T, d, V.shape[3], p, chunk, normalize, scale, _dtype_name(Q), impl, keep_state, gated, d_tile)
+
+
+# What the library says about a problem depends on its fields alone, so a problem's struct, support status and workspace are
+# looked up once per set of fields, not once per call (three of the six microseconds a small call spent before its launch).
+@functools.lru_cache(maxsize=512, typed=True)     # (typed: 2.0 is refused where 2 is taken)
+def _plan(for_backward, B, H, T, d, v, p, chunk, normalize, scale, dtype, impl, keep_state, gated, d_tile):
+    """-> (pointer to the problem, power_attn_supported's status, workspace bytes)"""
+    lib = load_library()
+    prob = make_problem(B, H, T, d, v, p, chunk, normalize, scale, dtype, impl, keep_state, gated, d_tile)
+    ref = ctypes.pointer(prob)
+    return ref, int(lib.power_attn_supported(ref, for_backward)), int(lib.power_attn_workspace_bytes(ref, for_backward))
+
+
+def _plan_of(for_backward, Q, V, p, chunk, normalize, scale, impl, keep_state, gated, d_tile):
+    if Q.dim() != 4 or V.dim() != 4:
+        raise PowerAttnError("tensors must be [B, H, T, d]")
+    B, H, T, d = Q.shape
+    return _plan(for_backward, B, H, T, d, V.shape[3], p, chunk, bool(normalize), float(scale), _dtype_name(Q), impl,
+                 bool(keep_state), gated, d_tile)
 
 
 def _dev_ptr(t, like=None, name="tensor"):
@@ -158,12 +180,29 @@ def _dev_ptr(t, like=None, name="tensor"):
         raise PowerAttnError(f"{name} must be contiguous")
     if like is not None and (t.dtype != like.dtype or t.device != like.device):
         raise PowerAttnError(f"{name} must match the dtype and device of Q")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
+    """The current stream of the current device, as the library takes it."""
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+class _OnDevice:
+    """with torch.cuda.device(device), where `device` is not the current one already"""
+    __slots__ = ("guard",)
+
+    def __init__(self, device):
+        import torch
+        self.guard = None if device.index == torch._C._cuda_getDevice() else torch.cuda.device(device)
+
+    def __enter__(self):
+        if self.guard is not None:
+            self.guard.__enter__()
+
+    def __exit__(self, *exc):
+        return None if self.guard is None else self.guard.__exit__(*exc)
 
 
 def power_attn_workspace_bytes(prob: PaProblem, for_backward: bool) -> int:
@@ -182,21 +221,21 @@ def power_attn_state_rows(prob: PaProblem) -> int:
     return int(load_library().power_attn_state_rows(ctypes.byref(prob)))
 
 
-def _workspace(lib, prob, for_backward, workspace, device):
+def _workspace(need, workspace, device):
+    """-> (the tensor, its pointer)"""
     import torch
-    need = int(lib.power_attn_workspace_bytes(ctypes.byref(prob), int(for_backward)))
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
-    if workspace.numel() * workspace.element_size() < need:
+    elif workspace.numel() * workspace.element_size() < need:
         raise PowerAttnError(f"workspace holds {workspace.numel() * workspace.element_size()} bytes, {need} needed")
-    return workspace, need
+    return workspace, workspace.data_ptr()
 
 
 def _gate_ptr(log_g, Q, name):
     import torch
     if not log_g.is_cuda or not log_g.is_contiguous() or log_g.dtype != torch.float32 or tuple(log_g.shape) != tuple(Q.shape[:3]):
         raise PowerAttnError(f"{name} must be a contiguous float32 [B, H, T] tensor on the GPU")
-    return ctypes.c_void_p(log_g.data_ptr())
+    return log_g.data_ptr()
 
 
 def power_attn_fwd(Q, K, V, p: int, chunk: int, normalize: bool = True, scale: float = 1.0, impl: str = "auto",
@@ -206,26 +245,23 @@ def power_attn_fwd(Q, K, V, p: int, chunk: int, normalize: bool = True, scale: f
     power_attn_bwd(..., keep_state=True).  log_g (float32 [B, H, T], <= 0) switches gating on."""
     import torch
     lib = load_library()
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V")):
-        _dev_ptr(t, None, name)
-    prob = _problem_of(Q, V, p, chunk, normalize, scale, impl, keep_state, log_g is not None, d_tile)
+    q, k, v = _dev_ptr(Q, None, "Q"), _dev_ptr(K, Q, "K"), _dev_ptr(V, Q, "V")
+    prob, status, need = _plan_of(0, Q, V, p, chunk, normalize, scale, impl, keep_state, log_g is not None, d_tile)
     if keep_state and workspace is None:
         raise PowerAttnError("keep_state=True needs a workspace that outlives the call")
-    _check(lib, lib.power_attn_supported(ctypes.byref(prob), 0), "power_attn_fwd")
-    with torch.cuda.device(Q.device):
+    if status != 0:
+        _check(lib, status, "power_attn_fwd")
+    with _OnDevice(Q.device):
         O = torch.empty_like(V) if out is None else out
         Z = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device) if out_z is None else out_z
-        workspace, need = _workspace(lib, prob, False, workspace, Q.device)
+        workspace, ws = _workspace(need, workspace, Q.device)
         if log_g is None:
-            st = lib.power_attn_fwd(ctypes.byref(prob), _dev_ptr(Q, name="Q"), _dev_ptr(K, Q, "K"), _dev_ptr(V, Q, "V"),
-                                    _dev_ptr(O, Q, "O"), ctypes.c_void_p(Z.data_ptr()),
-                                    ctypes.c_void_p(workspace.data_ptr()), need, _stream())
+            st = lib.power_attn_fwd(prob, q, k, v, _dev_ptr(O, Q, "O"), Z.data_ptr(), ws, need, _stream())
         else:
-            st = lib.power_attn_fwd_gated(ctypes.byref(prob), _dev_ptr(Q, name="Q"), _dev_ptr(K, Q, "K"),
-                                          _dev_ptr(V, Q, "V"), _gate_ptr(log_g, Q, "log_g"), _dev_ptr(O, Q, "O"),
-                                          ctypes.c_void_p(Z.data_ptr()), ctypes.c_void_p(workspace.data_ptr()), need,
+            st = lib.power_attn_fwd_gated(prob, q, k, v, _gate_ptr(log_g, Q, "log_g"), _dev_ptr(O, Q, "O"), Z.data_ptr(), ws, need,
                                           _stream())
-    _check(lib, st, "power_attn_fwd")
+    if st != 0:
+        _check(lib, st, "power_attn_fwd")
     return O, Z
 
 
@@ -235,7 +271,7 @@ def power_attn_fwd_static(Q, K, V, O, Z, p: int, chunk: int, normalize: bool = T
     lib = load_library()
     prob = _problem_of(Q, V, p, chunk, normalize, scale, impl)
     st = lib.power_attn_fwd_static(ctypes.byref(prob), _dev_ptr(Q, name="Q"), _dev_ptr(K, Q, "K"), _dev_ptr(V, Q, "V"),
-                                   _dev_ptr(O, Q, "O"), ctypes.c_void_p(Z.data_ptr()), _stream())
+                                   _dev_ptr(O, Q, "O"), Z.data_ptr(), _stream())
     _check(lib, st, "power_attn_fwd_static")
     return O, Z
 
@@ -246,32 +282,29 @@ def power_attn_bwd(Q, K, V, O, Z, dO, p: int, chunk: int, normalize: bool = True
     log_g is given."""
     import torch
     lib = load_library()
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V"), (dO, "dO")):
-        _dev_ptr(t, None, name)
-    prob = _problem_of(Q, V, p, chunk, normalize, scale, impl, keep_state, log_g is not None, d_tile)
+    q, k, v, g = _dev_ptr(Q, None, "Q"), _dev_ptr(K, Q, "K"), _dev_ptr(V, Q, "V"), _dev_ptr(dO, Q, "dO")
+    prob, status, need = _plan_of(1, Q, V, p, chunk, normalize, scale, impl, keep_state, log_g is not None, d_tile)
     if keep_state and workspace is None:
         raise PowerAttnError("keep_state=True needs the workspace the forward pass used")
-    _check(lib, lib.power_attn_supported(ctypes.byref(prob), 1), "power_attn_bwd")
-    with torch.cuda.device(Q.device):
+    if status != 0:
+        _check(lib, status, "power_attn_bwd")
+    with _OnDevice(Q.device):
         if out is None:
             dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
         else:
             dQ, dK, dV = out
-        workspace, need = _workspace(lib, prob, True, workspace, Q.device)
-        o_ptr = _dev_ptr(O, Q, "O") if O is not None else ctypes.c_void_p(0)
-        z_ptr = ctypes.c_void_p(Z.data_ptr()) if Z is not None else ctypes.c_void_p(0)
+        workspace, ws = _workspace(need, workspace, Q.device)
+        o = _dev_ptr(O, Q, "O") if O is not None else None
+        z = Z.data_ptr() if Z is not None else None
+        dq, dk, dv = _dev_ptr(dQ, Q, "dQ"), _dev_ptr(dK, Q, "dK"), _dev_ptr(dV, Q, "dV")
         if log_g is None:
-            st = lib.power_attn_bwd(ctypes.byref(prob), _dev_ptr(Q, name="Q"), _dev_ptr(K, Q, "K"), _dev_ptr(V, Q, "V"),
-                                    o_ptr, z_ptr, _dev_ptr(dO, Q, "dO"), _dev_ptr(dQ, Q, "dQ"), _dev_ptr(dK, Q, "dK"),
-                                    _dev_ptr(dV, Q, "dV"), ctypes.c_void_p(workspace.data_ptr()), need, _stream())
+            st = lib.power_attn_bwd(prob, q, k, v, o, z, g, dq, dk, dv, ws, need, _stream())
         else:
             dlog_g = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-            st = lib.power_attn_bwd_gated(ctypes.byref(prob), _dev_ptr(Q, name="Q"), _dev_ptr(K, Q, "K"),
-                                          _dev_ptr(V, Q, "V"), _gate_ptr(log_g, Q, "log_g"), o_ptr, z_ptr,
-                                          _dev_ptr(dO, Q, "dO"), _dev_ptr(dQ, Q, "dQ"), _dev_ptr(dK, Q, "dK"),
-                                          _dev_ptr(dV, Q, "dV"), ctypes.c_void_p(dlog_g.data_ptr()),
-                                          ctypes.c_void_p(workspace.data_ptr()), need, _stream())
-    _check(lib, st, "power_attn_bwd")
+            st = lib.power_attn_bwd_gated(prob, q, k, v, _gate_ptr(log_g, Q, "log_g"), o, z, g, dq, dk, dv, dlog_g.data_ptr(), ws, need,
+                                          _stream())
+    if st != 0:
+        _check(lib, st, "power_attn_bwd")
     if log_g is not None:
         return dQ, dK, dV, dlog_g
     return dQ, dK, dV
@@ -338,8 +371,9 @@ def power_attn_decode_step(prob: PaProblem, q, k, v, state, log_g=None, out=None
     lib = load_library()
     o = out if out is not None else torch.empty_like(v)
     z = out_z if out_z is not None else torch.empty(v.shape[:2], dtype=torch.float32, device=v.device)
-    lg = None if log_g is None else _dev_ptr(log_g, name="log_g")
-    _check(lib, lib.power_attn_decode_step(ctypes.byref(prob), _dev_ptr(q, name="q"), _dev_ptr(k, q, "k"), _dev_ptr(v, q, "v"), lg,
-                                           _dev_ptr(state, name="state"), state.numel(), _dev_ptr(o, q, "o"),
-                                           _dev_ptr(z, name="z"), _stream()), "power_attn_decode_step")
+    st = lib.power_attn_decode_step(prob, _dev_ptr(q, name="q"), _dev_ptr(k, q, "k"), _dev_ptr(v, q, "v"),
+                                    None if log_g is None else _dev_ptr(log_g, name="log_g"), _dev_ptr(state, name="state"), state.numel(),
+                                    _dev_ptr(o, q, "o"), _dev_ptr(z, name="z"), _stream())
+    if st != 0:
+        _check(lib, st, "power_attn_decode_step")
     return o, z
