@@ -117,9 +117,10 @@ __global__ __launch_bounds__(256) void k_decode_step(const T* __restrict__ q, co
     }
 }
 
-// The same for v in {4, 8, ..., 128} (a power of two): v / 4 lanes share a row, each with four
-// columns (16-byte accesses), so a wave has 256 / v rows in flight per pass and two passes
-// unrolled - the row-at-a-time kernel above leaves the memory system mostly idle.
+// The same for v in {16, 32, 64, 128}: v / 4 lanes share a row, each with four columns (16-byte accesses).  A call for one
+// sequence is a chain of memory latencies, so everything a block reads is asked for at its start, up to eight rows per lane
+// before the first of them is used: a block's 128 rows are two or three latencies deep (d = 64, one sequence, 12 heads: 6.2 us
+// with two rows in flight, 5.2 now; 64 sequences, at the rate of a large copy either way).
 template <typename T, int P, int V>
 __global__ __launch_bounds__(256) void k_decode_step_vec(const T* __restrict__ q, const T* __restrict__ k,
                                                          const T* __restrict__ vin, const float* __restrict__ log_g,
@@ -127,11 +128,34 @@ __global__ __launch_bounds__(256) void k_decode_step_vec(const T* __restrict__ q
                                                          const uchar4* __restrict__ idx, const float* __restrict__ mult,
                                                          float* __restrict__ part, long long D, int d, float scale) {
     constexpr int LPR = V / 4, RPW = 64 / LPR, RPB = 4 * RPW;   // lanes per row, rows per wave and per block pass
+    constexpr int PASSES = DRB / RPB, GP = PASSES < 8 ? PASSES : 8;
+    static_assert(DRB % RPB == 0 && PASSES % GP == 0 && GP % 2 == 0 && DRB <= 256, "whole groups of passes");
     __shared__ float qs[DMAX], ks[DMAX];
     __shared__ __attribute__((aligned(16))) float vs[DMAX];
     __shared__ __attribute__((aligned(16))) float red[4][DMAX + 4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int blk = blockIdx.x, bh = blockIdx.y, nblk = gridDim.x;
+    const long long r_begin = (long long)blk * DRB;
+    const long long r_end = r_begin + DRB < D ? r_begin + DRB : D;
+    const int c4 = lane % LPR, rl = w * RPW + lane / LPR;        // column quad, row inside a block pass
+    float4 st[GP];
+    uchar4 ix[GP];
+    float mu[GP];
+    auto row_of = [&](int pass) { return r_begin + (long long)pass * RPB + rl; };
+    auto fetch = [&](int p0) {
+#pragma unroll
+        for (int i = 0; i < GP; ++i) {
+            const long long r = row_of(p0 + i), rr = r < r_end ? r : r_begin;
+            st[i] = *((const float4*)(S + ((size_t)bh * D + rr) * V) + c4);
+            ix[i] = idx[rr];
+            mu[i] = mult[rr];
+        }
+    };
+    fetch(0);
+    const long long rz = r_begin + tid;                          // the row whose normaliser this thread updates
+    const bool okz = rz < r_end;
+    const uchar4 iz = idx[okz ? rz : r_begin];
+    const float mz = mult[okz ? rz : r_begin], gz = gam[(size_t)bh * D + (okz ? rz : r_begin)];
     if (tid < d) {
         qs[tid] = scale * io<T>::ld(q + (size_t)bh * d + tid);
         ks[tid] = io<T>::ld(k + (size_t)bh * d + tid);
@@ -140,37 +164,34 @@ __global__ __launch_bounds__(256) void k_decode_step_vec(const T* __restrict__ q
     const float g = log_g != nullptr ? __expf(log_g[bh]) : 1.f;
     __syncthreads();
 
-    const long long r_begin = (long long)blk * DRB;
-    const long long r_end = r_begin + DRB < D ? r_begin + DRB : D;
-    const int c4 = lane % LPR, rl = w * RPW + lane / LPR;        // column quad, row inside a block pass
     const float4 vv = *(const float4*)&vs[4 * c4];
     float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
-    static_assert(DRB % (2 * RPB) == 0 || RPB > DRB / 2, "two passes per trip");
-    for (long long r0 = r_begin; r0 < r_end; r0 += 2 * RPB) {
-        const long long ra = r0 + rl, rb = r0 + RPB + rl;
-        const bool oka = ra < r_end, okb = rb < r_end;
-        float4* pa = (float4*)(S + ((size_t)bh * D + (oka ? ra : r_begin)) * V) + c4;
-        float4* pb = (float4*)(S + ((size_t)bh * D + (okb ? rb : r_begin)) * V) + c4;
-        const float4 sa = *pa, sb = *pb;
-        const uchar4 ia = idx[oka ? ra : r_begin], ib = idx[okb ? rb : r_begin];
-        const float cka = mult[oka ? ra : r_begin] * monomial<P>(ks, ia), cqa = oka ? monomial<P>(qs, ia) : 0.f;
-        const float ckb = mult[okb ? rb : r_begin] * monomial<P>(ks, ib), cqb = okb ? monomial<P>(qs, ib) : 0.f;
-        const float4 na = make_float4(g * sa.x + cka * vv.x, g * sa.y + cka * vv.y, g * sa.z + cka * vv.z, g * sa.w + cka * vv.w);
-        const float4 nb = make_float4(g * sb.x + ckb * vv.x, g * sb.y + ckb * vv.y, g * sb.z + ckb * vv.z, g * sb.w + ckb * vv.w);
-        if (oka) *pa = na;
-        if (okb) *pb = nb;
-        y.x += cqa * na.x + cqb * nb.x;
-        y.y += cqa * na.y + cqb * nb.y;
-        y.z += cqa * na.z + cqb * nb.z;
-        y.w += cqa * na.w + cqb * nb.w;
+#pragma unroll
+    for (int p0 = 0; p0 < PASSES; p0 += GP) {
+        if (p0 > 0) fetch(p0);
+#pragma unroll
+        for (int i = 0; i < GP; i += 2) {
+            const long long ra = row_of(p0 + i), rb = row_of(p0 + i + 1);
+            const bool oka = ra < r_end, okb = rb < r_end;
+            const float4 sa = st[i], sb = st[i + 1];
+            const float cka = mu[i] * monomial<P>(ks, ix[i]), cqa = oka ? monomial<P>(qs, ix[i]) : 0.f;
+            const float ckb = mu[i + 1] * monomial<P>(ks, ix[i + 1]), cqb = okb ? monomial<P>(qs, ix[i + 1]) : 0.f;
+            const float4 na = make_float4(g * sa.x + cka * vv.x, g * sa.y + cka * vv.y, g * sa.z + cka * vv.z, g * sa.w + cka * vv.w);
+            const float4 nb = make_float4(g * sb.x + ckb * vv.x, g * sb.y + ckb * vv.y, g * sb.z + ckb * vv.z, g * sb.w + ckb * vv.w);
+            if (oka) *((float4*)(S + ((size_t)bh * D + ra) * V) + c4) = na;
+            if (okb) *((float4*)(S + ((size_t)bh * D + rb) * V) + c4) = nb;
+            y.x += cqa * na.x + cqb * nb.x;
+            y.y += cqa * na.y + cqb * nb.y;
+            y.z += cqa * na.z + cqb * nb.z;
+            y.w += cqa * na.w + cqb * nb.w;
+        }
     }
     float zp = 0.f;
-    for (long long r = r_begin + tid; r < r_end; r += 256) {
-        const uchar4 ix = idx[r];
-        const float ck = mult[r] * monomial<P>(ks, ix), cq = monomial<P>(qs, ix);
-        const float s = g * gam[(size_t)bh * D + r] + ck;
-        gam[(size_t)bh * D + r] = s;
-        zp += cq * s;
+    if (okz) {
+        const float ck = mz * monomial<P>(ks, iz), cq = monomial<P>(qs, iz);
+        const float s = g * gz + ck;
+        gam[(size_t)bh * D + rz] = s;
+        zp = cq * s;
     }
     // rows of a wave: lanes LPR apart hold the same columns
 #pragma unroll
@@ -549,9 +570,19 @@ __global__ __launch_bounds__(256) void k_decode_finish(const float* __restrict__
                                                        float* __restrict__ z, int v, int normalize) {
     __shared__ float zs;
     const int bh = blockIdx.x, tid = threadIdx.x;
+    // (the parts of 16 blocks at a time on their way: one by one, 17 blocks were 17 latencies, 6.3 us; 2.5 now)
     float acc = 0.f;
-    if (tid <= v)
-        for (int b = 0; b < nblk; ++b) acc += part[((size_t)bh * nblk + b) * (v + 1) + tid];
+    if (tid <= v) {
+        const float* src = part + (size_t)bh * nblk * (v + 1) + tid;
+        for (int b0 = 0; b0 < nblk; b0 += 16) {
+            float x[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = src[(size_t)min(b0 + i, nblk - 1) * (v + 1)];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (b0 + i < nblk) acc += x[i];
+        }
+    }
     if (tid == v) zs = acc;
     __syncthreads();
     const float zz = zs;
