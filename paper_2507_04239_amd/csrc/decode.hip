@@ -14,6 +14,8 @@
 //     part  [B*H][nblk][v+1]             partial read-outs of the step in flight
 // A step reads and writes S and gamma once: it is bound by HBM bandwidth, 8 bytes per state
 // element and token.
+#include <type_traits>
+
 #include "mfma_common.hpp"
 
 namespace pa {
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(256) void k_decode_absorb(const T* __restrict__ K, 
 
 // Rows (i, j0 .. j0 + 7) of a p = 2 state from j = i on, token by token in float32 as above, by one wave: lane = column.
 // (Kept small: the matrix-core kernel below reaches it only for sums that are not finite, and shares its registers with it.)
-template <int HD, bool GATED>
+template <int HD, bool GATED, bool GAM = true>      // GAM: the normaliser too
 __device__ __forceinline__ void absorb_rows(const bf16_t* __restrict__ Kh, const bf16_t* __restrict__ Vh, const float* __restrict__ lgh,
                                             float* __restrict__ Sh, float* __restrict__ gamh, int Tlen, int i, int j0, int lane) {
     using namespace mfma;
@@ -305,7 +307,7 @@ __device__ __forceinline__ void absorb_rows(const bf16_t* __restrict__ Kh, const
     float acc[NR][NC], accz[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        accz[r] = g0[r];
+        accz[r] = GAM ? g0[r] : 0.f;
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[r][c] = S0[r * HD + 64 * c];
     }
@@ -329,7 +331,7 @@ __device__ __forceinline__ void absorb_rows(const bf16_t* __restrict__ Kh, const
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         if (j0 + r < i) continue;
-        if (lane == 0) g0[r] = accz[r];
+        if (GAM && lane == 0) g0[r] = accz[r];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (lane < HD) S0[r * HD + 64 * c] = acc[r][c];
@@ -341,38 +343,29 @@ __device__ __forceinline__ void absorb_rows(const bf16_t* __restrict__ Kh, const
 // (its upper and its lower half), and the two MFMAs that contract the halves with the values form the float32 sum of exact
 // products.  With gates the product carries its token's decay to the end of the 64-token tile, is a float32 number like any
 // other and takes three parts; the accumulators decay from tile to tile.  The sum over the prompt joins the state, which
-// has decayed across the whole prompt, at the end.
+// has decayed across the whole prompt, at the end.  The parts of an infinite product, and of any product beside an infinite
+// value, are not the product's (inf - inf, 0 inf): a wave that ends with anything but finite sums forms its rows token by token
+// instead (absorb_rows), at the vector kernel's speed.
 //
-// A state row is a pair i <= j.  A wave owns the rows of 16 consecutive j (operand row = j) for 2 consecutive i: k_j for 8
-// tokens per lane is formed once per 32 tokens and multiplied by two broadcast k_i.  Eight such waves share the staged tokens
-// (four waves of 4 i each take 169 us at the size below: too few waves to cover the LDS and MFMA latency).  Tokens are staged feature-major, so
-// that every operand is one 16-byte LDS read.  Blocks on the diagonal also form the pairs j < i and drop them (23 % more
-// products at d = 64).  The parts of an infinite product, and of any product beside an infinite value, are not the product's
-// (inf - inf, 0 inf): a wave that ends with anything but finite sums forms its rows token by token instead (absorb_rows), at
-// the vector kernel's speed.  The vector ALU (4 operations per product and lane) and the matrix pipe are loaded
-// about equally, each less than half of the time; the rest is the chain barrier, LDS read, product, MFMA of a tile.
-// MI355X, B4 H12 T3000 d64: 2160 us on the vector ALUs (k_decode_absorb, one thread per row and 4 columns) -> 156 us.
+// d = 32: a state row is a pair i <= j.  A wave owns the rows of 16 consecutive j (operand row = j) for 2 consecutive i: k_j for 8
+// tokens per lane is formed once per 32 tokens and multiplied by two broadcast k_i.  Eight such waves share the staged tokens.
+// Tokens are staged feature-major, so that every operand is one 16-byte LDS read.  Blocks on the diagonal also form the pairs
+// j < i and drop them.
 constexpr int AXT = 64;         // tokens per tile
 constexpr int AXP = AXT + 8;    // pitch of a feature's tokens: 16 rows read 16 bytes each from distinct banks
-template <int HD>
 struct AbsorbTile {
-    bf16_t k[HD][AXP], v[HD][AXP];
+    bf16_t k[32][AXP], v[32][AXP];
     float w[AXT];               // decay of each token to the end of the tile
 };
-// the units of a head: (j block, i pair) with the pair not beyond the block's last row
-template <int HD>
-constexpr int absorb_units() {
-    return (HD / 16) * (HD / 16 + 1) * 4;
-}
-template <int HD, bool GATED>
-__global__ __launch_bounds__(512, HD == 128 ? 2 : HD == 32 ? (GATED ? 5 : 6) : 4) void k_decode_absorb_mfma(const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-                                                               const float* __restrict__ log_g, float* __restrict__ S,
-                                                               float* __restrict__ gam, long long D, int Tlen) {
+constexpr int ABSORB_UNITS = 2 * 3 * 4;     // (j block, i pair) with the pair not beyond the block's last row
+template <bool GATED>
+__global__ __launch_bounds__(512, GATED ? 5 : 6) void k_decode_absorb_32(const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+                                                                         const float* __restrict__ log_g, float* __restrict__ S,
+                                                                         float* __restrict__ gam, long long D, int Tlen) {
+    constexpr int HD = 32;
     using namespace mfma;
     constexpr int NV = HD / 16, NP = GATED ? 3 : 2, NI = 2;
-    constexpr int NPC = (HD + 63) / 64;     // pieces of 8 features per thread and operand (d = 32: of the first four waves)
-    extern __shared__ __attribute__((aligned(16))) unsigned char absorb_smem[];
-    AbsorbTile<HD>* tiles = reinterpret_cast<AbsorbTile<HD>*>(absorb_smem);      // [2]
+    __shared__ __attribute__((aligned(16))) AbsorbTile tiles[2];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r16 = lane & 15, g = lane >> 4;
     const size_t bh = blockIdx.y;
     int unit = 8 * (int)blockIdx.x + w, jb = 0;       // jb has 8 jb + 8 pairs
@@ -391,31 +384,26 @@ __global__ __launch_bounds__(512, HD == 128 ? 2 : HD == 32 ? (GATED ? 5 : 6) : 4
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones.v[e] = (__bf16)1.f;
 
-    // thread: token `lane` of the tile, features 8 (NPC w + c) .. + 7.  Tokens past the end are zeros (log-gate 0).
-    Frag kr[NPC], vr[NPC];
+    // thread: token `lane` of the tile, features 8 w .. 8 w + 7 (the first four waves).  Tokens past the end are zeros (log-gate 0).
+    Frag kr, vr;
     float lg = 0.f, decay = 1.f;
     auto load = [&](int t0) {
         const int t = t0 + lane;
-        const size_t off = (size_t)min(t, Tlen - 1) * HD + 8 * NPC * w;
+        const size_t off = (size_t)min(t, Tlen - 1) * HD + 8 * w;
         if (GATED) lg = t < Tlen ? log_g[bh * Tlen + t] : 0.f;
-        if (HD == 32 && w >= 4) return;
-#pragma unroll
-        for (int c = 0; c < NPC; ++c) {
-            kr[c].u = *(const uint4*)(Kh + off + 8 * c);
-            vr[c].u = *(const uint4*)(Vh + off + 8 * c);
-            if (t >= Tlen) kr[c].u = vr[c].u = make_uint4(0, 0, 0, 0);
-        }
+        if (w >= 4) return;
+        kr.u = *(const uint4*)(Kh + off);
+        vr.u = *(const uint4*)(Vh + off);
+        if (t >= Tlen) kr.u = vr.u = make_uint4(0, 0, 0, 0);
     };
     float tile_decay = 1.f;     // across the tile that `store` was last called for
-    auto store = [&](AbsorbTile<HD>& dst) {
-        if (HD != 32 || w < 4)
-#pragma unroll
-        for (int c = 0; c < NPC; ++c)
+    auto store = [&](AbsorbTile& dst) {
+        if (w < 4)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int f = 8 * (NPC * w + c) + e;
-                dst.k[f][lane] = (bf16_t)(((e & 1) ? kr[c].q[e / 2] >> 16 : kr[c].q[e / 2]) & 0xffffu);
-                dst.v[f][lane] = (bf16_t)(((e & 1) ? vr[c].q[e / 2] >> 16 : vr[c].q[e / 2]) & 0xffffu);
+                const int f = 8 * w + e;
+                dst.k[f][lane] = (bf16_t)(((e & 1) ? kr.q[e / 2] >> 16 : kr.q[e / 2]) & 0xffffu);
+                dst.v[f][lane] = (bf16_t)(((e & 1) ? vr.q[e / 2] >> 16 : vr.q[e / 2]) & 0xffffu);
             }
         if (GATED) {
             float s = lg;       // sum of the log-gates of this token and those after it in the tile
@@ -438,7 +426,7 @@ __global__ __launch_bounds__(512, HD == 128 ? 2 : HD == 32 ? (GATED ? 5 : 6) : 4
     for (int t0 = 0; t0 < Tlen; t0 += AXT, buf ^= 1) {
         const bool more = t0 + AXT < Tlen;
         if (more) load(t0 + AXT);
-        const AbsorbTile<HD>& tl = tiles[buf];
+        const AbsorbTile& tl = tiles[buf];
         if (GATED) {
             decay *= cur_decay;
 #pragma unroll
@@ -532,22 +520,432 @@ __global__ __launch_bounds__(512, HD == 128 ? 2 : HD == 32 ? (GATED ? 5 : 6) : 4
     });
 }
 
-template <int HD, bool GATED>
-bool absorb_mfma_t(const pa_problem& pr, const DecodeLayout& L, const void* K, const void* V, const float* log_g, char* st,
-                   hipStream_t s) {
-    static_assert(absorb_units<HD>() % 8 == 0, "whole workgroups");
-    constexpr size_t smem = 2 * sizeof(AbsorbTile<HD>);
-    auto kern = k_decode_absorb_mfma<HD, GATED>;
-    if (smem > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) {
-            note_hip_error(e, "hipFuncSetAttribute(max dynamic LDS)");
-            return false;
+// d = 64 and 128, in larger blocks (32x32x16).  A wave owns 2 R values i by 16 values j of one state and all columns, at most 128
+// accumulators: a row block is 2 i x 16 j, so a lane needs k_i of one token per row block and the multiply fetches the token it
+// stands at from its 16-lane row by DPP; k_j for its 8 tokens is read once per 16 tokens and serves R row blocks.  Tokens stay
+// row-major in LDS, operands along tokens come through the transposing read.
+// Bound by the vector instructions beside the MFMAs: a row block and 16 tokens are 4 MFMAs at d = 64 (32 cycles each) and 8
+// products in two parts each (4 instructions; subtracting by v_dot2_f32_bf16 instead takes one fewer and 25 % longer: it gets in
+// the MFMAs' way).  So the pieces of the next step's products stand between this step's MFMAs, a pair's one MFMA apart, with no
+// result read soon after, and a stage's first operands are read before the barrier that ends the stage before it (three buffers).
+// The normaliser is k k^T, whose products the matrix cores form exactly from the bf16 tokens: workgroups of their own with
+// 32 x 32 blocks of it (a column of ones beside the values is half a column block more MFMAs at d = 64).
+// MI355X, 48 heads of 3000 tokens (16x16x32 in the manner of d = 32 -> this): d = 64 142 -> 97 us, gated 220 -> 156;
+// d = 128 1020 -> 568, gated 1332 -> 1007; 12 heads, d = 64: 99 -> 44.
+template <int HD, int R>
+struct AbsorbBlk {
+    static constexpr int AU = 2 * R, NC = HD / 32, PER = 16 / AU;
+    static constexpr int G = (HD / 16) * (HD / 16 + 1) / 2 * PER / 4;      // workgroups of 4 waves
+    static constexpr int NB = HD / 32, NU = NB * (NB + 1) / 2, GN = (NU + 3) / 4;      // normaliser: waves and workgroups
+    static constexpr int XF = HD == 64 ? 64 : 32;      // features staged for the products: all, or a workgroup's 16 i and 16 j
+    static constexpr int XP = XF + 16, YP = HD + 16;   // pitches: 8 rows x 32 bytes of a transposing read on distinct banks
+    static constexpr int ST = 64;                      // tokens per stage
+    static_assert(HD == 64 || PER % 4 == 0, "the waves of a workgroup share their 16 i and 16 j at d = 128");
+};
+template <int HD, int R>
+struct AbsorbSmem {
+    bf16_t x[3][AbsorbBlk<HD, R>::ST][AbsorbBlk<HD, R>::XP];
+    bf16_t y[3][AbsorbBlk<HD, R>::ST][AbsorbBlk<HD, R>::YP];
+    float w[3][AbsorbBlk<HD, R>::ST];      // gates: each token's decay to the end of its stage
+    float td[3];                           // ... and across the stage
+};
+struct AbsorbArgs {
+    const bf16_t *K, *V;
+    const float* log_g;
+    float *S, *gam;
+    long long D;
+    int T, heads;
+};
+// x = the sum of bf16 numbers, the upper 16 bits first (two x at a time), what is left stays in x
+__device__ __forceinline__ uint32_t upper_halves(const float (&x)[2]) {
+    return __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
+}
+__device__ __forceinline__ uint32_t split_pair(float (&x)[2]) {
+#pragma clang fp contract(off)      // (a product that is used twice cannot take its factor by DPP)
+    const uint32_t u = upper_halves(x);
+    x[0] -= __uint_as_float(__float_as_uint(x[0]) & 0xffff0000u);
+    x[1] -= __uint_as_float(__float_as_uint(x[1]) & 0xffff0000u);
+    return u;
+}
+
+template <int N>
+__device__ __forceinline__ float row_shl(float x) {     // the value of the lane N further on in this lane's 16-lane row, 0 past its end
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x100 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+
+template <int HD, int R_, bool GATED, bool NORM>
+__device__ __forceinline__ void absorb_body(const AbsorbArgs& A, AbsorbSmem<HD, R_>& sm, size_t bh, int g) {
+    using namespace mfma;
+    using C = AbsorbBlk<HD, R_>;
+    constexpr int R = NORM ? 1 : R_, NC = NORM ? 1 : C::NC, NP = GATED ? 3 : 2, ST = C::ST;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int hl = lane >> 5, row16 = (lane >> 4) & 1, i16 = lane & 15, T = A.T;
+    int J = 0, a0 = 0, nr = 0, nc = 0;      // 16 j from 16 J, AU i from a0; normaliser: rows 32 nr .., columns 32 nc ..
+    bool idle = false;
+    if (NORM) {
+        int u = 4 * g + w;
+        idle = u >= C::NU;
+        for (u = min(u, C::NU - 1); u > nc; u -= ++nc) {}
+        nr = u;
+    } else {
+        int u = 4 * g + w;
+        for (; u >= C::PER * (J + 1); ++J) u -= C::PER * (J + 1);
+        a0 = C::AU * u;
+    }
+    const int I = a0 >> 4;                  // (d = 128: the same for all four waves)
+    const bf16_t *Kh = A.K + bh * T * HD, *Vh = A.V + bh * T * HD;
+    const bf16_t* Yh = NORM ? Kh : Vh;
+    const float* lgh = GATED ? A.log_g + bh * T : nullptr;
+    float* Sh = A.S + bh * A.D * HD;
+    float* gh = A.gam + bh * A.D;
+
+    // staging: 16-byte pieces of rows.  Tokens past the end are zeros (log-gate 0).
+    constexpr int NY = HD / 32, NX = NORM ? 0 : C::XF / 32;
+    uint4 xr[NX > 0 ? NX : 1], yr[NY];
+    float lg = 0.f, decay = 1.f;
+    auto load = [&](int t0) {
+#pragma unroll
+        for (int q = 0; q < NY; ++q) {
+            const int id = tid + 256 * q, row = t0 + id / (HD / 8);
+            yr[q] = *(const uint4*)(Yh + (size_t)min(row, T - 1) * HD + 8 * (id % (HD / 8)));
+        }
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+            const int id = tid + 256 * q, c8 = id % (C::XF / 8), row = t0 + id / (C::XF / 8);
+            const int f = HD == 64 ? 8 * c8 : (c8 < 2 ? 16 * I + 8 * c8 : 16 * J + 8 * (c8 - 2));
+            xr[q] = *(const uint4*)(Kh + (size_t)min(row, T - 1) * HD + f);
+        }
+        if (GATED && tid < ST) lg = t0 + tid < T ? lgh[t0 + tid] : 0.f;
+    };
+    auto only = [](const uint4& u, bool yes) { return make_uint4(yes ? u.x : 0u, yes ? u.y : 0u, yes ? u.z : 0u, yes ? u.w : 0u); };
+    auto put = [&](int buf, int t0) {
+#pragma unroll
+        for (int q = 0; q < NY; ++q) {
+            const int id = tid + 256 * q, row = id / (HD / 8);
+            *(uint4*)&sm.y[buf][row][8 * (id % (HD / 8))] = only(yr[q], t0 + row < T);
+        }
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+            const int id = tid + 256 * q, row = id / (C::XF / 8);
+            *(uint4*)&sm.x[buf][row][8 * (id % (C::XF / 8))] = only(xr[q], t0 + row < T);
+        }
+        if (GATED && w == 0) {
+            // sums of the log-gates from each token on, in its row of 16 lanes, then the rows after it
+            float sum = lg;
+            sum += row_shl<1>(sum);
+            sum += row_shl<2>(sum);
+            sum += row_shl<4>(sum);
+            sum += row_shl<8>(sum);
+            const float t1 = lane_value(sum, 16), t2 = lane_value(sum, 32), t3 = lane_value(sum, 48);
+            const float rest = lane < 16 ? t1 + (t2 + t3) : lane < 32 ? t2 + t3 : lane < 48 ? t3 : 0.f;
+            sm.w[buf][lane] = expf(row_shl<1>(sum) + rest);
+            if (lane == 0) sm.td[buf] = expf(sum + rest);
+        }
+    };
+
+    f32x16 acc[R][NC];
+#pragma unroll
+    for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) acc[rb][cb] = zero16();
+    float big = 0.f;            // normaliser: the largest magnitude that goes into a product
+
+    // k-slots of a 16-token step: half hl has tokens 4 hl + 0 .. 3 and 8 + 4 hl + 0 .. 3
+    const uint32_t sel = row16 ? 0x07060c0cu : 0x05040c0cu;      // the upper or lower bf16 of a dword as float32
+    const int xa_tok = 16 * (i16 >> 3) + 8 * ((i16 >> 2) & 1) + 4 * hl + (i16 & 3);
+    const int tr_tok = 4 * hl + (i16 >> 2), tr_col = 16 * row16 + 4 * (i16 & 3);
+    const int xa_col = HD == 64 ? a0 : (a0 & 15), xb_col = (HD == 64 ? 16 * J : 16) + 4 * (i16 & 3);
+    struct Ops {            // LDS operands of one step; the next step's are read before this one's are used
+        Frag v[NC], xb;     // (normaliser: xb holds the rows)
+        float4 w0, w1;
+    };
+    auto read_ops = [&](Ops& o, int buf, int ks) {
+        const int t = 16 * ks + tr_tok;
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) o.v[cb] = tr_frag(&sm.y[buf][t][32 * (nc + cb) + tr_col], C::YP);
+        o.xb = NORM ? tr_frag(&sm.y[buf][t][32 * nr + tr_col], C::YP) : tr_frag(&sm.x[buf][t][xb_col], C::XP);
+        if (GATED) {
+            o.w0 = *(const float4*)&sm.w[buf][16 * ks + 4 * hl];
+            o.w1 = *(const float4*)&sm.w[buf][16 * ks + 8 + 4 * hl];
+        }
+    };
+    using XaRaw = std::conditional_t<R == 4, uint4, std::conditional_t<R == 2, uint2, uint32_t>>;
+    auto read_xa = [&](int buf, int kp) { return *(const XaRaw*)&sm.x[buf][32 * kp + xa_tok][xa_col]; };
+    auto elem = [&](const Ops& c, int j) {      // k_j (normaliser: k_i) of the step in c, token j, with its decay
+        float x = (j & 1) ? bf_hi(c.xb.q[j / 2]) : bf_lo(c.xb.q[j / 2]);
+        if (GATED) x *= j == 0 ? c.w0.x : j == 1 ? c.w0.y : j == 2 ? c.w0.z : j == 3 ? c.w0.w : j == 4 ? c.w1.x : j == 5 ? c.w1.y : j == 6 ? c.w1.z : c.w1.w;
+        return x;
+    };
+    // Stages n and n + 1 are in LDS while n is worked on, n + 2 goes there during it and n + 3 is on its way in registers
+    // (stages past the end are zeros: no branches)
+    load(0);
+    put(0, 0);
+    load(ST);
+    put(1, ST);
+    load(2 * ST);
+    lds_barrier();
+    int buf = 0, nbuf = 1, pbuf = 2;
+    auto ahead = [&](int t0) {
+        put(pbuf, t0 + 2 * ST);
+        load(t0 + 3 * ST);
+    };
+    auto turn = [&] {
+        lds_barrier();
+        const int b = buf;
+        buf = nbuf;
+        nbuf = pbuf;
+        pbuf = b;
+    };
+    auto scale = [&](int rb, float f) {
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[rb][cb][i] *= f;
+    };
+    if constexpr (NORM) {
+        for (int t0 = 0; t0 < T; t0 += ST) {
+            ahead(t0);
+            if (GATED) {
+                const float f = sm.td[buf];
+                decay *= f;
+                scale(0, f);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                Ops c;
+                read_ops(c, buf, ks);
+                Frag part[NP];
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {
+                    float x[2] = {elem(c, j), elem(c, j + 1)};
+                    big = fmaxf(fmaxf(big, fmaxf(fabsf(x[0]), fabsf(x[1]))), fmaxf(fabsf(bf_lo(c.v[0].q[j / 2])), fabsf(bf_hi(c.v[0].q[j / 2]))));
+                    if (GATED) {
+#pragma unroll
+                        for (int n = 0; n + 1 < NP; ++n) part[n].q[j / 2] = split_pair(x);
+                        part[NP - 1].q[j / 2] = upper_halves(x);
+                    }
+                }
+                if (GATED) {
+#pragma unroll
+                    for (int n = 0; n < NP; ++n) acc[0][0] = mfma32(part[n].v, c.v[0].v, acc[0][0]);
+                } else {
+                    acc[0][0] = mfma32(c.xb.v, c.v[0].v, acc[0][0]);
+                }
+            }
+            turn();
+        }
+    } else {
+        constexpr int AHEAD = R == 1 ? 2 : 1, NO = 2 * AHEAD;       // steps that operands are read ahead of their products
+        Ops o[NO];
+        XaRaw xw[2];
+        Frag part[2][NP];
+        float xb[8], xa[2], x[4][2];
+        // Step u (taken modulo a stage's 4 R) in small pieces: its factors k_i, the products 2 p and 2 p + 1, and their parts
+        auto factor = [&](int u) {
+            const XaRaw& raw = xw[(u / R & 3) >> 1];
+            const int rb = u % R;
+            uint32_t d;
+            if constexpr (R == 4) d = rb == 0 ? raw.x : rb == 1 ? raw.y : rb == 2 ? raw.z : raw.w;
+            else if constexpr (R == 2) d = rb == 0 ? raw.x : raw.y;
+            else d = raw;
+            xa[u & 1] = __uint_as_float(__builtin_amdgcn_perm(d, 0u, sel));
+        };
+        auto product = [&](int u, int p) {
+            const int ks = u / R & 3;
+#pragma unroll
+            for (int j = 2 * p; j < 2 * p + 2; ++j) {
+                if (u % R == 0) xb[j] = elem(o[ks % NO], j);
+                float m;
+                switch (8 * (ks & 1) + j) {
+#define PA_LANE(L_) case L_: m = row_lane<L_>(xa[u & 1]); break;
+                    PA_LANE(0) PA_LANE(1) PA_LANE(2) PA_LANE(3) PA_LANE(4) PA_LANE(5) PA_LANE(6) PA_LANE(7)
+                    PA_LANE(8) PA_LANE(9) PA_LANE(10) PA_LANE(11) PA_LANE(12) PA_LANE(13) PA_LANE(14)
+#undef PA_LANE
+                    default: m = row_lane<15>(xa[u & 1]);
+                }
+                x[p][j & 1] = m * xb[j];
+            }
+        };
+        auto piece = [&](int u, int p, int n) {
+            part[u & 1][n].q[p] = n + 1 < NP ? split_pair(x[p]) : upper_halves(x[p]);
+        };
+#pragma unroll
+        for (int n = 0; n < AHEAD; ++n) read_ops(o[n], 0, n);
+        xw[0] = read_xa(0, 0);
+        factor(0);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            product(0, p);
+#pragma unroll
+            for (int n = 0; n < NP; ++n) piece(0, p, n);
+        }
+        factor(1);
+        product(1, 0);
+        for (int t0 = 0; t0 < T; t0 += ST) {
+            float f = 1.f;
+            if (GATED) {
+                f = sm.td[buf];
+                decay *= f;
+                scale(0, f);
+            }
+            // (after the last stage the next one's operands are read from what stands there, and dropped)
+#pragma unroll
+            for (int i = 0; i < 4 * R; ++i) {
+                const int ks = i / R, rb = i % R;
+                if (rb == 0) {
+                    read_ops(o[(ks + AHEAD) % NO], ks + AHEAD < 4 ? buf : nbuf, (ks + AHEAD) & 3);
+                    if (ks == 0) xw[1] = read_xa(buf, 1);
+                    if (ks == 2) xw[0] = read_xa(nbuf, 0);
+                    if (ks == 1) ahead(t0);
+                }
+                // Between this step's MFMAs the pieces of the next one, a pair's one MFMA apart: none waits for another's result.
+                // Pair p's first part comes with MFMA at(p) of the step before its own, its product one MFMA sooner.
+                constexpr int NM = NP * NC;
+                auto at = [](int p) { return p * NM / 4; };
+#pragma unroll
+                for (int n = 0; n < NM; ++n) {
+                    acc[rb][n % NC] = mfma32(part[i & 1][n / NC].v, o[ks % NO].v[n % NC].v, acc[rb][n % NC]);
+                    if (n == NM - 2) factor(i + 2);
+#pragma unroll
+                    for (int u = i; u < i + 3; ++u)
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) {
+                            const int rel = n + (i + 1 - u) * NM - at(p);
+                            if (rel == -1) product(u, p);
+                            if (rel >= 0 && rel < NP) piece(u, p, rel);
+                        }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (GATED && ks == 0 && rb + 1 < R) scale(rb + 1, f);
+            }
+            turn();
         }
     }
+    if (idle) return;
+
+    float nought = 0.f * decay;         // NaN if any sum is infinite or NaN
+#pragma unroll
+    for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) nought += 0.f * acc[rb][cb][i];
+    if constexpr (NORM) {
+        // element 4 q + r of a lane: row i = 32 nr + 8 q + 4 hl + r, column j = 32 nc + (lane & 31)
+        const int j = 32 * nc + (lane & 31);
+        float old[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int i = min(32 * nr + 8 * (e >> 2) + 4 * hl + (e & 3), j);
+            old[e] = gh[i * HD - i * (i - 1) / 2 + j - i];
+            if (GATED && decay == 0.f) nought += 0.f * old[e];      // (a product of gates that has vanished keeps an infinity, a gate of zero does not)
+        }
+        // Products beyond float32 are infinite one by one, also where the matrix cores would add them to something finite
+        const bool plain = __all(nought == 0.f && big < 0x1p63f);
+        if (!plain) {
+#pragma unroll 1
+            for (int t = 0; t < T; ++t) {
+                const float gt = GATED ? __expf(lgh[t]) : 1.f, kj = io<bf16_t>::ld(Kh + (size_t)t * HD + j);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int i = min(32 * nr + 8 * (e >> 2) + 4 * hl + (e & 3), j);
+                    const float coef = (i == j ? 1.f : 2.f) * (io<bf16_t>::ld(Kh + (size_t)t * HD + i) * kj);
+                    old[e] = GATED ? gt * old[e] + coef : old[e] + coef;
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int i = 32 * nr + 8 * (e >> 2) + 4 * hl + (e & 3);
+            if (i <= j) gh[i * HD - i * (i - 1) / 2 + j - i] = plain ? decay * old[e] + (i == j ? 1.f : 2.f) * acc[0][0][e] : old[e];
+        }
+    } else {
+        // element 4 q + r of row block rb: i = a0 + 2 rb + (q >> 1), j = 16 J + 8 (q & 1) + 4 hl + r, column 32 cb + (lane & 31)
+        auto row_of = [&](int rb, int e, int& i, int& j) {
+            i = a0 + 2 * rb + (e >> 3);
+            j = 16 * J + 8 * ((e >> 2) & 1) + 4 * hl + (e & 3);
+            const int jj = max(i, j);
+            return (size_t)(i * HD - i * (i - 1) / 2 + jj - i) * HD + (lane & 31);
+        };
+        if (GATED && decay == 0.f)
+#pragma unroll 1
+            for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+#pragma unroll
+                    for (int cb = 0; cb < NC; ++cb) {
+                        int i, j;
+                        nought += 0.f * Sh[row_of(rb, e, i, j) + 32 * cb];
+                    }
+        if (!__all(nought == 0.f)) {
+#pragma unroll 1
+            for (int n = 0; n < 2 * C::AU; ++n)
+                absorb_rows<HD, GATED, false>(Kh, Vh, lgh, Sh, gh, T, __builtin_amdgcn_readfirstlane(a0) + n / 2,
+                                              __builtin_amdgcn_readfirstlane(16 * J) + 8 * (n & 1), lane);
+            return;
+        }
+#pragma unroll
+        for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < NC; ++cb) {
+                float old[16];
+                int i, j;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) old[e] = Sh[row_of(rb, e, i, j) + 32 * cb];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    float* dst = Sh + row_of(rb, e, i, j) + 32 * cb;
+                    if (j >= i) *dst = decay * old[e] + (i == j ? 1.f : 2.f) * acc[rb][cb][e];
+                }
+            }
+    }
+}
+
+template <int HD, int R, bool GATED>
+__global__ __launch_bounds__(256, 2) void k_decode_absorb_blk(AbsorbArgs A) {
+    using C = AbsorbBlk<HD, R>;
+    __shared__ __attribute__((aligned(16))) AbsorbSmem<HD, R> sm;
+    // (the normaliser's workgroups, the shortest, after all others)
+    const int first = (int)mfma::xcd_grid(A.heads * C::G);
+    if ((int)blockIdx.x < first) {
+        const int item = mfma::xcd_item(A.heads * C::G, blockIdx.x);
+        if (item >= 0) absorb_body<HD, R, GATED, false>(A, sm, item / C::G, item % C::G);
+    } else {
+        const int item = mfma::xcd_item(A.heads * C::GN, blockIdx.x - first);
+        if (item >= 0) absorb_body<HD, R, GATED, true>(A, sm, item / C::GN, item % C::GN);
+    }
+}
+
+template <int HD, int R, bool GATED>
+bool launch_absorb_blk(const AbsorbArgs& a, hipStream_t s) {
+    using C = AbsorbBlk<HD, R>;
     LaunchScope ls("decode_absorb", s);
-    hipLaunchKernelGGL(kern, dim3(absorb_units<HD>() / 8, pr.B * pr.H), dim3(512), smem, s, (const bf16_t*)K, (const bf16_t*)V, log_g,
-                       (float*)(st + L.off_s), (float*)(st + L.off_gam), L.D, pr.T);
+    const dim3 grid(mfma::xcd_grid(a.heads * C::G) + mfma::xcd_grid(a.heads * C::GN));
+    hipLaunchKernelGGL((k_decode_absorb_blk<HD, R, GATED>), grid, dim3(256), 0, s, a);
+    return launch_ok();
+}
+// Large blocks form fewest operands per MFMA, small ones spread few states over the chip.  d = 64: R = 1 while all its workgroups
+// run at once, two to a CU (3000 tokens, R = 1 and 4: 12 heads 44 and 83 us, 24 heads 65 and 86, 48 heads 122 and 97); R = 2 is
+// between them or behind everywhere.  d = 128: R = 2 above one workgroup of R = 1 per CU (3000 tokens, R = 1 and 2: 1 head 51 and
+// 77 us, 12 heads 184 and 158, 96 heads 1301 and 1125), with gates R = 1 throughout: R = 2 has no registers left for a second
+// wave per SIMD (48 heads 1007 and 1030 us, 192 heads of 1000 tokens 1504 and 1664).
+bool absorb_blk(const AbsorbArgs& a, int d, hipStream_t s) {
+    const bool gated = a.log_g != nullptr;
+    if (d == 64) {
+        if (a.heads * AbsorbBlk<64, 1>::G <= 512) return gated ? launch_absorb_blk<64, 1, true>(a, s) : launch_absorb_blk<64, 1, false>(a, s);
+        return gated ? launch_absorb_blk<64, 4, true>(a, s) : launch_absorb_blk<64, 4, false>(a, s);
+    }
+    if (gated) return launch_absorb_blk<128, 1, true>(a, s);
+    return a.heads * AbsorbBlk<128, 1>::G <= 256 ? launch_absorb_blk<128, 1, false>(a, s) : launch_absorb_blk<128, 2, false>(a, s);
+}
+
+template <bool GATED>
+bool launch_absorb_32(const AbsorbArgs& a, hipStream_t s) {
+    LaunchScope ls("decode_absorb", s);
+    hipLaunchKernelGGL((k_decode_absorb_32<GATED>), dim3(ABSORB_UNITS / 8, a.heads), dim3(512), 0, s, a.K, a.V, a.log_g, a.S, a.gam, a.D, a.T);
     return launch_ok();
 }
 bool absorb_mfma_applies(const pa_problem& pr) {
@@ -555,13 +953,9 @@ bool absorb_mfma_applies(const pa_problem& pr) {
 }
 bool absorb_mfma(const pa_problem& pr, const DecodeLayout& L, const void* K, const void* V, const float* log_g, char* st,
                  hipStream_t s) {
-#define PA_GO(DD)                                                                  \
-    if (pr.d == DD)                                                                \
-        return log_g != nullptr ? absorb_mfma_t<DD, true>(pr, L, K, V, log_g, st, s) \
-                                : absorb_mfma_t<DD, false>(pr, L, K, V, log_g, st, s);
-    PA_GO(32) PA_GO(64) PA_GO(128)
-#undef PA_GO
-    return false;
+    const AbsorbArgs a{(const bf16_t*)K, (const bf16_t*)V, log_g, (float*)(st + L.off_s), (float*)(st + L.off_gam), L.D, pr.T, pr.B * pr.H};
+    if (pr.d != 32) return absorb_blk(a, pr.d, s);
+    return log_g != nullptr ? launch_absorb_32<true>(a, s) : launch_absorb_32<false>(a, s);
 }
 
 // grid B*H: sums the blocks' partial read-outs, divides, stores

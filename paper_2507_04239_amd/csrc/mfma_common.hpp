@@ -57,6 +57,39 @@ union Frag {
     uint2 h[2];
 };
 
+template <int L>
+__device__ __forceinline__ float row_lane(float x) {   // the value of lane L of this lane's 16-lane row
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + L, 0xf, 0xf, false));
+}
+__device__ __forceinline__ f32x16 zero16() {
+    f32x16 v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = 0.f;
+    return v;
+}
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+// 8 k-slots (rows base + 0 .. 3 of the lanes' 16-lane group, and 8 rows further), one column per lane
+__device__ __forceinline__ Frag tr_frag(const bf16_t* p, int pitch) {
+    union {
+        Frag f;
+        bf16x4 h[2];
+    } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)p);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 8 * pitch));
+    return u.f;
+}
+
+// Work items in contiguous runs per XCD (workgroups are dealt to the 8 XCDs round-robin by their linear id), so that the items
+// that read the same memory sit side by side on one L2
+__device__ __forceinline__ int xcd_item(int total, int block) {
+    const int xcd = block & 7, q = block >> 3;
+    const int base = total / 8, extra = total % 8;
+    if (q >= base + (xcd < extra ? 1 : 0)) return -1;
+    return xcd * base + min(xcd, extra) + q;
+}
+__device__ __forceinline__ int xcd_item(int total) { return xcd_item(total, (int)blockIdx.x); }
+__host__ __device__ inline unsigned xcd_grid(int total) { return 8u * (unsigned)((total + 7) / 8); }
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also fences global memory,
 // i.e. waits for every outstanding global load, which would drain a register prefetch ring.
 __device__ __forceinline__ void lds_barrier() {

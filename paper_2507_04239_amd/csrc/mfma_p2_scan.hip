@@ -85,12 +85,6 @@ struct ScanOps {          // LDS operands of one k-step for one lane
     uint4 b[4];              // Y^T fragments, 4 column blocks
 };
 
-// the value of lane L of this lane's 16-lane row
-template <int L>
-__device__ __forceinline__ float row_lane(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + L, 0xf, 0xf, false));
-}
-
 template <bool GAMMA, bool REV>
 __device__ __forceinline__ void scan_load_ops(ScanOps& o, const ScanSmem& sm, int buf, int s, int fa0, int fa_step,
                                               int fb, int r16, int g) {

@@ -130,3 +130,47 @@ def test_hand_over_of_numbers_that_are_not_finite(what, d, gated):
             # two float32 sums of T terms, each product rounded up to three times
             assert np.all(np.abs(got[fin].astype(np.float64) - want[fin]) <= 2 * (T + 8) * 2.0 ** -24 * mag[fin].astype(np.float64) + 1e-30)
     assert bad > 0
+
+
+@pytest.mark.parametrize("gated", [False, True], ids=["plain", "gated"])
+@pytest.mark.parametrize("d,heads", [(64, 25), (64, 26), (128, 3), (128, 4)])      # the last with small blocks, the first with large ones
+@pytest.mark.parametrize("T", [1, 64, 129, 193])
+def test_exact_hand_over_of_many_heads(T, d, heads, gated):
+    """Small and large blocks around the stages of 64 tokens, of which three are under way at once; one head in the middle holds an
+    infinite value and keys whose products are no float32 of either sign."""
+    import torch
+    print("case", T, d, heads, gated, flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(T + d + heads)
+    K, V = (torch.randn(1, heads, T, d, device="cuda:0", generator=gen).bfloat16() for _ in range(2))
+    lg = -0.05 * torch.rand(1, heads, T, device="cuda:0", generator=gen) if gated else None
+    odd = heads // 2
+    V[0, odd, T // 2, 5] = float("inf")
+    K[0, odd, T - 1, 3], K[0, odd, T - 1, 40] = 2.0 ** 66, 2.0 ** 67
+    K[0, odd, T // 3, 3], K[0, odd, T // 3, 40] = -2.0 ** 66, 2.0 ** 67
+    one = binding.make_problem(1, heads, 1, d, d, 2, 1, dtype="bf16", gated=gated)
+    state = binding.power_attn_decode_init(one)
+    prob = binding.make_problem(1, heads, T, d, d, 2, 1, dtype="bf16", gated=gated)
+    words = binding.power_attn_decode_absorb(prob, K, V, state, lg, fast=False).view(torch.float32)
+    D = d * (d + 1) // 2
+    n, off = heads * D * d, (heads * D * d * 4 + 255) // 256 * 64
+    S, gam = words[:n].view(heads, D, d), words[off:off + heads * D].view(heads, D)
+    i, j = torch.triu_indices(d, d, device="cuda:0")
+    for h in sorted({0, heads - 1, odd}):
+        if h == odd:
+            want_S, want_g = _recurrence(*(to_np(a[0, h].float()) for a in (K, V)), None if lg is None else to_np(lg[0, h]),
+                                         np.zeros((D, d), np.float32), np.zeros(D, np.float32))
+            for got, want in ((to_np(S[h]), want_S), (to_np(gam[h]), want_g)):
+                assert not np.isfinite(want).all()
+                assert np.array_equal(np.isnan(got), np.isnan(want))
+                inf = np.isinf(want)
+                assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+            continue
+        k, v = K[0, h].double(), V[0, h].double()
+        phi = k[:, i] * k[:, j] * torch.where(i == j, 1.0, 2.0)
+        if gated:
+            b = torch.cumsum(lg[0, h].double(), 0)
+            phi = phi * torch.exp(b[-1:] - b)[:, None]
+        pt = phi.t().contiguous()
+        tol = (T + 8) * 2.0 ** -24          # as above
+        assert bool(((S[h].double() - pt @ v).abs() <= tol * (pt.abs() @ v.abs()) + 1e-30).all())
+        assert bool(((gam[h].double() - pt.sum(1)).abs() <= tol * pt.abs().sum(1) + 1e-30).all())
