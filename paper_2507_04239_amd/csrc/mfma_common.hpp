@@ -6,7 +6,8 @@
 // multiplicity 2, which is applied once, to the state (instead of sqrt(2) on both sides).
 // Expanded operands are built in registers in MFMA operand order and never stored.
 //
-// MFMA used: v_mfma_f32_16x16x32_bf16.  Operand layout (lane l, r16 = l % 16, g = l / 16):
+// MFMAs used: v_mfma_f32_32x32x16_bf16 (mfma32 below) and v_mfma_f32_16x16x32_bf16.  Operand layout of the latter (lane l,
+// r16 = l % 16, g = l / 16):
 //   A: row r16,   k-slots 8g..8g+7        B: column r16, k-slots 8g..8g+7
 //   C: column r16, rows 4g..4g+3 (4 floats)
 // Only the pairing of A and B k-slots matters, so k-slots are assigned to whatever order
@@ -30,11 +31,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int DH = 64;                         // head size (d = v)
-constexpr int NTB = DH / 8;                    // 8-wide feature blocks
-constexpr int NTILES = NTB * (NTB + 1) / 2;    // 36 tiles of 64 expanded rows
-constexpr int TILE_ELEMS = 8 * DH * 8;         // elements of one state tile
-constexpr int STATE_ELEMS = NTILES * TILE_ELEMS;
-constexpr int QBLK = 128;                      // token rows per workgroup of the chunk kernels
+constexpr int QBLK = 128;                      // token rows the chunk length is a multiple of
 constexpr int TBLK = 64;                       // tokens per block of the feature-major copies
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -98,11 +95,6 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return (uint32_t)(size_t)((__attribute__((address_space(3))) const void*)p);
-}
-
-
 // Cross-lane sums without the LDS pipe: v_permlane16_swap / v_permlane32_swap exchange 16-lane rows (resp.
 // 32-lane halves) between two registers.
 __device__ __forceinline__ float xor16_sum(float x) {   // x + (value in lane ^ 16), in every lane
@@ -119,21 +111,9 @@ __device__ __forceinline__ float xor32_sum(float x) {
     halves(x, lo, hi);
     return lo + hi;
 }
-// wait until at most `n` of this wave's vector-memory operations are outstanding (they retire in order)
-template <int N>
-__device__ __forceinline__ void vm_wait() {
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 0xF) | (((N >> 4) & 0x3) << 14));
-}
 
 // ---- launchers (each defined next to its kernels) ------------------------------------------
-// feature-major copy in blocks of 64 tokens: [BH][T][DH] -> [BH][T/64][DH][64]
-// fac (may be null): per-token factors; the copy is then of x_t * sqrt(fac_t)
-// out_T (0: T): tokens per head the output buffer is laid out for
-bool launch_transpose(hipStream_t s, const bf16_t* in, bf16_t* out, int BH, int T, const float* fac = nullptr, int out_T = 0);
-// state scan; rev = 0: S_n from (Kt, Vt); rev = 1: R_m from (Qt, Ght) with the weights gz.
-// gam receives Gamma (rev = 0) or Omega (rev = 1).
-bool launch_scan(const char* name, hipStream_t s, bool rev, const bf16_t* Xt, const bf16_t* Yt, const float* wgt, bf16_t* stC,
-                 bf16_t* gam, int BH, int T, int cs, float out_scale, const float* lam = nullptr);
+
 // ---- resident-state kernels (chunk states kept in registers; see mfma_resident.hip) ----------------
 struct ResidentPlan {
     int nhp, nslab;            // half-pairs per wave; workgroups (slabs of state rows) per head
@@ -162,6 +142,16 @@ bool launch_transpose_hd(hipStream_t s, int HD, const bf16_t* in, bf16_t* out, i
 // sca[bh][t] = csca * x_t^T G x_t; vec, sca and wgt may each be null
 bool launch_gram_apply(hipStream_t s, int HD, const bf16_t* X, const bf16_t* gam, const float* wgt, float* vec, float* sca,
                        int BH, int T, int cs, float cvec, float csca);
+
+// a prompt of T tokens (a multiple of 64; d = 64) into decode states S [BH][D][64], gamd [BH][D]: scratch of tot_floats.
+// Gates: tw [BH][T], the decay from a token to the prompt's end, lam [BH] across the prompt, wK [BH][T][64] scratch
+struct QuadAbsorbPlan {
+    int cs, nseg;
+    size_t tot_floats;
+};
+QuadAbsorbPlan quad_absorb_plan(int BH, int T);
+bool launch_quad_absorb(hipStream_t s, const QuadAbsorbPlan& p, const bf16_t* K, const bf16_t* V, const float* tw, const float* lam,
+                        bf16_t* wK, float* tot, float* S, float* gamd, int D, int BH, int T);
 
 // ---- chunked form for any degree and tile width (state kept in memory; see mfma_tiled.hip) -------------
 // One tile of the tiled symmetric-power embedding: its p block indices (non-decreasing) and its multiplicity

@@ -81,6 +81,7 @@ struct ScanArgs {
     bf16_t *st, *gam;
     float* tot;              // [BH][nseg][NG + 1][TOTF]
     int T, cs, nchunk, nseg, seg_chunks, heads;
+    int tot_segs;            // TOT: segments whose total is formed (all, or all but the walk's last)
     float fold, out_scale;   // X is multiplied by fold (a power of two) on the way in, the state by out_scale on the way out
 };
 
@@ -388,7 +389,7 @@ template <int HD, bool REV, bool TOT, bool FOLD, bool GATED>
 __global__ __launch_bounds__(256, 2) void k_quad_scan(ScanArgs A) {
     __shared__ __attribute__((aligned(16))) ScanSmem<HD> sm;
     constexpr int G = ScanCfg<HD>::NG + 1;
-    const int segs = TOT ? A.nseg - 1 : A.nseg;
+    const int segs = TOT ? A.tot_segs : A.nseg;
     const int item = xcd_item(A.heads * segs * G);
     if (item < 0) return;
     const int g = item % G, hs = item / G;
@@ -935,6 +936,69 @@ __global__ __launch_bounds__(256) void k_quad_boundary(const bf16_t* __restrict_
     if (tid == 0) xb[((size_t)bh * nchunk + n) * QUAD_XPARTS + part] = red[0] + red[1] + red[2] + red[3];
 }
 
+// ---- a prompt into a decode state -------------------------------------------------------------------------
+// rows of X times the square root of their token's weight (p = 2: the weight of phi), in bf16
+__global__ __launch_bounds__(256) void k_quad_weigh(const bf16_t* __restrict__ X, const float* __restrict__ tw, bf16_t* __restrict__ out,
+                                                    size_t pieces) {
+    const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;      // 8 features of one token (d = 64)
+    if (id >= pieces) return;
+    const float f = sqrtf(tw[id / 8]);
+    float x[8];
+    unpack8(x, *(const uint4*)(X + 8 * id));
+    *(uint4*)(out + 8 * id) = make_uint4(pack2(f * x[0], f * x[1]), pack2(f * x[2], f * x[3]), pack2(f * x[4], f * x[5]), pack2(f * x[6], f * x[7]));
+}
+// S[row][:] = decay S + m sum over the segments' totals, row = the monomial (i, j), i <= j, of multiplicity m, and the normaliser
+// column likewise; the sum is rounded to bf16, as the states between chunks are.  A wave has one i and 8 consecutive j of one
+// state: what a scan wave's lanes hold of them are the accumulators 4 kq + r of one row block (a = a0 + 2 rb + (kq >> 1),
+// b = 8 (kq & 1) + 4 hl + r).  Bound by memory: totals in, state in and out.
+// Measured, scan and this (before: a scan over transposed copies, one workgroup per head and tile pair, into bf16 states):
+// B4 H12 T3072 164 -> 109 us, B1 H4 T65536 499 -> 112, B8 H16 T8192 884 -> 502.
+__global__ __launch_bounds__(256) void k_quad_absorb(const float* __restrict__ tot, int nseg, const float* __restrict__ lam,
+                                                     float* __restrict__ S, float* __restrict__ gamd, int D, int heads) {
+    using C = ScanCfg<64>;
+    constexpr int HD = 64, PERHEAD = HD * (HD / 8);
+    const int lane = threadIdx.x & 63, hl = lane >> 5, id = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int bh = id / PERHEAD, u = id % PERHEAD, i = u % HD, jb = u / HD;
+    if (bh >= heads || 8 * jb + 7 < i) return;
+    const int J = jb >> 1, unit = J * (J + 1) + (i >> 3);       // (two units of 8 a per 16 x 16)
+    const int rb = (i & 7) >> 1, kq = 2 * (i & 1) + (jb & 1);
+    const size_t seg = (size_t)(C::NG + 1) * C::TOTF;
+    const float* base = tot + (size_t)bh * nseg * seg;
+    const float* src = base + (size_t)(unit >> 2) * C::TOTF + (size_t)(unit & 3) * (C::TOTF / 4) + (rb * C::NC * 4 + kq) * 256 + 4 * lane;
+    // the normaliser's element (i, 8 jb + lane): rows 32 (w & 1) + 8 k + 4 h + r, columns 32 (w >> 1) + ..
+    const int jn = 8 * jb + (lane & 7), nw = (i >> 5) + 2 * (jn >> 5), nrow = i & 31;
+    const float* nsrc = base + (size_t)C::NG * C::TOTF + (size_t)nw * (C::TOTF / 4) + (nrow >> 3) * 256 +
+                        4 * (32 * ((nrow >> 2) & 1) + (jn & 31)) + (nrow & 3);
+    float4 a[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+    float gsum = 0.f;
+    for (int s = 0; s < nseg; ++s) {
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const float4 v = *(const float4*)(src + s * seg + cb * 4 * 256);
+            a[cb].x += v.x; a[cb].y += v.y; a[cb].z += v.z; a[cb].w += v.w;
+        }
+        gsum += nsrc[s * seg];
+    }
+    auto rounded = [](float x) { return (float)(__bf16)x; };
+    gsum = rounded(gsum);
+    const float decay = lam != nullptr ? lam[bh] : 1.f;
+    const int row0 = i * HD - i * (i - 1) / 2 - i;              // row of (i, j): row0 + j
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = 8 * jb + 4 * hl + r;
+            if (j < i) continue;
+            float* dst = S + ((size_t)bh * D + row0 + j) * HD + 32 * cb + (lane & 31);
+            const float x = rounded(r == 0 ? a[cb].x : r == 1 ? a[cb].y : r == 2 ? a[cb].z : a[cb].w);
+            *dst = decay * *dst + (i == j ? x : 2.f * x);
+        }
+    if (lane < 8 && jn >= i) {
+        float* dst = gamd + (size_t)bh * D + row0 + jn;
+        *dst = decay * *dst + (i == jn ? gsum : 2.f * gsum);
+    }
+}
+
 template <typename F>
 bool allow_smem(F* fn, size_t bytes) {
     if (bytes <= 64 * 1024) return true;
@@ -961,7 +1025,7 @@ bool scan_go(const char* name, hipStream_t s, ScanArgs a) {
     // (d = 64: the totals are the update-state, the running sum over them a pass of its own)
     if (a.nseg > 1) {
         LaunchScope ls(HD == 64 ? name : "mfma_state_totals", s);
-        hipLaunchKernelGGL((k_quad_scan<HD, REV, true, FOLD, GATED>), dim3(xcd_grid(a.heads * (a.nseg - 1) * G)), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_quad_scan<HD, REV, true, FOLD, GATED>), dim3(xcd_grid(a.heads * a.tot_segs * G)), dim3(256), 0, s, a);
         if (!launch_ok()) return false;
     }
     LaunchScope ls(HD == 64 ? "mfma_state_prefix" : name, s);
@@ -1002,7 +1066,7 @@ bool launch_quad_scan(const char* name, hipStream_t s, const QuadPlan& p, bool r
     if (p.nchunk < 2) return true;
     ScanArgs a{};
     a.X = X; a.Y = Y; a.gz = wgt; a.tw = tw; a.lam = lam; a.st = st; a.gam = gam; a.tot = tot;
-    a.T = T; a.cs = p.cs; a.nchunk = p.nchunk; a.nseg = p.nseg; a.seg_chunks = p.seg_chunks; a.heads = BH;
+    a.T = T; a.cs = p.cs; a.nchunk = p.nchunk; a.nseg = p.nseg; a.tot_segs = p.nseg - 1; a.seg_chunks = p.seg_chunks; a.heads = BH;
     float rest;
     split_scale(scale, a.fold, rest);
     a.out_scale = rest * rest;
@@ -1079,6 +1143,39 @@ bool launch_quad_boundary(hipStream_t s, const QuadPlan& p, const bf16_t* st, co
                           float* xb, int BH) {
     LaunchScope ls("mfma_gate_boundary", s);
     hipLaunchKernelGGL(k_quad_boundary, dim3(QUAD_XPARTS, p.nchunk, BH), dim3(256), 0, s, st, rc, gam, omg, xb, p.nchunk);
+    return launch_ok();
+}
+
+// segments of the prompt, each a workgroup's own: about two workgroups per CU, of at least four stages
+QuadAbsorbPlan quad_absorb_plan(int BH, int T) {
+    QuadAbsorbPlan p{};
+    const int want = std::max(1, 512 / (BH * (ScanCfg<64>::NG + 1)));
+    p.cs = std::max(256, ((T + want - 1) / want + 63) / 64 * 64);
+    p.nseg = (T + p.cs - 1) / p.cs;
+    p.tot_floats = (size_t)BH * p.nseg * (ScanCfg<64>::NG + 1) * ScanCfg<64>::TOTF;
+    return p;
+}
+bool launch_quad_absorb(hipStream_t s, const QuadAbsorbPlan& p, const bf16_t* K, const bf16_t* V, const float* tw, const float* lam,
+                        bf16_t* wK, float* tot, float* S, float* gamd, int D, int BH, int T) {
+    if (tw != nullptr) {
+        const size_t pieces = (size_t)BH * T * 8;
+        LaunchScope ls("decode_absorb_weigh", s);
+        hipLaunchKernelGGL(k_quad_weigh, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, K, tw, wK, pieces);
+        if (!launch_ok()) return false;
+        K = wK;
+    }
+    ScanArgs a{};
+    a.X = K; a.Y = V; a.tot = tot;
+    a.T = T; a.cs = p.cs; a.nchunk = a.nseg = a.tot_segs = p.nseg; a.seg_chunks = 1; a.heads = BH;
+    a.fold = a.out_scale = 1.f;
+    {
+        LaunchScope ls("decode_absorb_scan", s);
+        hipLaunchKernelGGL((k_quad_scan<64, false, true, false, false>), dim3(xcd_grid(BH * p.nseg * (ScanCfg<64>::NG + 1))), dim3(256), 0, s,
+                           a);
+        if (!launch_ok()) return false;
+    }
+    LaunchScope ls("decode_absorb_convert", s);
+    hipLaunchKernelGGL(k_quad_absorb, dim3((unsigned)(BH * 64 * 8 / 4)), dim3(256), 0, s, (const float*)tot, p.nseg, lam, S, gamd, D, BH);
     return launch_ok();
 }
 

@@ -97,3 +97,33 @@ def test_runs_are_bit_identical_and_chunks_agree(d, T):
     for n in a:
         assert np.array_equal(a[n], b[n]), n
         assert np.array_equal(a[n], c[n]), n
+
+
+@pytest.mark.parametrize("gated", [False, True], ids=["plain", "gated"])
+@pytest.mark.parametrize("heads,T", [(1, 128), (3, 640), (90, 384), (2, 4224)])     # one segment, a short last one, long ones, many
+def test_prompt_totals(heads, T, gated):
+    """The decode state after a prompt, through the state scan: phi and the sum are rounded to bf16 (2^-8 each), with gates the two
+    scaled keys of a product as well; the sums are float32."""
+    import torch
+    from paper_2507_04239_amd import binding
+    print(f"heads={heads} T={T} gated={gated}", flush=True)
+    torch.manual_seed(T + heads)
+    K, V = (torch.randn(1, heads, T, 64, device="cuda:0").bfloat16() for _ in range(2))
+    lg = -0.02 * torch.rand(1, heads, T, device="cuda:0") if gated else None
+    prob = binding.make_problem(1, heads, T, 64, 64, 2, 1, dtype="bf16", gated=gated)
+    assert binding.power_attn_decode_absorb_workspace_bytes(prob) > 0
+    state = binding.power_attn_decode_init(binding.make_problem(1, heads, 1, 64, 64, 2, 1, dtype="bf16", gated=gated))
+    flat = binding.power_attn_decode_absorb(prob, K, V, state, lg, fast=True).view(torch.float32)
+    n, off = heads * 2080 * 64, (heads * 2080 * 64 * 4 + 255) // 256 * 64
+    S, gam = flat[:n].view(heads, 2080, 64), flat[off:off + heads * 2080].view(heads, 2080)
+    i, j = torch.triu_indices(64, 64, device="cuda:0")
+    for h in sorted({0, heads - 1}):
+        k, v = K[0, h].double(), V[0, h].double()
+        phi = k[:, i] * k[:, j] * torch.where(i == j, 1.0, 2.0)
+        if gated:
+            b = torch.cumsum(lg[0, h].double(), 0)
+            phi = phi * torch.exp(b[-1:] - b)[:, None]
+        pt = phi.t().contiguous()
+        tol = (4.1 if gated else 2.05) * 2.0 ** -8 + (T + 8) * 2.0 ** -24        # (and second-order terms)
+        assert bool(((S[h].double() - pt @ v).abs() <= tol * (pt.abs() @ v.abs())).all())
+        assert bool(((gam[h].double() - pt.sum(1)).abs() <= tol * pt.abs().sum(1)).all())
