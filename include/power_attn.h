@@ -82,12 +82,13 @@ typedef struct {
     int   chunk;        /* chunk size c of the chunked form.  chunk == T is the attention form (one chunk).
                            0: the library chooses between the two forms and the chunk size (see
                            power_attn_resolved_chunk).  A chunk that does not divide T (a ragged last
-                           chunk) is taken by the chunked bf16 MFMA kernels only (gated, or of the other
-                           degrees and head sizes: padded with zero rows inside the workspace); elsewhere it is
-                           PA_ERR_UNSUPPORTED.  bf16, p = 2, d = v = 64 or 128, not gated, under AUTO or MFMA: the
-                           kernels space their states as they run fastest (over 1000 tokens apart, and none at all for
-                           sequences up to 7 or 8 thousand tokens at d = 64, 14 to 18 thousand at d = 128), whatever
-                           multiple of 128 was asked for; the result does not depend on it beyond rounding */
+                           chunk) is taken by the chunked bf16 MFMA kernels only (of the other degrees and head
+                           sizes: padded with zero rows inside the workspace); elsewhere it is
+                           PA_ERR_UNSUPPORTED.  bf16, p = 2, d = v = 64 (gated or not) or 128 (not gated), under AUTO or
+                           MFMA: the kernels space their states as they run fastest (over 1000 tokens apart, and none at
+                           all for sequences up to 7 or 8 thousand tokens at d = 64, 5632 with gates, 14 to 18 thousand
+                           at d = 128), whatever multiple of 128 was asked for; the result does not depend on it beyond
+                           rounding */
     int   normalize;    /* 1: divide by the sum of the scores; 0: leave un-normalised */
     float scale;        /* multiplies q.k before the power ("softmax scaling", App. E.1 step 2).  Some kernels multiply q
                            (or k) by it, or by its power of two, before the product: q.k, scale q, scale k and the

@@ -135,8 +135,8 @@ AttnLayout make_attn_layout(const pa_problem& pr, bool backward) {
     return L;
 }
 
-// Chunk-state kernels with phi in registers (mfma_quad.hip): what AUTO and MFMA run for the un-gated chunked form of p = 2 at
-// d = 64 and 128, whatever multiple of 128 tokens the chunk is.  The states they keep are QUAD_CHUNK tokens apart: the result does
+// Chunk-state kernels with phi in registers (mfma_quad.hip): what AUTO and MFMA run for the chunked form of p = 2 at d = 64 and
+// (un-gated) 128, whatever multiple of 128 tokens the chunk is.  The states they keep are quad_chunk tokens apart: the result does
 // not depend on the chunk beyond rounding, and states are rounded less often the fewer they are.
 bool quad_ok(const pa_problem& pr) {
     return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && (pr.d == 64 || pr.d == 128) && pr.v == pr.d && pr.chunk > 0 &&
@@ -152,7 +152,8 @@ int quad_chunk(int d) { return d == 64 ? 1280 : 1024; }
 // 81, 106, 12 x 8192 122, 120, 48 x 6144 214, 289, 48 x 8192 361, 384, 12 x 12288 253, 180; backward 12 x 6144 209, 290,
 // 12 x 8192 351, 329, 48 x 6144 746, 825, 48 x 8192 1282, 1124, 2 x 8192 158, 184; d = 128 forward 16 x 16384 1100, 1349,
 // 16 x 24576 2490, 2112, 2 x 16384 311, 371, 2 x 24576 522, 444; backward 16 x 12288 2187, 2782, 16 x 16384 3826, 3644,
-// 2 x 12288 738, 761, 2 x 16384 978, 868.
+// 2 x 12288 738, 761, 2 x 16384 978, 868; gated, d = 64, forward 12 x 6144 142, 131, 48 x 6144 277, 324, 12 x 8192 189, 139, backward
+// 12 x 6144 289, 272, 48 x 6144 964, 883, 12 x 8192 471, 324.
 int quad_whole_upto(int d, bool gated, bool backward) {
     if (gated) return 5632;
     return d == 64 ? (backward ? 7168 : 8191) : (backward ? 14336 : 18432);
@@ -202,8 +203,7 @@ QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
 }
 
 // The tiled kernels run when asked for by name or for a tile width, and wherever no other matrix-core kernel takes the
-// chunked form of the problem (degrees 3 and 4, d = 32) or they are the faster ones (d = 128: measured against the
-// resident-state walk, which has to cut the state into slabs there)
+// chunked form of the problem (degrees 3 and 4, d = 32)
 bool use_tiled(const pa_problem& pr) {
     if (!tiled_ok(pr)) return false;
     if (pr.impl == PA_IMPL_TILED) return true;

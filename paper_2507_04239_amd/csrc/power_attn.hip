@@ -71,16 +71,13 @@ pa_status validate(const pa_problem* pr) {
 
 // chunk == 0: the library picks between the attention form (one chunk: cost ~ T per token) and the
 // chunked form (cost ~ the state size per token), Sec. 2 "Chunked form".  Where the bf16 MFMA
-// kernels apply the choice is measured on MI355X.  p = 2, d = 64, which has both forms on the
-// matrix cores: the attention form up to T = 4096 (2048 with gating), and chunks of 256 beyond (128 when 256 does not
-// divide T).  (The attention form has become faster since the line was drawn: 12 heads, forward + backward, ms, chunk 256 and
-// whole sequence: T = 4096 0.24 and 0.13, 6144 0.40 and 0.30, 7168 0.46 and 0.39, 8192 0.48 and 0.49; gated, 16384 tokens in all,
-// 4096 1.11 and 0.63, 8192 1.10 and 1.19.)  Other
-// degrees and head sizes have matrix-core kernels for the attention form only, and that beats the
-// chunked form on the vector ALUs at any length the latter is sensible for.  Elsewhere the two costs
+// kernels apply the choice is measured on MI355X.  p = 2, d = 64: the attention form up to T = 4096 (2048 with gating), and
+// chunks of 256 beyond (128 when 256 does not divide T).  (These are the chunks reported; at d = 64 and 128 the chunked kernels
+// space their states themselves and run sequences up to lengths of their own as one, see quad_whole_upto in mfma_p2.hip, so at
+// d = 64 the line only decides what is reported.)  Degrees 3 and 4 stay with the attention form, see below.  Elsewhere the two costs
 // are compared by their multiply-add counts, T (4 d + 2) / 2 per token against 4 D (v + 1), with a
 // factor of two against the attention form: the generic kernels' in-chunk code does about half as many
-// multiply-adds per second as their state code (config 1, T = 256: 0.32 ms as one chunk, 0.14 ms chunked).
+// multiply-adds per second as their state code (f32, one head, T = 256, d = 16: 0.32 ms as one chunk, 0.14 ms chunked).
 int auto_chunk(const pa_problem& pr) {
     const bool may_mfma = pr.impl == PA_IMPL_AUTO || pr.impl == PA_IMPL_MFMA || pr.impl == PA_IMPL_RESIDENT || pr.impl == PA_IMPL_TILED;
     pa_problem probe = pr;
@@ -89,11 +86,10 @@ int auto_chunk(const pa_problem& pr) {
     // the chunked kernels, on the sequence rounded up to whole chunks when it is ragged (see Padding)
     probe.chunk = pr.T % 256 == 0 || pr.T % 128 != 0 ? 256 : 128;
     probe.T = (pr.T + probe.chunk - 1) / probe.chunk * probe.chunk;
-    // p = 2 at the other head sizes runs chunked on the tiled kernels (forward + backward, ms, chunk 256 and whole sequence).
-    // d = 128, 16 heads: T = 16384 8.8 .. 9.5 and 5.0, 24576 14.7 and 11.2, 32768 20.0 and 19.7; 128 heads of 32768 111 and 158.
-    // d = 32, 32 heads: T = 4096 0.37 and 0.18, 6144 0.54 and 0.36, 8192 0.70 and 0.63, 32768 2.7 and 8.8.  For the higher degrees
-    // the attention form stays ahead at every length measured (p = 3, d = 64, 4 heads: T = 16384 7.0 and 0.78, 131072 60 and 37;
-    // p = 4, d = 32, 16 heads: 16384 24 and 1.4, 65536 97 and 20).
+    // d = 128: where the chunked kernels' forward pass leaves the attention form by itself.  d = 32 runs chunked on the tiled
+    // kernels (32 heads, forward + backward, ms, chunk 256 and whole sequence): T = 4096 0.37 and 0.18, 6144 0.54 and 0.36,
+    // 8192 0.70 and 0.63, 32768 2.7 and 8.8.  For the higher degrees the attention form stays ahead at every length measured
+    // (p = 3, d = 64, 4 heads: T = 16384 7.0 and 0.78, 131072 60 and 37; p = 4, d = 32, 16 heads: 16384 24 and 1.4, 65536 97 and 20).
     const int attn_upto = pr.d == 128 ? 18432 : (pr.gated ? 2048 : 4096);
     if (may_mfma && pr.p == 2 && (pr.d == 32 || pr.d == 64 || pr.d == 128) && mfma_supported(probe, true) == PA_OK &&
         !(attn && pr.T <= attn_upto))
