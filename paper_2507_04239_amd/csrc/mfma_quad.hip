@@ -147,14 +147,14 @@ __device__ __forceinline__ void scan_body(const ScanArgs& A, ScanSmem<HD>& sm, i
         for (int q = 0; q < NY; ++q) {
             const int id = tid + 256 * q, row = t0 + id / (HD / 8);
             const uint4 u = *(const uint4*)(Yh + (size_t)min(row, A.T - 1) * HD + 8 * (id % (HD / 8)));
-            yr[q] = REV && row >= A.T ? make_uint4(0, 0, 0, 0) : u;
+            yr[q] = make_uint4(u.x, u.y, u.z, u.w);     // (by element: a copy of the whole puts the array into scratch memory)
         }
 #pragma unroll
         for (int q = 0; q < NX; ++q) {
             const int id = tid + 256 * q, c8 = id % (C::XF / 8), row = t0 + id / (C::XF / 8);
             const int f = HD == 64 ? 8 * c8 : (c8 < 2 ? 16 * I + 8 * c8 : 16 * J + 8 * (c8 - 2));
             const uint4 u = *(const uint4*)(Xh + (size_t)min(row, A.T - 1) * HD + f);
-            xr[q] = REV && row >= A.T ? make_uint4(0, 0, 0, 0) : u;
+            xr[q] = make_uint4(u.x, u.y, u.z, u.w);
         }
         if (WGT && tid < C::ST) {
             const int t = t0 + tid;
@@ -165,7 +165,17 @@ __device__ __forceinline__ void scan_body(const ScanArgs& A, ScanSmem<HD>& sm, i
             wr = t < A.T ? v : 0.f;
         }
     };
-    auto put = [&](int buf) {
+    auto put = [&](int buf, int t0) {
+        // (Only REV adds the last chunk.  Zeros are chosen here, in a branch of their own: chosen in the loads they break the
+        // 16-byte writes up: 12 heads of 65536 tokens at d = 64 358 us instead of 327)
+        if (REV && t0 + C::ST > A.T) {
+#pragma unroll
+            for (int q = 0; q < NY; ++q)
+                if (t0 + (tid + 256 * q) / (HD / 8) >= A.T) yr[q] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < NX; ++q)
+                if (t0 + (tid + 256 * q) / (C::XF / 8) >= A.T) xr[q] = make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
         for (int q = 0; q < NY; ++q) {
             const int id = tid + 256 * q;
@@ -345,7 +355,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs& A, ScanSmem<HD>& sm, i
         int n = REV ? c1 - 1 : c0, left = nadd;
         int t = n * A.cs, t_end = min(t + A.cs, A.T), buf = 0;
         load(t);
-        put(0);
+        put(0, t);
         lds_barrier();
         while (true) {
             // the stage after this one
@@ -363,7 +373,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs& A, ScanSmem<HD>& sm, i
                 if (GATED && left2 > 0) decay(lam[n2]);
             }
             if (left2 == 0) break;
-            put(buf ^ 1);
+            put(buf ^ 1, t2);
             lds_barrier();
             buf ^= 1;
             t = t2;
