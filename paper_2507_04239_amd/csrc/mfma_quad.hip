@@ -830,6 +830,9 @@ __global__ __launch_bounds__(64 * DphiCfg<HD>::NW, 2) void k_quad_dphi(StateArgs
                         asm volatile("; column %0" ::"n"(i));
                     }
             } else {
+                // The partner reads the last column's sums (land) behind the barrier that opened this column, so another barrier
+                // has to come before they are overwritten.  The second pair of tiles brings it, but column 1 has one pair only.
+                if (tj == 1) lds_barrier();
 #pragma unroll
                 for (int tb = 0; tb < 2; ++tb) hand[(w * 2 + tb) * 64 + lane] = make_float4(t2[tb][0], t2[tb][1], t2[tb][2], t2[tb][3]);
             }
