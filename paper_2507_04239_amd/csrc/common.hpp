@@ -58,14 +58,19 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // ---- kernel families ------------------------------------------------------------------
 // Per-token and per-chunk decay factors derived from the log-gates (all null when the problem
 // is not gated).  With bl_i the sum of the log-gates from the start of token i's chunk up to i:
-//   bl    [BH][T]       bl_i; a pair inside a chunk carries exp(bl_i - bl_j)
+//   bl    [BH][T]       bl_i; a pair inside a chunk carries exp(bl_i - bl_j).  Where blk is there (the matrix-core kernels) bl
+//                       starts anew every GATE_BLOCK tokens and a pair carries exp((blk_I - blk_J) + (bl_i - bl_j)), I and J
+//                       the blocks of i and j
+//   blk   [BH][blocks]  float64 sum of the chunk's log-gates before a block of GATE_BLOCK tokens
 //   qfac  [BH][T]       exp(bl_i): decay of query i since the start of its chunk
 //   kfac  [BH][T]       exp(bl_end - bl_j): decay of key j until the end of its chunk
 //   lam   [BH][chunks]  exp(bl_end): decay across the whole chunk
 // (a chunk being what the kernels that read them take for one: see mfma_gate_chunk)
 //   db    [BH][T]       backward pass: q_i . dq_i, written by the family's dQ kernel from its float32 accumulators
 //   db2   [BH][T]       backward pass: k_i . dk_i, likewise
+constexpr int GATE_BLOCK = 128;
 struct GateBuf {
+    double* blk = nullptr;
     float *bl = nullptr, *qfac = nullptr, *kfac = nullptr, *lam = nullptr, *db = nullptr, *db2 = nullptr;
     float* xb = nullptr;    // [BH][chunks] backward: <R_m, S_{m+1}>, the pairs that straddle the end of chunk m (0 for the last)
 };
@@ -81,7 +86,8 @@ struct Ctx {
 // gating (family-independent kernels)
 size_t gate_workspace_bytes(const pa_problem& pr, bool backward);
 GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base);
-pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk);
+// in_blocks: bl and blk (chunk a multiple of GATE_BLOCK, or the whole sequence), else bl from the start of the chunk
+pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk, bool in_blocks);
 // The family has already written gate.xb, q.dq into gate.db and k.dk into gate.db2.
 // fin_chunk: the token granularity of gate.xb (the problem's chunk, or what the family says); xparts: terms that an entry of
 // gate.xb is kept in

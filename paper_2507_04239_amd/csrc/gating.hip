@@ -12,35 +12,66 @@ namespace {
 
 constexpr int GT = 256;
 
-// One workgroup per (chunk, head): inclusive running sum of the chunk's log-gates, then the factors.
-__global__ __launch_bounds__(GT) void k_gate_prep(const float* __restrict__ log_g, float* __restrict__ bl,
+// Log-gates below this are a factor of zero in float32 all the same; clamped to it, a gate that closes for good (the start of a
+// document: -1e4, or minus infinity) leaves the digits of the sums it goes into to the gates beside it.
+constexpr float GATE_FLOOR = -104.f;
+
+__device__ __forceinline__ double wave_scan(double x, int lane) {      // inclusive, over the wave
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double y = __shfl_up(x, off);
+        if (lane >= off) x += y;
+    }
+    return x;
+}
+
+// One workgroup per (chunk, head): running sums of the chunk's log-gates, then the factors.  A pair's decay is a difference of two
+// sums, so a sum kept in one float32 from a distant start loses what the pair's own gates contribute: at 5120 tokens of mean
+// -0.02 the decays are off by 5e-5, with a gate of -1e4 every 300 tokens by 9e-2.  So sums run in float64 and are kept
+// relative to blocks of GATE_BLOCK tokens, as decays from blocks this short are when nothing is added to them.
+// A wave scans a block, two tokens per lane; one wave adds the blocks up.
+__global__ __launch_bounds__(GT) void k_gate_prep(const float* __restrict__ log_g, float* __restrict__ bl, double* __restrict__ blk,
                                                   float* __restrict__ qfac, float* __restrict__ kfac,
-                                                  float* __restrict__ lam, int T, int chunk) {
-    __shared__ float part[GT];
-    const int n = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
+                                                  float* __restrict__ lam, int T, int chunk, int head_blocks, int in_blocks) {
+    __shared__ double total_s;
+    const int n = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const size_t base = (size_t)bh * T + (size_t)n * chunk;
     const int len = min(chunk, T - n * chunk);    // (the last chunk may be shorter)
-    const int per = (len + GT - 1) / GT;          // consecutive tokens per thread
-    const int lo = min(tid * per, len), hi = min(lo + per, len);
-    float s = 0.f;
-    for (int i = lo; i < hi; ++i) s += log_g[base + i];
-    part[tid] = s;
+    const int nblk = (len + GATE_BLOCK - 1) / GATE_BLOCK, per = (chunk + GATE_BLOCK - 1) / GATE_BLOCK;
+    double* sums = blk + (size_t)bh * head_blocks + (size_t)n * per;
+    static_assert(GATE_BLOCK == 128, "two tokens per lane");
+    for (int b = w; b < nblk; b += GT / 64) {
+        const int i = b * GATE_BLOCK + 2 * lane;
+        float g0 = i < len ? log_g[base + i] : 0.f, g1 = i + 1 < len ? log_g[base + i + 1] : 0.f;
+        g0 = g0 < GATE_FLOOR ? GATE_FLOOR : g0;   // (a NaN stays one)
+        g1 = g1 < GATE_FLOOR ? GATE_FLOOR : g1;
+        const double incl = wave_scan((double)g0 + (double)g1, lane);
+        const double excl = __shfl_up(incl, 1);
+        if (i < len) bl[base + i] = (float)((lane > 0 ? excl : 0.) + g0);
+        if (i + 1 < len) bl[base + i + 1] = (float)incl;
+        if (lane == 63) sums[b] = incl;
+    }
     __syncthreads();
-    for (int off = 1; off < GT; off <<= 1) {      // inclusive scan of the per-thread sums
-        float add = tid >= off ? part[tid - off] : 0.f;
-        __syncthreads();
-        part[tid] += add;
-        __syncthreads();
+    if (w == 0) {
+        double before = 0.;
+        for (int b0 = 0; b0 < nblk; b0 += 64) {
+            const double s = b0 + lane < nblk ? sums[b0 + lane] : 0., incl = wave_scan(s, lane);
+            if (b0 + lane < nblk) sums[b0 + lane] = before + (incl - s);
+            before += __shfl(incl, 63);
+        }
+        if (lane == 0) {
+            total_s = before;
+            lam[(size_t)bh * gridDim.x + n] = __expf((float)before);
+        }
     }
-    const float total = part[GT - 1];
-    float run = tid > 0 ? part[tid - 1] : 0.f;
-    for (int i = lo; i < hi; ++i) {
-        run += log_g[base + i];
-        bl[base + i] = run;
-        qfac[base + i] = __expf(run);
-        kfac[base + i] = __expf(total - run);
+    __syncthreads();
+    const double total = total_s;
+    for (int i = tid; i < len; i += GT) {
+        const double run = sums[i / GATE_BLOCK] + bl[base + i];
+        if (!in_blocks) bl[base + i] = (float)run;
+        qfac[base + i] = __expf((float)run);
+        kfac[base + i] = __expf((float)(total - run));
     }
-    if (tid == 0) lam[(size_t)bh * gridDim.x + n] = __expf(total);
 }
 
 // dlog_g[t] = sum_{i >= t} dL/db_i.  A running sum over the whole sequence would pile up the
@@ -91,11 +122,18 @@ static size_t chunk_slots(const pa_problem& pr) {
     return a > b ? a : b;
 }
 
+// blocks of GATE_BLOCK tokens per head: every chunk starts one
+static size_t blocks_of(int T, int chunk) { return (size_t)((T + chunk - 1) / chunk) * ((chunk + GATE_BLOCK - 1) / GATE_BLOCK); }
+static size_t blk_bytes(const pa_problem& pr) {
+    const size_t a = blocks_of(pr.T, pr.chunk), b = blocks_of(pr.T, GATE_BLOCK);      // (b: see gate_prepare)
+    return align_up((size_t)pr.B * pr.H * (a > b ? a : b) * sizeof(double), 256);
+}
+
 size_t gate_workspace_bytes(const pa_problem& pr, bool backward) {
     if (!pr.gated) return 0;
     const size_t BH = (size_t)pr.B * pr.H;
     const size_t tok = align_up(BH * pr.T * sizeof(float), 256);
-    return (backward ? 5 : 3) * tok + (backward ? 2 : 1) * align_up(BH * chunk_slots(pr) * sizeof(float), 256);
+    return blk_bytes(pr) + (backward ? 5 : 3) * tok + (backward ? 2 : 1) * align_up(BH * chunk_slots(pr) * sizeof(float), 256);
 }
 
 GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base) {
@@ -103,6 +141,8 @@ GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base) {
     if (!pr.gated) return g;
     const size_t BH = (size_t)pr.B * pr.H;
     const size_t tok = align_up(BH * pr.T * sizeof(float), 256);
+    g.blk = (double*)base;
+    base += blk_bytes(pr);
     g.bl = (float*)base;
     g.qfac = (float*)(base + tok);
     g.kfac = (float*)(base + 2 * tok);
@@ -115,11 +155,13 @@ GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base) {
     return g;
 }
 
-pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk) {
+pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk, bool in_blocks) {
     const pa_problem& pr = c.prob;
+    if (in_blocks && chunk != pr.T && chunk % GATE_BLOCK != 0) return PA_ERR_UNSUPPORTED;
+    const int head_blocks = (int)(in_blocks ? blocks_of(pr.T, GATE_BLOCK) : blocks_of(pr.T, chunk));   // in blocks: block t / GATE_BLOCK of a head
     LaunchScope ls("gate_prep", c.stream);
-    hipLaunchKernelGGL(k_gate_prep, dim3((pr.T + chunk - 1) / chunk, pr.B * pr.H), dim3(GT), 0, c.stream, log_g, c.gate.bl, c.gate.qfac,
-                       c.gate.kfac, c.gate.lam, pr.T, chunk);
+    hipLaunchKernelGGL(k_gate_prep, dim3((pr.T + chunk - 1) / chunk, pr.B * pr.H), dim3(GT), 0, c.stream, log_g, c.gate.bl, c.gate.blk,
+                       c.gate.qfac, c.gate.kfac, c.gate.lam, pr.T, chunk, head_blocks, in_blocks ? 1 : 0);
     return launch_ok() ? PA_OK : PA_ERR_HIP;
 }
 

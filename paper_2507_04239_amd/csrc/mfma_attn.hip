@@ -194,10 +194,17 @@ __device__ __forceinline__ void add_parts(f32x16& acc, const float* part, size_t
 // For a tile whose every pair is below the diagonal the factor is split at a reference m inside the
 // gap between the two sides, exp(b_i - m) exp(m - b_j), both <= 1: one of them is staged with the tile
 // (GateTile::f, per streamed row), the other is formed once per tile for the rows a lane owns.  Tiles
-// on the diagonal use the difference itself (GateTile::b), where a split could overflow.
+// on the diagonal use the difference itself (GateTile::b), where a split could overflow.  Sums are relative to blocks of
+// GATE_BLOCK tokens, which a tile and a wave's rows never straddle: the factor formed once per tile takes in what lies between
+// the two blocks, in float64.
+static_assert(GATE_BLOCK % AT == 0, "a tile lies in one block, and so do the 32 or 64 rows of a wave");
 struct GateTile {
     float b[AT], f[AT];
 };
+// exp(b_i - b_j) from sums relative to the blocks at i and j
+__device__ __forceinline__ float gate_factor(double blk_i, float b_i, double blk_j, float b_j) {
+    return __expf((float)((blk_i - blk_j) + ((double)b_i - (double)b_j)));
+}
 // streamed rows row0 .. row0 + 63 of one head; m_row: the row whose b is the reference;
 // sign = +1: f = exp(m - b) (streamed keys), -1: f = exp(b - m) (streamed queries)
 __device__ __forceinline__ void gate_tile_load(float& b, float& f, const float* __restrict__ bl_head, int row0, int m_row,
@@ -259,7 +266,7 @@ template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
 __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                        const bf16_t* __restrict__ V, bf16_t* __restrict__ O,
                                                        float* __restrict__ Z, int BH, Order order, int T, ScaleParts scale, int normalize,
-                                                       const float* __restrict__ bl, ChunkedIn ck) {
+                                                       GateSums sums, ChunkedIn ck) {
     constexpr int NI = OWN / 32, NK = HD / 16, NV = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
     AttnTile<HD>* kt = reinterpret_cast<AttnTile<HD>*>(attn_smem);      // [2]
@@ -289,19 +296,22 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
 #pragma unroll
         for (int vb = 0; vb < NV; ++vb) acc[vb][ib] = splat16(0.f);
     }
-    const float* bl_head = GATED ? bl + head : nullptr;
+    const float* bl_head = GATED ? sums.bl + head : nullptr;
+    const double* blk_head = GATED ? sums.blk + (size_t)at.head * ((T + GATE_BLOCK - 1) / GATE_BLOCK) : nullptr;
+    const double qblk = GATED ? blk_head[__builtin_amdgcn_readfirstlane(min(q0, T - 1) / GATE_BLOCK)] : 0.;
     float bq[NI];
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) bq[ib] = GATED ? bl_head[min(q0 + 32 * ib + r32, T - 1)] : 0.f;
 
     // one 64-key tile; DIAG: some pair of the tile lies above the diagonal and has to be masked
+    double tblk = 0., tblk_next = 0.;      // of the tile's block, and the next tile's
     auto tile = [&](auto diag_c, int buf, int key0) {
         constexpr bool DIAG = decltype(diag_c)::value;
         float fq[NI];
         if (GATED && !DIAG) {
             const float m = gtile[buf].b[AT - 1];          // the tile's last key
 #pragma unroll
-            for (int ib = 0; ib < NI; ++ib) fq[ib] = __expf(bq[ib] - m);
+            for (int ib = 0; ib < NI; ++ib) fq[ib] = gate_factor(qblk, bq[ib], tblk, m);
         }
         f32x16 c[2][NI];        // S^T: key 32 kb + 8 k + 4 h + r, query 32 ib + r32
         auto scores = [&](int kb) {
@@ -355,6 +365,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     float gb = 0.f, gf = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
+    if (GATED) tblk = blk_head[t_lo * AT / GATE_BLOCK];
     if (GATED) gate_tile_load(gb, gf, bl_head, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
@@ -362,6 +373,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     __syncthreads();
     for (int t = t_lo; t < ntile; ++t) {
         const int buf = (t - t_lo) & 1, key0 = t * AT;
+        if (GATED) tblk_next = blk_head[min(key0 + AT, T - 1) / GATE_BLOCK];
         if (t + 1 < ntile) {
             PA_TILE_LOAD(kr, Kh, key0 + AT, false)
             PA_TILE_LOAD(vr, Vh, key0 + AT, false)
@@ -376,6 +388,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
             PA_TILE_STORE(vt[buf ^ 1], vr)
             if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf, tid);
         }
+        tblk = tblk_next;
         __syncthreads();
     }
 
@@ -446,7 +459,7 @@ template <int P, int HD, int OWN, bool GATED, bool CHUNKED>
 __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                  const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                  const float* __restrict__ gz, bf16_t* __restrict__ dQ, int BH, int T,
-                                                 ScaleParts scale, const float* __restrict__ bl, float* __restrict__ qdq,
+                                                 ScaleParts scale, GateSums sums, float* __restrict__ qdq,
                                                  ChunkedIn ck) {
     constexpr int NI = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
@@ -479,10 +492,12 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
         for (int fb = 0; fb < NF; ++fb) acc[fb][ib] = splat16(0.f);
     }
 
-    const float* bl_head = GATED ? bl + head : nullptr;
+    const float* bl_head = GATED ? sums.bl + head : nullptr;
+    const double* blk_head = GATED ? sums.blk + (size_t)at.head * ((T + GATE_BLOCK - 1) / GATE_BLOCK) : nullptr;
     // gated: rsum = sum_j e_ij c_ij^p = q_i . dq_i / (p rest^p), the row's share of the gate gradient, summed
     // here from the unrounded terms (the dot product of the stored dq with q carries bf16 noise that a
     // sum over a block of tokens amplifies)
+    const double qblk = GATED ? blk_head[__builtin_amdgcn_readfirstlane(min(q0, T - 1) / GATE_BLOCK)] : 0.;
     float bq[NI], rsum[NI];
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
@@ -490,13 +505,14 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
         rsum[ib] = 0.f;
     }
 
+    double tblk = 0., tblk_next = 0.;      // of the tile's block, and the next tile's
     auto tile = [&](auto diag_c, int buf, int key0) {
         constexpr bool DIAG = decltype(diag_c)::value;
         float fq[NI];
         if (GATED && !DIAG) {
             const float m = gtile[buf].b[AT - 1];          // the tile's last key
 #pragma unroll
-            for (int ib = 0; ib < NI; ++ib) fq[ib] = __expf(bq[ib] - m);
+            for (int ib = 0; ib < NI; ++ib) fq[ib] = gate_factor(qblk, bq[ib], tblk, m);
         }
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
@@ -547,6 +563,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
     float gb = 0.f, gf2 = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
+    if (GATED) tblk = blk_head[t_lo * AT / GATE_BLOCK];
     if (GATED) gate_tile_load(gb, gf2, bl_head, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
@@ -554,6 +571,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
     __syncthreads();
     for (int t = t_lo; t < ntile; ++t) {
         const int buf = (t - t_lo) & 1, key0 = t * AT;
+        if (GATED) tblk_next = blk_head[min(key0 + AT, T - 1) / GATE_BLOCK];
         if (t + 1 < ntile) {
             PA_TILE_LOAD(kr, Kh, key0 + AT, false)
             PA_TILE_LOAD(vr, Vh, key0 + AT, false)
@@ -568,6 +586,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
             PA_TILE_STORE(vt[buf ^ 1], vr)
             if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf2, tid);
         }
+        tblk = tblk_next;
         __syncthreads();
     }
 
@@ -602,7 +621,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
                                                    const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                    const float* __restrict__ gz, bf16_t* __restrict__ dK,
                                                    bf16_t* __restrict__ dV, int BH, int T, ScaleParts scale,
-                                                   const float* __restrict__ bl, float* __restrict__ kdk,
+                                                   GateSums sums, float* __restrict__ kdk,
                                                    float* __restrict__ wsum, ChunkedIn ck) {
     constexpr int NJ = OWN / 32, NK = HD / 16, NF = HD / 32, WG = 4 * OWN;
     extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
@@ -638,9 +657,11 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
         }
     }
 
-    const float* bl_head = GATED ? bl + head : nullptr;
+    const float* bl_head = GATED ? sums.bl + head : nullptr;
+    const double* blk_head = GATED ? sums.blk + (size_t)at.head * ((T + GATE_BLOCK - 1) / GATE_BLOCK) : nullptr;
     // gated: csum = sum_i e_ij a_ij = k_j . dk_j / (p rest^p), the key's share of the gate gradient, from the
     // unrounded weights
+    const double kblk = GATED ? blk_head[__builtin_amdgcn_readfirstlane(min(k0, T - 1) / GATE_BLOCK)] : 0.;
     float bk[NJ], csum[NJ];
 #pragma unroll
     for (int kb = 0; kb < NJ; ++kb) {
@@ -649,13 +670,14 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     }
 
     float wprev = 0.f;   // the wave's total of csum at the end of the last complete block of queries
+    double tblk = 0., tblk_next = 0.;
     auto tile = [&](auto diag_c, int buf, int q0) {
         constexpr bool DIAG = decltype(diag_c)::value;
         float fk[NJ];
         if (GATED && !DIAG) {
             const float m = gtile[buf].b[0];               // the tile's first query
 #pragma unroll
-            for (int kb = 0; kb < NJ; ++kb) fk[kb] = __expf(m - bk[kb]);
+            for (int kb = 0; kb < NJ; ++kb) fk[kb] = gate_factor(tblk, m, kblk, bk[kb]);
         }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
@@ -718,6 +740,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     PA_TILE_LOAD(qr, Qh, t_first * AT, false)
     PA_TILE_LOAD(gr, Gh_h, t_first * AT, true)
     if (tid < AT) gzr = t_first * AT + tid < T ? gzh[t_first * AT + tid] : 0.f;
+    if (GATED) tblk = blk_head[t_first * AT / GATE_BLOCK];
     if (GATED) gate_tile_load(gb, gf2, bl_head, t_first * AT, t_first * AT, -1.f, tid, T);
     PA_TILE_STORE(qt[0], qr)
     PA_TILE_STORE(gt[0], gr)
@@ -726,6 +749,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     __syncthreads();
     for (int t = t_first; t < ntile; ++t) {
         const int buf = (t - t_first) & 1, q0 = t * AT;
+        if (GATED) tblk_next = blk_head[min(q0 + AT, T - 1) / GATE_BLOCK];
         if (t + 1 < ntile) {
             PA_TILE_LOAD(qr, Qh, q0 + AT, false)
             PA_TILE_LOAD(gr, Gh_h, q0 + AT, true)
@@ -755,6 +779,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
             if (tid < AT) gzt[buf ^ 1][tid] = gzr;
             if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf2, tid);
         }
+        tblk = tblk_next;
         __syncthreads();
     }
 
@@ -796,7 +821,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_bwd(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ V, const bf16_t* __restrict__ Gh,
                                                        const float* __restrict__ gz, bf16_t* __restrict__ dQ,
                                                        bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int BH, Order order,
-                                                       int T, ScaleParts scale, const float* __restrict__ bl, float* __restrict__ qdq,
+                                                       int T, ScaleParts scale, GateSums sums, float* __restrict__ qdq,
                                                        float* __restrict__ kdk, float* __restrict__ wsum, ChunkedIn ckq,
                                                        ChunkedIn ckk) {
     Place at = place(order);
@@ -804,9 +829,9 @@ __global__ __launch_bounds__(256, WPE) void k_attn_bwd(const bf16_t* __restrict_
     if (WHAT == Bwd::both) at.rank >>= 1;
     if (at.rank >= (T + 4 * OWN - 1) / (4 * OWN) || at.head >= BH) return;
     if (dq)
-        dq_block<P, HD, OWN, GATED, CHUNKED>(at, Q, K, V, Gh, gz, dQ, BH, T, scale, bl, qdq, ckq);
+        dq_block<P, HD, OWN, GATED, CHUNKED>(at, Q, K, V, Gh, gz, dQ, BH, T, scale, sums, qdq, ckq);
     else
-        dkdv_block<P, HD, OWN, GATED, CHUNKED>(at, Q, K, V, Gh, gz, dK, dV, BH, T, scale, bl, kdk, wsum, ckk);
+        dkdv_block<P, HD, OWN, GATED, CHUNKED>(at, Q, K, V, Gh, gz, dK, dV, BH, T, scale, sums, kdk, wsum, ckk);
 }
 
 template <int HD>
@@ -887,7 +912,7 @@ int head_group(int BH, int T, const ChunkedIn& ck) {
 bool fwd_wide(int BH, int T) { return T >= 2048 && (long long)BH * ((T + 255) / 256) >= 1024; }
 template <int P, int HD, bool GATED, bool CHUNKED, int OWN>
 bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
-             int normalize, const float* bl, ChunkedIn ck) {
+             int normalize, GateSums sums, ChunkedIn ck) {
     constexpr int WG = 4 * OWN;
     auto kern = k_attn_fwd<P, HD, OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
@@ -895,22 +920,21 @@ bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, b
     Order order{head_group<HD, CHUNKED, WG>(BH, T, ck)};
     const dim3 grid = block_grid(BH, (T + WG - 1) / WG, order);
     hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, BH, order, T,
-                       split_scale(scale), normalize, bl, ck);
+                       split_scale(scale), normalize, sums, ck);
     return launch_ok();
 }
 template <int P, int HD, bool GATED, bool CHUNKED = false>
 bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
-           int normalize, const float* bl, ChunkedIn ck = ChunkedIn(), const char* name = "attn_fwd") {
+           int normalize, GateSums sums, ChunkedIn ck = ChunkedIn(), const char* name = "attn_fwd") {
     if constexpr (HD == 64 && !CHUNKED)
-        if (fwd_wide(BH, T)) return fwd_own<P, HD, GATED, CHUNKED, 64>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
-    return fwd_own<P, HD, GATED, CHUNKED, Shape<HD>::FWD_OWN>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
+        if (fwd_wide(BH, T)) return fwd_own<P, HD, GATED, CHUNKED, 64>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck);
+    return fwd_own<P, HD, GATED, CHUNKED, Shape<HD>::FWD_OWN>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck);
 }
 
 template <int P, int HD, bool GATED, bool CHUNKED = false>
 bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* O, const float* Z, const bf16_t* dO,
            bf16_t* Gh, float* gz, bf16_t* dQ, bf16_t* dK, bf16_t* dV, int BH, int T, float scale, int normalize,
            const AttnGate& gate, ChunkedIn ckq = ChunkedIn(), ChunkedIn ckk = ChunkedIn()) {
-    const float* bl = gate.bl;
     const long long rows = (long long)BH * T;
     if (!CHUNKED) {
         constexpr int RPB = 256 / (HD / 4);
@@ -931,7 +955,7 @@ bool bwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, con
         Order order{head_group<HD, CHUNKED, WG>(BH, T, ckq)};
         const dim3 grid = block_grid(BH, wgs, order);
         hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, Gh, gz, dQ, dK, dV, BH, order, T,
-                           split_scale(scale), bl, gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
+                           split_scale(scale), gate.sums, gate.qdq, gate.kdk, gate.wsum, ckq, ckk);
         return launch_ok();
     };
     // One launch holds every wave to the registers of the larger half (d = 64: two waves of dQ per SIMD instead of three), which
@@ -964,11 +988,11 @@ int attn_gate_block(int d) { return 4 * (d == 128 ? Shape<128>::DKDV_OWN : d == 
 bool attn_shape_ok(int p, int d) { return (p == 2 || p == 3 || p == 4) && (d == 32 || d == 64 || d == 128); }
 
 bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
-                     int T, float scale, int normalize, const float* bl) {
+                     int T, float scale, int normalize, GateSums sums) {
 #define PA_CASE(PP, DD)                                                                                      \
     if (p == PP && d == DD)                                                                                  \
-        return bl != nullptr ? fwd_t<PP, DD, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl)            \
-                             : fwd_t<PP, DD, false>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl);
+        return sums.bl != nullptr ? fwd_t<PP, DD, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums)            \
+                             : fwd_t<PP, DD, false>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums);
     PA_CASE(2, 32) PA_CASE(2, 64) PA_CASE(2, 128)
     PA_CASE(3, 32) PA_CASE(3, 64) PA_CASE(3, 128)
     PA_CASE(4, 32) PA_CASE(4, 64) PA_CASE(4, 128)
@@ -978,7 +1002,7 @@ bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t*
 
 bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
                       int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart, const char* label,
-                      const float* bl) {
+                      GateSums sums) {
     ChunkedIn ck;
     ck.label = label;
     ck.cs = cs;
@@ -986,9 +1010,9 @@ bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t
     ck.part = part;
     ck.zpart = zpart;
     if (cs % AT != 0) return false;
-    if (bl != nullptr) return p == 2 && d == 64 && fwd_t<2, 64, true, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, bl, ck);
+    if (sums.bl != nullptr) return p == 2 && d == 64 && fwd_t<2, 64, true, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck);
 #define PA_CASE(PP, DD) \
-    if (p == PP && d == DD) return fwd_t<PP, DD, false, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, nullptr, ck);
+    if (p == PP && d == DD) return fwd_t<PP, DD, false, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, GateSums(), ck);
     PA_CASE(2, 32) PA_CASE(2, 64) PA_CASE(2, 128)
     PA_CASE(3, 32) PA_CASE(3, 64)
     PA_CASE(4, 32)
@@ -1025,7 +1049,7 @@ bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t
     ckq.dot = dotq;
     ckk.dot = dotk;
     if (cs % AT != 0) return false;
-    if (gate.bl != nullptr)
+    if (gate.sums.bl != nullptr)
         return p == 2 && d == 64 &&
                bwd_t<2, 64, true, true>(s, Q, K, V, nullptr, nullptr, nullptr, const_cast<bf16_t*>(Gh), const_cast<float*>(gz), dQ, dK, dV, BH, T,
                                         scale, 1, gate, ckq, ckk);
@@ -1044,7 +1068,7 @@ bool launch_attn_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t*
                      float scale, int normalize, const AttnGate& gate) {
 #define PA_CASE(PP, DD)                                                                                                          \
     if (p == PP && d == DD)                                                                                                      \
-        return gate.bl != nullptr ? bwd_t<PP, DD, true>(s, Q, K, V, O, Z, dO, Gh, gz, dQ, dK, dV, BH, T, scale, normalize, gate) \
+        return gate.sums.bl != nullptr ? bwd_t<PP, DD, true>(s, Q, K, V, O, Z, dO, Gh, gz, dQ, dK, dV, BH, T, scale, normalize, gate) \
                                   : bwd_t<PP, DD, false>(s, Q, K, V, O, Z, dO, Gh, gz, dQ, dK, dV, BH, T, scale, normalize, gate);
     PA_CASE(2, 32) PA_CASE(2, 64) PA_CASE(2, 128)
     PA_CASE(3, 32) PA_CASE(3, 64) PA_CASE(3, 128)

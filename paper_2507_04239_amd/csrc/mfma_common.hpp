@@ -207,33 +207,38 @@ constexpr int QUAD_XPARTS = 8;
 bool launch_quad_boundary(hipStream_t s, const QuadPlan& p, const bf16_t* st, const bf16_t* rc, const bf16_t* gam, const bf16_t* omg,
                           float* xb, int BH);
 
+// running sums of the log-gates as the attention kernels read them (see GateBuf; null: no gates)
+struct GateSums {
+    const float* bl = nullptr;
+    const double* blk = nullptr;
+};
 // attention form (chunk == T): p in {2, 3, 4}, d = v in {32, 64, 128}, any T.
 // Gh [BH][T][d] bf16 and gz [BH][T] float32 are scratch of the backward pass.
 bool attn_shape_ok(int p, int d);
 // bl (null when not gated): [BH][T] running sums of the log-gates from the start of the sequence
 bool launch_attn_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
-                     int T, float scale, int normalize, const float* bl = nullptr);
+                     int T, float scale, int normalize, GateSums sums = GateSums());
 // The in-chunk part of the chunked form on the attention-form kernels (keys of the query's own chunk of cs
 // tokens), plus what came through the state: part[slab][BH][T][d] (float32, nslab slabs) joins the numerator,
 // zpart[BH][T] the denominator
 bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH,
                       int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart,
-                      const char* label = "chunk_fwd", const float* bl = nullptr);
+                      const char* label = "chunk_fwd", GateSums sums = GateSums());
 // ghat = dO / Z (bf16) and gz = -(ghat . O) (float32) per token, d in {32, 64, 128}
 bool launch_attn_prep(hipStream_t s, int d, const bf16_t* dO, const bf16_t* O, const float* Z, bf16_t* Gh, float* gz, long long rows,
                       int normalize);
-// Gated backward pass (bl non-null; T a multiple of attn_gate_block(d)): also leaves what the gradient of
+// Gated backward pass (sums non-null; T a multiple of attn_gate_block(d)): also leaves what the gradient of
 // the log-gates needs: qdq [BH][T] = q_i . dq_i, kdk [BH][T] = k_j . dk_j (from float32 accumulators) and
 // xb [BH][T / block] = the sum of e_ij a_ij over the pairs j <= end of block m < i.
 // wsum: scratch, BH * (T / block)^2 * 4 floats.
 struct AttnGate {
-    const float* bl = nullptr;
+    GateSums sums;
     float *qdq = nullptr, *kdk = nullptr, *xb = nullptr, *wsum = nullptr;
 };
 int attn_gate_block(int d);
 // backward of launch_chunk_fwd: the in-chunk gradients plus the per-slab parts that came through the states (float32
-// [slab][BH][T][d]; the slab counts include the normaliser's slab where there is one).  Gated (p = 2, d = 64): gate.bl, running
-// sums from the start of the chunk, gate.qdq and gate.kdk, to which the states' parts dotq and dotk [BH][T] are added.
+// [slab][BH][T][d]; the slab counts include the normaliser's slab where there is one).  Gated (p = 2, d = 64): gate.sums
+// from the start of the chunk, gate.qdq and gate.kdk, to which the states' parts dotq and dotk [BH][T] are added.
 bool launch_chunk_bwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* Gh,
                       const float* gz, bf16_t* dQ, bf16_t* dK, bf16_t* dV, int BH, int T, int cs, float scale, const float* part_dq,
                       int nslab_dq, const float* part_dk, int nslab_dk, const float* part_dv, int nslab_dv,

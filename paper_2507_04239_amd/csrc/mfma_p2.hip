@@ -263,7 +263,7 @@ pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, vo
     const int BH = pr.B * pr.H;
     if (use_attn(pr, false)) {
         PA_TRY(launch_attn_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH, pr.T,
-                               pr.scale, pr.normalize, c.gate.bl))
+                               pr.scale, pr.normalize, GateSums{c.gate.bl, c.gate.blk}))
         return PA_OK;
     }
     if (use_quad(pr)) {
@@ -276,7 +276,7 @@ pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, vo
         PA_TRY(launch_quad_read("mfma_query_state", c.stream, L.pl, false, (const bf16_t*)Q, st, gam, part, zpart, BH, pr.T, pr.scale,
                                 c.gate.qfac))
         PA_TRY(launch_chunk_fwd(c.stream, pr.p, pr.d, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, Z, BH, pr.T,
-                                L.pl.cs, pr.scale, pr.normalize, part, 1, zpart, "mfma_fwd_chunk", c.gate.bl))
+                                L.pl.cs, pr.scale, pr.normalize, part, 1, zpart, "mfma_fwd_chunk", GateSums{c.gate.bl, c.gate.blk}))
         return PA_OK;
     }
     if (use_tiled(pr)) {
@@ -367,7 +367,7 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
         const AttnLayout A = make_attn_layout(pr, true);
         AttnGate ag;
         if (pr.gated) {
-            ag.bl = c.gate.bl;       // with chunk == T: running sums from the start of the sequence
+            ag.sums = GateSums{c.gate.bl, c.gate.blk};
             ag.qdq = c.gate.db;
             ag.kdk = c.gate.db2;
             ag.xb = c.gate.xb;
@@ -410,7 +410,7 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
         }
         if (side.ok && (hipEventRecord(side.join, s2) != hipSuccess || hipStreamWaitEvent(s, side.join, 0) != hipSuccess)) return PA_ERR_HIP;
         AttnGate ag;
-        ag.bl = gt.bl;
+        ag.sums = GateSums{gt.bl, gt.blk};
         ag.qdq = gt.db;
         ag.kdk = gt.db2;
         PA_TRY(launch_chunk_bwd(s, pr.p, pr.d, q, k, v, Gh, gz, (bf16_t*)dQ, (bf16_t*)dK, (bf16_t*)dV, BH, pr.T, L.pl.cs, pr.scale, pdq,
@@ -539,7 +539,7 @@ pa_status mfma_absorb(const pa_problem& pr, const void* K, const void* V, const 
         gp.chunk = pr.T;
         gp.gated = 1;
         Ctx c{gp, s, ws, L.total, gate_buffers(gp, false, ws + L.off_gate)};
-        pa_status st = gate_prepare(c, log_g, pr.T);
+        pa_status st = gate_prepare(c, log_g, pr.T, true);
         if (st != PA_OK) return st;
         kfac = c.gate.kfac;
         lam = c.gate.lam;

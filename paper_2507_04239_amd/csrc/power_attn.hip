@@ -233,7 +233,7 @@ pa_status run_fwd(const pa_problem* prob, const void* Q, const void* K, const vo
     }
     Ctx c{*prob, s, (char*)workspace, workspace_bytes, gate_buffers(*prob, false, (char*)workspace + fam)};
     if (gated) {
-        st = gate_prepare(c, log_g, impl == PA_IMPL_MFMA ? mfma_gate_chunk(*prob, false) : prob->chunk);
+        st = gate_prepare(c, log_g, impl == PA_IMPL_MFMA ? mfma_gate_chunk(*prob, false) : prob->chunk, impl == PA_IMPL_MFMA);
         if (st != PA_OK) return st;
     }
     st = impl == PA_IMPL_MFMA ? mfma_fwd(c, Q, K, V, O, Z) : generic_fwd(c, Q, K, V, O, Z);
@@ -304,7 +304,7 @@ pa_status run_bwd(const pa_problem* prob, const void* Q, const void* K, const vo
     Ctx c{*prob, s, (char*)workspace, workspace_bytes, gate_buffers(*prob, true, (char*)workspace + fam)};
     if (gated) {
         // the factors are rebuilt here: the forward pass keeps its own copy only inside its workspace
-        st = gate_prepare(c, log_g, impl == PA_IMPL_MFMA ? mfma_gate_chunk(*prob, true) : prob->chunk);
+        st = gate_prepare(c, log_g, impl == PA_IMPL_MFMA ? mfma_gate_chunk(*prob, true) : prob->chunk, impl == PA_IMPL_MFMA);
         if (st != PA_OK) return st;
     }
     st = impl == PA_IMPL_MFMA ? mfma_bwd(c, Q, K, V, O, Z, dO, dQ, dK, dV) : generic_bwd(c, Q, K, V, O, Z, dO, dQ, dK, dV);

@@ -71,3 +71,46 @@ def test_gated_and_ungated_entry_points_refuse_each_other():
     assert st == 1   # PA_ERR_INVALID_ARG: a gated problem through the un-gated call
     st = lib.power_attn_fwd_gated(ctypes.byref(prob), vp(x), vp(x), vp(x), None, vp(x), vp(z), vp(ws), ws.numel(), None)
     assert st == 1   # log_g missing
+
+
+STRONG = [
+    # T, chunk, strong gate, every so many tokens (chunk 0: the attention form)
+    (2048, 0, -1e4, 300),
+    (5120, 128, -1e4, 300),
+    (5632, 256, float("-inf"), 300),      # the longest sequence that runs whole ...
+    (5633, 128, -1e5, 300),               # ... and the shortest with states, ragged
+    (7680, 256, float("-inf"), 1280),     # at the first token of every chunk of the states
+    (6500, 384, -1e3, 37),
+    (5120, 128, 0.0, 300),                # weak gates alone
+]
+
+
+@pytest.mark.parametrize("T,chunk,strong,every", STRONG)
+def test_strong_gates_leave_the_decays_beside_them_exact(T, chunk, strong, every):
+    """Gates that close for good (the start of a document), down to minus infinity, among weak ones.  q = k = one unit vector, so that
+    a weight is its decay alone and O, Z, dV are sums of decays: each is rounded to bf16 once, and once more in a state of bf16."""
+    import torch
+    print(f"T={T} chunk={chunk} strong={strong} every={every}", flush=True)
+    rng = np.random.default_rng(T)
+    Q = np.zeros((1, 2, T, 64), dtype=np.float32)
+    Q[..., 0] = 1.0
+    V, G = (torch.from_numpy(rng.standard_normal((1, 2, T, 64), dtype=np.float32)).bfloat16().float().numpy() for _ in range(2))
+    lg = (-0.02 * rng.standard_exponential((1, 2, T))).astype(np.float32)
+    if strong < 0:
+        lg[:, :, every::every] = strong
+    got = run_fwd_bwd(Q, Q, V, G, 2, chunk or T, "bf16", normalize=False, log_g=lg)
+    i = torch.arange(T, device="cuda:0")
+    for h in range(2):
+        b = torch.cumsum(torch.from_numpy(np.maximum(lg[0, h], -1e4)).to("cuda:0", torch.float64), 0)
+        w = torch.where(i[:, None] >= i[None, :], torch.exp((b[:, None] - b[None, :]).clamp(max=0.0)), 0.0)
+        v, g = (torch.from_numpy(a[0, h]).to("cuda:0", torch.float64) for a in (V, G))
+        wt = w.t().contiguous()
+        want = {"O": (w @ v, w @ v.abs()), "Z": (w.sum(1), w.sum(1)), "dV": (wt @ g, wt @ g.abs())}
+        for name, (x, size) in want.items():
+            err = (torch.from_numpy(got[name][0, h]).to("cuda:0", torch.float64) - x).abs()
+            tol = 2.0 ** -8 * size + (0.0 if name == "Z" else 2.0 ** -8) * x.abs() + 1e-4 * size     # (the last: float32 sums, exp)
+            worst = float((err / tol).max())
+            print(f"  head {h} {name}: {worst:.3f} of the bound", flush=True)
+            assert worst <= 1.0, f"{name} head {h}: {worst} of the bound"
+    for name in ("dQ", "dK", "dlog_g"):
+        assert np.isfinite(got[name]).all(), name
