@@ -16,12 +16,25 @@ constexpr int GT = 256;
 // document: -1e4, or minus infinity) leaves the digits of the sums it goes into to the gates beside it.
 constexpr float GATE_FLOOR = -104.f;
 
-__device__ __forceinline__ double wave_scan(double x, int lane) {      // inclusive, over the wave
+// the value of another lane of the wave by DPP; lanes without a source, or whose row of 16 is not in ROWS, get 0
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_move(double x) {
+    union {
+        double d;
+        int i[2];
+    } u, v;
+    u.d = x;
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
+    for (int k = 0; k < 2; ++k) v.i[k] = __builtin_amdgcn_update_dpp(0, u.i[k], CTRL, ROWS, 0xf, false);
+    return v.d;
+}
+__device__ __forceinline__ double wave_scan(double x) {      // inclusive, over the wave: in each row of 16 lanes, then across the rows
+    x += lane_move<0x111, 0xf>(x);
+    x += lane_move<0x112, 0xf>(x);
+    x += lane_move<0x114, 0xf>(x);
+    x += lane_move<0x118, 0xf>(x);
+    x += lane_move<0x142, 0xa>(x);      // lane 15 of rows 0 and 2 to the row after
+    x += lane_move<0x143, 0xc>(x);      // lane 31 to rows 2 and 3
     return x;
 }
 
@@ -29,48 +42,75 @@ __device__ __forceinline__ double wave_scan(double x, int lane) {      // inclus
 // sums, so a sum kept in one float32 from a distant start loses what the pair's own gates contribute: at 5120 tokens of mean
 // -0.02 the decays are off by 5e-5, with a gate of -1e4 every 300 tokens by 9e-2.  So sums run in float64 and are kept
 // relative to blocks of GATE_BLOCK tokens, as decays from blocks this short are when nothing is added to them.
-// A wave scans a block, two tokens per lane; one wave adds the blocks up.
+// A wave scans a block, two tokens per lane, and holds GB blocks at a time; the workgroup's blocks meet in LDS.
 __global__ __launch_bounds__(GT) void k_gate_prep(const float* __restrict__ log_g, float* __restrict__ bl, double* __restrict__ blk,
                                                   float* __restrict__ qfac, float* __restrict__ kfac,
                                                   float* __restrict__ lam, int T, int chunk, int head_blocks, int in_blocks) {
-    __shared__ double total_s;
+    constexpr int WAVES = GT / 64, GB = 4, STEP = WAVES * GB;
+    static_assert(GATE_BLOCK == 128, "two tokens per lane");
+    __shared__ double sums[2][STEP];
     const int n = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const size_t base = (size_t)bh * T + (size_t)n * chunk;
     const int len = min(chunk, T - n * chunk);    // (the last chunk may be shorter)
-    const int nblk = (len + GATE_BLOCK - 1) / GATE_BLOCK, per = (chunk + GATE_BLOCK - 1) / GATE_BLOCK;
-    double* sums = blk + (size_t)bh * head_blocks + (size_t)n * per;
-    static_assert(GATE_BLOCK == 128, "two tokens per lane");
-    for (int b = w; b < nblk; b += GT / 64) {
-        const int i = b * GATE_BLOCK + 2 * lane;
-        float g0 = i < len ? log_g[base + i] : 0.f, g1 = i + 1 < len ? log_g[base + i + 1] : 0.f;
-        g0 = g0 < GATE_FLOOR ? GATE_FLOOR : g0;   // (a NaN stays one)
-        g1 = g1 < GATE_FLOOR ? GATE_FLOOR : g1;
-        const double incl = wave_scan((double)g0 + (double)g1, lane);
-        const double excl = __shfl_up(incl, 1);
-        if (i < len) bl[base + i] = (float)((lane > 0 ? excl : 0.) + g0);
-        if (i + 1 < len) bl[base + i + 1] = (float)incl;
-        if (lane == 63) sums[b] = incl;
-    }
-    __syncthreads();
-    if (w == 0) {
-        double before = 0.;
-        for (int b0 = 0; b0 < nblk; b0 += 64) {
-            const double s = b0 + lane < nblk ? sums[b0 + lane] : 0., incl = wave_scan(s, lane);
-            if (b0 + lane < nblk) sums[b0 + lane] = before + (incl - s);
-            before += __shfl(incl, 63);
+    const int nblk = (len + GATE_BLOCK - 1) / GATE_BLOCK;
+    double* blk_out = blk + (size_t)bh * head_blocks + (size_t)n * ((chunk + GATE_BLOCK - 1) / GATE_BLOCK);
+    auto gate = [&](int i) {
+        const float g = i < len ? log_g[base + i] : 0.f;
+        return g < GATE_FLOOR ? GATE_FLOOR : g;   // (a NaN stays one)
+    };
+    float g[GB][2];
+    double incl[GB];
+    // the blocks b0 + WAVES u + w; their sums to sums[buf]
+    auto scan = [&](int b0, int buf) {
+#pragma unroll
+        for (int u = 0; u < GB; ++u) {
+            const int i = (b0 + WAVES * u + w) * GATE_BLOCK + 2 * lane;
+            g[u][0] = gate(i);
+            g[u][1] = gate(i + 1);
         }
-        if (lane == 0) {
-            total_s = before;
-            lam[(size_t)bh * gridDim.x + n] = __expf((float)before);
+#pragma unroll
+        for (int u = 0; u < GB; ++u) {
+            incl[u] = wave_scan((double)g[u][0] + (double)g[u][1]);
+            if (lane == 63) sums[buf][WAVES * u + w] = incl[u];
         }
+        __syncthreads();
+    };
+    double total = 0.;
+    int buf = 0;
+    for (int b0 = 0; b0 < nblk; b0 += STEP, buf ^= 1) {
+        scan(b0, buf);
+        for (int k = 0; k < min(STEP, nblk - b0); ++k) total += sums[buf][k];
     }
-    __syncthreads();
-    const double total = total_s;
-    for (int i = tid; i < len; i += GT) {
-        const double run = sums[i / GATE_BLOCK] + bl[base + i];
-        if (!in_blocks) bl[base + i] = (float)run;
-        qfac[base + i] = __expf((float)run);
-        kfac[base + i] = __expf((float)(total - run));
+    if (tid == 0) lam[(size_t)bh * gridDim.x + n] = __expf((float)total);
+    double before = 0.;
+    for (int b0 = 0; b0 < nblk; b0 += STEP, buf ^= 1) {
+        if (nblk > STEP) scan(b0, buf);           // (else the blocks are still here, and their sums in the other buffer)
+        const double* in = nblk > STEP ? sums[buf] : sums[buf ^ 1];
+        for (int k = 0; k < min(STEP, nblk - b0); ++k) {
+            const int u = k / WAVES;
+            if (k % WAVES == w) {
+                const int i = (b0 + k) * GATE_BLOCK + 2 * lane;
+                double x = 0., pair = 0.;
+#pragma unroll
+                for (int v = 0; v < GB; ++v)
+                    if (v == u) {
+                        x = lane_move<0x138, 0xf>(incl[v]) + (double)g[v][0];      // (from the lane before)
+                        pair = incl[v];
+                    }
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float rel = (float)(e == 0 ? x : pair);
+                    const double run = before + rel;
+                    if (i + e < len) {
+                        bl[base + i + e] = in_blocks ? rel : (float)run;
+                        qfac[base + i + e] = __expf((float)run);
+                        kfac[base + i + e] = __expf((float)(total - run));
+                    }
+                }
+                if (lane == 0) blk_out[b0 + k] = before;
+            }
+            before += in[k];
+        }
     }
 }
 

@@ -195,29 +195,31 @@ __device__ __forceinline__ void add_parts(f32x16& acc, const float* part, size_t
 // gap between the two sides, exp(b_i - m) exp(m - b_j), both <= 1: one of them is staged with the tile
 // (GateTile::f, per streamed row), the other is formed once per tile for the rows a lane owns.  Tiles
 // on the diagonal use the difference itself (GateTile::b), where a split could overflow.  Sums are relative to blocks of
-// GATE_BLOCK tokens, which a tile and a wave's rows never straddle: the factor formed once per tile takes in what lies between
-// the two blocks, in float64.
+// GATE_BLOCK tokens, which a tile and a wave's rows never straddle: the reference takes in what lies between the two blocks,
+// a difference in float64.
 static_assert(GATE_BLOCK % AT == 0, "a tile lies in one block, and so do the 32 or 64 rows of a wave");
-struct GateTile {
+struct alignas(16) GateTile {
     float b[AT], f[AT];
+    float m;        // the reference, from the start of the workgroup's first block
 };
-// exp(b_i - b_j) from sums relative to the blocks at i and j
-__device__ __forceinline__ float gate_factor(double blk_i, float b_i, double blk_j, float b_j) {
-    return __expf((float)((blk_i - blk_j) + ((double)b_i - (double)b_j)));
-}
-// streamed rows row0 .. row0 + 63 of one head; m_row: the row whose b is the reference;
+// streamed rows row0 .. row0 + 63 of one head; m_row: the row whose b is the reference; own: blk of the workgroup's first row;
 // sign = +1: f = exp(m - b) (streamed keys), -1: f = exp(b - m) (streamed queries)
-__device__ __forceinline__ void gate_tile_load(float& b, float& f, const float* __restrict__ bl_head, int row0, int m_row,
-                                               float sign, int tid, int T) {
+__device__ __forceinline__ void gate_tile_load(float& b, float& f, float& m, const float* __restrict__ bl_head,
+                                               const double* __restrict__ blk_head, double own, int row0, int m_row, float sign,
+                                               int tid, int T) {
     if (tid < AT) {
         b = bl_head[min(row0 + tid, T - 1)];
-        f = __expf(sign * (bl_head[min(m_row, T - 1)] - b));
+        m = bl_head[min(m_row, T - 1)];
+        f = __expf(sign * (m - b));
+        // (a vector load: a scalar one makes the tile's LDS reads wait for it, 2 % of the kernel)
+        m += (float)(blk_head[min(row0 + tid, T - 1) / GATE_BLOCK] - own);
     }
 }
-__device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, int tid) {
+__device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, float m, int tid) {
     if (tid < AT) {
         t.b[tid] = b;
         t.f[tid] = f;
+        if (tid == 0) t.m = m;
     }
 }
 
@@ -298,20 +300,21 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     }
     const float* bl_head = GATED ? sums.bl + head : nullptr;
     const double* blk_head = GATED ? sums.blk + (size_t)at.head * ((T + GATE_BLOCK - 1) / GATE_BLOCK) : nullptr;
-    const double qblk = GATED ? blk_head[__builtin_amdgcn_readfirstlane(min(q0, T - 1) / GATE_BLOCK)] : 0.;
+    const double own_blk = GATED ? blk_head[i0 / GATE_BLOCK] : 0.;
+    float d_blk = 0.f;       // from there to the wave's block
+    if (GATED && WG > GATE_BLOCK) d_blk = (float)(blk_head[min(q0, T - 1) / GATE_BLOCK] - own_blk);
     float bq[NI];
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) bq[ib] = GATED ? bl_head[min(q0 + 32 * ib + r32, T - 1)] : 0.f;
 
     // one 64-key tile; DIAG: some pair of the tile lies above the diagonal and has to be masked
-    double tblk = 0., tblk_next = 0.;      // of the tile's block, and the next tile's
     auto tile = [&](auto diag_c, int buf, int key0) {
         constexpr bool DIAG = decltype(diag_c)::value;
         float fq[NI];
         if (GATED && !DIAG) {
-            const float m = gtile[buf].b[AT - 1];          // the tile's last key
+            const float m = gtile[buf].m - d_blk;          // the tile's last key, from the queries' block
 #pragma unroll
-            for (int ib = 0; ib < NI; ++ib) fq[ib] = gate_factor(qblk, bq[ib], tblk, m);
+            for (int ib = 0; ib < NI; ++ib) fq[ib] = __expf(bq[ib] - m);
         }
         f32x16 c[2][NI];        // S^T: key 32 kb + 8 k + 4 h + r, query 32 ib + r32
         auto scores = [&](int kb) {
@@ -362,22 +365,20 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     const int t_lo = CHUNKED ? (i0 / ck.cs) * ck.cs / AT : 0;
     const int k_lo = CHUNKED ? (q0 / ck.cs) * ck.cs : 0;
     uint4 kr[HD / 32], vr[HD / 32];
-    float gb = 0.f, gf = 0.f;
+    float gb = 0.f, gf = 0.f, gm = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
-    if (GATED) tblk = blk_head[t_lo * AT / GATE_BLOCK];
-    if (GATED) gate_tile_load(gb, gf, bl_head, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
+    if (GATED) gate_tile_load(gb, gf, gm, bl_head, blk_head, own_blk, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
-    if (GATED) gate_tile_store(gtile[0], gb, gf, tid);
+    if (GATED) gate_tile_store(gtile[0], gb, gf, gm, tid);
     __syncthreads();
     for (int t = t_lo; t < ntile; ++t) {
         const int buf = (t - t_lo) & 1, key0 = t * AT;
-        if (GATED) tblk_next = blk_head[min(key0 + AT, T - 1) / GATE_BLOCK];
         if (t + 1 < ntile) {
             PA_TILE_LOAD(kr, Kh, key0 + AT, false)
             PA_TILE_LOAD(vr, Vh, key0 + AT, false)
-            if (GATED) gate_tile_load(gb, gf, bl_head, key0 + AT, key0 + 2 * AT - 1, 1.f, tid, T);
+            if (GATED) gate_tile_load(gb, gf, gm, bl_head, blk_head, own_blk, key0 + AT, key0 + 2 * AT - 1, 1.f, tid, T);
         }
         if (active && key0 <= q0 + OWN - 1 && key0 >= k_lo) {
             if (key0 + AT - 1 > q0) tile(std::true_type{}, buf, key0);
@@ -386,9 +387,8 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
         if (t + 1 < ntile) {
             PA_TILE_STORE(kt[buf ^ 1], kr)
             PA_TILE_STORE(vt[buf ^ 1], vr)
-            if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf, tid);
+            if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf, gm, tid);
         }
-        tblk = tblk_next;
         __syncthreads();
     }
 
@@ -497,7 +497,9 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
     // gated: rsum = sum_j e_ij c_ij^p = q_i . dq_i / (p rest^p), the row's share of the gate gradient, summed
     // here from the unrounded terms (the dot product of the stored dq with q carries bf16 noise that a
     // sum over a block of tokens amplifies)
-    const double qblk = GATED ? blk_head[__builtin_amdgcn_readfirstlane(min(q0, T - 1) / GATE_BLOCK)] : 0.;
+    const double own_blk = GATED ? blk_head[i0 / GATE_BLOCK] : 0.;
+    float d_blk = 0.f;       // from there to the wave's block
+    if (GATED && WG > GATE_BLOCK) d_blk = (float)(blk_head[min(q0, T - 1) / GATE_BLOCK] - own_blk);
     float bq[NI], rsum[NI];
 #pragma unroll
     for (int ib = 0; ib < NI; ++ib) {
@@ -505,14 +507,13 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
         rsum[ib] = 0.f;
     }
 
-    double tblk = 0., tblk_next = 0.;      // of the tile's block, and the next tile's
     auto tile = [&](auto diag_c, int buf, int key0) {
         constexpr bool DIAG = decltype(diag_c)::value;
         float fq[NI];
         if (GATED && !DIAG) {
-            const float m = gtile[buf].b[AT - 1];          // the tile's last key
+            const float m = gtile[buf].m - d_blk;          // the tile's last key, from the queries' block
 #pragma unroll
-            for (int ib = 0; ib < NI; ++ib) fq[ib] = gate_factor(qblk, bq[ib], tblk, m);
+            for (int ib = 0; ib < NI; ++ib) fq[ib] = __expf(bq[ib] - m);
         }
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
@@ -560,22 +561,20 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
     const int t_lo = CHUNKED ? (i0 / ck.cs) * ck.cs / AT : 0;     // chunked: keys of the query's own chunk only
     const int k_lo = CHUNKED ? (q0 / ck.cs) * ck.cs : 0;
     uint4 kr[HD / 32], vr[HD / 32];
-    float gb = 0.f, gf2 = 0.f;
+    float gb = 0.f, gf2 = 0.f, gm = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
-    if (GATED) tblk = blk_head[t_lo * AT / GATE_BLOCK];
-    if (GATED) gate_tile_load(gb, gf2, bl_head, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
+    if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
-    if (GATED) gate_tile_store(gtile[0], gb, gf2, tid);
+    if (GATED) gate_tile_store(gtile[0], gb, gf2, gm, tid);
     __syncthreads();
     for (int t = t_lo; t < ntile; ++t) {
         const int buf = (t - t_lo) & 1, key0 = t * AT;
-        if (GATED) tblk_next = blk_head[min(key0 + AT, T - 1) / GATE_BLOCK];
         if (t + 1 < ntile) {
             PA_TILE_LOAD(kr, Kh, key0 + AT, false)
             PA_TILE_LOAD(vr, Vh, key0 + AT, false)
-            if (GATED) gate_tile_load(gb, gf2, bl_head, key0 + AT, key0 + 2 * AT - 1, 1.f, tid, T);
+            if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, key0 + AT, key0 + 2 * AT - 1, 1.f, tid, T);
         }
         if (active && key0 <= q0 + OWN - 1 && key0 >= k_lo) {
             if (key0 + AT - 1 > q0) tile(std::true_type{}, buf, key0);
@@ -584,9 +583,8 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
         if (t + 1 < ntile) {
             PA_TILE_STORE(kt[buf ^ 1], kr)
             PA_TILE_STORE(vt[buf ^ 1], vr)
-            if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf2, tid);
+            if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf2, gm, tid);
         }
-        tblk = tblk_next;
         __syncthreads();
     }
 
@@ -661,7 +659,9 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     const double* blk_head = GATED ? sums.blk + (size_t)at.head * ((T + GATE_BLOCK - 1) / GATE_BLOCK) : nullptr;
     // gated: csum = sum_i e_ij a_ij = k_j . dk_j / (p rest^p), the key's share of the gate gradient, from the
     // unrounded weights
-    const double kblk = GATED ? blk_head[__builtin_amdgcn_readfirstlane(min(k0, T - 1) / GATE_BLOCK)] : 0.;
+    const double own_blk = GATED ? blk_head[j0 / GATE_BLOCK] : 0.;
+    float d_blk = 0.f;       // from there to the wave's block
+    if (GATED && WG > GATE_BLOCK) d_blk = (float)(blk_head[min(k0, T - 1) / GATE_BLOCK] - own_blk);
     float bk[NJ], csum[NJ];
 #pragma unroll
     for (int kb = 0; kb < NJ; ++kb) {
@@ -670,14 +670,13 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     }
 
     float wprev = 0.f;   // the wave's total of csum at the end of the last complete block of queries
-    double tblk = 0., tblk_next = 0.;
     auto tile = [&](auto diag_c, int buf, int q0) {
         constexpr bool DIAG = decltype(diag_c)::value;
         float fk[NJ];
         if (GATED && !DIAG) {
-            const float m = gtile[buf].b[0];               // the tile's first query
+            const float m = gtile[buf].m - d_blk;          // the tile's first query, from the keys' block
 #pragma unroll
-            for (int kb = 0; kb < NJ; ++kb) fk[kb] = gate_factor(tblk, m, kblk, bk[kb]);
+            for (int kb = 0; kb < NJ; ++kb) fk[kb] = __expf(m - bk[kb]);
         }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
@@ -736,25 +735,23 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     const int ntile = ((CHUNKED ? min(((j0 + WG - 1) / ck.cs + 1) * ck.cs, T) : T) + AT - 1) / AT;
     const int q_hi = CHUNKED ? (k0 / ck.cs + 1) * ck.cs : T + AT;
     uint4 qr[HD / 32], gr[HD / 32];
-    float gzr = 0.f, gb = 0.f, gf2 = 0.f;
+    float gzr = 0.f, gb = 0.f, gf2 = 0.f, gm = 0.f;
     PA_TILE_LOAD(qr, Qh, t_first * AT, false)
     PA_TILE_LOAD(gr, Gh_h, t_first * AT, true)
     if (tid < AT) gzr = t_first * AT + tid < T ? gzh[t_first * AT + tid] : 0.f;
-    if (GATED) tblk = blk_head[t_first * AT / GATE_BLOCK];
-    if (GATED) gate_tile_load(gb, gf2, bl_head, t_first * AT, t_first * AT, -1.f, tid, T);
+    if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, t_first * AT, t_first * AT, -1.f, tid, T);
     PA_TILE_STORE(qt[0], qr)
     PA_TILE_STORE(gt[0], gr)
     if (tid < AT) gzt[0][tid] = gzr;
-    if (GATED) gate_tile_store(gtile[0], gb, gf2, tid);
+    if (GATED) gate_tile_store(gtile[0], gb, gf2, gm, tid);
     __syncthreads();
     for (int t = t_first; t < ntile; ++t) {
         const int buf = (t - t_first) & 1, q0 = t * AT;
-        if (GATED) tblk_next = blk_head[min(q0 + AT, T - 1) / GATE_BLOCK];
         if (t + 1 < ntile) {
             PA_TILE_LOAD(qr, Qh, q0 + AT, false)
             PA_TILE_LOAD(gr, Gh_h, q0 + AT, true)
             if (tid < AT) gzr = q0 + AT + tid < T ? gzh[q0 + AT + tid] : 0.f;
-            if (GATED) gate_tile_load(gb, gf2, bl_head, q0 + AT, q0 + AT, -1.f, tid, T);
+            if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, q0 + AT, q0 + AT, -1.f, tid, T);
         }
         if (active && q0 + AT - 1 >= k0 && q0 < q_hi) {
             if (q0 < k0 + OWN - 1) tile(std::true_type{}, buf, q0);   // some pair of this tile lies above the diagonal
@@ -777,9 +774,8 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
             PA_TILE_STORE(qt[buf ^ 1], qr)
             PA_TILE_STORE(gt[buf ^ 1], gr)
             if (tid < AT) gzt[buf ^ 1][tid] = gzr;
-            if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf2, tid);
+            if (GATED) gate_tile_store(gtile[buf ^ 1], gb, gf2, gm, tid);
         }
-        tblk = tblk_next;
         __syncthreads();
     }
 
