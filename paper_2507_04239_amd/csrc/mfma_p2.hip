@@ -163,7 +163,7 @@ bool quad_states(const pa_problem& pr, bool backward) { return use_quad(pr) && p
 bool quad_kept(const pa_problem& pr) { return pr.keep_state != 0 && quad_states(pr, false); }
 struct QuadLayout {
     QuadPlan pl;
-    size_t off_tot, off_st, off_gam, off_part, off_zpart;
+    size_t off_st, off_gam, off_part, off_zpart, off_tot;
     size_t off_gh, off_gz, off_rc, off_omg, off_pdq, off_pdk;   // backward only
     size_t off_tot2;                                            // scratch of the other scan, where both run side by side
     size_t off_dotq, off_dotk;                                  // ... gated: the states' part of q . dq and k . dk
@@ -180,19 +180,23 @@ QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
         off = align_up(off + bytes, 256);
         return o;
     };
-    L.off_tot = take(L.pl.tot_floats * sizeof(float));
+    // A scan's totals are dead before the first kernel behind it on its stream writes a part: they share the parts' space.
+    const size_t tot = L.pl.tot_floats * sizeof(float), slab = rows * pr.d * sizeof(float);
     L.off_st = take(nslot * L.pl.state_elems * 2);
     L.off_gam = take(nslot * L.pl.gam_elems * 2);
-    L.off_part = take(rows * pr.d * sizeof(float));
     L.off_zpart = take(rows * sizeof(float));
-    if (backward || pr.keep_state) {
+    L.off_part = L.off_tot = off;        // forward: the read-out; backward: dV and then dK, behind the scan of R
+    if (!backward && !pr.keep_state) {
+        take(std::max(slab, tot));
+    } else {
+        take(std::max(2 * align_up(slab, 256), tot));
+        L.off_pdk = L.off_part + align_up(slab, 256);
         L.off_gh = take(rows * pr.d * 2);
         L.off_gz = take(rows * sizeof(float));
         L.off_rc = take(nslot * L.pl.state_elems * 2);
         L.off_omg = take(nslot * L.pl.gam_elems * 2);
-        L.off_pdq = take(rows * pr.d * sizeof(float));
-        L.off_pdk = take(rows * pr.d * sizeof(float));
-        L.off_tot2 = quad_kept(pr) ? L.off_tot : take(L.pl.tot_floats * sizeof(float));
+        L.off_pdq = L.off_tot2 = off;    // dQ, behind the scan of S unless the forward pass has left that
+        take(quad_kept(pr) ? slab : std::max(slab, tot));
         if (pr.gated) {
             L.off_dotq = take(rows * sizeof(float));
             L.off_dotk = take(rows * sizeof(float));

@@ -72,6 +72,20 @@ def test_float32_attention_form_asks_for_no_states(lib, d, p, chunk):
         assert bytes_of(pr, False) >= 4 * 6 * T * d
 
 
+def test_scratch_of_the_state_scans_shares_the_space_of_what_follows(lib):
+    """12 heads of 65536 tokens, d = 64: 51 states of 295 KB and float32 totals of 786 KB a head; the totals are dead when the parts
+    [T][64] in float32 are written.  (States and totals apart from the parts: 881 MB forward, 2063 MB backward.)"""
+    heads, T = 12, 65536
+    state, total, part, bf16 = (heads * n for n in (51 * (36 * 4096 + 4096) * 2, 52 * 6 * 4 * 32768, T * 64 * 4, T * 64 * 2))
+    small = 3 * heads * T * 4 + 16 * 256
+    pr = binding.make_problem(1, heads, T, 64, 64, 2, 128)
+    assert total > part and 2 * part < total
+    assert binding.power_attn_workspace_bytes(pr, False) <= state + total + small
+    assert binding.power_attn_workspace_bytes(pr, True) <= 2 * (state + total) + bf16 + small
+    kept = binding.make_problem(1, heads, T, 64, 64, 2, 128, keep_state=True)
+    assert binding.power_attn_workspace_bytes(kept, True) <= 2 * state + total + part + bf16 + small
+
+
 def test_state_rows_match_the_embedding_dimension(lib):
     import math
     for d, p in [(16, 2), (32, 4), (12, 3)]:
