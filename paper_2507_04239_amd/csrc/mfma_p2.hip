@@ -137,7 +137,7 @@ AttnLayout make_attn_layout(const pa_problem& pr, bool backward) {
 
 // Chunk-state kernels with phi in registers (mfma_quad.hip): what AUTO and MFMA run for the chunked form of p = 2 at d = 64 and
 // (un-gated) 128, whatever multiple of 128 tokens the chunk is.  The states they keep are quad_chunk tokens apart: the result does
-// not depend on the chunk beyond rounding, and states are rounded less often the fewer they are.
+// not depend on that beyond rounding, and states are rounded less often the fewer they are.
 bool quad_ok(const pa_problem& pr) {
     return pr.dtype == PA_DTYPE_BF16 && pr.p == 2 && (pr.d == 64 || pr.d == 128) && pr.v == pr.d && pr.chunk > 0 &&
            pr.chunk % QBLK == 0 && pr.chunk < pr.T && (!pr.gated || pr.d == 64) && pr.d_tile == 0 && (size_t)pr.B * pr.H <= 65535u;
@@ -147,7 +147,9 @@ bool use_quad(const pa_problem& pr) { return (pr.impl == PA_IMPL_AUTO || pr.impl
 // best (ms, forward + backward): 12 heads of 65536, d = 64: 512 3.23, 768 3.00, 1024 3.05, 1280 2.97, 1536 3.03, 2048 3.24;
 // 32 heads of 32768, d = 128: 512 17.6, 768 18.4, 1024 17.4, 1536 18.0, 2048 18.0.  (Multiples of 256 at d = 64 and of 512 at
 // d = 128 fill the workgroups of the per-chunk kernels.)
-int quad_chunk(int d) { return d == 64 ? 1280 : 1024; }
+// A longer chunk is taken as asked for: fewer states is how a caller trades time for memory (backward, 32 heads of 32768, d = 128:
+// 6.4 GB of workspace at 1024 tokens, 4.1 at 2048, 2.9 at 4096).
+int quad_chunk(const pa_problem& pr) { return std::max(pr.d == 64 ? 1280 : 1024, pr.chunk); }
 // Shorter sequences run as one chunk, without a state: (heads x tokens: us whole, with states)  d = 64 forward 12 x 6144
 // 81, 106, 12 x 8192 122, 120, 48 x 6144 214, 289, 48 x 8192 361, 384, 12 x 12288 253, 180; backward 12 x 6144 209, 290,
 // 12 x 8192 351, 329, 48 x 6144 746, 825, 48 x 8192 1282, 1124, 2 x 8192 158, 184; d = 128 forward 16 x 16384 1100, 1349,
@@ -172,7 +174,7 @@ struct QuadLayout {
 QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
     QuadLayout L{};
     const size_t BH = (size_t)pr.B * pr.H, rows = BH * pr.T;
-    L.pl = quad_plan(pr.d, (int)BH, pr.T, quad_chunk(pr.d));
+    L.pl = quad_plan(pr.d, (int)BH, pr.T, quad_chunk(pr));
     const size_t nslot = BH * (L.pl.nchunk - 1);
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -217,11 +219,11 @@ bool use_tiled(const pa_problem& pr) {
 
 }  // namespace
 
-int mfma_gate_chunk(const pa_problem& pr, bool backward) { return use_attn(pr, backward) ? pr.T : quad_chunk(pr.d); }
+int mfma_gate_chunk(const pa_problem& pr, bool backward) { return use_attn(pr, backward) ? pr.T : quad_chunk(pr); }
 int mfma_gate_fin_chunk(const pa_problem& pr, int& xparts) {
     const bool attn = use_attn(pr, true);
     xparts = attn ? 1 : QUAD_XPARTS;
-    return attn ? attn_gate_block(pr.d) : quad_chunk(pr.d);
+    return attn ? attn_gate_block(pr.d) : quad_chunk(pr);
 }
 
 // (whole, a gated sequence has to be a multiple of the attention form's key block)

@@ -86,6 +86,18 @@ def test_scratch_of_the_state_scans_shares_the_space_of_what_follows(lib):
     assert binding.power_attn_workspace_bytes(kept, True) <= 2 * state + total + part + bf16 + small
 
 
+@pytest.mark.parametrize("d,heads,T,gated", [(64, 12, 65536, False), (64, 1, 16384, True), (128, 32, 32768, False)])
+def test_a_longer_chunk_takes_less_workspace(lib, d, heads, T, gated):
+    """The chunk is how a caller trades time for memory: beyond the spacing the kernels choose, each doubling drops half of the states."""
+    for backward in (False, True):
+        need = [binding.power_attn_workspace_bytes(binding.make_problem(1, heads, T, d, d, 2, c, gated=gated), backward)
+                for c in (128, 1024, 2048, 4096, 8192)]
+        state = (d // 8 * (d // 8 + 1) // 2 * 64 * d + d * d) * 2 * heads * (2 if backward else 1)
+        assert need[0] == need[1]
+        for n, (a, b) in enumerate(zip(need[1:], need[2:])):
+            assert a - b >= (T // (2048 << n) // 2 - 1) * state, (backward, need)
+
+
 def test_state_rows_match_the_embedding_dimension(lib):
     import math
     for d, p in [(16, 2), (32, 4), (12, 3)]:
