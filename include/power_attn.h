@@ -137,7 +137,9 @@ pa_status power_attn_fwd(const pa_problem* prob,
  * kernels as power_attn_fwd, with the workspace taken from a device array that is part of the
  * library itself (PA_STATIC_SCRATCH_BYTES, one copy per GPU, held until the process ends).  The call
  * allocates nothing.  A problem whose power_attn_workspace_bytes(prob, 0) exceeds
- * power_attn_static_scratch_bytes() is refused with PA_ERR_WORKSPACE and nothing is launched
+ * power_attn_static_scratch_bytes() is refused with PA_ERR_WORKSPACE and nothing is launched, but for bf16, p = 2, d = v = 64
+ * or 128 under AUTO or MFMA where ceil(T / chunk) bf16 states and one float per element of O do fit: such a problem runs with
+ * its states further apart, or as the attention form (so does chunk = 0 at d = 128, T < 24576).
  * (prob->keep_state is honoured only in the sense that the states stay in that array).  All calls
  * on one GPU share the array: calls that overlap on one GPU (different streams or host threads)
  * race; calls on one stream are ordered and safe.  Everything else as power_attn_fwd. */

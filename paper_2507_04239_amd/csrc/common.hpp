@@ -126,6 +126,8 @@ long long mfma_state_rows(const pa_problem& pr);
 pa_status mfma_supported(const pa_problem& pr, bool backward);
 // the family runs a sequence that is not a multiple of the chunk as it is
 bool mfma_takes_ragged(const pa_problem& pr, bool backward);
+// a problem whose workspace exceeds `bytes` (chosen: its chunk is the library's choice) with another chunk that fits; false: none
+bool mfma_fit(pa_problem& pr, bool chosen, size_t bytes);
 // gated: tokens after which the running sums of the log-gates start anew
 int mfma_gate_chunk(const pa_problem& pr, bool backward);
 pa_status mfma_fwd(const Ctx& c, const void* Q, const void* K, const void* V, void* O, float* Z);

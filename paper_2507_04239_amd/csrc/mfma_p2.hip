@@ -261,6 +261,28 @@ size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
     return make_attn_layout(pr, backward).total;
 }
 
+// Scratch of a fixed size.  The totals of the scan and the spacing are the kernels' own affair: what counts is whether the states as
+// far apart as they were asked for fit, beside one float32 value per element of O.  They are then formed as far apart as it takes,
+// or not at all (the attention form needs no scratch).  12 heads of 65536 tokens at a chunk of 128 do not fit and are refused.
+bool mfma_fit(pa_problem& pr, bool chosen, size_t bytes) {
+    if (!use_quad(pr) || pr.gated) return false;
+    pa_problem w = pr;
+    w.keep_state = 0;                  // (states that stay in the scratch serve nobody)
+    const size_t BH = (size_t)pr.B * pr.H, nasked = (size_t)((pr.T + pr.chunk - 1) / pr.chunk);
+    const QuadPlan pl = quad_plan(pr.d, (int)BH, pr.T, quad_chunk(pr));
+    const size_t asked = BH * (nasked * (pl.state_elems + pl.gam_elems) * 2 + (size_t)pr.T * pr.d * sizeof(float));
+    // (d = 128: a chunk chosen by the library was the whole sequence up to 24575 tokens before it was chosen for speed alone)
+    const bool whole = chosen && pr.d == 128 && pr.T < 24576;
+    if (asked > bytes && !whole) return false;
+    for (long long c = quad_chunk(pr); c < pr.T; c *= 2) {
+        w.chunk = (int)c;
+        if (mfma_workspace_bytes(w, false) <= bytes) break;
+        w.chunk = pr.T;
+    }
+    pr = w;
+    return true;
+}
+
 #define PA_TRY(CALL) \
     if (!(CALL)) return PA_ERR_HIP;
 

@@ -464,7 +464,12 @@ size_t power_attn_static_scratch_bytes(void) { return STATIC_SCRATCH_BYTES; }
 
 pa_status power_attn_fwd_static(const pa_problem* prob, const void* Q, const void* K, const void* V, void* O, float* Z,
                                 void* hip_stream) {
-    if (power_attn_workspace_bytes(prob, 0) > STATIC_SCRATCH_BYTES) return PA_ERR_WORKSPACE;
+    pa_problem fitted;
+    if (power_attn_workspace_bytes(prob, 0) > STATIC_SCRATCH_BYTES) {
+        fitted = resolved(prob);
+        if (!mfma_fit(fitted, prob->chunk == 0, STATIC_SCRATCH_BYTES)) return PA_ERR_WORKSPACE;
+        prob = &fitted;
+    }
     void* ptr = nullptr;
     pa_status st = static_scratch(&ptr);
     if (st != PA_OK) return st;

@@ -235,3 +235,33 @@ def test_decode_state_size_host_logic():
         assert need <= B * H * D * (d + 1) * 4 + D * 8 + B * H * ((D + 127) // 128) * (d + 1) * 4 + 5 * 256
     assert binding.power_attn_decode_state_bytes(binding.make_problem(1, 1, 1, 200, 200, 2, 1)) == 0   # head size above 128
     assert binding.power_attn_decode_state_bytes(binding.make_problem(1, 1, 1, 16, 16, 5, 1, normalize=False)) == 0
+
+
+STATIC_LONG = [
+    # B, H, T, d, chunk: more than the static scratch as the kernels would space their states, less as asked for
+    (1, 1, 24576, 64, 1024), (1, 1, 22528, 64, 1024), (1, 3, 9000, 64, 1024), (1, 1, 20480, 128, 0), (3, 11, 18500, 128, 0),
+]
+
+
+def test_static_scratch_takes_the_states_that_fit_as_asked_for(lib):
+    """Without a GPU a call that is taken ends at the scratch array's address (4: HIP error), a refused one before (3)."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch")
+    fake = ctypes.c_void_p(256)
+
+    def status(*a, **k):
+        return lib.power_attn_fwd_static(ctypes.byref(binding.make_problem(*a, **k)), fake, fake, fake, fake, fake, None)
+
+    for B, H, T, d, c in STATIC_LONG:
+        pr = binding.make_problem(B, H, T, d, d, 2, c)
+        assert binding.power_attn_workspace_bytes(pr, False) > lib.power_attn_static_scratch_bytes()
+        assert status(B, H, T, d, d, 2, c) == 4, (B, H, T, d, c)
+    for T in (16384, 57344):
+        for c in (512, 1024, 2048, 4096, 8192, 28672):
+            if c < T and T * 256 + T // c * 303104 <= 16 << 20:
+                assert status(1, 1, T, 64, 64, 2, c) == 4, (T, c)
+    # refused as ever: too many states, or too many tokens
+    for a in ((1, 12, 65536, 64, 64, 2, 128), (1, 1, 65536, 64, 64, 2, 32768), (1, 1, 24576, 64, 64, 2, 128), (1, 1, 24576, 128, 128, 2, 0),
+              (1, 1, 20480, 128, 128, 2, 2048)):
+        assert status(*a) == 3, a

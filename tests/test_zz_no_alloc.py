@@ -63,3 +63,22 @@ def test_static_scratch_refuses_what_does_not_fit():
     x = torch.zeros(8, device="cuda:0")
     p = ctypes.c_void_p(x.data_ptr())
     assert lib.power_attn_fwd_static(ctypes.byref(prob), p, p, p, p, p, None) == 3   # PA_ERR_WORKSPACE; nothing launched
+
+
+@pytest.mark.parametrize("B,H,T,d,chunk", [(1, 1, 16384, 64, 8192), (1, 1, 24576, 64, 1024), (1, 3, 9000, 64, 1024), (1, 1, 57344, 64, 28672),
+                                           (1, 2, 20480, 128, 0)])
+def test_static_scratch_spaces_the_states_to_fit(B, H, T, d, chunk):
+    """Where the states do not fit as the kernels would space them they stand further apart, or not at all: the same sums, rounded
+    elsewhere."""
+    import torch
+    from paper_2507_04239_amd.binding import power_attn_fwd, power_attn_fwd_static
+    print(B, H, T, d, chunk, flush=True)
+    torch.manual_seed(T)
+    q, k, v = ((torch.randn(B, H, T, d, device="cuda:0") * s).bfloat16() for s in (d ** -0.5, d ** -0.5, 1.0))
+    O, Z = torch.full_like(v, float("nan")), torch.full((B, H, T), float("nan"), device="cuda:0")
+    power_attn_fwd_static(q, k, v, O, Z, 2, chunk)
+    want_O, want_Z = power_attn_fwd(q, k, v, 2, T)
+    for got, want in ((O, want_O), (Z, want_Z)):
+        got, want = got.float().cpu().numpy(), want.float().cpu().numpy()
+        assert np.isfinite(got).all()
+        assert rel_l2(got, want) <= TOL["bf16"] and max_row_err(got, want) <= ROW_TOL["bf16"]
