@@ -543,7 +543,7 @@ AbsorbLayout make_absorb_layout(const pa_problem& pr) {
     AbsorbLayout L{};
     L.pl = quad_absorb_plan(pr.B * pr.H, pr.T);
     L.off_wk = align_up(L.pl.tot_floats * sizeof(float), 256);
-    L.off_gate = align_up(L.off_wk + (size_t)pr.B * pr.H * pr.T * DH * sizeof(bf16_t), 256);
+    L.off_gate = align_up(L.off_wk + (pr.gated ? (size_t)pr.B * pr.H * pr.T * DH * sizeof(bf16_t) : 0), 256);      // (weighted keys)
     pa_problem gp = pr;
     gp.chunk = pr.T;
     L.total = L.off_gate + gate_workspace_bytes(gp, false);

@@ -237,6 +237,15 @@ def test_decode_state_size_host_logic():
     assert binding.power_attn_decode_state_bytes(binding.make_problem(1, 1, 1, 16, 16, 5, 1, normalize=False)) == 0
 
 
+def test_prompt_scratch_holds_weighted_keys_only_with_gates(lib):
+    """Un-gated, the scratch of the hand-over is the float32 totals of its segments and nothing per token."""
+    size = binding.power_attn_decode_absorb_workspace_bytes
+    for heads, T in ((12, 65536), (1, 128), (200, 512)):
+        plain, gated = (size(binding.make_problem(1, heads, T, 64, 64, 2, 1, gated=g)) for g in (False, True))
+        assert plain % (heads * 6 * 4 * 32768) == 0 and plain > 0
+        assert gated >= plain + heads * T * 64 * 2
+
+
 STATIC_LONG = [
     # B, H, T, d, chunk: more than the static scratch as the kernels would space their states, less as asked for
     (1, 1, 24576, 64, 1024), (1, 1, 22528, 64, 1024), (1, 3, 9000, 64, 1024), (1, 1, 20480, 128, 0), (3, 11, 18500, 128, 0),
