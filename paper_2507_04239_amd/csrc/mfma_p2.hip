@@ -247,15 +247,7 @@ long long mfma_state_rows(const pa_problem& pr) {
 }
 
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
-    if (use_quad(pr)) {
-        // (a ragged sequence asks for a little more than the next whole number of chunks, as it did when it ran padded)
-        pa_problem up = pr;
-        up.T = (pr.T + pr.chunk - 1) / pr.chunk * pr.chunk;
-        auto bytes = [&](const pa_problem& p) {
-            return quad_states(p, backward) ? make_quad_layout(p, backward).total : make_attn_layout(p, backward).total;
-        };
-        return std::max(bytes(pr), bytes(up)) + (up.T > pr.T ? 256 : 0);
-    }
+    if (use_quad(pr)) return quad_states(pr, backward) ? make_quad_layout(pr, backward).total : make_attn_layout(pr, backward).total;
     if (use_tiled(pr)) return make_tiled_layout(pr, backward).total;
     if (use_resident(pr)) return make_res_layout(pr, backward).total;
     return make_attn_layout(pr, backward).total;

@@ -41,10 +41,16 @@ def test_validation_and_sizes(lib):
     ragged = binding.make_problem(1, 1, 256, 16, 16, 2, 48)
     assert lib.power_attn_supported(ctypes.byref(ragged), 0) == 2
     assert binding.power_attn_workspace_bytes(ragged, False) == 0
-    ragged_mfma = binding.make_problem(1, 2, 300, 64, 64, 2, 128)
-    assert lib.power_attn_supported(ctypes.byref(ragged_mfma), 1) == 0
-    whole = binding.make_problem(1, 2, 384, 64, 64, 2, 128)
-    assert binding.power_attn_workspace_bytes(ragged_mfma, True) > binding.power_attn_workspace_bytes(whole, True) > 0
+    # padded inside the workspace by the tiled kernels (d = 32); the kernels of d = 64 take any length
+    for d, padded in ((32, True), (64, False)):
+        for T in (300, 9000):
+            ragged_mfma = binding.make_problem(1, 2, T, d, d, 2, 128)
+            assert lib.power_attn_supported(ctypes.byref(ragged_mfma), 1) == 0
+            whole = binding.make_problem(1, 2, (T + 127) // 128 * 128, d, d, 2, 128)
+            for backward in (False, True):
+                a, b = (binding.power_attn_workspace_bytes(pr, backward) for pr in (ragged_mfma, whole))
+                assert a > b > 0 if padded else a <= b, (d, T, backward)
+    assert binding.power_attn_workspace_bytes(ragged_mfma, True) > 0
     odd_p = binding.make_problem(1, 1, 256, 16, 16, 3, 32, normalize=True)
     assert lib.power_attn_supported(ctypes.byref(odd_p), 0) == 1
     odd_p_unnorm = binding.make_problem(1, 1, 256, 16, 16, 3, 32, normalize=False)
