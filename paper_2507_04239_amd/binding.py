@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import operator
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -156,7 +157,7 @@ def _problem_of(Q, V, p, chunk, normalize, scale, impl, keep_state=False, gated=
 
 # What the library says about a problem depends on its fields alone, so a problem's struct, support status and workspace are
 # looked up once per set of fields, not once per call (three of the six microseconds a small call spent before its launch).
-@functools.lru_cache(maxsize=512, typed=True)     # (typed: 2.0 is refused where 2 is taken)
+@functools.lru_cache(maxsize=512)
 def _plan(for_backward, B, H, T, d, v, p, chunk, normalize, scale, dtype, impl, keep_state, gated, d_tile):
     """-> (pointer to the problem, power_attn_supported's status, workspace bytes)"""
     lib = load_library()
@@ -169,8 +170,9 @@ def _plan_of(for_backward, Q, V, p, chunk, normalize, scale, impl, keep_state, g
     if Q.dim() != 4 or V.dim() != 4:
         raise PowerAttnError("tensors must be [B, H, T, d]")
     B, H, T, d = Q.shape
-    return _plan(for_backward, B, H, T, d, V.shape[3], p, chunk, bool(normalize), float(scale), _dtype_name(Q), impl,
-                 bool(keep_state), gated, d_tile)
+    # (integers by value: what stands for one, a 0-d array or tensor, may not hash, or hashes by identity and can change)
+    return _plan(for_backward, B, H, T, d, V.shape[3], operator.index(p), operator.index(chunk), bool(normalize), float(scale),
+                 _dtype_name(Q), impl, bool(keep_state), gated, int(d_tile))
 
 
 def _dev_ptr(t, like=None, name="tensor"):

@@ -243,6 +243,29 @@ def test_decode_state_size_host_logic():
     assert binding.power_attn_decode_state_bytes(binding.make_problem(1, 1, 1, 16, 16, 5, 1, normalize=False)) == 0
 
 
+def test_plans_are_kept_by_value(lib):
+    """What is looked up once per set of fields: integers of any kind are taken by their value at the call, floats are refused."""
+    import numpy as np
+    import torch
+    Q = torch.empty(1, 1, 1024, 32, dtype=torch.bfloat16)
+
+    def degree(p, chunk=1024, d_tile=0):
+        ref, status, _ = binding._plan_of(0, Q, Q, p, chunk, False, 1.0, "auto", False, False, d_tile)
+        assert status == 0
+        return ref.contents.p, ref.contents.chunk, ref.contents.d_tile
+
+    for kind in (int, np.int64, np.array, torch.tensor):
+        assert degree(kind(2), kind(128), kind(8)) == (2, 128, 8), kind
+    p, chunk = torch.tensor(2), np.array(128)
+    assert degree(p, chunk) == (2, 128, 0)
+    p.fill_(3)
+    chunk[...] = 256
+    assert degree(p, chunk) == (3, 256, 0)
+    for bad in (dict(p=2.0), dict(p=2, chunk=128.0)):
+        with pytest.raises(TypeError):
+            degree(**bad)
+
+
 def test_prompt_scratch_holds_weighted_keys_only_with_gates(lib):
     """Un-gated, the scratch of the hand-over is the float32 totals of its segments and nothing per token."""
     size = binding.power_attn_decode_absorb_workspace_bytes
