@@ -72,7 +72,8 @@ constexpr int GATE_BLOCK = 128;
 struct GateBuf {
     double* blk = nullptr;
     float *bl = nullptr, *qfac = nullptr, *kfac = nullptr, *lam = nullptr, *db = nullptr, *db2 = nullptr;
-    float* xb = nullptr;    // [BH][chunks] backward: <R_m, S_{m+1}>, the pairs that straddle the end of chunk m (0 for the last)
+    float* xb = nullptr;    // [BH][chunks] backward: <R_m, S_{m+1}>, the pairs that straddle the end of chunk m (0 for the last);
+                            // see gate_gradient
 };
 
 struct Ctx {
@@ -91,7 +92,8 @@ pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk, bool in_bloc
 // The family has already written gate.xb, q.dq into gate.db and k.dk into gate.db2.
 // fin_chunk: the token granularity of gate.xb (the problem's chunk, or what the family says); xparts: terms that an entry of
 // gate.xb is kept in
-pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts);
+// (dotk: the states' part of gate.db2, and gate.xb is the pairs that straddle the whole chunk; null: its end)
+pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts, const float* dotk);
 
 // generic (vector-ALU, float32) family
 size_t generic_workspace_bytes(const pa_problem& pr, bool backward);
@@ -141,7 +143,8 @@ pa_status mfma_absorb(const pa_problem& pr, const void* K, const void* V, const 
                       float* gamd, int D);
 // destroys the calling thread's side stream and events of the MFMA backward pass, if it has any
 void mfma_release_side_stream();
-// tokens per entry of GateBuf::xb as mfma_bwd leaves it (gated problems), and the terms of an entry
-int mfma_gate_fin_chunk(const pa_problem& pr, int& xparts);
+// tokens per entry of GateBuf::xb as mfma_bwd leaves it in workspace ws (gated problems), the terms of an entry, and dotk of
+// gate_gradient
+int mfma_gate_fin_chunk(const pa_problem& pr, const char* ws, int& xparts, const float*& dotk);
 
 }  // namespace pa

@@ -120,6 +120,11 @@ __global__ __launch_bounds__(GT) void k_gate_prep(const float* __restrict__ log_
 //     X_m = sum_{j <= end_m < i} e_ij a_ij = < R_m , S_{m+1} >,
 // the inner product of the two states that meet at that chunk boundary, which each kernel family
 // computes from its states (xb); only the part inside the chunk is summed here.
+// dotk (may be null): the states' share of db2.  xb is then the pairs that straddle the whole chunk, and
+//     X_m = xb_m + sum_{j in m} dotk_j / p.
+// As the terms of db2 and of X_m cancel but for the keys before t, both have to be of one rounding: with X_m from the states and
+// db2 from products with them, the difference of the two is in every token of the chunk, and it is what a chunk of 1280 tokens is
+// long for (gates of mean -0.5: relative error of dlog_g 1.03e-2 that way, 3.6e-3 this way, as in the attention form).
 // db holds q_i . dq_i and db2 k_i . dk_i: dL/db_i = (db[i] - db2[i]) / p.
 __device__ __forceinline__ float gate_term(const float* __restrict__ db, const float* __restrict__ db2, float inv_p,
                                            size_t i) {
@@ -127,9 +132,9 @@ __device__ __forceinline__ float gate_term(const float* __restrict__ db, const f
 }
 
 __global__ __launch_bounds__(GT) void k_gate_finish(const float* __restrict__ db, const float* __restrict__ db2, float inv_p,
-                                                    const float* __restrict__ xb, int xparts, float* __restrict__ dlog_g,
-                                                    int T, int chunk) {
-    __shared__ float part[GT];
+                                                    const float* __restrict__ xb, int xparts, const float* __restrict__ dotk,
+                                                    float* __restrict__ dlog_g, int T, int chunk) {
+    __shared__ float part[GT], past[GT / 64];
     const int n = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
     const size_t base = (size_t)bh * T + (size_t)n * chunk;
     const int len = min(chunk, T - n * chunk);
@@ -138,6 +143,12 @@ __global__ __launch_bounds__(GT) void k_gate_finish(const float* __restrict__ db
     float s = 0.f;
     for (int i = lo; i < hi; ++i) s += gate_term(db, db2, inv_p, base + i);
     part[tid] = s;
+    if (dotk != nullptr) {
+        float k = 0.f;
+        for (int i = lo; i < hi; ++i) k += dotk[base + i];
+        for (int off = 32; off > 0; off >>= 1) k += __shfl_xor(k, off);
+        if ((tid & 63) == 0) past[tid >> 6] = k * inv_p;
+    }
     __syncthreads();
     for (int off = 1; off < GT; off <<= 1) {      // inclusive suffix scan of the per-thread sums
         const float add = tid + off < GT ? part[tid + off] : 0.f;
@@ -146,6 +157,7 @@ __global__ __launch_bounds__(GT) void k_gate_finish(const float* __restrict__ db
         __syncthreads();
     }
     float run = tid + 1 < GT ? part[tid + 1] : 0.f;
+    if (dotk != nullptr) run += past[0] + past[1] + past[2] + past[3];
     for (int k = 0; k < xparts; ++k) run += xb[((size_t)bh * gridDim.x + n) * xparts + k];
     for (int i = hi - 1; i >= lo; --i) {
         run += gate_term(db, db2, inv_p, base + i);
@@ -205,7 +217,7 @@ pa_status gate_prepare(const Ctx& c, const float* log_g, int chunk, bool in_bloc
     return launch_ok() ? PA_OK : PA_ERR_HIP;
 }
 
-pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts) {
+pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts, const float* dotk) {
     const pa_problem& pr = c.prob;
     // Under the sum normalisation q_i . dq_i is zero in exact arithmetic, yet the term stays: what the
     // device finds there is dO_i . (O_i - rounded O_i), and the k_j . dk_j of the keys after t contain
@@ -215,7 +227,7 @@ pa_status gate_gradient(const Ctx& c, float* dlog_g, int fin_chunk, int xparts) 
     // with it from rounded outputs, 3e-3 from the accumulators; no worse at weak decay.)
     LaunchScope ls("gate_finish", c.stream);
     hipLaunchKernelGGL(k_gate_finish, dim3((pr.T + fin_chunk - 1) / fin_chunk, pr.B * pr.H), dim3(GT), 0, c.stream, (const float*)c.gate.db,
-                       (const float*)c.gate.db2, 1.f / pr.p, (const float*)c.gate.xb, xparts, dlog_g, pr.T, fin_chunk);
+                       (const float*)c.gate.db2, 1.f / pr.p, (const float*)c.gate.xb, xparts, dotk, dlog_g, pr.T, fin_chunk);
     return launch_ok() ? PA_OK : PA_ERR_HIP;
 }
 

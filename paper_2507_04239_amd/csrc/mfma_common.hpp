@@ -202,10 +202,10 @@ bool launch_quad_read(const char* name, hipStream_t s, const QuadPlan& p, bool r
 // part[bh][t][:] = d/dX_t of phi(scale X_t) . (state of t's chunk . Y_t) and of wgt_t times the normaliser's part (wgt null: 1); dot[bh][t] (may be null) = X_t . part
 bool launch_quad_dphi(const char* name, hipStream_t s, const QuadPlan& p, bool rev, const bf16_t* X, const bf16_t* Y, const float* wgt,
                       const bf16_t* st, const bf16_t* gam, float* part, int BH, int T, float scale, const float* tw, float* dot);
-// d = 64: xb[bh][n][QUAD_XPARTS] = terms of the sum over the pairs that straddle the end of chunk n, from the states
+// d = 64: xb[bh][n][QUAD_XPARTS] = terms of the sum over the pairs that straddle the whole of chunk n, from the states
 constexpr int QUAD_XPARTS = 8;
 bool launch_quad_boundary(hipStream_t s, const QuadPlan& p, const bf16_t* st, const bf16_t* rc, const bf16_t* gam, const bf16_t* omg,
-                          float* xb, int BH);
+                          const float* lam, float* xb, int BH);
 
 // running sums of the log-gates as the attention kernels read them (see GateBuf; null: no gates)
 struct GateSums {

@@ -220,9 +220,10 @@ bool use_tiled(const pa_problem& pr) {
 }  // namespace
 
 int mfma_gate_chunk(const pa_problem& pr, bool backward) { return use_attn(pr, backward) ? pr.T : quad_chunk(pr); }
-int mfma_gate_fin_chunk(const pa_problem& pr, int& xparts) {
+int mfma_gate_fin_chunk(const pa_problem& pr, const char* ws, int& xparts, const float*& dotk) {
     const bool attn = use_attn(pr, true);
     xparts = attn ? 1 : QUAD_XPARTS;
+    dotk = attn ? nullptr : (const float*)(ws + make_quad_layout(pr, true).off_dotk);
     return attn ? attn_gate_block(pr.d) : quad_chunk(pr);
 }
 
@@ -426,7 +427,7 @@ pa_status mfma_bwd(const Ctx& c, const void* Q, const void* K, const void* V, co
         PA_TRY(launch_quad_dphi("mfma_dk_state", s, L.pl, true, k, v, nullptr, rc, omg, pdk, BH, pr.T, 1.0f, gt.kfac, dotk))
         if (pr.gated) {
             if (side.ok && hipStreamWaitEvent(s2, side.scanned, 0) != hipSuccess) return PA_ERR_HIP;
-            PA_TRY(launch_quad_boundary(s2, L.pl, st, rc, gam, omg, gt.xb, BH))
+            PA_TRY(launch_quad_boundary(s2, L.pl, st, rc, gam, omg, gt.lam, gt.xb, BH))
         }
         if (side.ok && (hipEventRecord(side.join, s2) != hipSuccess || hipStreamWaitEvent(s, side.join, 0) != hipSuccess)) return PA_ERR_HIP;
         AttnGate ag;

@@ -911,9 +911,9 @@ __global__ __launch_bounds__(64 * DphiCfg<HD>::NW, 2) void k_quad_dphi(StateArgs
     }
 }
 
-// ---- gated: the pairs that straddle a chunk boundary ----------------------------------------------------------
-// <R_m, S_{m+1}> + <Omega_m, Gamma_{m+1}>, which sit in the same slot; off-diagonal tiles carry their multiplicity in both states.
-// QUAD_XPARTS workgroups per boundary, every eighth tile (the normaliser's 64 x 64 is one more).
+// ---- gated: the pairs that straddle a chunk ---------------------------------------------------------------------
+// lam_n (<R_n, S_n> + <Omega_n, Gamma_n>), the states after and before chunk n; off-diagonal tiles carry their multiplicity in both.
+// QUAD_XPARTS workgroups per chunk, every eighth tile (the normaliser's 64 x 64 is one more).
 __device__ __forceinline__ float dot8(const uint4& a, const uint4& b) {
     float x[8], y[8], s = 0.f;
     unpack8(x, a);
@@ -924,17 +924,17 @@ __device__ __forceinline__ float dot8(const uint4& a, const uint4& b) {
 }
 __global__ __launch_bounds__(256) void k_quad_boundary(const bf16_t* __restrict__ st, const bf16_t* __restrict__ rc,
                                                        const bf16_t* __restrict__ gam, const bf16_t* __restrict__ omg,
-                                                       float* __restrict__ xb, int nchunk) {
+                                                       const float* __restrict__ lam, float* __restrict__ xb, int nchunk) {
     using D = QD<64>;
     __shared__ float red[4];
     const int part = blockIdx.x, n = blockIdx.y, bh = blockIdx.z, tid = threadIdx.x;
     float acc = 0.f;
-    if (n < nchunk - 1) {
-        const size_t slot = (size_t)bh * (nchunk - 1) + n;
+    if (n > 0 && n < nchunk - 1) {
+        const size_t slot = (size_t)bh * (nchunk - 1) + n, before = slot - 1;
         static_assert(D::TILE == D::GAM && D::TILE / 8 == 512, "two pieces per thread");
         for (int tile = part; tile <= D::NTILE; tile += QUAD_XPARTS) {
             const bool norm = tile == D::NTILE;
-            const uint4* a = (const uint4*)(norm ? gam + slot * D::GAM : st + slot * D::STATE + (size_t)tile * D::TILE) + tid;
+            const uint4* a = (const uint4*)(norm ? gam + before * D::GAM : st + before * D::STATE + (size_t)tile * D::TILE) + tid;
             const uint4* b = (const uint4*)(norm ? omg + slot * D::GAM : rc + slot * D::STATE + (size_t)tile * D::TILE) + tid;
             bool diag = norm;
             for (int t = 0; t < D::NB; ++t) diag = diag || tile == t * (t + 1) / 2 + t;
@@ -946,7 +946,7 @@ __global__ __launch_bounds__(256) void k_quad_boundary(const bf16_t* __restrict_
     for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     if ((tid & 63) == 0) red[tid >> 6] = acc;
     __syncthreads();
-    if (tid == 0) xb[((size_t)bh * nchunk + n) * QUAD_XPARTS + part] = red[0] + red[1] + red[2] + red[3];
+    if (tid == 0) xb[((size_t)bh * nchunk + n) * QUAD_XPARTS + part] = lam[(size_t)bh * nchunk + n] * (red[0] + red[1] + red[2] + red[3]);
 }
 
 // ---- a prompt into a decode state -------------------------------------------------------------------------
@@ -1153,9 +1153,9 @@ bool launch_quad_dphi(const char* name, hipStream_t s, const QuadPlan& p, bool r
 }
 
 bool launch_quad_boundary(hipStream_t s, const QuadPlan& p, const bf16_t* st, const bf16_t* rc, const bf16_t* gam, const bf16_t* omg,
-                          float* xb, int BH) {
+                          const float* lam, float* xb, int BH) {
     LaunchScope ls("mfma_gate_boundary", s);
-    hipLaunchKernelGGL(k_quad_boundary, dim3(QUAD_XPARTS, p.nchunk, BH), dim3(256), 0, s, st, rc, gam, omg, xb, p.nchunk);
+    hipLaunchKernelGGL(k_quad_boundary, dim3(QUAD_XPARTS, p.nchunk, BH), dim3(256), 0, s, st, rc, gam, omg, lam, xb, p.nchunk);
     return launch_ok();
 }
 

@@ -310,8 +310,9 @@ pa_status run_bwd(const pa_problem* prob, const void* Q, const void* K, const vo
     st = impl == PA_IMPL_MFMA ? mfma_bwd(c, Q, K, V, O, Z, dO, dQ, dK, dV) : generic_bwd(c, Q, K, V, O, Z, dO, dQ, dK, dV);
     if (st == PA_OK && gated) {
         int xparts = 1;
-        const int fin = impl == PA_IMPL_MFMA ? mfma_gate_fin_chunk(*prob, xparts) : prob->chunk;
-        st = gate_gradient(c, dlog_g, fin, xparts);
+        const float* dotk = nullptr;
+        const int fin = impl == PA_IMPL_MFMA ? mfma_gate_fin_chunk(*prob, c.ws, xparts, dotk) : prob->chunk;
+        st = gate_gradient(c, dlog_g, fin, xparts, dotk);
     }
     if (st != PA_OK || !pd.on) return st;
     const int row = asked.d * 2;

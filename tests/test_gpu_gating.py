@@ -114,3 +114,26 @@ def test_strong_gates_leave_the_decays_beside_them_exact(T, chunk, strong, every
             assert worst <= 1.0, f"{name} head {h}: {worst} of the bound"
     for name in ("dQ", "dK", "dlog_g"):
         assert np.isfinite(got[name]).all(), name
+
+
+@pytest.mark.parametrize("decay", [0.02, 0.1, 0.5])
+@pytest.mark.parametrize("T,chunk", [(8192, 128), (7000, 1920)])
+def test_gate_gradient_through_states_is_as_exact_as_without(T, chunk, decay):
+    """dlog_g is a small difference of sums over a chunk.  Against the definition in float64, the chunked kernels are no further off than
+    the attention form, which has no states, on the same tokens (a quarter allowed for: the two round at different places)."""
+    import torch
+    from test_gpu_quad import reference
+    print(f"T={T} chunk={chunk} decay={decay}", flush=True)
+    T0 = T // 128 * 128          # the attention form's lengths
+    rng = np.random.default_rng(T + int(100 * decay))
+    Q, K, V, G = (torch.from_numpy(rng.standard_normal((1, 1, T, 64), dtype=np.float32) * s).bfloat16().float().numpy()
+                  for s in (0.125, 0.125, 1.0, 1.0))
+    lg = (-decay * rng.standard_exponential((1, 1, T))).astype(np.float32)
+    err = []
+    for n, c in ((T, chunk), (T0, T0)):
+        a = [np.ascontiguousarray(x[:, :, :n]) for x in (Q, K, V, G, lg)]
+        got = run_fwd_bwd(*a[:4], 2, c, "bf16", log_g=a[4])["dlog_g"][0, 0]
+        want = reference(*(x[0, 0] for x in a[:4]), 1.0, True, a[4][0, 0])["dlog_g"]
+        err.append(float(np.linalg.norm(got - want) / np.linalg.norm(want)))
+    print(f"  {err[0]:.2e} with states, {err[1]:.2e} without", flush=True)
+    assert err[0] <= 1.25 * err[1], err
