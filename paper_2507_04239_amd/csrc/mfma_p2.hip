@@ -182,23 +182,30 @@ QuadLayout make_quad_layout(const pa_problem& pr, bool backward) {
         off = align_up(off + bytes, 256);
         return o;
     };
-    // A scan's totals are dead before the first kernel behind it on its stream writes a part: they share the parts' space.
+    // A scan's totals are dead before the first kernel behind it on its stream writes a part: they share the parts' space, once
+    // they are more than the 32 MB of all L2 caches.  (Below, lines of the totals are still in other XCDs' caches when the parts
+    // are written over them, and what is saved is little: shared and apart, forward, d = 64: 4 heads of 8192 tokens, 22 MB of totals,
+    // 81.7 and 79.6 us, 1 of 32768, 20 MB, 85.9 and 84.1; 4 of 16384, 41 MB, 101.7 and 101.4; 4 of 65536, 164 MB, 288 and 294.)
     const size_t tot = L.pl.tot_floats * sizeof(float), slab = rows * pr.d * sizeof(float);
+    const bool share = tot > (32u << 20);
     L.off_st = take(nslot * L.pl.state_elems * 2);
     L.off_gam = take(nslot * L.pl.gam_elems * 2);
     L.off_zpart = take(rows * sizeof(float));
-    L.off_part = L.off_tot = off;        // forward: the read-out; backward: dV and then dK, behind the scan of R
+    L.off_tot = share ? off : take(tot);
+    L.off_part = off;                    // forward: the read-out; backward: dV and then dK, behind the scan of R
+    const size_t over = share ? tot : 0;
     if (!backward && !pr.keep_state) {
-        take(std::max(slab, tot));
+        take(std::max(slab, over));
     } else {
-        take(std::max(2 * align_up(slab, 256), tot));
+        take(std::max(2 * align_up(slab, 256), over));
         L.off_pdk = L.off_part + align_up(slab, 256);
         L.off_gh = take(rows * pr.d * 2);
         L.off_gz = take(rows * sizeof(float));
         L.off_rc = take(nslot * L.pl.state_elems * 2);
         L.off_omg = take(nslot * L.pl.gam_elems * 2);
-        L.off_pdq = L.off_tot2 = off;    // dQ, behind the scan of S unless the forward pass has left that
-        take(quad_kept(pr) ? slab : std::max(slab, tot));
+        L.off_tot2 = share || quad_kept(pr) ? off : take(tot);
+        L.off_pdq = off;                 // dQ, behind the scan of S unless the forward pass has left that
+        take(quad_kept(pr) ? slab : std::max(slab, over));
         if (pr.gated) {
             L.off_dotq = take(rows * sizeof(float));
             L.off_dotk = take(rows * sizeof(float));
