@@ -143,6 +143,8 @@ pa_status mfma_absorb(const pa_problem& pr, const void* K, const void* V, const 
                       float* gamd, int D);
 // destroys the calling thread's side stream and events of the MFMA backward pass, if it has any
 void mfma_release_side_stream();
+// entries per head of GateBuf::xb where the chunked matrix-core kernels write it (0 elsewhere)
+size_t mfma_gate_slots(const pa_problem& pr);
 // tokens per entry of GateBuf::xb as mfma_bwd leaves it in workspace ws (gated problems), the terms of an entry, and dotk of
 // gate_gradient
 int mfma_gate_fin_chunk(const pa_problem& pr, const char* ws, int& xparts, const float*& dotk);

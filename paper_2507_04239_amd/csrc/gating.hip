@@ -173,6 +173,11 @@ static size_t chunk_slots(const pa_problem& pr) {
     const size_t a = (size_t)(pr.T / pr.chunk), b = (size_t)((pr.T + 127) / 128);
     return a > b ? a : b;
 }
+// ... and of xb, which the chunked matrix-core kernels leave in several terms per chunk of theirs
+static size_t xb_bytes(const pa_problem& pr) {
+    const size_t a = chunk_slots(pr), b = mfma_gate_slots(pr);
+    return align_up((size_t)pr.B * pr.H * (a > b ? a : b) * sizeof(float), 256);
+}
 
 // blocks of GATE_BLOCK tokens per head: every chunk starts one
 static size_t blocks_of(int T, int chunk) { return (size_t)((T + chunk - 1) / chunk) * ((chunk + GATE_BLOCK - 1) / GATE_BLOCK); }
@@ -185,7 +190,7 @@ size_t gate_workspace_bytes(const pa_problem& pr, bool backward) {
     if (!pr.gated) return 0;
     const size_t BH = (size_t)pr.B * pr.H;
     const size_t tok = align_up(BH * pr.T * sizeof(float), 256);
-    return blk_bytes(pr) + (backward ? 5 : 3) * tok + (backward ? 2 : 1) * align_up(BH * chunk_slots(pr) * sizeof(float), 256);
+    return blk_bytes(pr) + (backward ? 5 : 3) * tok + align_up(BH * chunk_slots(pr) * sizeof(float), 256) + (backward ? xb_bytes(pr) : 0);
 }
 
 GateBuf gate_buffers(const pa_problem& pr, bool backward, char* base) {

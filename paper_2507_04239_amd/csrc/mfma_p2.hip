@@ -227,6 +227,11 @@ bool use_tiled(const pa_problem& pr) {
 }  // namespace
 
 int mfma_gate_chunk(const pa_problem& pr, bool backward) { return use_attn(pr, backward) ? pr.T : quad_chunk(pr); }
+size_t mfma_gate_slots(const pa_problem& pr) {
+    if (!use_quad(pr) || !quad_states(pr, true)) return 0;
+    const int cs = quad_chunk(pr);
+    return (size_t)((pr.T + cs - 1) / cs) * QUAD_XPARTS;
+}
 int mfma_gate_fin_chunk(const pa_problem& pr, const char* ws, int& xparts, const float*& dotk) {
     const bool attn = use_attn(pr, true);
     xparts = attn ? 1 : QUAD_XPARTS;
