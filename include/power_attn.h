@@ -86,9 +86,9 @@ typedef struct {
                            sizes: padded with zero rows inside the workspace); elsewhere it is
                            PA_ERR_UNSUPPORTED.  bf16, p = 2, d = v = 64 (gated or not) or 128 (not gated), under AUTO or
                            MFMA: the kernels space their states as they run fastest, 1280 (d = 64) or 1024 tokens apart, where
-                           a shorter chunk was asked for, and form none at all for sequences up to 7 or 8 thousand
-                           tokens at d = 64, 5632 with gates, 14 to 18 thousand at d = 128; the result does not depend
-                           on it beyond rounding.  A longer chunk (a multiple of 128) is taken as it is, for less
+                           a shorter chunk was asked for, and form none at all for sequences up to 6 to 8 thousand
+                           tokens at d = 64, 5 thousand with gates, 8 to 24 thousand at d = 128 (by the number of
+                           heads); the result does not depend on it beyond rounding.  A longer chunk (a multiple of 128) is taken as it is, for less
                            workspace and a longer run */
     int   normalize;    /* 1: divide by the sum of the scores; 0: leave un-normalised */
     float scale;        /* multiplies q.k before the power ("softmax scaling", App. E.1 step 2).  Some kernels multiply q

@@ -126,8 +126,8 @@ bool f32_attn_bwd(const Ctx& c, const float* Q, const float* K, const float* V, 
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward);
 long long mfma_state_rows(const pa_problem& pr);
 pa_status mfma_supported(const pa_problem& pr, bool backward);
-// the family runs a sequence that is not a multiple of the chunk as it is
-bool mfma_takes_ragged(const pa_problem& pr, bool backward);
+// what the family needs the length of a sequence to be a multiple of: the chunk, or less
+int mfma_whole_rows(const pa_problem& pr, bool backward);
 // a problem whose workspace exceeds `bytes` (chosen: its chunk is the library's choice) with another chunk that fits; false: none
 bool mfma_fit(pa_problem& pr, bool chosen, size_t bytes);
 // gated: tokens after which the running sums of the log-gates start anew

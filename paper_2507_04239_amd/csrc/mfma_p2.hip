@@ -150,17 +150,29 @@ bool use_quad(const pa_problem& pr) { return (pr.impl == PA_IMPL_AUTO || pr.impl
 // A longer chunk is taken as asked for: fewer states is how a caller trades time for memory (backward, 32 heads of 32768, d = 128:
 // 6.4 GB of workspace at 1024 tokens, 4.1 at 2048, 2.9 at 4096).
 int quad_chunk(const pa_problem& pr) { return std::max(pr.d == 64 ? 1280 : 1024, pr.chunk); }
-// Shorter sequences run as one chunk, without a state: (heads x tokens: us whole, with states)  d = 64 forward 12 x 6144
-// 81, 106, 12 x 8192 122, 120, 48 x 6144 214, 289, 48 x 8192 361, 384, 12 x 12288 253, 180; backward 12 x 6144 209, 290,
-// 12 x 8192 351, 329, 48 x 6144 746, 825, 48 x 8192 1282, 1124, 2 x 8192 158, 184; d = 128 forward 16 x 16384 1100, 1349,
-// 16 x 24576 2490, 2112, 2 x 16384 311, 371, 2 x 24576 522, 444; backward 16 x 12288 2187, 2782, 16 x 16384 3826, 3644,
-// 2 x 12288 738, 761, 2 x 16384 978, 868; gated, d = 64, forward 12 x 6144 142, 131, 48 x 6144 277, 324, 12 x 8192 189, 139, backward
-// 12 x 6144 289, 272, 48 x 6144 964, 883, 12 x 8192 471, 324.
-int quad_whole_upto(int d, bool gated, bool backward) {
-    if (gated) return 5632;
-    return d == 64 ? (backward ? 7168 : 8191) : (backward ? 14336 : 18432);
+// Shorter sequences run as one chunk, without a state.  The whole pass grows with the square of the length once the chip is full
+// and with the length while it is not (few heads: one walk is the time); a pass with states has a constant part for few heads and
+// steps where a kernel's workgroups begin another round of the CUs.  So the line lies elsewhere for few heads.  Measured at 1 .. 20
+// heads, 24, 32, 40, 48, 64, 96 (heads x tokens: us whole, with states):
+//   d = 64 forward    1 x 7168 75, 76;       4 x 8192 86, 80;       12 x 8192 126, 132;     48 x 8192 387, 413;     12 x 9216 150, 138
+//   d = 64 backward   1 x 7168 131, 139;     8 x 7168 213, 215;     12 x 6144 214, 238;     12 x 7168 286, 259;     48 x 7168 1057, 979
+//   gated forward     1 x 5120 103, 96;      12 x 5120 109, 109;    16 x 5632 126, 136;     24 x 6144 160, 200
+//   gated backward    1 x 5120 169, 166;     12 x 6144 284, 271;    48 x 5120 709, 721;     48 x 6144 999, 919
+//   d = 128 forward   1 x 18432 342, 328;    2 x 20480 414, 428;    4 x 24576 671, 685;     8 x 24576 1263, 1430;   12 x 18432 1086, 1073;
+//                     16 x 18432 1396, 1686; 16 x 20480 1739, 1818; 32 x 18432 2892, 2919
+//   d = 128 backward  1 x 8192 494, 492;     3 x 10240 623, 619;    4 x 16384 1112, 1097;   8 x 16384 1999, 1989;   16 x 14336 2985, 2993;
+//                     32 x 14336 6252, 6081
+// With more than 6 heads a forward pass of 8192 tokens is up to 6 % faster whole, and runs with states all the same, as one with
+// gates between 5633 and 7168 does at 20 heads and more: the states may be kept for the backward pass, which gains more by them
+// (48 x 8192, d = 64, both passes: 413 + 956 us kept, 387 + 1138 whole and rebuilt), and results do not depend on keep_state.
+int quad_whole_upto(const pa_problem& pr, bool backward) {
+    const int heads = pr.B * pr.H;
+    if (pr.gated) return backward ? 5248 : heads <= 14 ? 5120 : 5632;
+    if (pr.d == 64) return backward ? (heads <= 10 ? 7296 : 6400) : (heads <= 6 ? 7424 : 8191);
+    if (backward) return heads <= 2 ? 8192 : heads == 3 ? 9984 : heads <= 10 ? 16384 : 14336;
+    return heads == 1 ? 17408 : heads <= 3 ? 20480 : heads <= 10 ? 24576 : heads >= 13 && heads <= 16 ? 20480 : 18432;
 }
-bool quad_states(const pa_problem& pr, bool backward) { return use_quad(pr) && pr.T > quad_whole_upto(pr.d, pr.gated, backward); }
+bool quad_states(const pa_problem& pr, bool backward) { return use_quad(pr) && pr.T > quad_whole_upto(pr, backward); }
 // the forward pass leaves its states for the backward pass
 bool quad_kept(const pa_problem& pr) { return pr.keep_state != 0 && quad_states(pr, false); }
 struct QuadLayout {
@@ -239,8 +251,11 @@ int mfma_gate_fin_chunk(const pa_problem& pr, const char* ws, int& xparts, const
     return attn ? attn_gate_block(pr.d) : quad_chunk(pr);
 }
 
-// (whole, a gated sequence has to be a multiple of the attention form's key block)
-bool mfma_takes_ragged(const pa_problem& pr, bool backward) { return use_quad(pr) && (!pr.gated || quad_states(pr, backward)); }
+// (whole, a gated sequence has to be a multiple of the attention form's key block, as all lines of quad_whole_upto are)
+int mfma_whole_rows(const pa_problem& pr, bool backward) {
+    if (!use_quad(pr)) return pr.chunk;
+    return pr.gated && !quad_states(pr, backward) ? attn_gate_block(pr.d) : 1;
+}
 
 pa_status mfma_supported(const pa_problem& pr, bool backward) {
     if (use_quad(pr)) return PA_OK;

@@ -141,9 +141,11 @@ struct Padding {
 Padding padding_for(const pa_problem& pr, bool backward) {
     Padding pd;
     pd.prob = pr;
-    if (pr.chunk <= 0 || pr.T % pr.chunk == 0 || mfma_takes_ragged(pr, backward)) return pd;
+    if (pr.chunk <= 0 || pr.T % pr.chunk == 0) return pd;
+    const int rows_of = mfma_whole_rows(pr, backward);
+    if (pr.T % rows_of == 0) return pd;
     pd.on = true;
-    pd.prob.T = (pr.T + pr.chunk - 1) / pr.chunk * pr.chunk;
+    pd.prob.T = (pr.T + rows_of - 1) / rows_of * rows_of;
     const size_t rows = (size_t)pr.B * pr.H * pd.prob.T;
     pd.tok = align_up(rows * pr.d * (pr.dtype == PA_DTYPE_BF16 ? 2 : 4), 256);
     pd.vec = align_up(rows * sizeof(float), 256);

@@ -50,18 +50,31 @@ def reference(Q, K, V, G, scale, normalize, log_g=None, block=2048):
 
 CASES = [
     # heads, T, d, chunk asked for, scale, normalize, keep (, mean log-gate)
-    (1, 7169, 64, 128, 1.0, True, True),       # the shortest backward pass with states: the forward pass has none to keep
-    (2, 8192, 64, 128, 0.3, True, True),       # ... and the shortest forward pass
+    (1, 7169, 64, 128, 1.0, True, True),       # whole
+    (1, 7297, 64, 128, 1.0, True, False),      # the shortest backward pass with states at 1 .. 10 heads
+    (12, 6401, 64, 128, 1.0, True, True),      # ... and at more; the forward pass has none to keep
+    (1, 7425, 64, 128, 1.0, False, False),     # the shortest forward pass at 1 .. 6 heads
+    (7, 8192, 64, 128, 1.0, True, True),       # ... and at more
+    (2, 8192, 64, 128, 0.3, True, True),
     (1, 8959, 64, 256, 1.0, True, False),      # 7 x 1280 - 1, 7 x 1280, one token of an eighth chunk
     (3, 8960, 64, 128, 1.0, True, False),
     (1, 8961, 64, 128, 2.0, True, True),
     (13, 9300, 64, 128, 1.0, False, False),
-    (1, 14337, 128, 128, 1.0, True, True),     # (d = 128: states 1024 apart)
+    (1, 8193, 128, 128, 1.0, True, True),      # d = 128: states 1024 apart; the shortest backward pass at 1 and 2 heads
+    (3, 9985, 128, 128, 1.0, True, False),     # ... at 3
+    (1, 14337, 128, 128, 1.0, True, True),
+    (11, 14337, 128, 128, 1.0, True, False),   # ... at more than 10
     (1, 18433, 128, 256, 0.7, True, True),
+    (4, 20000, 128, 256, 1.0, True, False),    # whole forward at 4 .. 10 heads, states backward
     (2, 19456, 128, 128, 1.0, True, False),    # 19 x 1024
     (14, 18500, 128, 256, 1.0, False, True),   # one walk per head: no segments
-    (1, 5632, 64, 128, 1.0, True, True, 0.02),     # gated: the longest sequence that runs whole
-    (2, 5633, 64, 128, 1.0, True, True, 0.02),     # ... and the shortest with states, 513 tokens in the last chunk
+    (1, 5120, 64, 128, 1.0, True, True, 0.02),     # gated: the longest sequence that runs whole
+    (2, 5121, 64, 128, 1.0, True, False, 0.02),    # ... and the shortest with states, one token in the last chunk; the backward pass padded
+    (1, 5249, 64, 384, 1.0, True, True, 0.02),     # ... and the shortest backward pass
+    (15, 5504, 64, 1024, 1.0, True, True, 0.02),   # whole forward at many heads (no multiple of the chunk), states backward
+    (15, 5400, 64, 4096, 1.0, True, False, 0.02),  # ... padded to whole blocks, not to whole chunks
+    (1, 5632, 64, 128, 1.0, True, True, 0.02),
+    (2, 5633, 64, 128, 1.0, True, True, 0.02),     # 513 tokens in the last chunk
     (1, 6400, 64, 256, 0.3, True, False, 0.1),     # 5 x 1280
     (13, 6401, 64, 384, 1.0, False, False, 0.005),
     (2, 9300, 64, 1408, 1.0, True, True),      # chunks beyond the spacing of the kernels: taken as they are
