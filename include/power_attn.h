@@ -88,8 +88,8 @@ typedef struct {
                            MFMA: the kernels space their states as they run fastest, 1280 (d = 64) or 1024 tokens apart, where
                            a shorter chunk was asked for, and form none at all for sequences up to 6 to 8 thousand
                            tokens at d = 64, 5 thousand with gates, 8 to 24 thousand at d = 128 (by the number of
-                           heads); the result does not depend on it beyond rounding.  A longer chunk (a multiple of 128) is taken as it is, for less
-                           workspace and a longer run */
+                           heads); the result does not depend on it beyond rounding.  Where states take over 256 MB a
+                           longer chunk (a multiple of 128) is taken as it is, for less workspace and a longer run */
     int   normalize;    /* 1: divide by the sum of the scores; 0: leave un-normalised */
     float scale;        /* multiplies q.k before the power ("softmax scaling", App. E.1 step 2).  Some kernels multiply q
                            (or k) by it, or by its power of two, before the product: q.k, scale q, scale k and the
@@ -138,8 +138,8 @@ pa_status power_attn_fwd(const pa_problem* prob,
  * library itself (PA_STATIC_SCRATCH_BYTES, one copy per GPU, held until the process ends).  The call
  * allocates nothing.  A problem whose power_attn_workspace_bytes(prob, 0) exceeds
  * power_attn_static_scratch_bytes() is refused with PA_ERR_WORKSPACE and nothing is launched, but for bf16, p = 2, d = v = 64
- * or 128 under AUTO or MFMA where ceil(T / chunk) bf16 states and one float per element of O do fit: such a problem runs with
- * its states further apart, or as the attention form (so does chunk = 0 at d = 128, T < 24576).
+ * or 128 under AUTO or MFMA where ceil(T / chunk) bf16 states and one float per element of O do fit: such a problem runs as
+ * the attention form (so does chunk = 0 at d = 128, T < 24576).
  * (prob->keep_state is honoured only in the sense that the states stay in that array).  All calls
  * on one GPU share the array: calls that overlap on one GPU (different streams or host threads)
  * race; calls on one stream are ordered and safe.  Everything else as power_attn_fwd. */

@@ -147,9 +147,17 @@ bool use_quad(const pa_problem& pr) { return (pr.impl == PA_IMPL_AUTO || pr.impl
 // best (ms, forward + backward): 12 heads of 65536, d = 64: 512 3.23, 768 3.00, 1024 3.05, 1280 2.97, 1536 3.03, 2048 3.24;
 // 32 heads of 32768, d = 128: 512 17.6, 768 18.4, 1024 17.4, 1536 18.0, 2048 18.0.  (Multiples of 256 at d = 64 and of 512 at
 // d = 128 fill the workgroups of the per-chunk kernels.)
-// A longer chunk is taken as asked for: fewer states is how a caller trades time for memory (backward, 32 heads of 32768, d = 128:
-// 6.4 GB of workspace at 1024 tokens, 4.1 at 2048, 2.9 at 4096).
-int quad_chunk(const pa_problem& pr) { return std::max(pr.d == 64 ? 1280 : 1024, pr.chunk); }
+// Where the states of both passes take more than 256 MB a longer chunk is taken as asked for: fewer states is how a caller trades
+// time for memory (backward, 32 heads of 32768, d = 128: 6.4 GB of workspace at 1024 tokens, 4.1 at 2048, 2.9 at 4096; 12 of 65536,
+// d = 64: 1459 MB at 1280, 822 at 4096, and 2319 us, 2993).  Below there is nothing to save (1 head of 16384, d = 64, forward: 79 us,
+// 253 at a chunk of 8192).
+int quad_chunk(const pa_problem& pr) {
+    const int own = pr.d == 64 ? 1280 : 1024;
+    if (pr.chunk <= own) return own;
+    const QuadPlan pl = quad_plan(pr.d, pr.B * pr.H, pr.T, own);
+    const size_t states = (size_t)pr.B * pr.H * (pl.nchunk - 1) * (pl.state_elems + pl.gam_elems) * 2;
+    return 2 * states > (256u << 20) ? pr.chunk : own;
+}
 // Shorter sequences run as one chunk, without a state.  The whole pass grows with the square of the length once the chip is full
 // and with the length while it is not (few heads: one walk is the time); a pass with states has a constant part for few heads and
 // steps where a kernel's workgroups begin another round of the CUs.  So the line lies elsewhere for few heads.  Measured at 1 .. 20
@@ -167,7 +175,7 @@ int quad_chunk(const pa_problem& pr) { return std::max(pr.d == 64 ? 1280 : 1024,
 // (48 x 8192, d = 64, both passes: 413 + 956 us kept, 387 + 1138 whole and rebuilt), and results do not depend on keep_state.
 int quad_whole_upto(const pa_problem& pr, bool backward) {
     const int heads = pr.B * pr.H;
-    if (pr.gated) return backward ? 5248 : heads <= 14 ? 5120 : 5632;
+    if (pr.gated) return backward ? 5248 : heads <= 11 ? 5120 : 5632;
     if (pr.d == 64) return backward ? (heads <= 10 ? 7296 : 6400) : (heads <= 6 ? 7424 : 8191);
     if (backward) return heads <= 2 ? 8192 : heads == 3 ? 9984 : heads <= 10 ? 16384 : 14336;
     return heads == 1 ? 17408 : heads <= 3 ? 20480 : heads <= 10 ? 24576 : heads >= 13 && heads <= 16 ? 20480 : 18432;
@@ -282,24 +290,17 @@ size_t mfma_workspace_bytes(const pa_problem& pr, bool backward) {
 }
 
 // Scratch of a fixed size.  The totals of the scan and the spacing are the kernels' own affair: what counts is whether the states as
-// far apart as they were asked for fit, beside one float32 value per element of O.  They are then formed as far apart as it takes,
-// or not at all (the attention form needs no scratch).  12 heads of 65536 tokens at a chunk of 128 do not fit and are refused.
+// far apart as they were asked for fit, beside one float32 value per element of O.  Such a problem runs as the attention form, which
+// needs no scratch, where the kernels' own spacing does not fit (1 head of 24576 tokens, d = 64: 252 us).
 bool mfma_fit(pa_problem& pr, bool chosen, size_t bytes) {
     if (!use_quad(pr) || pr.gated) return false;
-    pa_problem w = pr;
-    w.keep_state = 0;                  // (states that stay in the scratch serve nobody)
     const size_t BH = (size_t)pr.B * pr.H, nasked = (size_t)((pr.T + pr.chunk - 1) / pr.chunk);
     const QuadPlan pl = quad_plan(pr.d, (int)BH, pr.T, quad_chunk(pr));
     const size_t asked = BH * (nasked * (pl.state_elems + pl.gam_elems) * 2 + (size_t)pr.T * pr.d * sizeof(float));
     // (d = 128: a chunk chosen by the library was the whole sequence up to 24575 tokens before it was chosen for speed alone)
     const bool whole = chosen && pr.d == 128 && pr.T < 24576;
     if (asked > bytes && !whole) return false;
-    for (long long c = quad_chunk(pr); c < pr.T; c *= 2) {
-        w.chunk = (int)c;
-        if (mfma_workspace_bytes(w, false) <= bytes) break;
-        w.chunk = pr.T;
-    }
-    pr = w;
+    pr.chunk = pr.T;
     return true;
 }
 

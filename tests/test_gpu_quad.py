@@ -77,9 +77,10 @@ CASES = [
     (2, 5633, 64, 128, 1.0, True, True, 0.02),     # 513 tokens in the last chunk
     (1, 6400, 64, 256, 0.3, True, False, 0.1),     # 5 x 1280
     (13, 6401, 64, 384, 1.0, False, False, 0.005),
-    (2, 9300, 64, 1408, 1.0, True, True),      # chunks beyond the spacing of the kernels: taken as they are
-    (1, 20000, 64, 8192, 0.6, True, False),
-    (1, 18500, 128, 2176, 1.0, True, True),
+    (48, 13000, 64, 1408, 1.0, True, True),    # over 256 MB of states: chunks beyond the spacing of the kernels are taken as they are
+    (30, 22000, 64, 8192, 0.6, True, False),
+    (5, 18500, 128, 2176, 1.0, True, True),
+    (48, 13000, 64, 1920, 1.0, True, False, 0.02),
     (2, 7000, 64, 1920, 1.0, True, False, 0.02),
 ]
 
