@@ -262,7 +262,6 @@ struct ChunkedIn {
     const float* part2 = nullptr;    // dK / dV kernel: dV (nslab2 slabs)
     const float* zpart = nullptr;    // forward: denominator
     const float* dot = nullptr;      // gated, dQ and dK / dV kernels: the states' part of q . dq and k . dk
-    const char* label = "chunk_fwd"; // (host: the launch's name in the kernel times)
 };
 template <int P, int HD, int OWN, int WPE, bool GATED, bool CHUNKED = false>
 __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
@@ -908,11 +907,11 @@ int head_group(int BH, int T, const ChunkedIn& ck) {
 bool fwd_wide(int BH, int T) { return T >= 2048 && (long long)BH * ((T + 255) / 256) >= 1024; }
 template <int P, int HD, bool GATED, bool CHUNKED, int OWN>
 bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
-             int normalize, GateSums sums, ChunkedIn ck) {
+             int normalize, GateSums sums, ChunkedIn ck, const char* label) {
     constexpr int WG = 4 * OWN;
     auto kern = k_attn_fwd<P, HD, OWN, Shape<HD>::FWD_WPE, GATED, CHUNKED>;
     if (!allow_smem(kern, attn_smem_bytes<HD>())) return false;
-    LaunchScope ls(CHUNKED ? ck.label : "attn_fwd", s);
+    LaunchScope ls(label, s);
     Order order{head_group<HD, CHUNKED, WG>(BH, T, ck)};
     const dim3 grid = block_grid(BH, (T + WG - 1) / WG, order);
     hipLaunchKernelGGL(kern, grid, dim3(256), attn_smem_bytes<HD>(), s, Q, K, V, O, Z, BH, order, T,
@@ -921,10 +920,10 @@ bool fwd_own(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, b
 }
 template <int P, int HD, bool GATED, bool CHUNKED = false>
 bool fwd_t(hipStream_t s, const bf16_t* Q, const bf16_t* K, const bf16_t* V, bf16_t* O, float* Z, int BH, int T, float scale,
-           int normalize, GateSums sums, ChunkedIn ck = ChunkedIn(), const char* name = "attn_fwd") {
+           int normalize, GateSums sums, ChunkedIn ck = ChunkedIn(), const char* label = "attn_fwd") {
     if constexpr (HD == 64 && !CHUNKED)
-        if (fwd_wide(BH, T)) return fwd_own<P, HD, GATED, CHUNKED, 64>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck);
-    return fwd_own<P, HD, GATED, CHUNKED, Shape<HD>::FWD_OWN>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck);
+        if (fwd_wide(BH, T)) return fwd_own<P, HD, GATED, CHUNKED, 64>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck, label);
+    return fwd_own<P, HD, GATED, CHUNKED, Shape<HD>::FWD_OWN>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck, label);
 }
 
 template <int P, int HD, bool GATED, bool CHUNKED = false>
@@ -1000,15 +999,14 @@ bool launch_chunk_fwd(hipStream_t s, int p, int d, const bf16_t* Q, const bf16_t
                       int T, int cs, float scale, int normalize, const float* part, int nslab, const float* zpart, const char* label,
                       GateSums sums) {
     ChunkedIn ck;
-    ck.label = label;
     ck.cs = cs;
     ck.nslab = nslab;
     ck.part = part;
     ck.zpart = zpart;
     if (cs % AT != 0) return false;
-    if (sums.bl != nullptr) return p == 2 && d == 64 && fwd_t<2, 64, true, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck);
+    if (sums.bl != nullptr) return p == 2 && d == 64 && fwd_t<2, 64, true, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, sums, ck, label);
 #define PA_CASE(PP, DD) \
-    if (p == PP && d == DD) return fwd_t<PP, DD, false, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, GateSums(), ck);
+    if (p == PP && d == DD) return fwd_t<PP, DD, false, true>(s, Q, K, V, O, Z, BH, T, scale, normalize, GateSums(), ck, label);
     PA_CASE(2, 32) PA_CASE(2, 64) PA_CASE(2, 128)
     PA_CASE(3, 32) PA_CASE(3, 64)
     PA_CASE(4, 32)

@@ -474,7 +474,7 @@ template <int HD>
 __device__ __forceinline__ int xoff(int row, int chunk) {   // element offset of 16-byte chunk `chunk` of a row
     return row * HD + 8 * (chunk ^ (HD == 64 ? (row & 7) : (row & 15)));
 }
-// rows tok0 .. of X times fold into LDS, zeros past T (rows past the chunk are never stored)
+// rows tok0 .. of X times fold into LDS; rows past T repeat the last token's (results of rows past the chunk are never stored)
 template <int HD, int THREADS, int ROWS>
 __device__ __forceinline__ void stage_rows(bf16_t* xs, const bf16_t* __restrict__ Xh, int tok0, int T, float fold) {
 #pragma unroll
