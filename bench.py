@@ -37,8 +37,6 @@ def algorithmic_flops(w):
         "state_grad": state,
         "bwd_dq": state + pairs * (4 * d + 2 * v + 2),
         "bwd_dkdv": state + BH * (n - 1) * c * 2 * D * v + pairs * (2 * d + 2 * v),
-        "bwd_dk": state + pairs * 2 * d,
-        "bwd_dv": BH * (n - 1) * c * 2 * D * v + pairs * 2 * v,
     }
     # resident-state kernels: a walk does the update and one contraction with the state in one launch
     f["walk_fwd"] = 2 * state                                             # update-state + query-state
@@ -80,8 +78,6 @@ def algorithmic_bytes(w):
         "state_grad": states + 2 * tok + BH * T * 4,  # Q, ghat, gz in
         "bwd_dq": states + 5 * tok + BH * T * 4,     # Q, K, V, ghat, gz in; dQ out
         "bwd_dkdv": states + 6 * tok + BH * T * 4,   # Q, K, V, ghat, gz in; dK, dV out; R once
-        "bwd_dk": states + 5 * tok + BH * T * 4,
-        "bwd_dv": states + 4 * tok,                  # Q, K, ghat in; dV out
         "recompute": 0,
         # resident-state kernels: no state leaves the chip; what is credited is the token rows in and the
         # result out (the per-slab float32 partial results they exchange are overhead)
@@ -109,12 +105,7 @@ KERNEL_ROLE = {
     "f32_attn_dkdv": ("f32_dkdv", PEAK_FP32_VECTOR_TFLOPS),
     "mfma_state_scan": ("update_state", PEAK_BF16_MFMA_TFLOPS),
     "mfma_state_scan_bwd": ("recompute", PEAK_BF16_MFMA_TFLOPS),
-    "mfma_fwd_chunk": ("fwd_chunk", PEAK_BF16_MFMA_TFLOPS),
     "mfma_state_grad_scan": ("state_grad", PEAK_BF16_MFMA_TFLOPS),
-    "mfma_bwd_dq": ("bwd_dq", PEAK_BF16_MFMA_TFLOPS),
-    "mfma_bwd_dkdv": ("bwd_dkdv", PEAK_BF16_MFMA_TFLOPS),
-    "mfma_bwd_dk": ("bwd_dk", PEAK_BF16_MFMA_TFLOPS),
-    "mfma_bwd_dv": ("bwd_dv", PEAK_BF16_MFMA_TFLOPS),
     "res_state_walk": ("walk_fwd", PEAK_BF16_MFMA_TFLOPS),
     "res_state_totals": ("recompute", PEAK_BF16_MFMA_TFLOPS),
     "res_grad_totals": ("recompute", PEAK_BF16_MFMA_TFLOPS),
@@ -128,9 +119,8 @@ KERNEL_ROLE = {
     "tiled_dq": ("dphi", PEAK_BF16_MFMA_TFLOPS),
     "tiled_dk": ("dphi", PEAK_BF16_MFMA_TFLOPS),
     "tiled_dv": ("dv_readout", PEAK_BF16_MFMA_TFLOPS),
-    "mfma_fwd_chunk_partial": ("chunk_fwd", PEAK_BF16_MFMA_TFLOPS),
-    # p = 2, d = 64 / 128: states 1280 / 1024 tokens apart whatever the chunk (STATE_SPACING), the pairs in between on mfma_fwd_chunk
-    # and chunk_bwd_*
+    # p = 2, d = 64 / 128: the pairs between the states on mfma_fwd_chunk and chunk_bwd_*
+    "mfma_fwd_chunk": ("chunk_fwd", PEAK_BF16_MFMA_TFLOPS),
     "mfma_state_totals": ("recompute", PEAK_BF16_MFMA_TFLOPS),
     "mfma_query_state": ("query_state", PEAK_BF16_MFMA_TFLOPS),
     "mfma_dq_state": ("dphi", PEAK_BF16_MFMA_TFLOPS),
@@ -148,7 +138,7 @@ KERNEL_ROLE = {
 }
 
 
-STATE_SPACING = {64: 1280, 128: 1024}
+FORWARD_ROLES = ("update_state", "fwd_chunk", "query_state", "chunk_fwd", "walk_fwd", "fwd_total")
 
 
 def measured_traffic(workload, kernel):
@@ -427,10 +417,13 @@ def run_workload(args, name, cpu):
         step()
     kernels = binding.profile_end()
     total_alg = sum(algorithmic_flops(w)[k] for k in (("fwd_total", "bwd_total") if with_bwd else ("fwd_total",)))
-    spaced = "mfma_query_state" in kernels
-    wk = dict(w, chunk=STATE_SPACING[w["d"]]) if spaced else w          # what a kernel is credited with
-    roles = dict(KERNEL_ROLE, mfma_fwd_chunk=("chunk_fwd", PEAK_BF16_MFMA_TFLOPS)) if spaced else KERNEL_ROLE
-    fl, by = algorithmic_flops(wk), algorithmic_bytes(wk)
+    # what a kernel is credited with goes by the states that its pass really forms (float32: by the chunked form asked for)
+    spacing = [binding.power_attn_state_spacing(prob, b) for b in (False, True)]
+    models = [dict(w, chunk=s if w["dtype"] == "bf16" else w["chunk"]) for s in spacing]
+    roles = KERNEL_ROLE
+    (fl_f, by_f), (fl, by) = ((algorithmic_flops(m), algorithmic_bytes(m)) for m in models)
+    fl.update({r: fl_f[r] for r in FORWARD_ROLES})
+    by.update({r: by_f[r] for r in FORWARD_ROLES if r in by_f})
     per_kernel = {}
     for kname, (launches, ms_total) in kernels.items():
         per_kernel[kname] = {"launches_per_step": launches / args.steps, "avg_ms": ms_total / launches}
@@ -467,7 +460,8 @@ def run_workload(args, name, cpu):
         "vs_baseline": None, "dtype": w["dtype"], "data": "synthetic",
         "config": {"workload": name, "B": w["B"], "H": w["H"], "T": w["T"], "d": w["d"], "p": p, "chunk": w["chunk"],
                    "chunk_requested": chunk, "normalize": norm, "pass": "fwd+bwd" if with_bwd else "fwd", "impl": args.impl, "d_tile": args.d_tile, "keep_state": keep, "serial_kernels": args.serial_kernels, "gated": args.gated,
-                   "state_rows": binding.power_attn_state_rows(prob)},
+                   "state_rows": binding.power_attn_state_rows(prob),
+                   "state_spacing": spacing[0], "state_spacing_bwd": spacing[1]},
         "timing": timing,
         "step_algorithmic_tflop": total_alg / 1e12,
         "step_frac_of_bf16_mfma_peak": total_alg / (ms_per_step * 1e-3) / 1e12 / PEAK_BF16_MFMA_TFLOPS,

@@ -210,10 +210,14 @@ pa_status power_attn_decode_step(const pa_problem* prob, const void* q, const vo
                                  void* o, float* z, void* hip_stream);
 
 /* The chunk size the calls use for `prob` (prob->chunk itself unless it is 0; 0 on an invalid problem).  Where the kernels space
- * their states themselves (see pa_problem.chunk) it only says that the chunked form is asked for.  Un-gated float32
+ * their states themselves (see pa_problem.chunk and power_attn_state_spacing) it only says that the chunked form is asked for.  Un-gated float32
  * calls under PA_IMPL_AUTO with d = v in {16, 32, 64, 128} and T <= 4096 (<= 16384 where B H T <= 262144) run the attention
  * form at any chunk; the chunk, and the state rows below, are then those of the chunked form it takes the place of. */
 int power_attn_resolved_chunk(const pa_problem* prob);
+
+/* Tokens between the chunk states that power_attn_fwd (for_backward = 0) or power_attn_bwd (1) forms for `prob`; T where it forms
+ * none, 0 on an invalid or unsupported problem. */
+int power_attn_state_spacing(const pa_problem* prob, int for_backward);
 
 /* Expanded state rows the chosen kernel family keeps per head for `prob`: C(d+p-1, p) for
  * the generic family (Lemma 4.2), C(d/d_tile+p-1, p) * d_tile^p for the tiled one

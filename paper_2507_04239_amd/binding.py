@@ -35,6 +35,7 @@ EXPORTED_SYMBOLS = (
     "power_attn_fwd_gated",
     "power_attn_bwd_gated",
     "power_attn_state_rows",
+    "power_attn_state_spacing",
     "power_attn_resolved_chunk",
     "power_attn_status_string",
     "power_attn_last_hip_error",
@@ -88,6 +89,8 @@ def load_library():
     lib.power_attn_supported.argtypes = [P, ctypes.c_int]
     lib.power_attn_resolved_chunk.restype = ctypes.c_int
     lib.power_attn_resolved_chunk.argtypes = [P]
+    lib.power_attn_state_spacing.restype = ctypes.c_int
+    lib.power_attn_state_spacing.argtypes = [P, ctypes.c_int]
     lib.power_attn_state_rows.restype = ctypes.c_longlong
     lib.power_attn_state_rows.argtypes = [P]
     lib.power_attn_decode_state_bytes.restype = ctypes.c_size_t
@@ -217,6 +220,10 @@ def power_attn_supported(prob: PaProblem, for_backward: bool) -> bool:
 
 def power_attn_resolved_chunk(prob: PaProblem) -> int:
     return int(load_library().power_attn_resolved_chunk(ctypes.byref(prob)))
+
+
+def power_attn_state_spacing(prob: PaProblem, for_backward: bool) -> int:
+    return int(load_library().power_attn_state_spacing(ctypes.byref(prob), int(for_backward)))
 
 
 def power_attn_state_rows(prob: PaProblem) -> int:

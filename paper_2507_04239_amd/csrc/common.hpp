@@ -126,6 +126,8 @@ bool f32_attn_bwd(const Ctx& c, const float* Q, const float* K, const float* V, 
 size_t mfma_workspace_bytes(const pa_problem& pr, bool backward);
 long long mfma_state_rows(const pa_problem& pr);
 pa_status mfma_supported(const pa_problem& pr, bool backward);
+// tokens between the states that a pass forms, T if it forms none
+int mfma_state_spacing(const pa_problem& pr, bool backward);
 // what the family needs the length of a sequence to be a multiple of: the chunk, or less
 int mfma_whole_rows(const pa_problem& pr, bool backward);
 // a problem whose workspace exceeds `bytes` (chosen: its chunk is the library's choice) with another chunk that fits; false: none

@@ -246,6 +246,10 @@ bool use_tiled(const pa_problem& pr) {
 
 }  // namespace
 
+int mfma_state_spacing(const pa_problem& pr, bool backward) {
+    if (use_quad(pr)) return quad_states(pr, backward) ? quad_chunk(pr) : pr.T;
+    return use_attn(pr, backward) ? pr.T : pr.chunk;
+}
 int mfma_gate_chunk(const pa_problem& pr, bool backward) { return use_attn(pr, backward) ? pr.T : quad_chunk(pr); }
 size_t mfma_gate_slots(const pa_problem& pr) {
     if (!use_quad(pr) || !quad_states(pr, true)) return 0;

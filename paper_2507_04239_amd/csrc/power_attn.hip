@@ -498,6 +498,20 @@ pa_status power_attn_bwd_gated(const pa_problem* prob, const void* Q, const void
     return run_bwd(prob, Q, K, V, log_g, O, Z, dO, dQ, dK, dV, dlog_g, workspace, workspace_bytes, hip_stream, 1);
 }
 
+int power_attn_state_spacing(const pa_problem* prob, int for_backward) {
+    if (validate(prob) != PA_OK) return 0;
+    const pa_problem asked = resolved(prob);
+    const Padding pd = padding_for(asked, for_backward != 0);
+    pa_status why;
+    const int impl = choose(pd.prob, for_backward != 0, &why);
+    if (impl < 0 || (pd.on && impl != PA_IMPL_MFMA)) return 0;
+    if (impl == PA_IMPL_MFMA) {
+        const int s = mfma_state_spacing(pd.prob, for_backward != 0);
+        return s < asked.T ? s : asked.T;
+    }
+    return f32_attn_applies(pd.prob) ? asked.T : asked.chunk;
+}
+
 const char* power_attn_last_hip_error(void) { return g_last_error; }
 
 void power_attn_release_thread(void) { mfma_release_side_stream(); }

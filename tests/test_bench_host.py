@@ -46,6 +46,15 @@ def test_algorithmic_models_headline():
     assert b.PEAK_HBM_GBS == 8000.0 and b.PEAK_BF16_MFMA_TFLOPS == 2500.0
 
 
+def test_every_kernel_role_is_one_the_library_reports():
+    """Names of kernels that are no longer there credit nothing."""
+    b = _bench()
+    csrc = os.path.join(ROOT, "paper_2507_04239_amd", "csrc")
+    text = "".join(open(os.path.join(csrc, f)).read() for f in os.listdir(csrc) if f.endswith((".hip", ".hpp")))
+    for name in b.KERNEL_ROLE:
+        assert f'"{name}"' in text, name
+
+
 def test_algorithmic_models_scale_with_degree_and_head_size():
     b = _bench()
     w4 = dict(B=2, H=8, T=16384, d=32, p=4, chunk=128, dtype="bf16")

@@ -45,6 +45,8 @@ def test_bench_line_small_forward_config():
     assert rf["bound"] in ("hbm", "mfma", "alu") and rf["unit"] in ("GB/s", "TFLOP/s")
     assert abs(rf["frac"] - rf["achieved"] / rf["peak"]) < 1e-9 and 0.0 < rf["frac"] < 1.0
     assert rf["kernel"] in j["kernels"]
+    # the states the kernels form, which is not the chunk asked for
+    assert j["config"]["chunk"] == 128 and j["config"]["state_spacing"] == 1280
     # the matrix-core kernels ran (not the vector-ALU fallback), and back to back they take about a step
     assert "mfma_state_scan" in j["kernels"] and "mfma_fwd_chunk" in j["kernels"]
     serial = sum(k["avg_ms"] * k["launches_per_step"] for k in j["kernels"].values())

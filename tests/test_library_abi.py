@@ -246,6 +246,21 @@ def test_decode_state_size_host_logic():
     assert binding.power_attn_decode_state_bytes(binding.make_problem(1, 1, 1, 16, 16, 5, 1, normalize=False)) == 0
 
 
+def test_state_spacing(lib):
+    """What a pass forms: T where it has no states, else what the kernels choose, or a longer chunk that is taken as asked for."""
+    mk, spacing = binding.make_problem, binding.power_attn_state_spacing
+    assert [spacing(mk(1, 12, 65536, 64, 64, 2, 128), b) for b in (False, True)] == [1280, 1280]
+    assert [spacing(mk(1, 32, 32768, 128, 128, 2, 256), b) for b in (False, True)] == [1024, 1024]
+    assert [spacing(mk(1, 12, 65536, 64, 64, 2, 4096), b) for b in (False, True)] == [4096, 4096]
+    assert [spacing(mk(1, 12, 7000, 64, 64, 2, 128), b) for b in (False, True)] == [7000, 1280]
+    assert [spacing(mk(1, 12, 5001, 64, 64, 2, 128, gated=True), b) for b in (False, True)] == [5001, 5001]       # (padded)
+    assert spacing(mk(2, 8, 16384, 32, 32, 4, 128), False) == 128 and spacing(mk(2, 8, 16384, 32, 32, 4, 0), False) == 16384
+    assert spacing(mk(1, 2, 4096, 64, 64, 2, 256, impl="resident"), True) == 256
+    assert spacing(mk(1, 1, 256, 16, 16, 2, 32, dtype="f32"), False) == 256
+    assert spacing(mk(1, 1, 256, 16, 16, 2, 32, dtype="f32", impl="generic"), False) == 32
+    assert spacing(mk(1, 1, 256, 16, 16, 2, 48), False) == 0 and spacing(mk(1, 1, 256, 16, 16, 3, 32), False) == 0
+
+
 def test_plans_are_kept_by_value(lib):
     """What is looked up once per set of fields: integers of any kind are taken by their value at the call, floats are refused."""
     import numpy as np
