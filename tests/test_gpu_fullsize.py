@@ -100,8 +100,7 @@ def test_headline_config3_fwd_bwd():
 
 
 def test_headline_shape_with_the_library_chosen_chunk():
-    """The headline shape with chunk = 0: the library resolves it to 256, where the two 128-token blocks of a
-    chunk are dealt to the same XCD.  One head in full against the chunked float64 oracle, sampled rows of
+    """The headline shape with chunk = 0, which the library resolves to 256.  One head in full against the chunked float64 oracle, sampled rows of
     four heads against the definition."""
     from paper_2507_04239_amd import binding
     name = "cfg3_bf16_p2_T65536_d64_c128"
@@ -137,9 +136,15 @@ def test_config2_forward():
 
 
 def test_chunk_size_invariance_on_device():
-    """The result does not depend on the chunk size (App. A): 128, 256 and 512 agree on the device."""
+    """The result does not depend on the chunk size (App. A): 128, 256 and 512 agree on the device, on the kernels that take
+    them as they are, and so do states and none."""
     Q, K, V, G = inputs.make_qkvg(1, 2, 4096, 64, seed=77, dtype="bf16")
     outs = [run_fwd_bwd(Q, K, V, G, 2, c, "bf16") for c in (128, 256, 512)]
+    outs += [run_fwd_bwd(Q, K, V, G, 2, c, "bf16", impl="tiled") for c in (128, 256, 512)]
+    Q, K, V, G = inputs.make_qkvg(1, 2, 8960, 64, seed=78, dtype="bf16")
+    states, whole = (run_fwd_bwd(Q, K, V, G, 2, c, "bf16") for c in (128, 8960))
+    for key in ("O", "dQ", "dK", "dV"):
+        assert not np.array_equal(states[key], whole[key]) and rel_l2(states[key], whole[key]) <= 2 * TOL["bf16"], key
     for other in outs[1:]:
         for key in ("O", "dQ", "dK", "dV"):
             err = rel_l2(other[key], outs[0][key])

@@ -1,5 +1,6 @@
 """GPU parity of the bf16 MFMA kernel family (p = 2) against the float64 oracle, element by
-element, through the C ABI."""
+element, through the C ABI.  At these lengths d = 64 runs without a state whatever the chunk; the lengths with
+states are in test_gpu_quad.py."""
 import numpy as np
 import pytest
 
@@ -59,9 +60,8 @@ def test_mfma_backward_full_tensors(case, keep_state):
 
 def test_mfma_back_to_back_steps_share_workspace():
     """Two forward+backward steps with different inputs, queued one after the other on the same
-    workspace without host synchronisation in between: the second forward pass overwrites states
-    the first backward pass (which runs part of its kernels on a stream of the library's own)
-    still reads unless the passes are ordered correctly."""
+    workspace without host synchronisation in between.  (With states, which the second forward pass would
+    overwrite under the first backward pass: test_gpu_quad.py.)"""
     import torch
     from paper_2507_04239_amd import binding, power_attn_bwd, power_attn_fwd
     from gpu_util import to_dev, to_np
@@ -132,8 +132,8 @@ RAGGED_CASES = [
 @pytest.mark.parametrize("keep_state", [False, True], ids=["recompute", "keep_state"])
 @pytest.mark.parametrize("case", RAGGED_CASES, ids=lambda c: "-".join(str(x) for x in c))
 def test_mfma_ragged_last_chunk(case, keep_state):
-    """A sequence that is not a multiple of the chunk: the chunked kernels run it padded with zero
-    rows; every output of the T real tokens against the oracle."""
+    """A sequence that is not a multiple of the chunk: taken as it is, with gates padded to whole blocks of keys; every
+    output of the T real tokens against the oracle."""
     B, H, T, chunk, normalize, gated = case
     print("case", case, "keep_state", keep_state, flush=True)
     Q, K, V, G = inputs.make_qkvg(B, H, T, 64, seed=5100 + RAGGED_CASES.index(case), dtype="bf16")

@@ -27,7 +27,7 @@ def reference(Q, K, V, G, scale, normalize, log_g=None, block=2048):
             f = torch.exp((b_sum[a:b, None] - b_sum[None, :b]).clamp_(max=0.0))
             w *= f
         Z[a:b] = w.sum(1)
-        den = Z[a:b, None] if normalize else 1.0
+        den = torch.where(Z[a:b, None] == 0, float("inf"), Z[a:b, None]) if normalize else 1.0      # (a row without weight gives 0)
         O[a:b] = (w @ v[:b]) / den
         gh = g[a:b] / den
         e = gh @ vt
@@ -115,6 +115,130 @@ def test_runs_are_bit_identical_and_chunks_agree(d, T):
     for n in a:
         assert np.array_equal(a[n], b[n]), n
         assert np.array_equal(a[n], c[n]), n
+
+
+def device_inputs(seed, heads, T, d, gated):
+    import torch
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    x = [(torch.randn(1, heads, T, d, device="cuda:0", generator=gen) * s).bfloat16() for s in (d ** -0.5, d ** -0.5, 1.0, 1.0)]
+    return x + [-0.02 * torch.rand(1, heads, T, device="cuda:0", generator=gen) if gated else None]
+
+
+def step(x, ws, keep):
+    from paper_2507_04239_amd import power_attn_bwd, power_attn_fwd
+    q, k, v, g, lg = x
+    O, Z = power_attn_fwd(q, k, v, 2, 128, workspace=ws, keep_state=keep, log_g=lg)
+    return (O, Z, *power_attn_bwd(q, k, v, O, Z, g, 2, 128, workspace=ws, keep_state=keep, log_g=lg))
+
+
+def scratch(x, keep):
+    import torch
+    from paper_2507_04239_amd import binding
+    B, H, T, d = x[0].shape
+    prob = binding.make_problem(B, H, T, d, d, 2, 128, keep_state=keep, gated=x[4] is not None)
+    assert binding.power_attn_state_spacing(prob, False) < T and binding.power_attn_state_spacing(prob, True) < T
+    need = max(binding.power_attn_workspace_bytes(prob, b) for b in (False, True))
+    return torch.full((need,), 255, dtype=torch.uint8, device="cuda:0")        # (NaN in float32 and bf16: nothing unwritten is read)
+
+
+def alone(x, keep):
+    import torch
+    out = step(x, scratch(x, keep), keep)
+    torch.cuda.synchronize()
+    return out
+
+
+SHARED = [(64, 9000, False, True), (64, 9000, False, False), (64, 7000, True, True), (64, 7000, True, False), (128, 18560, False, True),
+          (128, 18560, False, False)]
+
+
+@pytest.mark.parametrize("d,T,gated,keep", SHARED)
+def test_steps_queued_on_one_workspace(d, T, gated, keep):
+    """Steps on different inputs, one after the other on one workspace without waiting: the next forward pass overwrites states that the
+    backward pass before it, on two streams, still reads, and totals overwrite parts, unless all is ordered.  Bits as alone."""
+    import torch
+    print(f"d={d} T={T} gated={gated} keep={keep}", flush=True)
+    xs = [device_inputs(seed, 1, T, d, gated) for seed in (1, 2, 3)]
+    want = [alone(x, keep) for x in xs]
+    ws = scratch(xs[0], keep)
+    got = [step(x, ws, keep) for x in xs]
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert all(torch.equal(s, t) and bool(torch.isfinite(s.float()).all()) for s, t in zip(a, b))
+
+
+def test_two_threads_with_states():
+    """Two host threads, each with a stream, a side stream of the library's and a workspace of its own, at the same time: bits as alone."""
+    import threading
+    import torch
+    from paper_2507_04239_amd import binding
+    print("two threads", flush=True)
+    shapes = [(64, 9000, False), (64, 7000, True)]
+    xs = [device_inputs(10 + i, 2, T, d, g) for i, (d, T, g) in enumerate(shapes)]
+    want = [alone(x, False) for x in xs]
+    got, errors = [None, None], []
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                ws = scratch(xs[i], False)
+                for _ in range(4):
+                    got[i] = step(xs[i], ws, False)
+                stream.synchronize()
+            binding.load_library().power_attn_release_thread()
+        except Exception as e:   # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for a, b in zip(got, want):
+        assert all(torch.equal(s, t) for s, t in zip(a, b))
+
+
+@pytest.mark.parametrize("d,T", [(64, 9000), (128, 18560)])
+def test_replayed_step_with_states(d, T):
+    """A captured step, replayed with the program's own work between: bits as alone each time."""
+    import torch
+    print(f"d={d} T={T}", flush=True)
+    a, b = device_inputs(21, 1, T, d, False), device_inputs(22, 1, T, d, False)
+    want = [alone(x, False) for x in (a, b)]
+    x = [None if t is None else t.clone() for t in a]
+    ws = scratch(x, False)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        step(x, ws, False)           # (the library's side stream exists before the capture)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        out = step(x, ws, False)
+    for n in (0, 1, 1, 0):
+        for s, t in zip(x[:4], (a, b)[n][:4]):
+            s.copy_(t)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(s, t) for s, t in zip(out, want[n])), n
+        ws.fill_(255)
+        step((b, a)[n], ws, False)   # eager work on the same workspace
+        torch.cuda.synchronize()
+
+
+def test_zero_rows_with_states():
+    """Queries that are all zero have Z = 0: O = 0 and no gradient flows through the row, in chunks with a state before them too."""
+    print("zero rows", flush=True)
+    T = 9000
+    Q, K, V, G = (t[0].float().cpu().numpy() for t in device_inputs(31, 1, T, 64, False)[:4])
+    for t in (5, 1279, 1280, 8960, 8999):
+        Q[0, t] = 0
+    K[0, 1300] = V[0, 2600] = 0
+    got = run_fwd_bwd(Q[None], K[None], V[None], G[None], 2, 128, "bf16")
+    assert_close({n: a[0, 0] for n, a in got.items()}, reference(Q[0], K[0], V[0], G[0], 1.0, True), "bf16", "zero rows")
+    for t in (5, 1279, 1280, 8960, 8999):
+        assert not got["O"][0, 0, t].any() and not got["dQ"][0, 0, t].any() and got["Z"][0, 0, t] == 0
 
 
 @pytest.mark.parametrize("gated", [False, True], ids=["plain", "gated"])

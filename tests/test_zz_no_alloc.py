@@ -39,7 +39,8 @@ def _both(lib, B, H, T, d, p, chunk, dtype, impl, seed):
 
 
 @pytest.mark.parametrize("dtype,impl,chunk,shapes", [
-    ("bf16", "mfma", 128, [(1, 2, 1024, 64), (1, 1, 256, 64)]),      # chunked matrix-core kernels: states in the scratch
+    ("bf16", "mfma", 128, [(1, 2, 1024, 64), (1, 1, 256, 64)]),      # matrix-core kernels without a state
+    ("bf16", "mfma", 128, [(1, 1, 9000, 64), (1, 1, 8200, 64)]),     # ... and with: states in the scratch
     ("f32", "generic", 32, [(1, 2, 512, 16), (1, 1, 96, 16)]),       # vector-ALU family
 ])
 def test_static_scratch_matches_workspace_call(dtype, impl, chunk, shapes):
