@@ -221,7 +221,8 @@ int power_attn_state_spacing(const pa_problem* prob, int for_backward);
 
 /* Expanded state rows the chosen kernel family keeps per head for `prob`: C(d+p-1, p) for
  * the generic family (Lemma 4.2), C(d/d_tile+p-1, p) * d_tile^p for the tiled one
- * (Sec. 4.1.1).  0 when no state is built (the attention-form kernels) and on an invalid problem. */
+ * (Sec. 4.1.1).  0 when no state is asked for (the attention form) and on an invalid problem; a sequence too short for a state
+ * (see pa_problem.chunk) has those of its chunked form. */
 long long power_attn_state_rows(const pa_problem* prob);
 
 const char* power_attn_status_string(pa_status s);

@@ -123,14 +123,14 @@ def test_automatic_chunk_choice():
     assert rc(mk(1, 12, 65536, 64, 64, 2, 128)) == 128
     assert rc(mk(1, 12, 65536, 64, 64, 2, 0)) == 256          # bf16, p = 2, d = 64: measured best chunk
     assert rc(mk(1, 12, 65536 + 128, 64, 64, 2, 0)) == 128    # 256 does not divide T
-    assert rc(mk(1, 12, 65536 + 5, 64, 64, 2, 0)) == 256      # ragged: chunked all the same, the sequence is padded
+    assert rc(mk(1, 12, 65536 + 5, 64, 64, 2, 0)) == 256      # ragged: chunked all the same
     assert rc(mk(1, 12, 3000, 64, 64, 2, 0)) == 3000          # short and ragged: attention form, any length
     assert rc(mk(4, 12, 4096, 64, 64, 2, 0)) == 4096          # short: attention form
     assert rc(mk(4, 12, 8192, 64, 64, 2, 0)) == 256
     assert rc(mk(4, 12, 4096, 64, 64, 2, 0, gated=True)) == 256
     assert rc(mk(4, 12, 2048, 64, 64, 2, 0, gated=True)) == 2048
     assert rc(mk(4, 12, 512, 64, 64, 2, 0)) == 512
-    # d = 128, p = 2: the tiled chunked kernels from about 24k tokens on (not gated: they take no gates)
+    # d = 128, p = 2: chunked from 18k tokens on (not gated: the chunked kernels take no gates there)
     assert rc(mk(8, 16, 32768, 128, 128, 2, 0)) == 256
     assert rc(mk(8, 16, 16384, 128, 128, 2, 0)) == 16384
     assert rc(mk(8, 16, 32768, 128, 128, 2, 0, gated=True)) == 32768
@@ -206,7 +206,7 @@ def test_support_matrix_host_logic():
     assert ok(mk(1, 2, 1024, 64, 64, 2, 128, impl="mfma"), True)
     assert rows(mk(1, 2, 1024, 64, 64, 2, 128, impl="mfma")) == 36 * 64            # tiled embedding, d_tile = 8
     assert not ok(mk(1, 2, 1024, 64, 64, 2, 64, impl="mfma"), True)
-    # d = 128 chunked: the tiled kernels (136 tiles of 64 rows); the resident-state kernels when asked for by name
+    # d = 128 chunked (136 tiles of 64 rows); the resident-state kernels when asked for by name
     assert ok(mk(1, 2, 1024, 128, 128, 2, 256, impl="mfma"), True)
     assert rows(mk(1, 2, 1024, 128, 128, 2, 256, impl="mfma")) == 136 * 64
     assert ok(mk(1, 2, 1024, 64, 64, 2, 128, impl="resident"), True)
