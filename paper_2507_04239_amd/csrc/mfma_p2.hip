@@ -165,7 +165,8 @@ int quad_chunk(const pa_problem& pr) {
 //   d = 64 forward    1 x 7168 75, 76;       4 x 8192 86, 80;       12 x 8192 126, 132;     48 x 8192 387, 413;     12 x 9216 150, 138
 //   d = 64 backward   1 x 7168 131, 139;     8 x 7168 213, 215;     12 x 6144 214, 238;     12 x 7168 286, 259;     48 x 7168 1057, 979
 //   gated forward     1 x 5120 103, 96;      12 x 5120 109, 109;    16 x 5632 126, 136;     24 x 6144 160, 200
-//   gated backward    1 x 5120 169, 166;     12 x 6144 284, 271;    48 x 5120 709, 721;     48 x 6144 999, 919
+//   gated backward    1 x 5120 169, 166;     12 x 5632 247, 263;    12 x 6144 284, 271;     16 x 5632 326, 292;     48 x 5120 709, 721;
+//                     48 x 6144 999, 919
 //   d = 128 forward   1 x 18432 342, 328;    2 x 20480 414, 428;    4 x 24576 671, 685;     8 x 24576 1263, 1430;   12 x 18432 1086, 1073;
 //                     16 x 18432 1396, 1686; 16 x 20480 1739, 1818; 32 x 18432 2892, 2919
 //   d = 128 backward  1 x 8192 494, 492;     3 x 10240 623, 619;    4 x 16384 1112, 1097;   8 x 16384 1999, 1989;   16 x 14336 2985, 2993;
@@ -175,7 +176,7 @@ int quad_chunk(const pa_problem& pr) {
 // (48 x 8192, d = 64, both passes: 413 + 956 us kept, 387 + 1138 whole and rebuilt), and results do not depend on keep_state.
 int quad_whole_upto(const pa_problem& pr, bool backward) {
     const int heads = pr.B * pr.H;
-    if (pr.gated) return backward ? 5248 : heads <= 11 ? 5120 : 5632;
+    if (pr.gated) return backward ? (heads >= 9 && heads <= 14 ? 5632 : 5248) : heads <= 11 ? 5120 : 5632;
     if (pr.d == 64) return backward ? (heads <= 10 ? 7296 : 6400) : (heads <= 6 ? 7424 : 8191);
     if (backward) return heads <= 2 ? 8192 : heads == 3 ? 9984 : heads <= 10 ? 16384 : 14336;
     return heads == 1 ? 17408 : heads <= 3 ? 20480 : heads <= 10 ? 24576 : heads >= 13 && heads <= 16 ? 20480 : 18432;
