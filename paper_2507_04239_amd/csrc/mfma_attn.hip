@@ -202,17 +202,18 @@ struct alignas(16) GateTile {
     float b[AT], f[AT];
     float m;        // the reference, from the start of the workgroup's first block
 };
-// streamed rows row0 .. row0 + 63 of one head; m_row: the row whose b is the reference; own: blk of the workgroup's first row;
-// sign = +1: f = exp(m - b) (streamed keys), -1: f = exp(b - m) (streamed queries)
+// streamed rows row0 .. row0 + 63 of one head, by the first wave; own: blk of the workgroup's first row; KEYS: f = exp(m - b), m the b
+// of the last row, else f = exp(b - m), m that of the first.  (Vector loads and a lane's value: scalar loads make the tile's LDS reads
+// wait for them, 2 % of the kernel.)
+template <bool KEYS>
 __device__ __forceinline__ void gate_tile_load(float& b, float& f, float& m, const float* __restrict__ bl_head,
-                                               const double* __restrict__ blk_head, double own, int row0, int m_row, float sign,
-                                               int tid, int T) {
+                                               const double* __restrict__ blk_head, double own, int row0, int tid, int T) {
     if (tid < AT) {
-        b = bl_head[min(row0 + tid, T - 1)];
-        m = bl_head[min(m_row, T - 1)];
-        f = __expf(sign * (m - b));
-        // (a vector load: a scalar one makes the tile's LDS reads wait for it, 2 % of the kernel)
-        m += (float)(blk_head[min(row0 + tid, T - 1) / GATE_BLOCK] - own);
+        const int row = min(row0 + tid, T - 1);
+        b = bl_head[row];
+        const float ref = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b), KEYS ? AT - 1 : 0));
+        f = __expf(KEYS ? ref - b : b - ref);
+        m = ref + (float)(blk_head[row / GATE_BLOCK] - own);
     }
 }
 __device__ __forceinline__ void gate_tile_store(GateTile& t, float b, float f, float m, int tid) {
@@ -367,7 +368,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
     float gb = 0.f, gf = 0.f, gm = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
-    if (GATED) gate_tile_load(gb, gf, gm, bl_head, blk_head, own_blk, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
+    if (GATED) gate_tile_load<true>(gb, gf, gm, bl_head, blk_head, own_blk, t_lo * AT, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
     if (GATED) gate_tile_store(gtile[0], gb, gf, gm, tid);
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(256, WPE) void k_attn_fwd(const bf16_t* __restrict_
         if (t + 1 < ntile) {
             PA_TILE_LOAD(kr, Kh, key0 + AT, false)
             PA_TILE_LOAD(vr, Vh, key0 + AT, false)
-            if (GATED) gate_tile_load(gb, gf, gm, bl_head, blk_head, own_blk, key0 + AT, key0 + 2 * AT - 1, 1.f, tid, T);
+            if (GATED) gate_tile_load<true>(gb, gf, gm, bl_head, blk_head, own_blk, key0 + AT, tid, T);
         }
         if (active && key0 <= q0 + OWN - 1 && key0 >= k_lo) {
             if (key0 + AT - 1 > q0) tile(std::true_type{}, buf, key0);
@@ -563,7 +564,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
     float gb = 0.f, gf2 = 0.f, gm = 0.f;
     PA_TILE_LOAD(kr, Kh, t_lo * AT, false)
     PA_TILE_LOAD(vr, Vh, t_lo * AT, false)
-    if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, t_lo * AT, t_lo * AT + AT - 1, 1.f, tid, T);
+    if (GATED) gate_tile_load<true>(gb, gf2, gm, bl_head, blk_head, own_blk, t_lo * AT, tid, T);
     PA_TILE_STORE(kt[0], kr)
     PA_TILE_STORE(vt[0], vr)
     if (GATED) gate_tile_store(gtile[0], gb, gf2, gm, tid);
@@ -573,7 +574,7 @@ __device__ __forceinline__ void dq_block(Place at, const bf16_t* __restrict__ Q,
         if (t + 1 < ntile) {
             PA_TILE_LOAD(kr, Kh, key0 + AT, false)
             PA_TILE_LOAD(vr, Vh, key0 + AT, false)
-            if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, key0 + AT, key0 + 2 * AT - 1, 1.f, tid, T);
+            if (GATED) gate_tile_load<true>(gb, gf2, gm, bl_head, blk_head, own_blk, key0 + AT, tid, T);
         }
         if (active && key0 <= q0 + OWN - 1 && key0 >= k_lo) {
             if (key0 + AT - 1 > q0) tile(std::true_type{}, buf, key0);
@@ -738,7 +739,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
     PA_TILE_LOAD(qr, Qh, t_first * AT, false)
     PA_TILE_LOAD(gr, Gh_h, t_first * AT, true)
     if (tid < AT) gzr = t_first * AT + tid < T ? gzh[t_first * AT + tid] : 0.f;
-    if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, t_first * AT, t_first * AT, -1.f, tid, T);
+    if (GATED) gate_tile_load<false>(gb, gf2, gm, bl_head, blk_head, own_blk, t_first * AT, tid, T);
     PA_TILE_STORE(qt[0], qr)
     PA_TILE_STORE(gt[0], gr)
     if (tid < AT) gzt[0][tid] = gzr;
@@ -750,7 +751,7 @@ __device__ __forceinline__ void dkdv_block(Place at, const bf16_t* __restrict__ 
             PA_TILE_LOAD(qr, Qh, q0 + AT, false)
             PA_TILE_LOAD(gr, Gh_h, q0 + AT, true)
             if (tid < AT) gzr = q0 + AT + tid < T ? gzh[q0 + AT + tid] : 0.f;
-            if (GATED) gate_tile_load(gb, gf2, gm, bl_head, blk_head, own_blk, q0 + AT, q0 + AT, -1.f, tid, T);
+            if (GATED) gate_tile_load<false>(gb, gf2, gm, bl_head, blk_head, own_blk, q0 + AT, tid, T);
         }
         if (active && q0 + AT - 1 >= k0 && q0 < q_hi) {
             if (q0 < k0 + OWN - 1) tile(std::true_type{}, buf, q0);   // some pair of this tile lies above the diagonal
