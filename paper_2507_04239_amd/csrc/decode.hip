@@ -1074,9 +1074,9 @@ size_t decode_absorb_workspace_bytes(const pa_problem& pr) {
 
 // With a workspace, and where the matrix-core scan applies, the prompt goes through that (the sums are then rounded to bf16
 // once, like the chunk states of the forward pass).  The exact matrix-core kernel runs every other bf16, p = 2 prompt.  At
-// d = 64 the scan is the faster one for long prompts of few heads (12 heads of 65536 tokens: 579 us against 1896; 12 of 2048:
-// 45 against 70) and the exact kernel for short ones (48 heads of 512: 39 against 77), but which of the two rounds its sums is
-// the caller's choice, made with the workspace, so the line does not follow the time.  The rest takes the float32 kernel on the
+// d = 64 the scan is the faster one for long prompts of few heads (12 heads of 32768 tokens: 148 us against 376; 12 of 3072:
+// 34 against 41) and the exact kernel for short ones and many heads (48 of 512: 29 against 38; 48 of 3072: 95 against 98), but which
+// of the two rounds its sums is the caller's choice, made with the workspace, so the line does not follow the time.  The rest takes the float32 kernel on the
 // vector ALUs.
 pa_status decode_absorb(const pa_problem& pr, const void* K, const void* V, const float* log_g, void* state, void* ws,
                         size_t ws_bytes, hipStream_t s) {

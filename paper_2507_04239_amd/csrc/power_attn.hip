@@ -86,7 +86,7 @@ int auto_chunk(const pa_problem& pr) {
     // the chunked kernels, on the sequence rounded up to whole chunks when it is ragged (see Padding)
     probe.chunk = pr.T % 256 == 0 || pr.T % 128 != 0 ? 256 : 128;
     probe.T = (pr.T + probe.chunk - 1) / probe.chunk * probe.chunk;
-    // d = 128: where the chunked kernels' forward pass leaves the attention form by itself.  d = 32 runs chunked on the tiled
+    // d = 128: where the chunked kernels' forward pass leaves the attention form by itself at most numbers of heads.  d = 32 runs chunked on the tiled
     // kernels (32 heads, forward + backward, ms, chunk 256 and whole sequence): T = 4096 0.37 and 0.18, 6144 0.54 and 0.36,
     // 8192 0.70 and 0.63, 32768 2.7 and 8.8.  For the higher degrees the attention form stays ahead at every length measured
     // (p = 3, d = 64, 4 heads: T = 16384 7.0 and 0.78, 131072 60 and 37; p = 4, d = 32, 16 heads: 16384 24 and 1.4, 65536 97 and 20).
