@@ -3,6 +3,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -385,8 +386,10 @@ size_t power_attn_workspace_bytes(const pa_problem* prob, int for_backward) {
     pa_status why;
     int impl = choose(pd.prob, for_backward != 0, &why);
     if (impl < 0 || (pd.on && impl != PA_IMPL_MFMA)) return 0;
-    return family_bytes(impl, pd.prob, for_backward != 0) + gate_workspace_bytes(pd.prob, for_backward != 0) +
-           padding_bytes(pd, for_backward != 0);
+    const size_t need = family_bytes(impl, pd.prob, for_backward != 0) + gate_workspace_bytes(pd.prob, for_backward != 0) +
+                        padding_bytes(pd, for_backward != 0);
+    // (a forward pass that keeps states is given the backward pass's size, and may form states where that pass forms none)
+    return for_backward != 0 && prob->keep_state ? std::max(need, power_attn_workspace_bytes(prob, 0)) : need;
 }
 
 long long power_attn_state_rows(const pa_problem* prob) {

@@ -107,6 +107,18 @@ def test_a_longer_chunk_takes_less_workspace(lib, d, heads, T, gated):
             assert a - b >= (T // (2048 << n) // 2 - 1) * state, (backward, need)
 
 
+@pytest.mark.parametrize("d,gated", [(64, False), (64, True), (128, False)])
+def test_kept_states_fit_what_the_backward_pass_asks_for(lib, d, gated):
+    """keep_state: both passes take the backward pass's size, also where only the forward pass forms states."""
+    lines = {64: (5120, 5632, 6400, 7168, 7296, 7424, 8191), 128: (8192, 9984, 14336, 16384, 17408, 18432, 20480, 24576)}[d]
+    for heads in (1, 2, 3, 6, 8, 9, 11, 12, 14, 16, 48):
+        for T in sorted({t + k for t in lines for k in (-128, 0, 1, 100, 128)}):
+            for chunk in (128, 1024, 2048):
+                pr = binding.make_problem(1, heads, T, d, d, 2, chunk, keep_state=True, gated=gated)
+                need = [binding.power_attn_workspace_bytes(pr, b) for b in (False, True)]
+                assert need[0] <= need[1], (heads, T, chunk, need)
+
+
 def test_state_rows_match_the_embedding_dimension(lib):
     import math
     for d, p in [(16, 2), (32, 4), (12, 3)]:
