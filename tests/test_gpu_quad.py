@@ -70,6 +70,7 @@ CASES = [
     (14, 18500, 128, 256, 1.0, False, True),   # one walk per head: no segments
     (1, 5120, 64, 128, 1.0, True, True, 0.02),     # gated: the longest sequence that runs whole
     (2, 5121, 64, 128, 1.0, True, False, 0.02),    # ... and the shortest with states, one token in the last chunk; the backward pass padded
+    (2, 5121, 64, 128, 1.0, True, True, 0.02),     # ... kept states that the backward pass does not use, in the workspace it asks for
     (1, 5249, 64, 384, 1.0, True, True, 0.02),     # ... and the shortest backward pass
     (15, 5504, 64, 1024, 1.0, True, True, 0.02),   # whole forward at many heads (no multiple of the chunk), states backward
     (15, 5400, 64, 4096, 1.0, True, False, 0.02),  # ... padded to whole blocks, not to whole chunks
