@@ -1,6 +1,6 @@
 """Float64 CPU oracle for causal power attention (test infrastructure, NOT the product).
 
-This file is the checker the HIP library is compared against.  It is slow on purpose:
+The HIP library is compared against this file.  It is slow on purpose:
 plain numpy in float64, one head at a time, no blocking or fusion beyond what the
 definitions state.  Only tests, the smoke check and the benchmark's ``cpu_baseline``
 leg may import it; the product path never does, and it shares no code with the HIP

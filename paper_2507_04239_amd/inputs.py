@@ -5,7 +5,7 @@ random numbers, rounds them to the storage dtype and names the workload shapes.
 Recipe (all five workloads): q, k ~ N(0,1) * d^-1/2, v ~ N(0,1), upstream gradient
 dY ~ N(0,1), iid, layout [B, H, T, d] row-major, value width v = d.  Values are drawn in
 float32 from numpy's PCG64 with one independent stream per tensor, then (for bf16
-workloads) rounded to nearest-even bf16, so both the GPU and the CPU checker see
+workloads) rounded to nearest-even bf16, so both the GPU and the CPU oracle see
 exactly the same representable numbers.
 """
 from __future__ import annotations
